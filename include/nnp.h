@@ -310,10 +310,9 @@ nnp_status nnp_read_buffer(nnp_model* m, nnp_buffer which, void* dst_host, size_
  * or of 32 atoms with 16 for the smallest species, with four or eight
  * wavefronts;
  * descriptor forward: a wavefront, a 16-lane or an 8-lane row per atom, or
- * wavefronts of two or four atoms sharing their lanes over chunks; descriptor
- * adjoint: a wavefront or half a wavefront per atom, and a wide-load form of
- * its reverse-slot search; neighbour search: one
- * wavefront per atom, or several per cell sharing its centre atoms).
+ * wavefronts of two or four atoms sharing their lanes over chunks; neighbour
+ * search: one wavefront per atom, or several per cell sharing its centre
+ * atoms; the descriptor adjoint has one kernel).
  * nnp_autotune reruns the
  * stages after the cell list `reps` times (1..256) per candidate on the
  * workspace of the previous compute call (same size and geometry; the
@@ -357,9 +356,7 @@ typedef enum {
  *     32-atom (8) or 16-atom (9) tile per wavefront with no barrier (celu'
  *     then comes from the BF16-rounded activation: dE/dx differs from the
  *     other BF16 kernels by rounding);
- *   descriptor adjoint: 0 one wavefront per atom; 1 half a wavefront per atom;
- *     2 as 0, with the centre's place in each neighbour's list counted with
- *     wide loads instead of a binary search (for lists far beyond the caches).
+ *   descriptor adjoint: 0, 1 and 2 run the same kernel.
  * All variants compute the same quantities (integer stages bit-identically,
  * floating point to rounding).
  * Drops the cached graph.  NNP_EINVAL for an unknown stage or variant.

@@ -26,6 +26,9 @@ COMMON = [
     "-ffp-contract=fast-honor-pragmas",
     # packed FP32 instructions stay off: ordinary scalar code only
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # matrix-core results in ordinary vector registers: the kernels stay below
+    # 256 of them, and results in accumulation registers cost a move each way
+    "-mllvm", "-amdgpu-mfma-vgpr-form=1",
     "-I", INCLUDE, "-I", CSRC,
     "-Wall", "-Wno-unused-function", "-Wno-unknown-pragmas",
 ]

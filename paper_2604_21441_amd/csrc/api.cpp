@@ -90,7 +90,6 @@ size_t carve_workspace(const nnp_model& m, Workspace& w, char* base) {
   take(w.d_nbr_ang, n * w.max_ang);
   take(w.d_rad_off, n * (m.S + 1));
   take(w.d_ang_off, n * (m.S + 1));
-  take(w.d_angpos, n * w.max_ang);
   take(w.d_contrib, n * w.max_rad);
   take(w.d_self, 3 * n);
   take(w.d_part, (size_t)w.max_part);
@@ -410,13 +409,8 @@ nnp_status nnp_create(const nnp_config* cfg, uint64_t seed, const float* weights
     for (int b = a; b < S; ++b) {
       p.pair_a[q] = a;
       p.pair_b[q] = b;
-      p.class_of[a][b] = q;
-      p.class_of[b][a] = q;
       ++q;
     }
-  p.class_tab = 0;
-  for (int a = 0; a < S; ++a)
-    for (int b = 0; b < S; ++b) p.class_tab |= (uint64_t)p.class_of[a][b] << (4 * (4 * a + b));
 
   // weights
   size_t per_species = 0;
@@ -430,10 +424,13 @@ nnp_status nnp_create(const nnp_config* cfg, uint64_t seed, const float* weights
   std::vector<uint8_t> mat;
   std::vector<float> vec;
   pack_weights(*m, mat, vec, m->mat_per_species, m->vec_per_species);
+  const size_t shifts_at = vec.size();
+  vec.insert(vec.end(), p.rad_shift_s, p.rad_shift_s + kRadShifts);
   hipError_t e = hipMalloc(&m->d_wmat, mat.size());
   if (e == hipSuccess) e = hipMemcpy(m->d_wmat, mat.data(), mat.size(), hipMemcpyHostToDevice);
   if (e == hipSuccess) e = dalloc(&m->d_wvec, vec.size());
   if (e == hipSuccess) e = hipMemcpy(m->d_wvec, vec.data(), vec.size() * sizeof(float), hipMemcpyHostToDevice);
+  m->d_shifts = m->d_wvec + shifts_at;
   if (e == hipSuccess && prec == NNP_BF16) {
     std::vector<uint16_t> rows;
     pack_rows_bf16(*m, rows, m->wrow_per_species);
@@ -953,6 +950,7 @@ nnp_status nnp_autotune(nnp_model* m, int32_t reps, int32_t* chosen, hipStream_t
   nnp_status status = NNP_OK;
   for (int st : stages) {
     if (m->pinned[st] >= 0) continue;   // a pinned stage keeps its variant
+    if (st == kTuneAdjoint) continue;   // its variants are one kernel
     int nv = st == kTuneNeighbours && m->geo.n_bins < 2 ? 1 : kStageVariants[st];
     int best = 0;
     float best_ms = 0.f;

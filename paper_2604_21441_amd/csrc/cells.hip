@@ -605,7 +605,6 @@ struct NeighArgs {
   float cull2;             // (sqrt(rc2) + kCullMargin)^2: stencil cells beyond it hold no neighbour
   int* rad;
   int* ang;
-  int* angpos;
   int* rad_off;
   int* ang_off;
   int max_rad, max_ang;
@@ -618,9 +617,9 @@ constexpr int kMaxStencil = 27;
 // the (deduplicated) 27-cell stencil are visited in ascending cell order --
 // hence ascending slot order -- one candidate per lane, and the accepted ones
 // are compacted with a ballot, so every species segment of a list is sorted
-// by slot.  Angular neighbours (r < rc_ang) also record their position in
-// the radial list.  Lists never hold more than their capacity; an overflow
-// sets the device status word.
+// by slot.  Angular neighbours (r < rc_ang) are the same sequence thinned out.
+// Lists never hold more than their capacity; an overflow sets the device
+// status word.
 // Candidates of one species per atom held in LDS (flattened stencil ranges);
 // a longer candidate sequence falls back to a binary search over the ranges.
 constexpr int kCandCap = 1024;
@@ -689,7 +688,6 @@ __global__ __launch_bounds__(64) void k_neighbours(NeighArgs a, Geometry g) {
 
   int* rad = a.rad + (int64_t)i * a.max_rad;
   int* ang = a.ang + (int64_t)i * a.max_ang;
-  int* angpos = a.angpos + (int64_t)i * a.max_ang;
   int nr = 0, na = 0;   // list lengths so far (wavefront-uniform)
   bool overflow = false;
   // Accepted candidates are appended in lane order: a lane's place is the
@@ -761,15 +759,12 @@ __global__ __launch_bounds__(64) void k_neighbours(NeighArgs a, Geometry g) {
       const bool in_r = valid && r2 < a.rc2;
       const uint64_t mr = __builtin_amdgcn_ballot_w64(in_r);
       const int pr = nr + below(mr);
-      // angular entries point into the radial list
+      // angular entries are also in the radial list
       const bool in_a = valid && r2 < a.rca2 && pr < a.max_rad;
       const uint64_t ma = __builtin_amdgcn_ballot_w64(in_a);
       const int pa = na + below(ma);
       if (in_r && pr < a.max_rad) rad[(unsigned)pr] = j;
-      if (in_a && pa < a.max_ang) {
-        ang[(unsigned)pa] = j;
-        angpos[(unsigned)pa] = pr;
-      }
+      if (in_a && pa < a.max_ang) ang[(unsigned)pa] = j;
       nr += __popcll(mr);
       na += __popcll(ma);
       if (nr > a.max_rad || na > a.max_ang) {
@@ -922,10 +917,7 @@ __global__ __launch_bounds__(64) void k_neighbours_cell(NeighArgs a, Geometry g,
           const uint64_t ma = __ballot(in_a2);
           const int pa = base_a + __popcll(ma & lt);
           if (in_r && pr < a.max_rad) a.rad[(int64_t)i * a.max_rad + pr] = j;
-          if (in_a2 && pa < a.max_ang) {
-            a.ang[(int64_t)i * a.max_ang + pa] = j;
-            a.angpos[(int64_t)i * a.max_ang + pa] = pr;
-          }
+          if (in_a2 && pa < a.max_ang) a.ang[(int64_t)i * a.max_ang + pa] = j;
           if (lane == ci) {
             nr += __popcll(mr);
             na += __popcll(ma);
@@ -1038,7 +1030,6 @@ __global__ __launch_bounds__(64) void k_pairs_lists(NeighArgs a, Geometry g, con
   const float4 pi = a.spos[i];
   const uint64_t lt = __lanemask_lt();
   int* ang = a.ang + (int64_t)i * a.max_ang;
-  int* angpos = a.angpos + (int64_t)i * a.max_ang;
   int na = 0;
   bool dup = false;
   for (int c0 = 0; c0 < n; c0 += 64) {
@@ -1055,7 +1046,6 @@ __global__ __launch_bounds__(64) void k_pairs_lists(NeighArgs a, Geometry g, con
     const int pa = na + __popcll(ma & lt);
     if (in_a && pa < a.max_ang) {
       ang[pa] = j;
-      angpos[pa] = t;
       arow[pa] = j;
     }
     na += __popcll(ma);
@@ -1202,7 +1192,6 @@ hipError_t launch_neighbours(nnp_model& m, int n, hipStream_t st) {
   }
   a.rad = m.d_nbr_rad;
   a.ang = m.d_nbr_ang;
-  a.angpos = m.d_angpos;
   a.rad_off = m.d_rad_off;
   a.ang_off = m.d_ang_off;
   a.max_rad = m.max_rad;
@@ -1249,7 +1238,6 @@ hipError_t launch_pair_lists(nnp_model& m, int n, int n_atoms, int n_pairs, cons
   }
   a.rad = m.d_nbr_rad;
   a.ang = m.d_nbr_ang;
-  a.angpos = m.d_angpos;
   a.rad_off = m.d_rad_off;
   a.ang_off = m.d_ang_off;
   a.max_rad = m.max_rad;

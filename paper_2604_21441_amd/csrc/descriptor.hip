@@ -770,309 +770,383 @@ __global__ __launch_bounds__(256) void k_desc_fwd_pool(FwdArgs a, DescParams p, 
 
 // Adjoint, one wavefront per centre atom i (no global atomics).
 //
-// E depends on d_ij = x_j - x_i, so a pair vector v = dE/d(d_ij) contributes
-// -v to F_j and +v to F_i.  The wavefront
-//   1. stages the centre's dE/dx row in LDS;
-//   2. evaluates the radial terms, one neighbour per lane, storing v in an
-//      FP64 LDS slot per radial neighbour;
-//   3. caches the geometry of the angular neighbours in LDS;
-//   4. evaluates the angular triplets (j < k, k-major), each lane walking a
-//      contiguous range: v_j goes to j's slot with an FP64 LDS atomic add,
-//      v_k is summed in registers while k stays the same;
-//   5. hands each neighbour's total to that neighbour: the centre's position
-//      in the neighbour's own list (lists are symmetric and sorted by slot
-//      within each species segment) is found by binary search, and the
-//      total, rounded once to FP32, is stored there -- each entry has exactly
-//      one writer;
-//   6. stores the centre's own total (FP64).
+// With d_ij = x_j - x_i, F_i = sum_j dE_i/dd_ij - sum_j dE_j/dd_ji.
+//   Radial terms of both centres depend on the same r_ij and differ only in
+//   the weights (dE_i/dG of j's species, dE_j/dG of i's species), so atom i
+//   adds the two rows of 16 weights and evaluates the pair once for both:
+//   nothing has to be handed to j, which does the same from its side.
+//   Angular terms of centre i act on its angular neighbours: their totals are
+//   summed in FP64 in LDS and handed over, rounded once to FP32, through the
+//   centre's slot in each neighbour's own angular list (lists are symmetric
+//   and sorted by slot within a species segment; each entry has one writer).
 // k_force_gather then sums, per atom and in FP64, its own total and the
-// entries of its list, and adds the result to the caller's force array.
+// entries of its angular list.
+//
+// The wavefront
+//   1. computes the geometry, one radial neighbour per lane; lanes within the
+//      angular cutoff (the lists' own predicate, so ranks equal list places)
+//      leave a record in LDS;
+//   2. sums the radial terms in quads: a quad of lanes per neighbour, four of
+//      the 16 shifts per lane, so that dE_j/dG is read as one 64-byte piece;
+//   3. evaluates the angular triplets (adj_triplets);
+//   4. finds the places in the neighbours' lists, two lanes per neighbour.
+//
+// After a list has overflowed its capacity (the device status says so) lists
+// are cut off and no longer symmetric.  The wavefront then looks every place
+// up in the radial lists (contrib rows follow those), leaves out dE_j/dG for
+// a neighbour whose list does not hold the centre, and hands over through the
+// radial entries.
+//
+// Bound by VALU issue: 927 VALU instructions per wavefront in the water box
+// of 98,304 atoms, of which the triplet loop is 515 (210 per pass of 64), fill
+// 98 % of the 161 us.  Handing over every radial neighbour through a search
+// for its slot, as before, took 195 us there and 577 us (now 431) at 261,000
+// atoms, and moved 12 bytes per radial instead of per angular neighbour
+// through contrib (gather 46 -> 28 us).  Tried: the triplets' contractions on
+// the matrix cores (4x4x1 FP32, one product per quad of lanes, weights in
+// registers): 12 % fewer VALU instructions, but 461 us at 261,000 atoms, the
+// 16 products per pass costing more issue time than they save.
 struct BwdArgs {
   const int* order;        // bin-major visiting order of the slots
   const float4* spos;
   const int* rad;
   const int* ang;
-  const int* angpos;
   const int* rad_off;
   const int* ang_off;
   int max_rad, max_ang, n;
+  float rca2;              // the angular predicate of the neighbour search
   const float* g;
-  float3* contrib;   // [n][max_rad]
+  const float4* shifts;    // the 16 scaled radial shifts
+  const int* status;
+  float3* contrib;   // [n][max_ang]; [n][max_rad] after an overflow
   double* self;      // [n][3]
 };
 
-// Sum over the LANES lanes of one atom (xor offsets below LANES stay inside it).
-template <int LANES>
-__device__ __forceinline__ double part_sum_d(double v) {
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// LDS of the wavefront (bytes, a multiple of 16): two float4 records per
+// angular neighbour, their FP64 slots (which share space with the radial
+// partial sums, 64 neighbours x 4 lanes x 2), the dE/dx row, and 64 x 8 bytes
+// of exchange.
+__host__ __device__ __forceinline__ size_t adj_slots_bytes(int max_ang) {
+  const size_t slots = sizeof(double) * 3 * (size_t)max_ang, partial = sizeof(float2) * 4 * 64;
+  return ((slots > partial ? slots : partial) + 15) & ~(size_t)15;
+}
+__host__ __device__ __forceinline__ size_t adj_lds(int max_ang, int stride) {
+  return sizeof(float4) * 2 * (size_t)max_ang + adj_slots_bytes(max_ang) + sizeof(float) * (size_t)stride +
+         sizeof(uint2) * 64;
+}
+
+// Sum over the 64 lanes with two FP64 matrix products by ones: the first
+// sums over the four 16-lane rows (the product's K), the four accumulators of
+// a lane then hold a quarter of the 16 sums, one quarter per row of lanes.
+__device__ __forceinline__ double wave_sum_mfma(double v) {
+  v4d d = v4d{0.0, 0.0, 0.0, 0.0};
+  d = __builtin_amdgcn_mfma_f64_16x16x4f64(v, 1.0, d, 0, 0, 0);
+  const double s = (d[0] + d[1]) + (d[2] + d[3]);
+  d = v4d{0.0, 0.0, 0.0, 0.0};
+  d = __builtin_amdgcn_mfma_f64_16x16x4f64(s, 1.0, d, 0, 0, 0);
+  return d[0];
+}
+
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Place of i in j's radial list (its segment of species si), or -1.
+__device__ __forceinline__ int radial_place(const BwdArgs& a, int S1, int i, int si, int j) {
+  const int* jrow = a.rad + (int64_t)j * a.max_rad;
+  int l = a.rad_off[(int64_t)j * S1 + si], h = a.rad_off[(int64_t)j * S1 + si + 1] - 1;
+  while (l < h) {
+    const int mid = (l + h) >> 1;
+    if (jrow[mid] < i) l = mid + 1; else h = mid;
+  }
+  return l <= h && jrow[l] == i ? l : -1;
+}
+
+// LDS of a wavefront and what its triplet loop needs.
+struct AdjWave {
+  const float4 *G1, *G2;   // angular neighbours' records
+  double *sx, *sy, *sz;    // their FP64 slots
+  const float* gl;         // the centre's dE/dx row
+  int lane;
+};
+
+// The sums over the shifts and sections that a triplet's derivatives need,
+// with Ab_n = bs_n^(zeta - 1): SA = sum h_n A_n, SP and SQ = sum h_n Ab_n
+// (cos, sin) and sdr = sum h'_n A_n.
+struct AdjSums {
+  float SA, SP, SQ, sdr;
+};
+
+// Derivatives of one triplet (inner neighbour j, outer k) to its two pair
+// vectors.
+__device__ __forceinline__ void adj_vectors(const DescParams& p, const float4& j1, const float4& j2, const float4& k1,
+                                            const float4& k2, float cs, float qq, const AdjSums& t, float3* v,
+                                            float3* w) {
+#pragma clang fp contract(off)
+  const float F = j2.x * k2.x;
+  const float dTdc = F * (p.zeta * 0.95f) * fmaf(-qq, t.SQ, t.SP);
+  const float hdr = F * (0.5f * p.c_sdr) * t.sdr;
+  const float cj = dTdc * j2.z, ck = dTdc * k2.z;
+  const float ej = fmaf(-cj, cs, fmaf(j2.y * k2.x, t.SA, hdr));
+  const float ek = fmaf(-ck, cs, fmaf(j2.x * k2.y, t.SA, hdr));
+  *v = make_float3(fmaf(cj, k1.x, ej * j1.x), fmaf(cj, k1.y, ej * j1.y), fmaf(cj, k1.z, ej * j1.z));
+  *w = make_float3(fmaf(ck, j1.x, ek * k1.x), fmaf(ck, j1.y, ek * k1.y), fmaf(ck, j1.z, ek * k1.z));
+}
+
+__device__ __forceinline__ void adj_add(const AdjWave& wv, int u, float x, float y, float z) {
+  unsafeAtomicAdd(wv.sx + u, (double)x);
+  unsafeAtomicAdd(wv.sy + u, (double)y);
+  unsafeAtomicAdd(wv.sz + u, (double)z);
+}
+
+// Triplets (k-major, j < k, a contiguous range per lane), the weights of each
+// triplet's class read from LDS: j's total goes to its FP64 slot with an LDS
+// atomic, k's is summed in registers and flushed when k changes.
+template <int S>
+__device__ __forceinline__ void adj_triplets(const AdjWave& wv, const DescParams& p, int na) {
+  const int lane = wv.lane;
+  const int T = na * (na - 1) / 2;
+  const int r0 = (T * lane) >> 6, r1 = (T * (lane + 1)) >> 6;   // T < 2^15
+  if (r0 >= r1) return;
+  int j, k;
+  pair_start(r0, true, 0, &j, &k);
+  const float zm1 = p.zeta - 1.f;
+  float kx = 0.f, ky = 0.f, kz = 0.f;   // running total of the current k
+  float4 k1 = wv.G1[k], k2 = wv.G2[k];
+  for (int r = r0; r < r1; ++r) {
+#pragma clang fp contract(off)
+    const float4 j1 = wv.G1[j], j2 = wv.G2[j];
+    const int sj = __float_as_int(j2.w) & 3, sk = __float_as_int(k2.w) & 3;   // sj <= sk (rows are grouped by species)
+    const int q = sj * (2 * S - 1 - sj) / 2 + sk;                             // class of (sj, sk)
+    const float4* g4 = reinterpret_cast<const float4*>(wv.gl + S * kRadShifts + q * kAngShifts * kAngSects);
+    const float cs = fmaf(j1.x, k1.x, fmaf(j1.y, k1.y, j1.z * k1.z));
+    const float rb = j1.w + k1.w;
+    float h[kAngSects] = {0.f, 0.f, 0.f, 0.f}, ht[kAngSects] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int off = LANES / 2; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+    for (int m = 0; m < kAngShifts; ++m) {
+      const float4 gv = g4[m];
+      const float tt = rb - p.ang_shift_s[m];
+      const float B = ex2(-(tt * tt)), tB = tt * B;
+      h[0] = fmaf(gv.x, B, h[0]);
+      h[1] = fmaf(gv.y, B, h[1]);
+      h[2] = fmaf(gv.z, B, h[2]);
+      h[3] = fmaf(gv.w, B, h[3]);
+      ht[0] = fmaf(gv.x, tB, ht[0]);
+      ht[1] = fmaf(gv.y, tB, ht[1]);
+      ht[2] = fmaf(gv.z, tB, ht[2]);
+      ht[3] = fmaf(gv.w, tB, ht[3]);
+    }
+    const float ct = 0.95f * cs;
+    const float s2 = fmaf(-ct, ct, 1.f);
+    const float ist = rsq(s2);
+    const float st = s2 * ist;
+    AdjSums t = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int n = 0; n < kAngSects; ++n) {
+      const float bs = fmaf(st, p.sin_sect[n], fmaf(ct, p.cos_sect[n], 1.f));
+      const float Ab = ex2(zm1 * lg2(bs));   // bs^(zeta - 1)
+      const float wn = h[n] * Ab;
+      t.SA = fmaf(wn, bs, t.SA);
+      t.SP = fmaf(wn, p.cos_sect[n], t.SP);
+      t.SQ = fmaf(wn, p.sin_sect[n], t.SQ);
+      t.sdr = fmaf(ht[n] * Ab, bs, t.sdr);
+    }
+    float3 v, w;
+    adj_vectors(p, j1, j2, k1, k2, cs, ct * ist, t, &v, &w);
+    adj_add(wv, j, v.x, v.y, v.z);
+    kx += w.x;
+    ky += w.y;
+    kz += w.z;
+    if (++j == k || r + 1 == r1) {   // k changes, or the range ends
+      adj_add(wv, k, kx, ky, kz);
+      kx = ky = kz = 0.f;
+      j = 0;
+      if (r + 1 < r1) {
+        ++k;
+        k1 = wv.G1[k];
+        k2 = wv.G2[k];
+      }
+    }
+  }
 }
 
-// Bytes of LDS per atom of the adjoint: FP64 slots, the dE/dx row, padding to
-// 16 bytes, two float4 records per angular neighbour (a multiple of 16).
-__host__ __device__ __forceinline__ size_t bwd_lds_per_atom(int max_rad, int max_ang, int stride) {
-  return sizeof(double) * 3 * (size_t)max_rad + sizeof(float) * (size_t)stride +
-         sizeof(float) * 2 * ((size_t)max_rad & 1) + sizeof(float4) * 2 * (size_t)max_ang;
-}
-
-// LANES lanes per atom: 64 (one atom per wavefront) or 32 (two atoms per
-// wavefront, so that the ~153 triplets of an atom in water fill the lanes
-// with less rounding).  WIDE: the centre's place in each neighbour's list is
-// counted with wide loads instead of a binary search (step 5).
-template <int LANES, bool WIDE>
-__global__ __launch_bounds__(64) void k_desc_bwd(BwdArgs a, DescParams p, Geometry geo) {
-  constexpr int APW = 64 / LANES;   // atoms per wavefront
-  extern __shared__ double smem_d[];
-  const int part = threadIdx.x / LANES;
-  const int lane = threadIdx.x % LANES;
-  char* region = reinterpret_cast<char*>(smem_d) + part * bwd_lds_per_atom(a.max_rad, a.max_ang, p.stride);
-  double* sx = reinterpret_cast<double*>(region);   // per radial neighbour, FP64
-  double* sy = sx + a.max_rad;
-  double* sz = sy + a.max_rad;
-  float* gl = reinterpret_cast<float*>(sz + a.max_rad);   // [stride] dE/dx of the centre
-  // angular neighbours: (u, r hq) and (fc sq_pref, dfc sq_pref, 1/r, radial position * 8 + species)
-  float4* G1 = reinterpret_cast<float4*>(gl + p.stride + 2 * (a.max_rad & 1));   // 16-byte aligned
+template <int S>
+__global__ __launch_bounds__(64, 7) void k_desc_adj(BwdArgs a, DescParams p, Geometry geo) {
+  constexpr int S1 = S + 1, P = S * (S + 1) / 2, D = kRadShifts * S + kAngShifts * kAngSects * P;
+  extern __shared__ float4 smem_b[];
+  const int lane = threadIdx.x;
+  // angular neighbours: (u, r hq) and (fc sq_pref, dfc sq_pref, 1/r, slot * 4 + species)
+  float4* G1 = smem_b;
   float4* G2 = G1 + a.max_ang;
-  const int li = xcd_block(blockIdx.x, gridDim.x) * APW + part;
-  const bool valid = li < a.n;
-  const int i = valid ? a.order[li] : 0;
-  const Consts c = make_consts(p);
+  double* sx = reinterpret_cast<double*>(G2 + a.max_ang);   // FP64 slots of the angular neighbours
+  double* sy = sx + a.max_ang;
+  double* sz = sy + a.max_ang;
+  float2* part = reinterpret_cast<float2*>(sx);             // radial partial sums (before the slots are used)
+  float* gl = reinterpret_cast<float*>(reinterpret_cast<char*>(sx) + adj_slots_bytes(a.max_ang));   // dE/dx row
+  uint2* ex = reinterpret_cast<uint2*>(gl + p.stride);
+  const int i = a.order[xcd_block(blockIdx.x, gridDim.x)];
+  const bool full = (*a.status & kStatusCapacity) != 0;
   const float4 pi = a.spos[i];
+  const int si = __float_as_int(pi.w);
   const MinImage mi = min_image_at(geo, i);
-  const int S1 = p.S + 1;
-  const int nr = valid ? a.rad_off[(int64_t)i * S1 + p.S] : 0;
-  const int na = valid ? a.ang_off[(int64_t)i * S1 + p.S] : 0;
+  const int nr = a.rad_off[(int64_t)i * S1 + S];
+  int ao[S1];   // angular segments of the species (uniform)
+#pragma unroll
+  for (int s = 0; s < S1; ++s) ao[s] = a.ang_off[(int64_t)i * S1 + s];
   const int* rrow = a.rad + (int64_t)i * a.max_rad;
-  const int* arow = a.ang + (int64_t)i * a.max_ang;
-  float fx = 0.f, fy = 0.f, fz = 0.f;   // this lane's share of the centre's total
-
-  // 1. dE/dx row
-  if (valid) {
+  const int c4 = lane & 3;
+  const float4 sh = a.shifts[c4];
+  {
     const float4* g4 = reinterpret_cast<const float4*>(a.g + (int64_t)i * p.stride);
     float4* l4 = reinterpret_cast<float4*>(gl);
-    for (int q = lane; q < p.D / 4; q += LANES) l4[q] = g4[q];
-  }
-  // 3. angular neighbour geometry (before the barrier, together with 1.)
-  for (int u = lane; u < na; u += LANES) {
-    const float4 pj = a.spos[arow[u]];
-    Geo d = displacement(pi, pj, mi);
-    const float arg = d.r * c.inv2rca;
-    G1[u] = make_float4(d.dx * d.ir, d.dy * d.ir, d.dz * d.ir, d.r * p.hq_eta_a);
-    G2[u] = make_float4(fmaf(0.5f, cos_rev(arg), 0.5f) * p.sq_pref, c.dfc_a * sin_rev(arg) * p.sq_pref, d.ir,
-                        __int_as_float(a.angpos[(int64_t)i * a.max_ang + u] * 8 + __float_as_int(pj.w)));
-  }
-  __syncthreads();
-  // 2. radial pairs
-  {
-    const float c1 = p.c1_rad;   // d/dr of -(r sq - Rs sq)^2 per (r sq - Rs sq), in ln units
-    for (int t = lane; t < nr; t += LANES) {
-#pragma clang fp contract(off)   // keep r sq in a register: one SGPR operand per shift
-      const float4 pj = a.spos[rrow[t]];
-      const int sj = __float_as_int(pj.w);
-      Geo d = displacement(pi, pj, mi);
-      const float arg = d.r * c.inv2rc;
-      const float fc = fmaf(0.5f, cos_rev(arg), 0.5f);
-      const float dfc = c.dfc_r * sin_rev(arg);
-      const float rs = d.r * p.sq_eta_r;
-      const float4* g4 = reinterpret_cast<const float4*>(gl + sj * kRadShifts);
-      float s0 = 0.f, s1 = 0.f;
 #pragma unroll
-      for (int q = 0; q < kRadShifts / 4; ++q) {
-        const float4 gv = g4[q];
-        const float gk[4] = {gv.x, gv.y, gv.z, gv.w};
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float tt = rs - p.rad_shift_s[4 * q + u];
-          const float B = gk[u] * ex2(-(tt * tt));
-          s0 += B;
-          s1 = fmaf(B, tt, s1);
-        }
-      }
-      const float dTdr = fmaf(dfc, s0, c1 * fc * s1);
-      const float w = dTdr * d.ir;
-      const float vx = w * d.dx, vy = w * d.dy, vz = w * d.dz;
-      sx[t] = vx;
-      sy[t] = vy;
-      sz[t] = vz;
-      fx += vx; fy += vy; fz += vz;
+    for (int q = 0; q < D / 4; q += 64)
+      if (D / 4 - q >= 64 || lane < D / 4 - q) l4[q + lane] = g4[q + lane];
+  }
+
+  // 1., 2. geometry and radial pairs, 64 neighbours at a time
+  float fx = 0.f, fy = 0.f, fz = 0.f;   // this lane's share of the centre's radial total
+  int na_seen = 0;
+  for (int c0 = 0; c0 < nr; c0 += 64) {
+    const int cnt = min(64, nr - c0);
+    const bool valid = lane < cnt;
+    const int j = valid ? rrow[c0 + lane] : i;
+    const float4 pj = a.spos[j];
+    float dx, dy, dz, r2;
+    pair_d_exact(pi, pj, mi, &dx, &dy, &dz, &r2);
+    const float ir = rsq(r2), r = r2 * ir;
+    const int js = j * 4 + __float_as_int(pj.w);
+    ex[lane] = make_uint2(__float_as_uint(r * p.sq_eta_r), (uint32_t)js);
+    const bool in_a = valid && r2 < a.rca2;
+    const uint64_t ma = __builtin_amdgcn_ballot_w64(in_a);
+    const int u = na_seen + lanes_below(ma);
+    na_seen += __popcll(ma);
+    if (in_a && u < ao[S]) {
+      const float arg = r * p.inv2rca;
+      G1[u] = make_float4(dx * ir, dy * ir, dz * ir, r * p.hq_eta_a);
+      G2[u] = make_float4(fmaf(0.5f, cos_rev(arg), 0.5f) * p.sq_pref, p.dfc_a * sin_rev(arg) * p.sq_pref, ir,
+                          __int_as_float(js));
     }
-  }
-  __syncthreads();
-  // 4. angular triplets (j < k, k-major), a contiguous range per lane
-  const int T = na * (na - 1) / 2;
-  const int r0 = (int)(((int64_t)T * lane) / LANES);
-  const int r1 = (int)(((int64_t)T * (lane + 1)) / LANES);
-  if (r0 < r1) {
+    wave_sync();
+    const int np = (cnt + 15) >> 4;
+    float4 gj[4];
+    uint2 en[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q < np) {   // neighbours beyond cnt hold the centre itself; their sums are not read
+        en[q] = ex[16 * q + (lane >> 2)];
+        gj[q] = *reinterpret_cast<const float4*>(a.g + (uint64_t)(en[q].y >> 2) * (uint32_t)p.stride +
+                                                 (si * kRadShifts + 4 * c4));
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q < np) {
 #pragma clang fp contract(off)
-    int k = (int)((1.f + __builtin_amdgcn_sqrtf(1.f + 8.f * (float)r0)) * 0.5f);
-    if (k * (k - 1) / 2 > r0) --k;
-    if ((k + 1) * k / 2 <= r0) ++k;
-    int j = r0 - k * (k - 1) / 2;
-    const float c_sdr = p.c_sdr;     // d rbar-term per (rbar sa - Ra sa), sa = 2 hq
-    const float c_dc = p.zeta * 0.95f;
-    float kx = 0.f, ky = 0.f, kz = 0.f;   // running total of the current k
-    float4 k1 = G1[k], k2 = G2[k];
-    for (int r = r0; r < r1; ++r) {
-      const float4 j1 = G1[j], j2 = G2[j];
-      const int wj = __float_as_int(j2.w), wk = __float_as_int(k2.w);
-      const int sj = wj & 7, sk = wk & 7;                   // sj <= sk (rows are grouped by species)
-      const int q = (int)(p.class_tab >> (4 * (4 * sj + sk))) & 15;
-      const float4* g4 = reinterpret_cast<const float4*>(gl + p.S * kRadShifts + q * kAngShifts * kAngSects);
-      const float cs = fmaf(j1.x, k1.x, fmaf(j1.y, k1.y, j1.z * k1.z));
-      const float ct = 0.95f * cs;
-      const float s2 = fmaf(-ct, ct, 1.f);
-      const float ist = rsq(s2);
-      const float st = s2 * ist;
-      const float qq = ct * ist;
-      const float rb = j1.w + k1.w;
-      float A[kAngSects], Ab[kAngSects];
-#pragma unroll
-      for (int n = 0; n < kAngSects; ++n) {
-        const float base = fmaf(st, p.sin_sect[n], fmaf(ct, p.cos_sect[n], 1.f));
-        const float An = ex2(p.zeta * lg2(base));
-        A[n] = An;
-        Ab[n] = An * __builtin_amdgcn_rcpf(base);
-      }
-      float h[kAngSects] = {0.f, 0.f, 0.f, 0.f};
-      float sdr = 0.f;
-#pragma unroll
-      for (int m = 0; m < kAngShifts; ++m) {
-        const float4 gv = g4[m];
-        const float tt = rb - p.ang_shift_s[m];
-        const float B = ex2(-(tt * tt));
-        h[0] = fmaf(gv.x, B, h[0]);
-        h[1] = fmaf(gv.y, B, h[1]);
-        h[2] = fmaf(gv.z, B, h[2]);
-        h[3] = fmaf(gv.w, B, h[3]);
-        const float km = fmaf(gv.x, A[0], fmaf(gv.y, A[1], fmaf(gv.z, A[2], gv.w * A[3])));
-        sdr = fmaf(tt * B, km, sdr);
-      }
-      float SA = 0.f, SP = 0.f, SQ = 0.f;
-#pragma unroll
-      for (int n = 0; n < kAngSects; ++n) {
-        SA = fmaf(h[n], A[n], SA);
-        const float wn = h[n] * Ab[n];
-        SP = fmaf(wn, p.cos_sect[n], SP);
-        SQ = fmaf(wn, p.sin_sect[n], SQ);
-      }
-      const float F = j2.x * k2.x;
-      const float dTdc = F * c_dc * fmaf(-qq, SQ, SP);
-      const float hdr = 0.5f * F * c_sdr * sdr;
-      const float dTdrj = fmaf(j2.y * k2.x, SA, hdr);
-      const float dTdrk = fmaf(j2.x * k2.y, SA, hdr);
-      const float cj = dTdc * j2.z, ck = dTdc * k2.z;
-      const float vjx = fmaf(cj, fmaf(-cs, j1.x, k1.x), dTdrj * j1.x);
-      const float vjy = fmaf(cj, fmaf(-cs, j1.y, k1.y), dTdrj * j1.y);
-      const float vjz = fmaf(cj, fmaf(-cs, j1.z, k1.z), dTdrj * j1.z);
-      const float vkx = fmaf(ck, fmaf(-cs, k1.x, j1.x), dTdrk * k1.x);
-      const float vky = fmaf(ck, fmaf(-cs, k1.y, j1.y), dTdrk * k1.y);
-      const float vkz = fmaf(ck, fmaf(-cs, k1.z, j1.z), dTdrk * k1.z);
-      const int pj = wj >> 3;
-      unsafeAtomicAdd(sx + pj, (double)vjx);
-      unsafeAtomicAdd(sy + pj, (double)vjy);
-      unsafeAtomicAdd(sz + pj, (double)vjz);
-      kx += vkx; ky += vky; kz += vkz;
-      fx += vjx + vkx;
-      fy += vjy + vky;
-      fz += vjz + vkz;
-      if (++j == k || r + 1 == r1) {   // k changes (or the range ends): flush its total
-        const int pk = wk >> 3;
-        unsafeAtomicAdd(sx + pk, (double)kx);
-        unsafeAtomicAdd(sy + pk, (double)ky);
-        unsafeAtomicAdd(sz + pk, (double)kz);
-        kx = ky = kz = 0.f;
-        if (j == k) {
-          j = 0;
-          ++k;
-          if (r + 1 < r1) {
-            k1 = G1[k];
-            k2 = G2[k];
-          }
-        }
+        const float4 gi = *reinterpret_cast<const float4*>(gl + (en[q].y & 3) * kRadShifts + 4 * c4);
+        const float rs = __uint_as_float(en[q].x);
+        const float t0 = rs - sh.x, t1 = rs - sh.y, t2 = rs - sh.z, t3 = rs - sh.w;
+        const float b0 = (gi.x + gj[q].x) * ex2(-(t0 * t0)), b1 = (gi.y + gj[q].y) * ex2(-(t1 * t1));
+        const float b2 = (gi.z + gj[q].z) * ex2(-(t2 * t2)), b3 = (gi.w + gj[q].w) * ex2(-(t3 * t3));
+        part[(16 * q + (lane >> 2)) * 4 + c4] =
+            make_float2((b0 + b1) + (b2 + b3), fmaf(b3, t3, fmaf(b2, t2, fmaf(b1, t1, b0 * t0))));
       }
     }
-  }
-  __syncthreads();
-  // 5. each neighbour's total goes to the centre's slot in the neighbour's list:
-  // in j's species segment [lo, hi) (sorted by slot) the centre sits after the
-  // entries below i.  A binary search finds it with one dependent load per
-  // halving.  The WIDE form counts the entries below i 32 at a time from
-  // eight independent aligned 16-byte loads: one or two round trips instead
-  // of about six, for four times the bytes.  That wins when the lists are
-  // far beyond the caches (261k atoms: 687 -> 642 us) and loses while they
-  // are cache-resident (12k atoms: 34 -> 42 us), so it is a tuned variant.
-  const int si = __float_as_int(pi.w);
-  const bool wide = WIDE && (a.max_rad & 3) == 0;   // rows start on 16-byte boundaries
-  for (int t = lane; t < nr; t += LANES) {
-    const int j = rrow[t];
-    const int* jrow = a.rad + (int64_t)j * a.max_rad;
-    const int lo = a.rad_off[(int64_t)j * S1 + si], hi = a.rad_off[(int64_t)j * S1 + si + 1];
-    int pos = -1;
-    if (wide) {
-      // lower bound of i in j's segment [lo, hi), 32 entries per round.  The
-      // key of entry e is -inf before lo, +inf from hi on and the (sorted)
-      // entry in between; keys are monotone, so the groups of four whose
-      // first key is below i form a prefix, and the boundary lies in the
-      // last of them (or at the next group's first entry).
-      for (int e0 = lo & ~3; e0 < hi; e0 += 32) {
-        int4 q[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)   // a load starting before hi stays inside the row (max_rad % 4 == 0)
-          q[u] = e0 + 4 * u < hi ? reinterpret_cast<const int4*>(jrow + e0)[u]
-                                 : make_int4(INT_MAX, INT_MAX, INT_MAX, INT_MAX);
-        int g = (e0 < lo || q[0].x < i) ? 1 : 0;   // e0 >= lo - 3: only group 0 can start before lo
-#pragma unroll
-        for (int u = 1; u < 8; ++u) g += q[u].x < i ? 1 : 0;
-        int x = 0, at = q[0].x;   // x: keys below i in this round; at: the entry at x
-        if (g > 0) {
-          const int gs = g - 1;
-          int4 sel[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) sel[u] = q[u];
-#pragma unroll
-          for (int b = 1; b < 8; b <<= 1)   // multiplexer tree: sel[0] = q[gs]
-#pragma unroll
-            for (int u = 0; u + b < 8; u += 2 * b)
-              if (gs & b) sel[u] = sel[u + b];
-          int nxt = INT_MAX;   // first entry of group gs + 1
-#pragma unroll
-          for (int u = 1; u < 8; ++u) nxt = gs + 1 == u ? q[u].x : nxt;
-          const int eb = e0 + 4 * gs;
-          const int w[4] = {sel[0].x, sel[0].y, sel[0].z, sel[0].w};
-          x = 4 * gs + 1;
-          at = nxt;
-#pragma unroll
-          for (int c = 3; c >= 1; --c) {   // keys are monotone: count those below i
-            const int e = eb + c;
-            const bool less = e < lo || (e < hi && w[c] < i);
-            x += less ? 1 : 0;
-          }
-          at = x == 4 * gs + 1 ? w[1] : x == 4 * gs + 2 ? w[2] : x == 4 * gs + 3 ? w[3] : nxt;
-        }
-        if (x < 32) {   // the first key >= i is in this round
-          if (e0 + x < hi && at == i) pos = e0 + x;
-          break;
+    wave_sync();
+    if (valid) {
+      const float4* q4 = reinterpret_cast<const float4*>(part + 4 * lane);
+      const float4 v0 = q4[0], v1 = q4[1];
+      float s0 = (v0.x + v0.z) + (v1.x + v1.z), s1 = (v0.y + v0.w) + (v1.y + v1.w);
+      if (full && radial_place(a, S1, i, si, j) < 0) {   // j's cut-off list does not hold i: dE_i/dG alone
+        s0 = s1 = 0.f;
+#pragma unroll 1
+        for (int k = 0; k < kRadShifts; ++k) {
+          const float t = r * p.sq_eta_r - reinterpret_cast<const float*>(a.shifts)[k];
+          const float b = gl[(js & 3) * kRadShifts + k] * ex2(-(t * t));
+          s0 += b;
+          s1 = fmaf(b, t, s1);
         }
       }
-    } else {
-      int l = lo, h = hi - 1;
-      while (l < h) {
-        const int mid = (l + h) >> 1;
-        if (jrow[mid] < i) l = mid + 1; else h = mid;
-      }
-      if (l <= h && jrow[l] == i) pos = l;
+      const float arg = r * p.inv2rc;
+      const float fc = fmaf(0.5f, cos_rev(arg), 0.5f);
+      const float w = fmaf(p.dfc_r * sin_rev(arg), s0, p.c1_rad * fc * s1) * ir;
+      fx = fmaf(w, dx, fx);
+      fy = fmaf(w, dy, fy);
+      fz = fmaf(w, dz, fz);
     }
-    if (pos >= 0)
-      a.contrib[(int64_t)j * a.max_rad + pos] = make_float3((float)-sx[t], (float)-sy[t], (float)-sz[t]);
+    wave_sync();
   }
-  // 6. the centre's own total
-  double dx = part_sum_d<LANES>((double)fx), dy = part_sum_d<LANES>((double)fy), dz = part_sum_d<LANES>((double)fz);
-  if (lane == 0 && valid) {
-    a.self[3 * (int64_t)i + 0] = dx;
-    a.self[3 * (int64_t)i + 1] = dy;
-    a.self[3 * (int64_t)i + 2] = dz;
+
+  // 3. angular triplets
+  const int na = min(ao[S], na_seen);   // (equal unless the radial list overflowed)
+  for (int u = lane; u < na; u += 64) sx[u] = sy[u] = sz[u] = 0.0;
+  wave_sync();
+  adj_triplets<S>(AdjWave{G1, G2, sx, sy, sz, gl, lane}, p, na);
+  wave_sync();
+  // 4. each angular neighbour's total goes to the centre's place in that
+  // neighbour's angular list: the entry equal to i in the segment of i's
+  // species, 16 entries a round by two lanes with two 16-byte loads each.
+  // Entries outside the segment cannot equal i (other species), or are left
+  // over from an earlier call beyond the list's end: the first match is the
+  // true one.
+  if (!full) {
+    const bool wide = (a.max_ang & 3) == 0;   // rows start on 16-byte boundaries
+    for (int u0 = 0; u0 < na; u0 += 32) {
+      const int u = u0 + (lane >> 1);
+      if (u < na) {
+        const uint32_t j = (uint32_t)__float_as_int(G2[u].w) >> 2;
+        const int* jrow = a.ang + (uint64_t)j * (uint32_t)a.max_ang;
+        const int* jo = a.ang_off + (uint64_t)j * S1 + si;
+        const int lo = jo[0], hi = jo[1];
+        int pos = INT_MAX;
+        if (wide) {
+          for (int e = (lo & ~3) + 8 * (lane & 1); e < hi && pos == INT_MAX; e += 16) {
+            const int4 q0 = *reinterpret_cast<const int4*>(jrow + e);
+            const int4 q1 = e + 4 < hi ? *reinterpret_cast<const int4*>(jrow + e + 4) : make_int4(-1, -1, -1, -1);
+            const int w[8] = {q0.x, q0.y, q0.z, q0.w, q1.x, q1.y, q1.z, q1.w};
+#pragma unroll
+            for (int c = 7; c >= 0; --c) pos = w[c] == i ? e + c : pos;
+          }
+        } else {
+          for (int e = lo + (lane & 1); e < hi; e += 2)
+            if (jrow[e] == i) pos = e;
+        }
+        if (pos < hi)
+          a.contrib[(uint64_t)j * (uint32_t)a.max_ang + pos] =
+              make_float3((float)-sx[u], (float)-sy[u], (float)-sz[u]);
+      }
+    }
+  } else {
+    int seen = 0;
+    for (int c0 = 0; c0 < nr; c0 += 64) {
+      const bool valid = c0 + lane < nr;
+      const int j = valid ? rrow[c0 + lane] : i;
+      const bool in_a = valid && pair_r2_exact(pi, a.spos[j], mi) < a.rca2;
+      const uint64_t ma = __builtin_amdgcn_ballot_w64(in_a);
+      const int u = seen + lanes_below(ma);
+      seen += __popcll(ma);
+      const int pos = valid ? radial_place(a, S1, i, si, j) : -1;
+      const bool any = in_a && u < na;
+      if (pos >= 0)
+        a.contrib[(int64_t)j * a.max_rad + pos] =
+            any ? make_float3((float)-sx[u], (float)-sy[u], (float)-sz[u]) : make_float3(0.f, 0.f, 0.f);
+      else if (valid)   // j does not see the centre: nothing comes back from it
+        a.contrib[(int64_t)i * a.max_rad + c0 + lane] = make_float3(0.f, 0.f, 0.f);
+    }
   }
+  // 5. the centre's own total
+  double tx = fx, ty = fy, tz = fz;
+  for (int u = lane; u < na; u += 64) {
+    tx += sx[u];
+    ty += sy[u];
+    tz += sz[u];
+  }
+  tx = wave_sum_mfma(tx);
+  ty = wave_sum_mfma(ty);
+  tz = wave_sum_mfma(tz);
+  if (lane < 3) a.self[3 * (int64_t)i + lane] = lane == 0 ? tx : lane == 1 ? ty : tz;
 }
 
 // FP64 energy reduction blocks, appended to the gather's grid (one launch for
@@ -1137,7 +1211,8 @@ __device__ __forceinline__ void energy_block(const EnergyArgs& ea, int sys) {
   }
 }
 
-// F_atom += self + sum over the atom's radial list entries (FP64): 16 lanes
+// F_atom += self + sum over the atom's angular list entries (its radial ones
+// after a list overflow, see k_desc_adj; FP64): 16 lanes
 // per atom, each summing a strided part of the row, then a shuffle tree.
 // With `assign` the sum overwrites F_atom (every row of the output is an NNP
 // atom and the call does not accumulate), which saves clearing it first.
@@ -1145,8 +1220,9 @@ __device__ __forceinline__ void energy_block(const EnergyArgs& ea, int sys) {
 __global__ __launch_bounds__(kBlock) void k_force_gather(const float3* __restrict__ contrib,
                                                          const double* __restrict__ self,
                                                          const int* __restrict__ rad_off,
+                                                         const int* __restrict__ ang_off,
                                                          const int* __restrict__ slot_atom, int n, int S,
-                                                         int max_rad, double* __restrict__ forces,
+                                                         int max_rad, int max_ang, double* __restrict__ forces,
                                                          double* __restrict__ link_forces, int assign,
                                                          int gather_blocks, EnergyArgs ea) {
   // the energy blocks come first, so that their serial reduction runs beside
@@ -1161,9 +1237,10 @@ __global__ __launch_bounds__(kBlock) void k_force_gather(const float3* __restric
   const int sub = gid & 15;
   double fx = 0.0, fy = 0.0, fz = 0.0;
   if (i < n) {
-    const int nr = rad_off[(int64_t)i * (S + 1) + S];
-    const float3* row = contrib + (int64_t)i * max_rad;   // 16 lanes read 192 contiguous bytes
-    for (int t = sub; t < nr; t += 16) {
+    const bool full = (*ea.status & kStatusCapacity) != 0;
+    const int cnt = (full ? rad_off : ang_off)[(int64_t)i * (S + 1) + S];
+    const float3* row = contrib + (int64_t)i * (full ? max_rad : max_ang);   // 16 lanes read 192 contiguous bytes
+    for (int t = sub; t < cnt; t += 16) {
       const float3 v = row[t];
       fx += v.x; fy += v.y; fz += v.z;
     }
@@ -1277,9 +1354,7 @@ hipError_t launch_descriptor_fwd(nnp_model& m, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Adjoint variants: 0 = one wavefront per atom (default; measured faster on
-// water boxes), 1 = half a wavefront per atom, 2 = variant 0 with the wide
-// reverse-slot count (for lists far beyond the caches).
+// The adjoint has one kernel; variants 0 to 2 are accepted and run it.
 int adjoint_variant(const nnp_model& m, int n) {
   const int v = stage_variant(m, kTuneAdjoint, n);
   return v >= 0 ? v : 0;
@@ -1292,23 +1367,24 @@ hipError_t launch_descriptor_bwd(nnp_model& m, int n, hipStream_t st) {
   a.spos = m.d_spos;
   a.rad = m.d_nbr_rad;
   a.ang = m.d_nbr_ang;
-  a.angpos = m.d_angpos;
   a.rad_off = m.d_rad_off;
   a.ang_off = m.d_ang_off;
   a.max_rad = m.max_rad;
   a.max_ang = m.max_ang;
   a.n = n;
+  a.rca2 = m.dp.rc_ang * m.dp.rc_ang;
   a.g = m.d_g;
+  a.shifts = reinterpret_cast<const float4*>(m.d_shifts);
+  a.status = m.d_status;
   a.contrib = m.d_contrib;
   a.self = m.d_self;
-  const size_t per_atom = bwd_lds_per_atom(m.max_rad, m.max_ang, m.stride);
-  const int v = adjoint_variant(m, n);
-  if (v == 1) {
-    hipLaunchKernelGGL((k_desc_bwd<32, false>), dim3((n + 1) / 2), dim3(64), 2 * per_atom, st, a, m.dp, m.geo);
-  } else if (v == 2) {
-    hipLaunchKernelGGL((k_desc_bwd<64, true>), dim3(n), dim3(64), per_atom, st, a, m.dp, m.geo);
-  } else {
-    hipLaunchKernelGGL((k_desc_bwd<64, false>), dim3(n), dim3(64), per_atom, st, a, m.dp, m.geo);
+  // one wavefront per workgroup: several, sharing nothing, measured slower
+  // (261,000 atoms 456, 458 and 465 us for one, two and four)
+  const size_t lds = adj_lds(m.max_ang, m.stride);
+  switch (m.S) {
+    case 2: hipLaunchKernelGGL(k_desc_adj<2>, dim3(n), dim3(64), lds, st, a, m.dp, m.geo); break;
+    case 4: hipLaunchKernelGGL(k_desc_adj<4>, dim3(n), dim3(64), lds, st, a, m.dp, m.geo); break;
+    default: return hipErrorInvalidValue;   // nnp_create accepts two- and four-species models
   }
   return hipGetLastError();
 }
@@ -1331,7 +1407,8 @@ hipError_t launch_force_gather(nnp_model& m, int n, double* forces, int assign, 
   const int gather_blocks = (int)((16 * (int64_t)n + kBlock - 1) / kBlock);
   const int energy_blocks = single ? 1 : n_sys;
   hipLaunchKernelGGL(k_force_gather, dim3((unsigned)(gather_blocks + energy_blocks)), dim3(kBlock), 0, st,
-                     m.d_contrib, m.d_self, m.d_rad_off, m.d_slot_atom, n, m.S, m.max_rad, forces, m.d_link_F,
+                     m.d_contrib, m.d_self, m.d_rad_off, m.d_ang_off, m.d_slot_atom, n, m.S, m.max_rad, m.max_ang, forces,
+                     m.d_link_F,
                      assign, gather_blocks, ea);
   return hipGetLastError();
 }

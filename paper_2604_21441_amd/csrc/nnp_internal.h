@@ -103,12 +103,10 @@ struct DescParams {
   // derivative factor), -2 eta_r / sq_eta_r and -eta_a / hq_eta_a (the chain
   // factors of the scaled Gaussians in the adjoint).
   float inv2rc, inv2rca, dfc_r, dfc_a, c1_rad, c_sdr;
-  uint64_t class_tab;                   // class of species pair (a, b) in bits 4 (4 a + b) .. +3
   float mm_cutoff, ke;
   int S, P, D, stride;                  // species, pair classes, descriptor length, row stride
   int extra;                            // 1 if the MM potential is the last input
   int pair_a[kMaxPairs], pair_b[kMaxPairs];
-  int class_of[kMaxSpecies][kMaxSpecies];  // unordered species pair -> class
 };
 
 // Geometry of the current call.
@@ -156,10 +154,11 @@ __device__ __forceinline__ MinImage min_image_at(const Geometry& g, int slot) {
   return min_image_of_system(g, g.sys_box ? g.sbin[slot] : 0);
 }
 
-// r^2 of d = pj - pi under the minimum image, every operation one IEEE FP32
+// d = pj - pi under the minimum image and r^2, every operation one IEEE FP32
 // operation in a fixed order (no contraction): the neighbour predicate of the
 // cell list and the pair lists.
-__device__ __forceinline__ float pair_r2_exact(const float4& pi, const float4& pj, const MinImage& b) {
+__device__ __forceinline__ void pair_d_exact(const float4& pi, const float4& pj, const MinImage& b, float* ox,
+                                             float* oy, float* oz, float* o2) {
 #pragma clang fp contract(off)
   float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
   if (b.on) {
@@ -171,7 +170,13 @@ __device__ __forceinline__ float pair_r2_exact(const float4& pi, const float4& p
   }
   float xx = dx * dx, yy = dy * dy, zz = dz * dz;
   float r2 = xx + yy;
-  return r2 + zz;
+  *ox = dx; *oy = dy; *oz = dz;
+  *o2 = r2 + zz;
+}
+__device__ __forceinline__ float pair_r2_exact(const float4& pi, const float4& pj, const MinImage& b) {
+  float dx, dy, dz, r2;
+  pair_d_exact(pi, pj, b, &dx, &dy, &dz, &r2);
+  return r2;
 }
 // Cells per dimension are capped so that a cell's coordinates pack into
 // 10 bits each (larger cells stay correct).
@@ -245,8 +250,8 @@ struct Workspace {
   int* d_nbr_ang = nullptr;
   int* d_rad_off = nullptr;
   int* d_ang_off = nullptr;
-  int* d_angpos = nullptr;     // [n][max_ang] position of each angular neighbour in the radial list
-  float3* d_contrib = nullptr; // [n][max_rad] force on atom i from the centre at its radial slot
+  float3* d_contrib = nullptr; // force on atom i from the centre at its angular slot, [n][max_ang]; after
+                               // a list overflow at its radial slot, [n][max_rad]
   double* d_self = nullptr;    // [n][3] force on each atom from its own environment
   double* d_part = nullptr;    // per-wavefront FP64 energy partials
   int max_part = 0;
@@ -282,6 +287,7 @@ struct nnp_model : nnp::Workspace {
   // device weights
   void* d_wmat = nullptr;
   float* d_wvec = nullptr;
+  const float* d_shifts = nullptr;      // the scaled radial shifts (behind the vectors in d_wvec)
   void* d_wrow = nullptr;               // BF16: W1, W2, W3 row-major (the LDS-resident network kernel)
   int64_t wrow_per_species = 0;         // elements per (member, species) in d_wrow
   int64_t mat_per_species = 0, vec_per_species = 0;
