@@ -59,7 +59,9 @@ WORKLOADS = {
 # VALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 3.93e13 lane-operations/s (unpacked FP32
 # and FP64 issue at that rate; transcendentals at a quarter of it, counted as 4 operations).
 PEAK_HBM_GBS = 8000.0
-PEAK_MFMA_TFLOPS = {"fp32": 157.3, "bf16": 2500.0}
+# The FP32 network form runs on FP16 operand pairs, three FP16 products per FP32 one ("split"); with
+# the MM channel it uses the FP32 matrix instructions.
+PEAK_MFMA_TFLOPS = {"fp32": 157.3, "split": 2500.0 / 3, "bf16": 2500.0}
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 
 # Algorithmic VALU lane-operations per unit of work (transcendental = 4): the arithmetic the
@@ -123,12 +125,17 @@ def kernel_sources():
     return out
 
 
+def network_form(prec, cfg):
+    """How the network's products run (a key of PEAK_MFMA_TFLOPS)."""
+    return "bf16" if prec == "bf16" else ("fp32" if cfg.get("extra_inputs", 0) else "split")
+
+
 def stage_kernel(stage, variants, prec, cfg, periodic=True):
     """Name (as the profiler prints it, without namespaces and arguments) of the kernel
     that runs a stage, given the variants the library reports."""
     widths = list(cfg["widths"])
     k0 = (widths[0] + 31) // 32 * 32
-    bf = "true" if prec == "bf16" else "false"
+    op = {"fp32": 0, "bf16": 1, "split": 2}[network_form(prec, cfg)]
     v = variants or {}
     if stage == "neighbours":
         return "k_neighbours" if v.get("neighbours", 0) == 0 else "k_neighbours_cell"
@@ -137,7 +144,7 @@ def stage_kernel(stage, variants, prec, cfg, periodic=True):
                 "k_desc_fwd_pool<4>"][v.get("descriptor", 1)]
     if stage == "network":
         nv = v.get("network", 2)
-        dims = f"{k0}, {widths[1]}, {widths[2]}, {widths[3]}, {bf}"
+        dims = f"{k0}, {widths[1]}, {widths[2]}, {widths[3]}, {op}"
         if widths[-1] == 2:   # charge output: one kernel template, (columns, mixed, wavefronts) per variant
             c, mixed, nw = {2: (2, False, 4), 3: (2, False, 4), 4: (2, True, 4), 5: (1, False, 8),
                             6: (2, True, 8), 7: (2, False, 8)}.get(nv, (1, False, 4))
@@ -147,6 +154,8 @@ def stage_kernel(stage, variants, prec, cfg, periodic=True):
         if nv in (8, 9):
             nv = 2
         cols = {1: 1, 2: 2, 3: 4 if k0 <= 128 else 2}.get(nv)
+        if nv == 3 and cols == 4 and op == 2:
+            return f"k_mlp_split8<{dims}, 4, false>"
         if nv == 4:
             return f"k_mlp_mixed<{dims}>"
         if nv in (5, 6, 7):
@@ -527,13 +536,14 @@ def _roofline(res, cfg, prec, stage, workload, periodic):
     if stage == "network":
         flops = network_flops_per_atom(widths) * n * res.get("n_members", 1)
         ach = flops / t / 1e12
-        return {"kernel": kernel, "bound": "mfma", "achieved": ach, "peak": PEAK_MFMA_TFLOPS[prec],
-                "unit": "TFLOP/s", "frac": ach / PEAK_MFMA_TFLOPS[prec], "traffic": traffic,
+        peak = PEAK_MFMA_TFLOPS[network_form(prec, cfg)]
+        return {"kernel": kernel, "bound": "mfma", "achieved": ach, "peak": peak,
+                "unit": "TFLOP/s", "frac": ach / peak, "traffic": traffic,
                 "algorithmic_per_launch": flops}
     if stage in ("adjoint", "descriptor"):
         if stage == "adjoint":
             ops = OPS_BWD_RAD_PAIR * res["rad_pairs"] + OPS_BWD_TRIPLET * res["triplets"]
-            byts = n * (4 * D + 16) + 12 * res["rad_pairs"] + 24 * n
+            byts = n * (4 * D + 16) + 24 * n
         else:
             ops = OPS_FWD_RAD_PAIR * res["rad_pairs"] + OPS_FWD_TRIPLET * res["triplets"]
             byts = n * (16 + 4 * D)

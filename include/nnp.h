@@ -121,8 +121,9 @@ typedef struct {
  * SplitMix64 outputs 2t and 2t+1 (Steele, Lea & Flood 2014) through Box-Muller
  * z = sqrt(-2 ln(1-u0)) cos(2 pi u1); W ~ N(0, 2/(fan_in+fan_out)),
  * b ~ N(0, 0.01); each value rounded once to FP32.
- * prec selects the network arithmetic: NNP_FP32 (FP32 matrix cores) or
- * NNP_BF16 (BF16 operands, FP32 accumulation).  Descriptors and their
+ * prec selects the network arithmetic: NNP_FP32 (FP32 accuracy: FP16 operand
+ * pairs of 22 bits with FP32 accumulation, or FP32 matrix instructions with
+ * the MM channel) or NNP_BF16 (BF16 operands, FP32 accumulation).  Descriptors and their
  * derivatives are FP32 in both forms; energies and force accumulation FP64.
  * Uses the current HIP device; allocates the device weights.  *out is set
  * on success.
@@ -346,8 +347,8 @@ typedef enum {
  *     segments and angular classes cut into equal chunks, one per lane
  *     (for several elements, whose classes hold few pairs each);
  *   network: 0 register-resident wavefronts; 1 / 2 / 3 row-split workgroups
- *     of 16 / 32 / 64 atoms (64 for water-sized networks only, wider ones
- *     use 32); 4 workgroups of 32 atoms, 16 for the species with the fewest
+ *     of 16 / 32 / 64 atoms (64 for water-sized networks only, in the FP32
+ *     form with eight wavefronts; wider ones use 32); 4 workgroups of 32 atoms, 16 for the species with the fewest
  *     atoms (more even workgroups for small systems); 5 / 6 / 7 as 1 / 4 / 2
  *     with eight wavefronts per workgroup instead of four (shorter chains
  *     per tile, for systems with few tiles or wide networks); 8 / 9 (BF16

@@ -423,11 +423,22 @@ nnp_status nnp_create(const nnp_config* cfg, uint64_t seed, const float* weights
   }
   std::vector<uint8_t> mat;
   std::vector<float> vec;
+  if (split_form(*m)) weight_bounds(*m);
   pack_weights(*m, mat, vec, m->mat_per_species, m->vec_per_species);
   const size_t shifts_at = vec.size();
   vec.insert(vec.end(), p.rad_shift_s, p.rad_shift_s + kRadShifts);
-  hipError_t e = hipMalloc(&m->d_wmat, mat.size());
-  if (e == hipSuccess) e = hipMemcpy(m->d_wmat, mat.data(), mat.size(), hipMemcpyHostToDevice);
+  hipError_t e;
+  if (split_form(*m)) {
+    float* raw = nullptr;
+    e = hipMalloc(&m->d_wmat, (size_t)m->mat_per_species * S * m->n_members * sizeof(float));
+    if (e == hipSuccess) e = dalloc(&raw, total);
+    if (e == hipSuccess) e = hipMemcpy(raw, m->w_host.data(), total * sizeof(float), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = pack_split(*m, raw, m->d_wmat);
+    if (raw) (void)hipFree(raw);   // waits for the packing
+  } else {
+    e = hipMalloc(&m->d_wmat, mat.size());
+    if (e == hipSuccess) e = hipMemcpy(m->d_wmat, mat.data(), mat.size(), hipMemcpyHostToDevice);
+  }
   if (e == hipSuccess) e = dalloc(&m->d_wvec, vec.size());
   if (e == hipSuccess) e = hipMemcpy(m->d_wvec, vec.data(), vec.size() * sizeof(float), hipMemcpyHostToDevice);
   m->d_shifts = m->d_wvec + shifts_at;

@@ -5,14 +5,14 @@
 // Layout trick.  Each wavefront owns 16 atoms of one species and computes the
 // TRANSPOSED products  H_l^T [features x 16 atoms] = W_l [out x in] * H_{l-1}^T,
 // so the weights are the A operand and the activations the B operand of
-// v_mfma_f32_16x16x{4f32,32_bf16}.  The accumulator layout of one 16x16
+// v_mfma_f32_16x16x{4_f32,32_f16,32_bf16}.  The accumulator layout of one 16x16
 // output tile (lane = atom + 16 q holds features 4q..4q+3) is exactly the B
 // operand layout the next layer needs for a 16-wide (FP32) or, taking two
-// tiles, 32-wide (BF16) K block, provided the K dimension is permuted the same
+// tiles, 32-wide (16-bit operands) K block, provided the K dimension is permuted the same
 // way in the packed weights.  The whole chain -- three hidden layers, the
 // output layer, and the three backward products -- therefore stays in
-// registers: no LDS, no barriers.  Weights are pre-packed on the host in
-// fragment order (one 16-byte load per lane per MFMA step).
+// registers: no LDS, no barriers.  Weights are pre-packed in fragment order
+// (one 16-byte load per lane per MFMA step; two for a pair of FP16 planes).
 //
 // Backward: e = w4 . h3 + b4, delta3 = w4 o celu'(u3), delta2 = (W3^T delta3) o
 // celu'(u2), delta1 = (W2^T delta2) o celu'(u1), dE/dx = W1^T delta1, with
@@ -28,17 +28,37 @@ namespace {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef __bf16 v4bf __attribute__((ext_vector_type(4)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 
 constexpr int kBlock = 256;
 constexpr float kLog2e = 1.4426950408889634f;
 
-__device__ __forceinline__ v4f mfma_step(const v4f& w, const v4f& b, v4f c) {
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[0], b[0], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[1], b[1], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[2], b[2], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[3], b[3], c, 0, 0, 0);
-  return c;
-}
+// How a product is computed.
+//   kOpF32   FP32 operands, 16x16x4 FP32 matrix instructions;
+//   kOpBF16  BF16 operands, 16x16x32;
+//   kOpSplit the FP32 form on the FP16 matrix cores: an operand x is held as
+//     hi = fp16(x s) and lo = fp16((x s - hi) 2^11), s a power of two for the
+//     whole operand (nnp_internal.h, SplitScales), and a product sums hi hi in
+//     one FP32 accumulator, hi lo + lo hi in another: three instructions of
+//     K = 32 instead of eight of K = 4 with twice the cycles each (48 against
+//     256 matrix-core cycles per 16 x 16 x 32 block).  hi + lo 2^-11 carries 22
+//     to 23 significant bits, the products are exact in FP32, and the term left
+//     out (lo lo) is below 2^-22 of hi hi; one accumulator takes 8 times fewer
+//     roundings than with the FP32 instruction.  Force error against float64
+//     as before (water, 12,288 atoms: 1.5e-6 both).  Network, FP32
+//     instructions -> split: 261,000 atoms 569 -> 239 us, 12,288 atoms 36.4 ->
+//     21.2, eight networks 235 -> 110, 29,000 H/C/N/O atoms 231 -> 100.  What
+//     bounds it at 261,000 atoms: the stream of weight fragments from L2
+//     (14 TB/s; 205 us when every fragment is a cache hit, 161 with variant 2)
+//     and the six dependent products of a tile; the matrix cores are busy for
+//     67 us of it and the VALU for about 100.
+enum Op { kOpF32 = 0, kOpBF16 = 1, kOpSplit = 2 };
+constexpr float kSplitUp = 2048.f, kSplitDown = 1.f / 2048.f;
+
+struct SplitFrag {
+  v8h hi, lo;
+};
 
 __device__ __forceinline__ v8bf to_bf16x8(const v4f& lo, const v4f& hi) {
   v8bf r;
@@ -53,69 +73,161 @@ __device__ __forceinline__ v4bf to_bf16x4(const v4f& v) {
   return r;
 }
 
+// hi and lo of v s.  Each line is one mixed-precision fma per element (a zero
+// addend is written so that the compiler keeps the fma, which rounds to FP16
+// in the same instruction).
+__device__ __forceinline__ void to_split4(const v4f& v, float s, v4h* hi, v4h* lo) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) (*hi)[t] = (_Float16)__builtin_fmaf(v[t], s, 0.f);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const float r = __builtin_fmaf(v[t], s, -(float)(*hi)[t]);
+    (*lo)[t] = (_Float16)__builtin_fmaf(r, kSplitUp, 0.f);
+  }
+}
+
+__device__ __forceinline__ v8h join_half(const v4h& a, const v4h& b) {
+  return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+__device__ __forceinline__ SplitFrag to_split8(const v4f& a, const v4f& b, float s) {
+  v4h ah, al, bh, bl;
+  to_split4(a, s, &ah, &al);
+  to_split4(b, s, &bh, &bl);
+  return SplitFrag{join_half(ah, bh), join_half(al, bl)};
+}
+
 // Weight fragments are streamed from L2 with a prefetch ring: the loads for
 // K block kb + kPrefetch are issued before the products of block kb, so
 // several fragment loads are in flight behind the matrix-core work.  (The
 // wide H/C/N/O networks keep a shallower ring to stay clear of spills.)
 // A BF16 step is an eighth of an FP32 step's matrix-core time, so its ring is
 // deeper.
-template <bool BF16, bool WIDE>
+template <int OP, bool WIDE>
 struct PrefetchDepth {
-  static constexpr int value = WIDE ? (BF16 ? 3 : 2) : (BF16 ? 6 : 3);
+  static constexpr int value = OP == kOpBF16 ? (WIDE ? 3 : 6) : OP == kOpSplit ? 2 : (WIDE ? 2 : 3);
 };
 
-template <bool BF16>
-struct Frag {
-  using T = v4f;
+// Operand fragments (FP32: 16 K values per step, four per lane; else 32 and
+// eight) and accumulators of one 16 x 16 tile.
+template <int OP>
+struct Ops;
+template <>
+struct Ops<kOpF32> {
+  using Frag = v4f;
+  using Acc = v4f;
+  static constexpr int kK = 16;
 };
 template <>
-struct Frag<true> {
-  using T = v8bf;
+struct Ops<kOpBF16> {
+  using Frag = v8bf;
+  using Acc = v4f;
+  static constexpr int kK = 32;
 };
+template <>
+struct Ops<kOpSplit> {
+  using Frag = SplitFrag;
+  struct Acc {
+    v4f a, l;   // hi hi, and 2^11 (hi lo + lo hi)
+  };
+  static constexpr int kK = 32;
+};
+using SplitAcc = Ops<kOpSplit>::Acc;
 
-__device__ __forceinline__ v4f mma(const v4f& w, const v4f& b, v4f c) { return mfma_step(w, b, c); }
-__device__ __forceinline__ v4f mma(const v8bf& w, const v8bf& b, v4f c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, b, c, 0, 0, 0);
+__device__ __forceinline__ void mma(const v4f& w, const v4f& b, v4f& c) {
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[0], b[0], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[1], b[1], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[2], b[2], c, 0, 0, 0);
+  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[3], b[3], c, 0, 0, 0);
+}
+__device__ __forceinline__ void mma(const v8bf& w, const v8bf& b, v4f& c) {
+  c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ void mma(const SplitFrag& w, const SplitFrag& b, SplitAcc& c) {
+  c.a = __builtin_amdgcn_mfma_f32_16x16x32_f16(w.hi, b.hi, c.a, 0, 0, 0);
+  c.l = __builtin_amdgcn_mfma_f32_16x16x32_f16(w.hi, b.lo, c.l, 0, 0, 0);
+  c.l = __builtin_amdgcn_mfma_f32_16x16x32_f16(w.lo, b.hi, c.l, 0, 0, 0);
 }
 
-// out[R/16 tiles] (+)= W[R x C] * in[C/16 tiles]; `in` is register resident.
-// Row tiles are processed in chunks of CH to bound the live accumulators.
-template <int R, int C, bool BF16, int CH>
-__device__ __forceinline__ void gemm_regs(const void* __restrict__ W, const v4f* in, v4f* out, int lane) {
-  static_assert(R % 16 == 0 && C % (BF16 ? 32 : 16) == 0, "tile sizes");
-  constexpr int kPrefetch = PrefetchDepth<BF16, (R > 160 || C > 160)>::value;
+// Start of an accumulator from the bias tile, and its value at the end (s:
+// the inverse of the operands' scales; it does not apply to unscaled forms).
+__device__ __forceinline__ void acc_start(v4f& c, const v4f& bias) { c = bias; }
+__device__ __forceinline__ void acc_start(SplitAcc& c, const v4f&) {
+  c.a = v4f{0.f, 0.f, 0.f, 0.f};
+  c.l = c.a;
+}
+__device__ __forceinline__ v4f acc_value(const v4f& c, const v4f&, float) { return c; }
+__device__ __forceinline__ v4f acc_value(const SplitAcc& c, const v4f& bias, float s) {
+  v4f r;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) r[t] = fmaf(fmaf(c.l[t], kSplitDown, c.a[t]), s, bias[t]);
+  return r;
+}
+
+// Fragment f of the packed weights, this lane's part (split: all hi parts of
+// the fragment, then all lo parts).  The fragment's address is uniform and
+// the lane's a 32-bit offset, so that no address is computed per lane.
+__device__ __forceinline__ void load_frag(const void* W, int f, int lane, v4f* out) {
+  *out = *reinterpret_cast<const v4f*>(static_cast<const char*>(W) + (size_t)f * 1024 + (uint32_t)lane * 16u);
+}
+__device__ __forceinline__ void load_frag(const void* W, int f, int lane, v8bf* out) {
+  *out = *reinterpret_cast<const v8bf*>(static_cast<const char*>(W) + (size_t)f * 1024 + (uint32_t)lane * 16u);
+}
+__device__ __forceinline__ void load_frag(const void* W, int f, int lane, SplitFrag* out) {
+  const char* p = static_cast<const char*>(W) + (size_t)f * 2048;
+  out->hi = *reinterpret_cast<const v8h*>(p + (uint32_t)lane * 16u);
+  out->lo = *reinterpret_cast<const v8h*>(p + 1024 + (uint32_t)lane * 16u);
+}
+
+// B fragment of K block kb from register tiles of 16 features.
+__device__ __forceinline__ void make_frag(const v4f* in, int kb, float, v4f* out) { *out = in[kb]; }
+__device__ __forceinline__ void make_frag(const v4f* in, int kb, float, v8bf* out) {
+  *out = to_bf16x8(in[2 * kb], in[2 * kb + 1]);
+}
+__device__ __forceinline__ void make_frag(const v4f* in, int kb, float s, SplitFrag* out) {
+  *out = to_split8(in[2 * kb], in[2 * kb + 1], s);
+}
+
+// out[R/16 tiles] = bias tiles `out` + W[R x C] * in[C/16 tiles]; `in` is
+// register resident.  Row tiles are processed in chunks of CH to bound the
+// live accumulators.
+template <int R, int C, int OP, int CH>
+__device__ __forceinline__ void gemm_regs(const void* __restrict__ W, const v4f* in, v4f* out, int lane, float s_in,
+                                          float s_out) {
+  static_assert(R % 16 == 0 && C % Ops<OP>::kK == 0, "tile sizes");
+  constexpr int kPrefetch = PrefetchDepth<OP, (R > 160 || C > 160)>::value;
   constexpr int RT = R / 16;
-  constexpr int KB = BF16 ? C / 32 : C / 16;
-  using F = typename Frag<BF16>::T;
-  const F* Wp = reinterpret_cast<const F*>(W);
+  constexpr int KB = C / Ops<OP>::kK;
+  using F = typename Ops<OP>::Frag;
 #pragma unroll
   for (int r0 = 0; r0 < RT; r0 += CH) {
     const int nr = (r0 + CH < RT ? CH : RT - r0);
     F ring[kPrefetch][CH];
+    typename Ops<OP>::Acc acc[CH];
+#pragma unroll
+    for (int r = 0; r < CH; ++r)
+      if (r < nr) acc_start(acc[r], out[r0 + r]);
 #pragma unroll
     for (int p = 0; p < kPrefetch; ++p)
 #pragma unroll
       for (int r = 0; r < CH; ++r)
-        if (p < KB && r < nr) ring[p][r] = Wp[((r0 + r) * KB + p) * 64 + lane];
+        if (p < KB && r < nr) load_frag(W, (r0 + r) * KB + p, lane, &ring[p][r]);
 #pragma unroll
     for (int kb = 0; kb < KB; ++kb) {
-      F cur[CH];
+      F cur[CH], b;
 #pragma unroll
       for (int r = 0; r < CH; ++r) {
         cur[r] = ring[kb % kPrefetch][r];
-        if (kb + kPrefetch < KB && r < nr) ring[kb % kPrefetch][r] = Wp[((r0 + r) * KB + kb + kPrefetch) * 64 + lane];
+        if (kb + kPrefetch < KB && r < nr) load_frag(W, (r0 + r) * KB + kb + kPrefetch, lane, &ring[kb % kPrefetch][r]);
       }
-      if constexpr (BF16) {
-        const v8bf b = to_bf16x8(in[2 * kb], in[2 * kb + 1]);
+      make_frag(in, kb, s_in, &b);
 #pragma unroll
-        for (int r = 0; r < CH; ++r)
-          if (r < nr) out[r0 + r] = mma(cur[r], b, out[r0 + r]);
-      } else {
-#pragma unroll
-        for (int r = 0; r < CH; ++r)
-          if (r < nr) out[r0 + r] = mma(cur[r], in[kb], out[r0 + r]);
-      }
+      for (int r = 0; r < CH; ++r)
+        if (r < nr) mma(cur[r], b, acc[r]);
     }
+#pragma unroll
+    for (int r = 0; r < CH; ++r)
+      if (r < nr) out[r0 + r] = acc_value(acc[r], out[r0 + r], s_out);
   }
 }
 
@@ -124,6 +236,20 @@ __device__ __forceinline__ float celu_f(float u, float alpha, float inv_alpha_l2
 }
 __device__ __forceinline__ float celu_grad_from_h(float h, float inv_alpha) {
   return h > 0.f ? 1.f : h * inv_alpha + 1.f;
+}
+// The forms the split products use: h = med3(u, alpha t - alpha, 0) with
+// t = 2^(u log2(e) / alpha), since 0 < u < alpha (t - 1) for u > 0 and
+// u <= alpha (t - 1) <= 0 otherwise, and celu' = min(h / alpha + 1, 1).
+template <int OP>
+__device__ __forceinline__ float celu_of(float u, float alpha, float inv_alpha_l2) {
+  if constexpr (OP == kOpSplit)
+    return __builtin_amdgcn_fmed3f(u, fmaf(alpha, __builtin_amdgcn_exp2f(u * inv_alpha_l2), -alpha), 0.f);
+  return celu_f(u, alpha, inv_alpha_l2);
+}
+template <int OP>
+__device__ __forceinline__ float celu_grad_of(float h, float inv_alpha) {
+  if constexpr (OP == kOpSplit) return fminf(fmaf(h, inv_alpha, 1.f), 1.f);
+  return celu_grad_from_h(h, inv_alpha);
 }
 
 // Packed per-(member, species) layout of the matrices, in elements:
@@ -142,63 +268,109 @@ struct Own {  // number of row tiles r = w + NW j owned by one of NW wavefronts
   static constexpr int n = (R + NW - 1) / NW;
 };
 
+// Bias tiles of the row tiles r = w + NW j of a layer with R outputs.
+template <int R, int NW>
+__device__ __forceinline__ void load_bias(const float* b, int w, int q, v4f* out) {
+#pragma unroll
+  for (int j = 0; j < Own<R / 16, NW>::n; ++j) {
+    const int r = w + NW * j;
+    out[j] = r < R / 16 ? *reinterpret_cast<const v4f*>(b + 16 * r + 4 * q) : v4f{0.f, 0.f, 0.f, 0.f};
+  }
+}
+
 // Layer outputs in LDS, per column tile c and row tile r (16 features):
 //   FP32: one v4f per lane at [(c * tiles + r) * 64 + lane];
 //   BF16: rounded once by the producer, two row tiles form the 16-byte B
 //     fragment of one 32-wide K block, [(c * tiles/2 + r/2) * 64 + lane],
-//     row tile r filling half r % 2 (the K permutation of the packed weights).
-template <bool BF16>
-__device__ __forceinline__ void put_tile(v4f* buf, int tiles, int c, int r, int lane, const v4f& v) {
-  if constexpr (BF16)
+//     row tile r filling half r % 2 (the K permutation of the packed weights);
+//   split: two planes (hi, lo) laid out as BF16, `plane` 16-byte pieces apart.
+template <int OP>
+__device__ __forceinline__ void put_tile(v4f* buf, int tiles, int plane, int c, int r, int lane, const v4f& v,
+                                         float s) {
+  if constexpr (OP == kOpBF16) {
     reinterpret_cast<v4bf*>(buf)[((c * (tiles / 2) + (r >> 1)) * 64 + lane) * 2 + (r & 1)] = to_bf16x4(v);
-  else
+  } else if constexpr (OP == kOpSplit) {
+    v4h hi, lo;
+    to_split4(v, s, &hi, &lo);
+    v4h* b = reinterpret_cast<v4h*>(buf) + ((c * (tiles / 2) + (r >> 1)) * 64 + lane) * 2 + (r & 1);
+    b[0] = hi;
+    b[2 * plane] = lo;
+  } else {
     buf[(c * tiles + r) * 64 + lane] = v;
+  }
 }
 
-// out[j][c] = A-rows (w + 4 j) of W [R x K] times the K/16 LDS tiles `in[c][kb]`.
-template <int R, int K, bool BF16, int C, int NW>
-__device__ __forceinline__ void gemm_lds(const void* __restrict__ W, const v4f* in, int in_tiles, v4f (*out)[C],
-                                         int w, int lane, int cw) {
-  constexpr int NJ = Own<R, NW>::n;
-  constexpr int KB = BF16 ? K / 32 : K / 16;
-  constexpr int kPrefetch = PrefetchDepth<BF16, (16 * R > 160 || K > 160)>::value;
-  using F = typename Frag<BF16>::T;
-  const F* Wp = reinterpret_cast<const F*>(W);
+__device__ __forceinline__ void get_frag(const v4f* buf, int tiles, int, int c, int kb, int lane, v4f* out) {
+  *out = buf[(c * tiles + kb) * 64 + lane];
+}
+__device__ __forceinline__ void get_frag(const v4f* buf, int tiles, int, int c, int kb, int lane, v8bf* out) {
+  *out = reinterpret_cast<const v8bf*>(buf)[(c * (tiles / 2) + kb) * 64 + lane];
+}
+__device__ __forceinline__ void get_frag(const v4f* buf, int tiles, int plane, int c, int kb, int lane,
+                                         SplitFrag* out) {
+  const v8h* b = reinterpret_cast<const v8h*>(buf) + (c * (tiles / 2) + kb) * 64 + lane;
+  out->hi = b[0];
+  out->lo = b[plane];
+}
+
+// out[j][c] = bias(j) + A-rows (w + NW j), j < NJ, of W [R tiles x K] times
+// the LDS tiles `in` (in_tiles row tiles per column tile).
+template <int R, int K, int OP, int C, int NW, int NJ>
+__device__ __forceinline__ void gemm_lds_rows(const void* __restrict__ W, const v4f* in, int in_tiles, int plane,
+                                              const v4f* bias, v4f (*out)[C], int w, int lane, int cw, float s_out) {
+  constexpr int KB = K / Ops<OP>::kK;
+  constexpr int kPrefetch = PrefetchDepth<OP, (16 * R > 160 || K > 160)>::value;
+  using F = typename Ops<OP>::Frag;
   F ring[kPrefetch][NJ];
+  typename Ops<OP>::Acc acc[NJ][C];
 #pragma unroll
   for (int p = 0; p < kPrefetch; ++p)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int r = w + NW * j;
-      if (p < KB && r < R) ring[p][j] = Wp[(r * KB + p) * 64 + lane];
-    }
+    for (int j = 0; j < NJ; ++j)
+      if (p < KB) load_frag(W, (w + NW * j) * KB + p, lane, &ring[p][j]);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc_start(acc[j][c], bias[j]);
 #pragma unroll
   for (int kb = 0; kb < KB; ++kb) {
     F cur[NJ];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
-      const int r = w + NW * j;
       cur[j] = ring[kb % kPrefetch][j];
-      if (kb + kPrefetch < KB && r < R) ring[kb % kPrefetch][j] = Wp[(r * KB + kb + kPrefetch) * 64 + lane];
+      if (kb + kPrefetch < KB) load_frag(W, (w + NW * j) * KB + kb + kPrefetch, lane, &ring[kb % kPrefetch][j]);
     }
     F bv[C];
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      if (c >= cw) continue;   // a narrow tile (workgroup-uniform)
-      if constexpr (BF16)
-        bv[c] = reinterpret_cast<const v8bf*>(in)[(c * (in_tiles / 2) + kb) * 64 + lane];
-      else
-        bv[c] = in[(c * in_tiles + kb) * 64 + lane];
-    }
+    for (int c = 0; c < C; ++c)
+      if (c < cw) get_frag(in, in_tiles, plane, c, kb, lane, &bv[c]);   // (a narrow tile is workgroup-uniform)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      const int r = w + NW * j;
-      if (r < R) {
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
-        for (int c = 0; c < C; ++c)
-          if (c < cw) out[j][c] = mma(cur[j], bv[c], out[j][c]);
-      }
-    }
+      for (int c = 0; c < C; ++c)
+        if (c < cw) mma(cur[j], bv[c], acc[j][c]);
+    // keep the ring: the scheduler would move the loads down to their use
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int c = 0; c < C; ++c) out[j][c] = acc_value(acc[j][c], bias[j], s_out);
+}
+
+// One wavefront-uniform branch on the number of row tiles the wavefront owns:
+// a test per tile inside the loop would cut it into short blocks.
+template <int R, int K, int OP, int C, int NW>
+__device__ __forceinline__ void gemm_lds(const void* __restrict__ W, const v4f* in, int in_tiles, int plane,
+                                         const v4f* bias, v4f (*out)[C], int w, int lane, int cw, float s_out) {
+  constexpr int most = Own<R, NW>::n, rest = R % NW;
+  if (rest == 0 || w < rest) {
+    gemm_lds_rows<R, K, OP, C, NW, most>(W, in, in_tiles, plane, bias, out, w, lane, cw, s_out);
+  } else {
+    if constexpr (most > 1)
+      gemm_lds_rows<R, K, OP, C, NW, most - 1>(W, in, in_tiles, plane, bias, out, w, lane, cw, s_out);
+#pragma unroll
+    for (int c = 0; c < C; ++c) out[most - 1][c] = v4f{0.f, 0.f, 0.f, 0.f};
   }
 }
 
@@ -206,7 +378,7 @@ __device__ __forceinline__ void gemm_lds(const void* __restrict__ W, const v4f* 
 // potential phi_i (input column phi_col): the atomic energy is e_i + q_i phi_i,
 // the backward seed of the last hidden layer is (w_e + phi_i w_q), and q_i is
 // written out for the MM adjoint (dE/dphi_i gets the direct term q_i).
-template <int K0, int N1, int N2, int N3, bool BF16, int C, bool MIXED, int NW, bool CHG>
+template <int K0, int N1, int N2, int N3, int OP, int C, bool MIXED, int NW, bool CHG>
 __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
   constexpr int oF1 = 0, oF2 = oF1 + N1 * K0, oF3 = oF2 + N2 * N1;
   constexpr int oB1 = oF3 + N3 * N2, oB2 = oB1 + K0 * N1, oB3 = oB2 + N1 * N2;
@@ -214,13 +386,15 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
   constexpr int owq = ob4 + 4, obq = owq + N3;   // charge row (CHG)
   constexpr int TX = (K0 > N2 ? K0 : N2) / 16;        // tiles of buffer X (x, then H2, then delta2)
   constexpr int TA = (N1 > N3 ? N1 : N3) / 16;        // tiles of buffer A (H1, then delta3, then delta1)
-  using Elem = typename std::conditional<BF16, __bf16, float>::type;
-  __shared__ v4f bufX[C * TX * (BF16 ? 32 : 64)];   // BF16 tiles take half the space
-  __shared__ v4f bufA[C * TA * (BF16 ? 32 : 64)];
+  using Elem = typename std::conditional<OP == kOpBF16, __bf16, float>::type;   // (a split pair is four bytes)
+  constexpr int kTile = OP == kOpBF16 ? 32 : 64;      // BF16 tiles take half the space
+  constexpr int PX = C * TX * 32, PA = C * TA * 32;   // 16-byte pieces per plane (split)
+  __shared__ v4f bufX[C * TX * kTile];
+  __shared__ v4f bufA[C * TA * kTile];
   __shared__ float epart[NW][C * 16];
   __shared__ float qpart[CHG ? NW : 1][C * 16];
 
-  const int w = threadIdx.x >> 6;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: uniform branches and weight addresses
   const int lane = threadIdx.x & 63;
   const int q = lane >> 4;
   const int col = lane & 15;
@@ -245,6 +419,10 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
   if (s < 0) return;   // whole workgroup exits together
   const float inv_alpha = 1.f / alpha;
   const float inv_alpha_l2 = kLog2e / alpha;
+  constexpr int kMost = Own<(K0 > N1 ? K0 : N1) / 16, NW>::n;
+  v4f zeros[kMost];
+#pragma unroll
+  for (int j = 0; j < kMost; ++j) zeros[j] = v4f{0.f, 0.f, 0.f, 0.f};
 
   float e_acc[C], q_acc[C];
 #pragma unroll
@@ -265,7 +443,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
 
     // stage x in fragment layout (again for every member: the buffer is reused
     // by later products): tile (c, kb), lane l holds x[row c*16 + l%16][16 kb + 4 (l/16) .. +3]
-    if constexpr (BF16) {   // K block kb of 32 features: tiles 2 kb and 2 kb + 1
+    if constexpr (OP != kOpF32) {   // K block kb of 32 features: tiles 2 kb and 2 kb + 1
       for (int t = threadIdx.x; t < C * (K0 / 32) * 64; t += 64 * NW) {
         const int l = t & 63, kb = (t >> 6) % (K0 / 32), c = (t >> 6) / (K0 / 32);
         const int row = row0 + c * 16 + (l & 15);
@@ -275,7 +453,14 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
           lo = *reinterpret_cast<const v4f*>(src);
           hi = *reinterpret_cast<const v4f*>(src + 16);
         }
-        reinterpret_cast<v8bf*>(bufX)[(c * (TX / 2) + kb) * 64 + l] = to_bf16x8(lo, hi);
+        const int at = (c * (TX / 2) + kb) * 64 + l;
+        if constexpr (OP == kOpBF16) {
+          reinterpret_cast<v8bf*>(bufX)[at] = to_bf16x8(lo, hi);
+        } else {
+          const SplitFrag f = to_split8(lo, hi, a.split.x);
+          reinterpret_cast<v8h*>(bufX)[at] = f.hi;
+          reinterpret_cast<v8h*>(bufX)[PX + at] = f.lo;
+        }
       }
     } else {
       for (int t = threadIdx.x; t < C * (K0 / 16) * 64; t += 64 * NW) {
@@ -289,70 +474,61 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
     __syncthreads();
 
     // ---- layer 1: h1 = celu(W1 x + b1)       X -> A
-    v4f h1[Own<N1, NW>::n][C];
-#pragma unroll
-    for (int j = 0; j < Own<N1, NW>::n; ++j) {
-      const int r = w + NW * j;
-      const v4f bias = r < N1 / 16 ? *reinterpret_cast<const v4f*>(V + ob1 + 16 * r + 4 * q) : v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < C; ++c) h1[j][c] = bias;
+    v4f h1[Own<N1 / 16, NW>::n][C];
+    {
+      v4f bias[Own<N1 / 16, NW>::n];
+      load_bias<N1, NW>(V + ob1, w, q, bias);
+      gemm_lds<N1 / 16, K0, OP, C, NW>(Wm + oF1, bufX, TX, PX, bias, h1, w, lane, cw, a.split.f1);
     }
-    gemm_lds<N1 / 16, K0, BF16, C, NW>(Wm + oF1, bufX, TX, h1, w, lane, cw);
 #pragma unroll
-    for (int j = 0; j < Own<N1, NW>::n; ++j) {
+    for (int j = 0; j < Own<N1 / 16, NW>::n; ++j) {
       const int r = w + NW * j;
       if (r < N1 / 16) {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
 #pragma unroll
-          for (int t = 0; t < 4; ++t) h1[j][c][t] = celu_f(h1[j][c][t], alpha, inv_alpha_l2);
-          put_tile<BF16>(bufA, TA, c, r, lane, h1[j][c]);
+          for (int t = 0; t < 4; ++t) h1[j][c][t] = celu_of<OP>(h1[j][c][t], alpha, inv_alpha_l2);
+          put_tile<OP>(bufA, TA, PA, c, r, lane, h1[j][c], a.split.h1);
         }
       }
     }
     __syncthreads();
 
     // ---- layer 2: h2 = celu(W2 h1 + b2)      A -> X
-    v4f h2[Own<N2, NW>::n][C];
-#pragma unroll
-    for (int j = 0; j < Own<N2, NW>::n; ++j) {
-      const int r = w + NW * j;
-      const v4f bias = r < N2 / 16 ? *reinterpret_cast<const v4f*>(V + ob2 + 16 * r + 4 * q) : v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < C; ++c) h2[j][c] = bias;
+    v4f h2[Own<N2 / 16, NW>::n][C];
+    {
+      v4f bias[Own<N2 / 16, NW>::n];
+      load_bias<N2, NW>(V + ob2, w, q, bias);
+      gemm_lds<N2 / 16, N1, OP, C, NW>(Wm + oF2, bufA, TA, PA, bias, h2, w, lane, cw, a.split.f2);
     }
-    gemm_lds<N2 / 16, N1, BF16, C, NW>(Wm + oF2, bufA, TA, h2, w, lane, cw);
     __syncthreads();   // everyone has read A (h1) and X (x) before X is overwritten
 #pragma unroll
-    for (int j = 0; j < Own<N2, NW>::n; ++j) {
+    for (int j = 0; j < Own<N2 / 16, NW>::n; ++j) {
       const int r = w + NW * j;
       if (r < N2 / 16) {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
 #pragma unroll
-          for (int t = 0; t < 4; ++t) h2[j][c][t] = celu_f(h2[j][c][t], alpha, inv_alpha_l2);
-          put_tile<BF16>(bufX, TX, c, r, lane, h2[j][c]);
+          for (int t = 0; t < 4; ++t) h2[j][c][t] = celu_of<OP>(h2[j][c][t], alpha, inv_alpha_l2);
+          put_tile<OP>(bufX, TX, PX, c, r, lane, h2[j][c], a.split.h2);
         }
       }
     }
     __syncthreads();
 
     // ---- layer 3 and the output layer; delta3 = w4 o celu'(h3)   X -> A
-    v4f h3[Own<N3, NW>::n][C];
-#pragma unroll
-    for (int j = 0; j < Own<N3, NW>::n; ++j) {
-      const int r = w + NW * j;
-      const v4f bias = r < N3 / 16 ? *reinterpret_cast<const v4f*>(V + ob3 + 16 * r + 4 * q) : v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int c = 0; c < C; ++c) h3[j][c] = bias;
+    v4f h3[Own<N3 / 16, NW>::n][C];
+    {
+      v4f bias[Own<N3 / 16, NW>::n];
+      load_bias<N3, NW>(V + ob3, w, q, bias);
+      gemm_lds<N3 / 16, N2, OP, C, NW>(Wm + oF3, bufX, TX, PX, bias, h3, w, lane, cw, a.split.f3);
     }
-    gemm_lds<N3 / 16, N2, BF16, C, NW>(Wm + oF3, bufX, TX, h3, w, lane, cw);
     float ep[C];
     float eq[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) ep[c] = eq[c] = 0.f;
 #pragma unroll
-    for (int j = 0; j < Own<N3, NW>::n; ++j) {
+    for (int j = 0; j < Own<N3 / 16, NW>::n; ++j) {
       const int r = w + NW * j;
       if (r < N3 / 16) {
         const v4f w4 = *reinterpret_cast<const v4f*>(V + ow4 + 16 * r + 4 * q);
@@ -363,16 +539,16 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
           v4f d;
 #pragma unroll
           for (int t = 0; t < 4; ++t) {
-            const float h = celu_f(h3[j][c][t], alpha, inv_alpha_l2);
+            const float h = celu_of<OP>(h3[j][c][t], alpha, inv_alpha_l2);
             ep[c] += w4[t] * h;
             if constexpr (CHG) {
               eq[c] += wq[t] * h;
-              d[t] = fmaf(phi[c], wq[t], w4[t]) * celu_grad_from_h(h, inv_alpha);
+              d[t] = fmaf(phi[c], wq[t], w4[t]) * celu_grad_of<OP>(h, inv_alpha);
             } else {
-              d[t] = w4[t] * celu_grad_from_h(h, inv_alpha);
+              d[t] = w4[t] * celu_grad_of<OP>(h, inv_alpha);
             }
           }
-          put_tile<BF16>(bufA, TA, c, r, lane, d);
+          put_tile<OP>(bufA, TA, PA, c, r, lane, d, a.split.d3);
         }
       }
     }
@@ -411,42 +587,34 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
     }
 
     // ---- delta2 = (W3^T delta3) o celu'(h2)    A -> X
-    v4f d2[Own<N2, NW>::n][C];
+    v4f d2[Own<N2 / 16, NW>::n][C];
+    gemm_lds<N2 / 16, N3, OP, C, NW>(Wm + oB3, bufA, TA, PA, zeros, d2, w, lane, cw, a.split.b3);
 #pragma unroll
-    for (int j = 0; j < Own<N2, NW>::n; ++j)
-#pragma unroll
-      for (int c = 0; c < C; ++c) d2[j][c] = v4f{0.f, 0.f, 0.f, 0.f};
-    gemm_lds<N2 / 16, N3, BF16, C, NW>(Wm + oB3, bufA, TA, d2, w, lane, cw);
-#pragma unroll
-    for (int j = 0; j < Own<N2, NW>::n; ++j) {
+    for (int j = 0; j < Own<N2 / 16, NW>::n; ++j) {
       const int r = w + NW * j;
       if (r < N2 / 16) {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
 #pragma unroll
-          for (int t = 0; t < 4; ++t) d2[j][c][t] *= celu_grad_from_h(h2[j][c][t], inv_alpha);
-          put_tile<BF16>(bufX, TX, c, r, lane, d2[j][c]);
+          for (int t = 0; t < 4; ++t) d2[j][c][t] *= celu_grad_of<OP>(h2[j][c][t], inv_alpha);
+          put_tile<OP>(bufX, TX, PX, c, r, lane, d2[j][c], a.split.d2);
         }
       }
     }
     __syncthreads();
 
     // ---- delta1 = (W2^T delta2) o celu'(h1)    X -> A
-    v4f d1[Own<N1, NW>::n][C];
+    v4f d1[Own<N1 / 16, NW>::n][C];
+    gemm_lds<N1 / 16, N2, OP, C, NW>(Wm + oB2, bufX, TX, PX, zeros, d1, w, lane, cw, a.split.b2);
 #pragma unroll
-    for (int j = 0; j < Own<N1, NW>::n; ++j)
-#pragma unroll
-      for (int c = 0; c < C; ++c) d1[j][c] = v4f{0.f, 0.f, 0.f, 0.f};
-    gemm_lds<N1 / 16, N2, BF16, C, NW>(Wm + oB2, bufX, TX, d1, w, lane, cw);
-#pragma unroll
-    for (int j = 0; j < Own<N1, NW>::n; ++j) {
+    for (int j = 0; j < Own<N1 / 16, NW>::n; ++j) {
       const int r = w + NW * j;
       if (r < N1 / 16) {
 #pragma unroll
         for (int c = 0; c < C; ++c) {
 #pragma unroll
-          for (int t = 0; t < 4; ++t) d1[j][c][t] *= celu_grad_from_h(h1[j][c][t], inv_alpha);
-          put_tile<BF16>(bufA, TA, c, r, lane, d1[j][c]);
+          for (int t = 0; t < 4; ++t) d1[j][c][t] *= celu_grad_of<OP>(h1[j][c][t], inv_alpha);
+          put_tile<OP>(bufA, TA, PA, c, r, lane, d1[j][c], a.split.d1);
         }
       }
     }
@@ -455,11 +623,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
     // ---- dE/dx = W1^T delta1 (row tiles over the input features), to memory
     {
       v4f gx[Own<K0 / 16, NW>::n][C];
-#pragma unroll
-      for (int j = 0; j < Own<K0 / 16, NW>::n; ++j)
-#pragma unroll
-        for (int c = 0; c < C; ++c) gx[j][c] = v4f{0.f, 0.f, 0.f, 0.f};
-      gemm_lds<K0 / 16, N1, BF16, C, NW>(Wm + oB1, bufA, TA, gx, w, lane, cw);
+      gemm_lds<K0 / 16, N1, OP, C, NW>(Wm + oB1, bufA, TA, PA, zeros, gx, w, lane, cw, a.split.b1);
 #pragma unroll
       for (int j = 0; j < Own<K0 / 16, NW>::n; ++j) {
         const int r = w + NW * j;
@@ -503,17 +667,17 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
   }
 }
 
-template <int K0, int N1, int N2, int N3, bool BF16, int C>
-__global__ __launch_bounds__(256, K0 <= 128 ? 2 : 1) void k_mlp_split(MlpArgs a, float alpha) {
-  mlp_split_body<K0, N1, N2, N3, BF16, C, false, 4, false>(a, alpha);
+template <int K0, int N1, int N2, int N3, int OP, int C>
+__global__ __launch_bounds__(256, K0 <= 128 ? (OP == kOpSplit && C <= 2 ? 3 : 2) : 1) void k_mlp_split(MlpArgs a, float alpha) {
+  mlp_split_body<K0, N1, N2, N3, OP, C, false, 4, false>(a, alpha);
 }
 
 // Eight wavefronts per 16-atom tile: each owns half as many row tiles of
 // every product, so a tile's chain is shorter.  For systems with too few
 // tiles to fill the GPU (a small ML region: a tile per species).
-template <int K0, int N1, int N2, int N3, bool BF16, int C, bool MIXED>
-__global__ __launch_bounds__(512) void k_mlp_split8(MlpArgs a, float alpha) {
-  mlp_split_body<K0, N1, N2, N3, BF16, C, MIXED, 8, false>(a, alpha);
+template <int K0, int N1, int N2, int N3, int OP, int C, bool MIXED>
+__global__ __launch_bounds__(512, K0 <= 128 && OP == kOpSplit && C <= 2 ? 4 : 2) void k_mlp_split8(MlpArgs a, float alpha) {
+  mlp_split_body<K0, N1, N2, N3, OP, C, MIXED, 8, false>(a, alpha);
 }
 
 // Mixed tiling: tiles of 32 atoms, of 16 for the species with the fewest
@@ -521,26 +685,26 @@ __global__ __launch_bounds__(512) void k_mlp_split8(MlpArgs a, float alpha) {
 // count matches the CUs better than one size does (water, 4,096 molecules:
 // 256 + 256 instead of 384 tiles).  Every atom's arithmetic is the same as
 // in the uniform tiling.
-template <int K0, int N1, int N2, int N3, bool BF16>
+template <int K0, int N1, int N2, int N3, int OP>
 __global__ __launch_bounds__(256, K0 <= 128 ? 2 : 1) void k_mlp_mixed(MlpArgs a, float alpha) {
-  mlp_split_body<K0, N1, N2, N3, BF16, 2, true, 4, false>(a, alpha);
+  mlp_split_body<K0, N1, N2, N3, OP, 2, true, 4, false>(a, alpha);
 }
 
 // The same kernels for networks with the charge output (MM channel models).
-template <int K0, int N1, int N2, int N3, bool BF16, int C, bool MIXED, int NW>
+template <int K0, int N1, int N2, int N3, int OP, int C, bool MIXED, int NW>
 __global__ __launch_bounds__(64 * NW, 1) void k_mlp_split_q(MlpArgs a, float alpha) {
-  mlp_split_body<K0, N1, N2, N3, BF16, C, MIXED, NW, true>(a, alpha);
+  mlp_split_body<K0, N1, N2, N3, OP, C, MIXED, NW, true>(a, alpha);
 }
 
 // Register-resident variant: each wavefront owns 16 atoms and keeps the whole
 // chain (activations and deltas) in registers; no LDS, no barriers.  Cheapest
 // when the products are short (BF16 operands).
-template <int K0, int N1, int N2, int N3, bool BF16>
+template <int K0, int N1, int N2, int N3, int OP>
 __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
   constexpr int oF1 = 0, oF2 = oF1 + N1 * K0, oF3 = oF2 + N2 * N1;
   constexpr int oB1 = oF3 + N3 * N2, oB2 = oB1 + K0 * N1, oB3 = oB2 + N1 * N2;
   constexpr int ob1 = 0, ob2 = ob1 + N1, ob3 = ob2 + N2, ow4 = ob3 + N3, ob4 = ow4 + N3;
-  using Elem = typename std::conditional<BF16, __bf16, float>::type;
+  using Elem = typename std::conditional<OP == kOpBF16, __bf16, float>::type;
 
   const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int lane = threadIdx.x & 63;
@@ -577,53 +741,54 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
     v4f h1[N1 / 16];
 #pragma unroll
     for (int r = 0; r < N1 / 16; ++r) h1[r] = *reinterpret_cast<const v4f*>(V + ob1 + 16 * r + 4 * q);
-    if constexpr (!BF16) {
-      const v4f* Wp = reinterpret_cast<const v4f*>(Wm + oF1);
-#pragma unroll 2
-      for (int kb = 0; kb < K0 / 16; ++kb) {
-        v4f xb = valid ? *reinterpret_cast<const v4f*>(xrow + 16 * kb + 4 * q) : v4f{0.f, 0.f, 0.f, 0.f};
+    {
+      typename Ops<OP>::Acc acc[N1 / 16];
+      constexpr int kK = Ops<OP>::kK, KB = K0 / kK;
 #pragma unroll
-        for (int r = 0; r < N1 / 16; ++r) h1[r] = mfma_step(Wp[(r * (K0 / 16) + kb) * 64 + lane], xb, h1[r]);
-      }
-    } else {
-      const v8bf* Wp = reinterpret_cast<const v8bf*>(Wm + oF1);
+      for (int r = 0; r < N1 / 16; ++r) acc_start(acc[r], h1[r]);
 #pragma unroll 2
-      for (int kb = 0; kb < K0 / 32; ++kb) {
-        v4f lo = v4f{0.f, 0.f, 0.f, 0.f}, hi = v4f{0.f, 0.f, 0.f, 0.f};
+      for (int kb = 0; kb < KB; ++kb) {
+        v4f xt[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
         if (valid) {
-          lo = *reinterpret_cast<const v4f*>(xrow + 32 * kb + 4 * q);
-          hi = *reinterpret_cast<const v4f*>(xrow + 32 * kb + 16 + 4 * q);
+          xt[0] = *reinterpret_cast<const v4f*>(xrow + kK * kb + 4 * q);
+          if constexpr (kK == 32) xt[1] = *reinterpret_cast<const v4f*>(xrow + kK * kb + 16 + 4 * q);
         }
-        v8bf xb = to_bf16x8(lo, hi);
+        typename Ops<OP>::Frag xb;
+        make_frag(xt, 0, a.split.x, &xb);
 #pragma unroll
-        for (int r = 0; r < N1 / 16; ++r)
-          h1[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Wp[(r * (K0 / 32) + kb) * 64 + lane], xb, h1[r], 0, 0, 0);
+        for (int r = 0; r < N1 / 16; ++r) {
+          typename Ops<OP>::Frag wf;
+          load_frag(Wm + oF1, r * KB + kb, lane, &wf);
+          mma(wf, xb, acc[r]);
+        }
       }
+#pragma unroll
+      for (int r = 0; r < N1 / 16; ++r) h1[r] = acc_value(acc[r], h1[r], a.split.f1);
     }
 #pragma unroll
     for (int r = 0; r < N1 / 16; ++r)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) h1[r][t] = celu_f(h1[r][t], alpha, inv_alpha_l2);
+      for (int t = 0; t < 4; ++t) h1[r][t] = celu_of<OP>(h1[r][t], alpha, inv_alpha_l2);
 
     // ---- layer 2
     v4f h2[N2 / 16];
 #pragma unroll
     for (int r = 0; r < N2 / 16; ++r) h2[r] = *reinterpret_cast<const v4f*>(V + ob2 + 16 * r + 4 * q);
-    gemm_regs<N2, N1, BF16, 4>(Wm + oF2, h1, h2, lane);
+    gemm_regs<N2, N1, OP, 4>(Wm + oF2, h1, h2, lane, a.split.h1, a.split.f2);
 #pragma unroll
     for (int r = 0; r < N2 / 16; ++r)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) h2[r][t] = celu_f(h2[r][t], alpha, inv_alpha_l2);
+      for (int t = 0; t < 4; ++t) h2[r][t] = celu_of<OP>(h2[r][t], alpha, inv_alpha_l2);
 
     // ---- layer 3
     v4f h3[N3 / 16];
 #pragma unroll
     for (int r = 0; r < N3 / 16; ++r) h3[r] = *reinterpret_cast<const v4f*>(V + ob3 + 16 * r + 4 * q);
-    gemm_regs<N3, N2, BF16, 4>(Wm + oF3, h2, h3, lane);
+    gemm_regs<N3, N2, OP, 4>(Wm + oF3, h2, h3, lane, a.split.h2, a.split.f3);
 #pragma unroll
     for (int r = 0; r < N3 / 16; ++r)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) h3[r][t] = celu_f(h3[r][t], alpha, inv_alpha_l2);
+      for (int t = 0; t < 4; ++t) h3[r][t] = celu_of<OP>(h3[r][t], alpha, inv_alpha_l2);
 
     // ---- output layer and delta3 (in place)
     float ep = 0.f;
@@ -633,7 +798,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         ep += w4[t] * h3[r][t];
-        h3[r][t] = w4[t] * celu_grad_from_h(h3[r][t], inv_alpha);
+        h3[r][t] = w4[t] * celu_grad_of<OP>(h3[r][t], inv_alpha);
       }
     }
     ep += __shfl_xor(ep, 16, 64);
@@ -644,21 +809,21 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
     v4f d2[N2 / 16];
 #pragma unroll
     for (int r = 0; r < N2 / 16; ++r) d2[r] = v4f{0.f, 0.f, 0.f, 0.f};
-    gemm_regs<N2, N3, BF16, 4>(Wm + oB3, h3, d2, lane);
+    gemm_regs<N2, N3, OP, 4>(Wm + oB3, h3, d2, lane, a.split.d3, a.split.b3);
 #pragma unroll
     for (int r = 0; r < N2 / 16; ++r)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) h2[r][t] = d2[r][t] * celu_grad_from_h(h2[r][t], inv_alpha);
+      for (int t = 0; t < 4; ++t) h2[r][t] = d2[r][t] * celu_grad_of<OP>(h2[r][t], inv_alpha);
 
     // ---- delta1 = (W2^T delta2) o celu'(h1)
     v4f d1[N1 / 16];
 #pragma unroll
     for (int r = 0; r < N1 / 16; ++r) d1[r] = v4f{0.f, 0.f, 0.f, 0.f};
-    gemm_regs<N1, N2, BF16, 4>(Wm + oB2, h2, d1, lane);
+    gemm_regs<N1, N2, OP, 4>(Wm + oB2, h2, d1, lane, a.split.d2, a.split.b2);
 #pragma unroll
     for (int r = 0; r < N1 / 16; ++r)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) h1[r][t] = d1[r][t] * celu_grad_from_h(h1[r][t], inv_alpha);
+      for (int t = 0; t < 4; ++t) h1[r][t] = d1[r][t] * celu_grad_of<OP>(h1[r][t], inv_alpha);
 
     // ---- dE/dx = W1^T delta1, in chunks of row tiles streamed to memory
     constexpr int CH = 8;
@@ -666,26 +831,25 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
 #pragma unroll
     for (int r0 = 0; r0 < RT0; r0 += CH) {
       v4f gx[CH];
+      typename Ops<OP>::Acc acc[CH];
+      constexpr int KB = N1 / Ops<OP>::kK;
+      const v4f none = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int c = 0; c < CH; ++c) gx[c] = v4f{0.f, 0.f, 0.f, 0.f};
-      if constexpr (!BF16) {
-        const v4f* Wp = reinterpret_cast<const v4f*>(Wm + oB1);
+      for (int c = 0; c < CH; ++c) acc_start(acc[c], none);
 #pragma unroll
-        for (int kb = 0; kb < N1 / 16; ++kb)
+      for (int kb = 0; kb < KB; ++kb) {
+        typename Ops<OP>::Frag b;
+        make_frag(h1, kb, a.split.d1, &b);
 #pragma unroll
-          for (int c = 0; c < CH; ++c)
-            if (r0 + c < RT0) gx[c] = mfma_step(Wp[((r0 + c) * (N1 / 16) + kb) * 64 + lane], h1[kb], gx[c]);
-      } else {
-        const v8bf* Wp = reinterpret_cast<const v8bf*>(Wm + oB1);
-#pragma unroll
-        for (int kb = 0; kb < N1 / 32; ++kb) {
-          v8bf b = to_bf16x8(h1[2 * kb], h1[2 * kb + 1]);
-#pragma unroll
-          for (int c = 0; c < CH; ++c)
-            if (r0 + c < RT0)
-              gx[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Wp[((r0 + c) * (N1 / 32) + kb) * 64 + lane], b, gx[c], 0, 0, 0);
-        }
+        for (int c = 0; c < CH; ++c)
+          if (r0 + c < RT0) {
+            typename Ops<OP>::Frag wf;
+            load_frag(Wm + oB1, (r0 + c) * KB + kb, lane, &wf);
+            mma(wf, b, acc[c]);
+          }
       }
+#pragma unroll
+      for (int c = 0; c < CH; ++c) gx[c] = acc_value(acc[c], none, a.split.b1);
       if (valid) {
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
@@ -1170,26 +1334,26 @@ void launch_lds(const nnp_model& m, const MlpArgs& a, int n, hipStream_t st) {
   hipLaunchKernelGGL((k_mlp_lds<K0, N1, N2, N3, C, NW>), dim3((unsigned)G), dim3(64 * NW), 0, st, a, m.celu_alpha);
 }
 
-template <int K0, int N1, int N2, int N3, bool BF16>
+template <int K0, int N1, int N2, int N3, int OP>
 hipError_t run_mlp(nnp_model& m, const MlpArgs& a, int n, int variant, hipStream_t st) {
   if (variant == 0) {        // register-resident, one wavefront per 16 atoms
     const int64_t waves = (n + 15) / 16 + m.S;
-    hipLaunchKernelGGL((k_mlp_reg<K0, N1, N2, N3, BF16>), dim3((unsigned)((waves * 64 + kBlock - 1) / kBlock)),
+    hipLaunchKernelGGL((k_mlp_reg<K0, N1, N2, N3, OP>), dim3((unsigned)((waves * 64 + kBlock - 1) / kBlock)),
                        dim3(kBlock), 0, st, a, m.celu_alpha);
   } else if (variant == 5) {   // 16 atoms per workgroup of eight wavefronts
     const int64_t tiles = (n + 15) / 16 + m.S;
-    hipLaunchKernelGGL((k_mlp_split8<K0, N1, N2, N3, BF16, 1, false>), dim3((unsigned)tiles), dim3(512), 0, st, a,
+    hipLaunchKernelGGL((k_mlp_split8<K0, N1, N2, N3, OP, 1, false>), dim3((unsigned)tiles), dim3(512), 0, st, a,
                        m.celu_alpha);
   } else if (variant == 6) {   // eight wavefronts, mixed tiling
     const int64_t tiles = (n + 15) / 16 + m.S;
-    hipLaunchKernelGGL((k_mlp_split8<K0, N1, N2, N3, BF16, 2, true>), dim3((unsigned)tiles), dim3(512), 0, st, a,
+    hipLaunchKernelGGL((k_mlp_split8<K0, N1, N2, N3, OP, 2, true>), dim3((unsigned)tiles), dim3(512), 0, st, a,
                        m.celu_alpha);
   } else if (variant == 7) {   // eight wavefronts, 32 atoms per workgroup
     const int64_t tiles = (n + 31) / 32 + m.S;
-    hipLaunchKernelGGL((k_mlp_split8<K0, N1, N2, N3, BF16, 2, false>), dim3((unsigned)tiles), dim3(512), 0, st, a,
+    hipLaunchKernelGGL((k_mlp_split8<K0, N1, N2, N3, OP, 2, false>), dim3((unsigned)tiles), dim3(512), 0, st, a,
                        m.celu_alpha);
   } else if (variant == 8 || variant == 9) {   // LDS-resident BF16 weights, a tile per wavefront
-    if constexpr (BF16 && K0 <= 128) {
+    if constexpr (OP == kOpBF16 && K0 <= 128) {
       if (variant == 8)
         launch_lds<K0, N1, N2, N3, 2, 8>(m, a, n, st);    // 32-atom tiles, 2 wavefronts per SIMD
       else
@@ -1197,21 +1361,25 @@ hipError_t run_mlp(nnp_model& m, const MlpArgs& a, int n, int variant, hipStream
     }
   } else if (variant == 4) {   // row split, 32 atoms per workgroup, 16 for the smallest species
     const int64_t tiles = (n + 15) / 16 + m.S;
-    hipLaunchKernelGGL((k_mlp_mixed<K0, N1, N2, N3, BF16>), dim3((unsigned)tiles), dim3(256), 0, st, a,
+    hipLaunchKernelGGL((k_mlp_mixed<K0, N1, N2, N3, OP>), dim3((unsigned)tiles), dim3(256), 0, st, a,
                        m.celu_alpha);
   } else if (variant == 3 && K0 <= 128) {   // row split, 64 atoms per workgroup (narrow networks)
     if constexpr (K0 <= 128) {
       const int64_t tiles = (n + 63) / 64 + m.S;
-      hipLaunchKernelGGL((k_mlp_split<K0, N1, N2, N3, BF16, 4>), dim3((unsigned)tiles), dim3(256), 0, st, a,
-                         m.celu_alpha);
+      if constexpr (OP == kOpSplit)   // two accumulators per tile: four wavefronts would spill
+        hipLaunchKernelGGL((k_mlp_split8<K0, N1, N2, N3, OP, 4, false>), dim3((unsigned)tiles), dim3(512), 0, st, a,
+                           m.celu_alpha);
+      else
+        hipLaunchKernelGGL((k_mlp_split<K0, N1, N2, N3, OP, 4>), dim3((unsigned)tiles), dim3(256), 0, st, a,
+                           m.celu_alpha);
     }
   } else if (variant >= 2) { // row split, 32 atoms per workgroup
     const int64_t tiles = (n + 31) / 32 + m.S;
-    hipLaunchKernelGGL((k_mlp_split<K0, N1, N2, N3, BF16, 2>), dim3((unsigned)tiles), dim3(256), 0, st, a,
+    hipLaunchKernelGGL((k_mlp_split<K0, N1, N2, N3, OP, 2>), dim3((unsigned)tiles), dim3(256), 0, st, a,
                        m.celu_alpha);
   } else {                   // row split, 16 atoms per workgroup
     const int64_t tiles = (n + 15) / 16 + m.S;
-    hipLaunchKernelGGL((k_mlp_split<K0, N1, N2, N3, BF16, 1>), dim3((unsigned)tiles), dim3(256), 0, st, a,
+    hipLaunchKernelGGL((k_mlp_split<K0, N1, N2, N3, OP, 1>), dim3((unsigned)tiles), dim3(256), 0, st, a,
                        m.celu_alpha);
   }
   return hipGetLastError();
@@ -1220,40 +1388,107 @@ hipError_t run_mlp(nnp_model& m, const MlpArgs& a, int n, int variant, hipStream
 // Networks with the charge output: the same tilings through k_mlp_split_q.
 // The register-resident kernel has no charge form; variant 0 runs as 1, and
 // the 64-atom tile (narrow networks only) as 2.
-template <int K0, int N1, int N2, int N3, bool BF16, int C, bool MIXED, int NW>
+template <int K0, int N1, int N2, int N3, int OP, int C, bool MIXED, int NW>
 void launch_q(const MlpArgs& a, int n, int S, float alpha, hipStream_t st) {
   const int64_t tiles = (C == 2 && !MIXED ? (n + 31) / 32 : (n + 15) / 16) + S;
-  hipLaunchKernelGGL((k_mlp_split_q<K0, N1, N2, N3, BF16, C, MIXED, NW>), dim3((unsigned)tiles), dim3(64 * NW), 0,
+  hipLaunchKernelGGL((k_mlp_split_q<K0, N1, N2, N3, OP, C, MIXED, NW>), dim3((unsigned)tiles), dim3(64 * NW), 0,
                      st, a, alpha);
 }
 
-template <int K0, int N1, int N2, int N3, bool BF16>
+template <int K0, int N1, int N2, int N3, int OP>
 hipError_t run_mlp_q(nnp_model& m, const MlpArgs& a, int n, int variant, hipStream_t st) {
   const float al = m.celu_alpha;
   switch (variant) {
-    case 2: case 3: launch_q<K0, N1, N2, N3, BF16, 2, false, 4>(a, n, m.S, al, st); break;
-    case 4: launch_q<K0, N1, N2, N3, BF16, 2, true, 4>(a, n, m.S, al, st); break;
-    case 5: launch_q<K0, N1, N2, N3, BF16, 1, false, 8>(a, n, m.S, al, st); break;
-    case 6: launch_q<K0, N1, N2, N3, BF16, 2, true, 8>(a, n, m.S, al, st); break;
-    case 7: launch_q<K0, N1, N2, N3, BF16, 2, false, 8>(a, n, m.S, al, st); break;
-    default: launch_q<K0, N1, N2, N3, BF16, 1, false, 4>(a, n, m.S, al, st); break;
+    case 2: case 3: launch_q<K0, N1, N2, N3, OP, 2, false, 4>(a, n, m.S, al, st); break;
+    case 4: launch_q<K0, N1, N2, N3, OP, 2, true, 4>(a, n, m.S, al, st); break;
+    case 5: launch_q<K0, N1, N2, N3, OP, 1, false, 8>(a, n, m.S, al, st); break;
+    case 6: launch_q<K0, N1, N2, N3, OP, 2, true, 8>(a, n, m.S, al, st); break;
+    case 7: launch_q<K0, N1, N2, N3, OP, 2, false, 8>(a, n, m.S, al, st); break;
+    default: launch_q<K0, N1, N2, N3, OP, 1, false, 4>(a, n, m.S, al, st); break;
   }
   return hipGetLastError();
+}
+
+// Packs the split FP32 form's matrices from the canonical weights: for every
+// (member, species) W1, W2, W3 and their transposes as A-operand fragments of
+// 16 rows x 32 columns (the BF16 form's K permutation), the FP16 hi parts of a
+// fragment before its lo parts, the weights multiplied by a power of two.
+struct PackArgs {
+  const float* w;        // canonical weights (draw order)
+  int64_t w_per_species; // floats per (member, species)
+  _Float16* out;
+  int64_t out_per_species;   // FP16 values per (member, species)
+  int widths[4];         // K0, N1, N2, N3
+  float scale[3];
+};
+
+__global__ __launch_bounds__(kBlock) void k_pack_split(PackArgs a) {
+  const float* W = a.w + (int64_t)blockIdx.y * a.w_per_species;
+  _Float16* out = a.out + (int64_t)blockIdx.y * a.out_per_species;
+  const int total = a.widths[0] * a.widths[1] + a.widths[1] * a.widths[2] + a.widths[2] * a.widths[3];
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
+  if (e >= 2 * total) return;
+  const bool trans = e >= total;
+  int t = trans ? e - total : e;
+  int64_t src = 0;   // the matrix in the canonical order: W_l, b_l, ...
+  int l = 0;
+  for (; t >= a.widths[l] * a.widths[l + 1]; ++l) {
+    t -= a.widths[l] * a.widths[l + 1];
+    src += (int64_t)a.widths[l] * a.widths[l + 1] + a.widths[l + 1];
+  }
+  const int in = a.widths[l], cols = trans ? a.widths[l + 1] : in;
+  const int f = t >> 9, lane = (t >> 3) & 63, j = t & 7, q = lane >> 4;
+  const int row = 16 * (f / (cols / 32)) + (lane & 15);
+  const int k = 32 * (f % (cols / 32)) + (j < 4 ? 4 * q + j : 16 + 4 * q + (j - 4));
+  const float x = W[src + (trans ? (int64_t)k * in + row : (int64_t)row * in + k)] * a.scale[l];
+  const _Float16 hi = (_Float16)x;
+  _Float16* o = out + 2 * (int64_t)(e - t) + (2 * f * 64 + lane) * 8 + j;
+  o[0] = hi;
+  o[512] = (_Float16)((x - (float)hi) * kSplitUp);
 }
 
 }  // namespace
 
 // Network kernel variant: 0 register-resident (16 atoms per wavefront),
 // 1 / 2 / 3 row split over 4 wavefronts with 16 / 32 / 64 atoms per workgroup
-// (64 only for the narrow water network; the wide one falls back to 32).  A
-// tuned choice for this size wins; otherwise the 32-atom row split, which
-// the tuner picked for the water boxes and the H/C/N/O batch in both forms.
+// (64 only for the narrow water network; the wide one falls back to 32), 5 / 6
+// / 7 over 8 wavefronts.  A tuned choice for this size wins; else, all of them
+// giving the same results bit for bit:
+//   while every 16-atom tile has a compute unit of its own, 16-atom tiles over
+//   8 wavefronts (the shortest chain per tile): 192 atoms FP32 11 us against
+//   15 for variant 2, 3,000 atoms 11.5 against 16, 60 H/C/N/O atoms with the
+//   MM channel 36 against 66, 8 networks and 3,900 atoms 69 against 111;
+//   beyond that 32-atom tiles over 8 wavefronts: FP32 6,600 atoms 14.4 against
+//   17.6, 48,000 atoms 48 against 51, 261,000 atoms 239 against 249, H/C/N/O
+//   batch of 29,000 atoms 105 against 116;
+//   except for large BF16 systems, whose short products are better off with
+//   more, smaller workgroups: 18,000 atoms 17.5 us with variant 2 against 19.9,
+//   36,000 atoms 25.4 against 27.9, 14,000 H/C/N/O atoms 31 against 37.
 int mlp_variant(const nnp_model& m, int n) {
   int v = stage_variant(m, kTuneNetwork, n);
   // the LDS-resident kernels: BF16, the water-sized network, one member
   if ((v == 8 || v == 9) && !(m.prec == NNP_BF16 && m.net_kind == 0 && m.n_members == 1 && m.d_wrow)) v = 2;
   if (v >= 0) return v;
-  return 2;
+  if ((n + 15) / 16 + m.S <= m.n_cu) return 5;
+  const int tiles = (n + 31) / 32, most = m.net_kind == 0 ? 2 * m.n_cu : m.n_cu;
+  return m.prec == NNP_BF16 && tiles > most ? 2 : 7;
+}
+
+hipError_t pack_split(const nnp_model& m, const float* weights, void* out) {
+  PackArgs a;
+  a.w = weights;
+  a.w_per_species = (int64_t)m.w_host.size() / (m.S * m.n_members);
+  a.out = static_cast<_Float16*>(out);
+  a.out_per_species = 2 * m.mat_per_species;
+  int total = 0;
+  for (int l = 0; l < 4; ++l) a.widths[l] = m.widths[l];
+  for (int l = 0; l < 3; ++l) {
+    a.scale[l] = m.w_scale[l];
+    total += m.widths[l] * m.widths[l + 1];
+  }
+  hipLaunchKernelGGL(k_pack_split, dim3((unsigned)((2 * total + kBlock - 1) / kBlock), (unsigned)(m.S * m.n_members)),
+                     dim3(kBlock), 0, nullptr, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_mlp(nnp_model& m, int n, hipStream_t st) {
@@ -1281,16 +1516,19 @@ hipError_t launch_mlp(nnp_model& m, int n, hipStream_t st) {
   const int v = mlp_variant(m, n);
   m.mlp_cols = v == 3 ? (m.net_kind == 0 ? 4 : 2) : (v == 2 || v == 4 || v == 6 || v == 7 || v == 8 ? 2 : 1);
   m.mlp_mixed = v == 4 || v == 6;
+  a.split = split_scales(m, m.max_rad, m.max_ang);
   switch (m.net_kind) {
     case 0:
-      return bf ? run_mlp<128, 160, 128, 96, true>(m, a, n, v, st) : run_mlp<128, 160, 128, 96, false>(m, a, n, v, st);
+      return bf ? run_mlp<128, 160, 128, 96, kOpBF16>(m, a, n, v, st) : run_mlp<128, 160, 128, 96, kOpSplit>(m, a, n, v, st);
     case 1:
-      return bf ? run_mlp<384, 256, 192, 160, true>(m, a, n, v, st) : run_mlp<384, 256, 192, 160, false>(m, a, n, v, st);
+      return bf ? run_mlp<384, 256, 192, 160, kOpBF16>(m, a, n, v, st)
+                : run_mlp<384, 256, 192, 160, kOpSplit>(m, a, n, v, st);
     case 2:
       if (m.charges)
-        return bf ? run_mlp_q<416, 256, 192, 160, true>(m, a, n, v, st)
-                  : run_mlp_q<416, 256, 192, 160, false>(m, a, n, v, st);
-      return bf ? run_mlp<416, 256, 192, 160, true>(m, a, n, v, st) : run_mlp<416, 256, 192, 160, false>(m, a, n, v, st);
+        return bf ? run_mlp_q<416, 256, 192, 160, kOpBF16>(m, a, n, v, st)
+                  : run_mlp_q<416, 256, 192, 160, kOpF32>(m, a, n, v, st);
+      return bf ? run_mlp<416, 256, 192, 160, kOpBF16>(m, a, n, v, st)
+                : run_mlp<416, 256, 192, 160, kOpF32>(m, a, n, v, st);
     default:
       return hipErrorInvalidValue;
   }

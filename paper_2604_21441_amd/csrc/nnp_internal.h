@@ -199,6 +199,24 @@ struct NbrLists {
   int max_rad, max_ang;
 };
 
+// Scales of the split FP32 network form (mlp.hip): every operand of a product
+// is multiplied by a power of two before it is split into FP16 pairs, and a
+// product's result by the inverse of its two operands' scales.  An operand's
+// scale takes a bound on its magnitude that follows from the weights and the
+// list capacities to 2^15 (split_scales), so that nothing overflows; values
+// down to 2^-29 of the bound keep the full 22 bits, smaller ones an absolute
+// error of 2^-50 of it.
+struct SplitScales {
+  float x = 1.f, h1 = 1.f, h2 = 1.f, d3 = 1.f, d2 = 1.f, d1 = 1.f;   // operands
+  float f1 = 1.f, f2 = 1.f, f3 = 1.f, b3 = 1.f, b2 = 1.f, b1 = 1.f;  // products
+};
+
+// Bounds of a model's matrices, largest over members and species: weights,
+// absolute row sums of the inputs of each kind, absolute column sums, biases.
+struct WeightBounds {
+  double w[3] = {0, 0, 0}, rad = 0, ang = 0, row[3] = {0, 0, 0}, col[3] = {0, 0, 0}, b[3] = {0, 0, 0}, w4 = 0;
+};
+
 // Network tile schedule: species buckets are bins [s*n_bins, (s+1)*n_bins).
 struct MlpArgs {
   const float* x;          // [n][stride]
@@ -216,6 +234,7 @@ struct MlpArgs {
   int phi_col;             // column of x holding the MM potential (models with charges)
   const void* wrow;        // BF16 models: W1, W2, W3 row-major per (member, species), or null
   int64_t wrow_per_species;
+  SplitScales split;       // split FP32 form
 };
 
 // Per-call device workspace: capacities and the arrays sized from them.
@@ -275,6 +294,8 @@ struct nnp_model : nnp::Workspace {
   std::vector<int> species;             // atomic numbers, ascending
   std::vector<int> widths;              // unpadded widths
   float celu_alpha = 0.1f;
+  nnp::WeightBounds bounds;             // split FP32 form
+  float w_scale[3] = {1.f, 1.f, 1.f};   // powers of two applied to W1, W2, W3 when they are packed
   nnp::DescParams dp{};
   int mlp_cols = 1;                     // column tiles (16 atoms each) per network workgroup
   int mlp_mixed = 0;                    // the species with the fewest atoms uses one column tile
@@ -373,6 +394,11 @@ nnp_status hip_error(hipError_t e, const char* what);
 // weights.cpp
 void draw_weights(uint64_t seed, const std::vector<int>& widths, int n_species, int n_members,
                   std::vector<float>& out);
+// Bounds of the weights, the scales of the packed matrices, and the scales of
+// the operands for lists of up to max_rad radial and max_ang angular neighbours.
+bool split_form(const nnp_model& m);   // the model's products run in the split FP32 form
+void weight_bounds(nnp_model& m);
+SplitScales split_scales(const nnp_model& m, int max_rad, int max_ang);
 void pack_weights(const nnp_model& m, std::vector<uint8_t>& mat, std::vector<float>& vec,
                   int64_t& mat_per_species, int64_t& vec_per_species);
 // BF16 (round to nearest even) copies of W1 [N1 x K0p] (zero columns beyond the
@@ -398,6 +424,8 @@ hipError_t launch_mm_bwd(nnp_model& m, int n, int n_mm, const float* mm_pos, con
                          double* forces, double* mm_forces, hipStream_t st);
 
 // mlp.hip
+// Device copy of the canonical weights -> the split FP32 form's fragments.
+hipError_t pack_split(const nnp_model& m, const float* weights, void* out);
 hipError_t launch_mlp(nnp_model& m, int n, hipStream_t st);
 
 // fills (api.cpp)

@@ -1,5 +1,6 @@
 // Host-side weight handling: the seeded draw (SplitMix64 + Box-Muller) and the
 // packing of every matrix into MFMA fragment order.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 
@@ -35,12 +36,12 @@ inline uint16_t bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// Pack M [R x C] (row-major, leading dimension ld, zero outside rows x cols)
-// as A-operand fragments.  FP32 (16x16x4): element (rt, kb, lane, s) =
-// M[16 rt + lane%16][16 kb + 4 (lane/16) + s].  BF16 (16x16x32): element
-// (rt, kb, lane, j) = M[16 rt + lane%16][32 kb + k(j)], k(j) = 4 (lane/16) + j
-// for j < 4 and 16 + 4 (lane/16) + (j - 4) otherwise -- the same K permutation
-// the kernel applies to the activations.
+// Pack M [R x C] (zero outside rows x cols) as A-operand fragments.  FP32
+// (16x16x4): element (rt, kb, lane, s) = M[16 rt + lane%16][16 kb + 4 (lane/16) + s].
+// BF16 (16x16x32): element (rt, kb, lane, j) = M[16 rt + lane%16][32 kb + k(j)],
+// k(j) = 4 (lane/16) + j for j < 4 and 16 + 4 (lane/16) + (j - 4) otherwise --
+// the same K permutation the kernel applies to the activations.  (The split
+// FP32 form is packed on the device, mlp.hip.)
 template <typename Get>
 void pack_matrix(Get get, int R, int C, bool bf16, std::vector<uint8_t>& out) {
   if (!bf16) {
@@ -68,6 +69,15 @@ void pack_matrix(Get get, int R, int C, bool bf16, std::vector<uint8_t>& out) {
   }
 }
 
+// 2^(to - ceil(log2 bound)), within FP32's normal range; 1 for a bound of zero
+// or one that is not finite.
+float scale_to(double bound, int to) {
+  if (!(bound > 0.0) || !std::isfinite(bound)) return 1.f;
+  int e = 0;
+  (void)std::frexp(bound, &e);   // bound <= 2^e
+  return std::ldexp(1.f, std::max(-100, std::min(100, to - e)));
+}
+
 }  // namespace
 
 void draw_weights(uint64_t seed, const std::vector<int>& widths, int n_species, int n_members,
@@ -87,9 +97,69 @@ void draw_weights(uint64_t seed, const std::vector<int>& widths, int n_species, 
       }
 }
 
+bool split_form(const nnp_model& m) { return m.prec == NNP_FP32 && m.extra == 0; }
+
+void weight_bounds(nnp_model& m) {
+  const int* n = m.widths.data();
+  WeightBounds& q = m.bounds;
+  q = WeightBounds{};
+  const float* p = m.w_host.data();
+  auto upto = [](double& a, double v) { if (std::isfinite(v) && v > a) a = v; };
+  std::vector<float> col;
+  for (int t = 0; t < m.n_members * m.S; ++t)
+    for (int l = 0; l < 4; ++l) {
+      const int in = n[l], out = n[l + 1], cut = l == 0 ? kRadShifts * m.S : 0;
+      const float* W = p;
+      const float* b = p + (size_t)in * out;
+      p = b + out;
+      col.assign(in, 0.f);
+      for (int r = 0; r < out; ++r, W += in) {
+        float head = 0.f, tail = 0.f, top = 0.f;   // FP32 sums: a bound may be a little off, the scales have room
+        for (int c = 0; c < cut; ++c) head += std::fabs(W[c]);
+        for (int c = cut; c < in; ++c) tail += std::fabs(W[c]);
+        for (int c = 0; c < in; ++c) {
+          const float v = std::fabs(W[c]);
+          top = v > top ? v : top;
+          col[c] += v;
+        }
+        if (l == 0) { upto(q.rad, head); upto(q.ang, tail); }
+        if (l < 3) { upto(q.w[l], top); upto(q.row[l], (double)head + tail); upto(q.b[l], std::fabs(b[r])); }
+        else upto(q.w4, top);
+      }
+      if (l < 3)
+        for (float v : col) upto(q.col[l], v);
+    }
+  for (int l = 0; l < 3; ++l) m.w_scale[l] = scale_to(q.w[l], 10);
+}
+
+// Each radial entry sums at most max_rad terms of at most 1, each angular one
+// at most max_ang (max_ang - 1) / 2 terms of at most 2; |celu(u)| <= |u| + alpha
+// and 0 <= celu' <= 1 carry the bounds through the layers.
+SplitScales split_scales(const nnp_model& m, int max_rad, int max_ang) {
+  const WeightBounds& q = m.bounds;
+  const double rad = max_rad, ang = (double)max_ang * (max_ang - 1);
+  const double h1 = q.rad * rad + q.ang * ang + q.b[0] + m.celu_alpha;
+  const double h2 = q.row[1] * h1 + q.b[1] + m.celu_alpha;
+  const double d3 = q.w4, d2 = q.col[2] * d3, d1 = q.col[1] * d2;
+  SplitScales s;
+  s.x = scale_to(std::max(rad, ang), 15);
+  s.h1 = scale_to(h1, 15);
+  s.h2 = scale_to(h2, 15);
+  s.d3 = scale_to(d3, 15);
+  s.d2 = scale_to(d2, 15);
+  s.d1 = scale_to(d1, 15);
+  s.f1 = 1.f / (s.x * m.w_scale[0]);
+  s.f2 = 1.f / (s.h1 * m.w_scale[1]);
+  s.f3 = 1.f / (s.h2 * m.w_scale[2]);
+  s.b3 = 1.f / (s.d3 * m.w_scale[2]);
+  s.b2 = 1.f / (s.d2 * m.w_scale[1]);
+  s.b1 = 1.f / (s.d1 * m.w_scale[0]);
+  return s;
+}
+
 void pack_weights(const nnp_model& m, std::vector<uint8_t>& mat, std::vector<float>& vec,
                   int64_t& mat_per_species, int64_t& vec_per_species) {
-  const bool bf = m.prec == NNP_BF16;
+  const bool bf = m.prec == NNP_BF16, matrices = !split_form(m);
   const int K0 = m.widths[0];          // real input width
   const int K0p = m.stride;            // padded
   const int N1 = m.widths[1], N2 = m.widths[2], N3 = m.widths[3];
@@ -118,12 +188,14 @@ void pack_weights(const nnp_model& m, std::vector<uint8_t>& mat, std::vector<flo
       auto t1 = [&](int r, int c) { return r < K0 ? W1[(size_t)c * K0 + r] : 0.f; };
       auto t2 = [&](int r, int c) { return W2[(size_t)c * N1 + r]; };
       auto t3 = [&](int r, int c) { return W3[(size_t)c * N2 + r]; };
-      pack_matrix(g1, N1, K0p, bf, mat);
-      pack_matrix(g2, N2, N1, bf, mat);
-      pack_matrix(g3, N3, N2, bf, mat);
-      pack_matrix(t1, K0p, N1, bf, mat);
-      pack_matrix(t2, N1, N2, bf, mat);
-      pack_matrix(t3, N2, N3, bf, mat);
+      if (matrices) {
+        pack_matrix(g1, N1, K0p, bf, mat);
+        pack_matrix(g2, N2, N1, bf, mat);
+        pack_matrix(g3, N3, N2, bf, mat);
+        pack_matrix(t1, K0p, N1, bf, mat);
+        pack_matrix(t2, N1, N2, bf, mat);
+        pack_matrix(t3, N2, N3, bf, mat);
+      }
       vec.insert(vec.end(), b1, b1 + N1);
       vec.insert(vec.end(), b2, b2 + N2);
       vec.insert(vec.end(), b3, b3 + N3);
