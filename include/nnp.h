@@ -341,7 +341,8 @@ typedef enum {
  * Pin the kernel variant of one stage for later calls, overriding the tuned
  * choice and the built-in default; variant = -1 removes the pin.  Variants:
  *   neighbours: 0 one wavefront per atom; 1 / 2 / 3 wavefronts per cell with
- *     about 8 / 5 / 3 centre atoms each (with a single bin, 0 is used);
+ *     about 16 / 8 / 4 centre atoms each (periodic boxes of at least three
+ *     cells per dimension, else 0 is used);
  *   descriptor forward: 0 one wavefront per atom; 1 / 2 one 16-lane / 8-lane
  *     row per atom; 3 / 4 two / four atoms per wavefront, their radial
  *     segments and angular classes cut into equal chunks, one per lane

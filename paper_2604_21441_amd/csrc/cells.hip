@@ -629,6 +629,13 @@ constexpr int kCandCap = 1024;
 // within many box lengths of the origin.
 constexpr float kCullMargin = 0.02f;
 
+// Accepted candidates are appended in lane order: a lane's place is the
+// number of accepting lanes below it.
+__device__ __forceinline__ unsigned place(uint64_t m, int before) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)before));
+}
+__device__ __forceinline__ int below(uint64_t m) { return (int)place(m, 0); }
+
 __global__ __launch_bounds__(64) void k_neighbours(NeighArgs a, Geometry g) {
 #pragma clang fp contract(off)
   __shared__ int s_start[kMaxStencil];
@@ -690,11 +697,6 @@ __global__ __launch_bounds__(64) void k_neighbours(NeighArgs a, Geometry g) {
   int* ang = a.ang + (int64_t)i * a.max_ang;
   int nr = 0, na = 0;   // list lengths so far (wavefront-uniform)
   bool overflow = false;
-  // Accepted candidates are appended in lane order: a lane's place is the
-  // number of accepting lanes below it.
-  auto below = [](uint64_t m) {
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-  };
   for (int s = 0; s < a.S; ++s) {
     if (lane == 0) {
       a.rad_off[(int64_t)i * (a.S + 1) + s] = nr;
@@ -783,160 +785,261 @@ __global__ __launch_bounds__(64) void k_neighbours(NeighArgs a, Geometry g) {
   }
 }
 
-// Same lists as k_neighbours, one wavefront per bin (periodic cell, or one
-// system of a batch): the bin's centre atoms (all species, up to 64 at a
-// time) are staged in LDS, and the stencil's candidates, one per lane and in
-// ascending slot order, are tested against every centre in turn, each
-// centre's accepted candidates being compacted with a ballot.  The stencil is
-// set up once per bin instead of once per atom.  Per-centre list lengths live
-// in the register of the lane with the centre's index.
+// Same lists as k_neighbours for periodic boxes, a wavefront per cell (or per
+// part of its atoms).  The stencil's candidates, all species in list order,
+// are flattened once, and their positions are kept in registers, 64 per
+// chunk: one shifted copy each, the image nearest to the cell's centre.  The
+// centres' positions are shifted the same way, so a pair costs three
+// subtractions and r^2 instead of the minimum image.  That r^2 differs from the predicate's
+// (pair_r2_exact on the caller's coordinates) by rounding only, so it decides
+// unless it falls within eps of a cutoff: two comparisons, one on each side,
+// must agree for every lane of a chunk.  A centre with a chunk where they do
+// not (about one in twenty), or whose lists would overflow, is done again with
+// the predicate itself, as is every centre of a cell with more candidates than
+// the registers hold.
+//
+// The shift picks the predicate's image: with at least four cells per
+// dimension a stencil pair is at most half a box apart; with three it can be
+// further, but the other image is then at least a cell away, which is more
+// than the cutoff by kCullMargin (cells_fast).
+//
+// Bound by instruction issue, scalar and vector: about 18 vector and 14 scalar
+// instructions per chunk and centre, 7 chunks per centre in water.
+// k_neighbours: 565 vector instructions per atom.  What decides per lane (the
+// margin, the capacity) instead of per chunk on scalars took the box of
+// 261,000 atoms from 181 to 136 us.
+template <int S, int NCH>
 __global__ __launch_bounds__(64) void k_neighbours_cell(NeighArgs a, Geometry g, int K) {
-#pragma clang fp contract(off)
-  __shared__ int s_start[kMaxStencil];
-  __shared__ int s_off[kMaxStencil];
-  __shared__ float4 s_cpos[64];
-  __shared__ int s_cid[64];
+  constexpr int kCap = 64 * NCH;
+  __shared__ int s_cand[kCap];
+  __shared__ int s_start[kMaxStencil * S], s_off[kMaxStencil * S + 1];
   const int b = xcd_block(blockIdx.x, gridDim.x);
   const int cell = b / K, part = b - cell * K;
   const int lane = threadIdx.x;
-  const MinImage mi = min_image_of_system(g, cell);   // a batch's bins are its systems
-  // stencil cells in ascending id order (see k_neighbours)
-  int nst = 1;
-  int my_cell = cell;
-  if (g.periodic) {
-    int c[3], nd[3], v[3][3];
-    c[0] = cell / (g.nc[1] * g.nc[2]);
-    c[1] = (cell / g.nc[2]) % g.nc[1];
-    c[2] = cell % g.nc[2];
+  const MinImage mi = min_image_of_system(g, 0);
+  const int cc[3] = {cell / (g.nc[1] * g.nc[2]), (cell / g.nc[2]) % g.nc[1], cell % g.nc[2]};
+  // stencil cells in ascending id order (see k_neighbours), one per lane
+  int my_cell = 0;
+  {
+    const int l = lane < kMaxStencil ? lane : 0;
+    const int o[3] = {l / 9, (l / 3) % 3, l % 3};
+    int v[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-      const int n = g.nc[k];
-      nd[k] = n >= 3 ? 3 : n;
-      if (n >= 3) {
-        if (c[k] == 0) { v[k][0] = 0; v[k][1] = 1; v[k][2] = n - 1; }
-        else if (c[k] == n - 1) { v[k][0] = 0; v[k][1] = n - 2; v[k][2] = n - 1; }
-        else { v[k][0] = c[k] - 1; v[k][1] = c[k]; v[k][2] = c[k] + 1; }
-      } else {
-        v[k][0] = 0; v[k][1] = 1; v[k][2] = 2;
-      }
+      const int n = g.nc[k], c = cc[k];
+      const int d = c == 0 ? (o[k] == 2 ? -1 : o[k]) : (c == n - 1 ? (o[k] == 0 ? 1 : o[k] - 2) : o[k] - 1);
+      const int w = c + d;
+      v[k] = w < 0 ? w + n : (w >= n ? w - n : w);
     }
-    nst = nd[0] * nd[1] * nd[2];
-    const int l = lane < nst ? lane : 0;
-    const int o0 = l / (nd[1] * nd[2]), o1 = (l / nd[2]) % nd[1], o2 = l % nd[2];
-    my_cell = (v[0][o0] * g.nc[1] + v[1][o1]) * g.nc[2] + v[2][o2];
+    my_cell = (v[0] * g.nc[1] + v[1]) * g.nc[2] + v[2];
   }
-
-  // centre atoms of this cell (species-major ranges of slots); this wavefront
-  // takes the part-th of K equal chunks of them
-  int c_lo[kMaxSpecies], c_n[kMaxSpecies];
-  int n_centres = 0;
+  // candidates: ranges of slots, species by species, flattened
+  int total = 0, first[S + 1], own_st[S], own_n[S], own_at[S], n_centres = 0;
+  const uint64_t own_lane = __ballot(lane < kMaxStencil && my_cell == cell);
+  const int own = __ffsll((unsigned long long)own_lane) - 1;
 #pragma unroll
-  for (int s = 0; s < kMaxSpecies; ++s) {
-    c_lo[s] = 0;
-    c_n[s] = 0;
-    if (s < a.S) {
-      c_lo[s] = a.bin_start[s * g.n_bins + cell];
-      c_n[s] = a.bin_start[s * g.n_bins + cell + 1] - c_lo[s];
-      n_centres += c_n[s];
+  for (int s = 0; s < S; ++s) {
+    first[s] = total;
+    int st = 0, cnt = 0;
+    if (lane < kMaxStencil) {
+      const int* r = a.bin_start + s * g.n_bins + my_cell;
+      st = r[0];
+      cnt = r[1] - st;
     }
+    int inc = cnt;
+#pragma unroll
+    for (int off = 1; off < 32; off <<= 1) {
+      const int u = __shfl_up(inc, off, 64);
+      if (lane >= off) inc += u;
+    }
+    const int at = total + inc - cnt;
+    if (lane < kMaxStencil) {
+      s_start[s * kMaxStencil + lane] = st;
+      s_off[s * kMaxStencil + lane] = at;
+      for (int q = 0; q < cnt && at + q < kCap; ++q) s_cand[at + q] = st + q;
+    }
+    own_st[s] = __builtin_amdgcn_readlane(st, own);
+    own_n[s] = __builtin_amdgcn_readlane(cnt, own);
+    own_at[s] = __builtin_amdgcn_readlane(at, own);
+    n_centres += own_n[s];
+    total += __builtin_amdgcn_readlane(inc, kMaxStencil - 1);
   }
+  first[S] = total;
+  // this wavefront's centres: the part-th of K equal pieces, all species
   const int chunk = (n_centres + K - 1) / K;
   const int q0 = part * chunk, q1 = min(n_centres, q0 + chunk);
-  const uint64_t lt = __lanemask_lt();
-  for (int cb = q0; cb < q1; cb += 64) {
-    const int nc = min(64, q1 - cb);
-    int my_i = -1;
-    if (lane < nc) {
-      int q = cb + lane, s = 0;
-      while (q >= c_n[s]) { q -= c_n[s]; ++s; }
-      my_i = c_lo[s] + q;
-      s_cid[lane] = my_i;
-      s_cpos[lane] = a.spos[my_i];
-    }
-    int nr = 0, na = 0;   // lists of centre `lane`
-    bool overflow = false;
-    for (int s = 0; s < a.S; ++s) {
-      if (lane < nc) {
-        a.rad_off[(int64_t)my_i * (a.S + 1) + s] = nr;
-        a.ang_off[(int64_t)my_i * (a.S + 1) + s] = na;
-      }
-      int st = 0, cnt = 0;
-      if (lane < nst) {
-        const int bb = s * g.n_bins + my_cell;
-        st = a.bin_start[bb];
-        cnt = a.bin_start[bb + 1] - st;
-      }
-      int inc = cnt;
+  if (q0 >= q1) return;
+  __syncthreads();
+  const bool fast_cell = total <= kCap;
+  const int nch = (total + 63) >> 6;
+  // candidates in registers, as the image nearest to the cell's centre
+  const float mx = ((float)cc[0] + 0.5f) * g.cell_len[0], my = ((float)cc[1] + 0.5f) * g.cell_len[1],
+              mz = ((float)cc[2] + 0.5f) * g.cell_len[2];
+  auto shift = [](float x, float m, float L, float iL) { return x - L * rintf((x - m) * iL); };
+  float cx[NCH], cy[NCH], cz[NCH], reach = 0.f;
+  int cj[NCH];
 #pragma unroll
-      for (int off = 1; off < 32; off <<= 1) {
-        const int u = __shfl_up(inc, off, 64);
-        if (lane >= off) inc += u;
-      }
-      const int total = __shfl(inc, nst - 1, 64);
-      __syncthreads();   // previous species' readers of s_start / s_off are done
-      if (lane < nst) {
-        s_start[lane] = st;
-        s_off[lane] = inc - cnt;
-      }
-      __syncthreads();
-      // candidate slot and position of the lane, one block of 64 ahead
-      auto fetch = [&](int c, int& j, float4& pj) {
-        j = -1;
-        pj = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (c < total) {
-          int lo = 0, hi = nst - 1;
-          while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (s_off[mid] <= c) lo = mid; else hi = mid - 1;
-          }
-          j = s_start[lo] + (c - s_off[lo]);
-          pj = a.spos[j];
-        }
-      };
-      int jn;
-      float4 pjn;
-      fetch(lane, jn, pjn);
-      for (int c0 = 0; c0 < total; c0 += 64) {
-        const int j = jn;
-        const float4 pj = pjn;
-        if (c0 + 64 < total) fetch(c0 + 64 + lane, jn, pjn);
-        for (int ci = 0; ci < nc; ++ci) {
-          const float4 pi = s_cpos[ci];
-          const int i = s_cid[ci];
-          bool in_r = false, in_a = false;
-          if (j >= 0 && j != i) {
-            const float r2 = pair_r2_exact(pi, pj, mi);
-            in_r = r2 < a.rc2;
-            in_a = r2 < a.rca2;
-          }
-          const int base_r = __builtin_amdgcn_readlane(nr, ci);
-          const int base_a = __builtin_amdgcn_readlane(na, ci);
-          const uint64_t mr = __ballot(in_r);
-          const int pr = base_r + __popcll(mr & lt);
-          const bool in_a2 = in_a && pr < a.max_rad;
-          const uint64_t ma = __ballot(in_a2);
-          const int pa = base_a + __popcll(ma & lt);
-          if (in_r && pr < a.max_rad) a.rad[(int64_t)i * a.max_rad + pr] = j;
-          if (in_a2 && pa < a.max_ang) a.ang[(int64_t)i * a.max_ang + pa] = j;
-          if (lane == ci) {
+  for (int c = 0; c < NCH; ++c) {
+    cj[c] = -1;
+    cx[c] = cy[c] = cz[c] = 3e18f;   // beyond every cutoff
+    if (fast_cell && c < nch && 64 * c + lane < total) cj[c] = s_cand[64 * c + lane];
+  }
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    if (cj[c] >= 0) {
+      const float4 q = a.spos[cj[c]];
+      cx[c] = shift(q.x, mx, g.box[0], g.inv_box[0]);
+      cy[c] = shift(q.y, my, g.box[1], g.inv_box[1]);
+      cz[c] = shift(q.z, mz, g.box[2], g.inv_box[2]);
+      reach = fmaxf(reach, fmaxf(fabsf(q.x), fmaxf(fabsf(q.y), fabsf(q.z))));
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) reach = fmaxf(reach, __shfl_xor(reach, off, 64));
+  // both distances round coordinates of up to reach + 2 L: each component is
+  // within 2^-21 (reach + 2 L) of the other, r^2 within 2 sqrt(3) rc times
+  // that (and its own rounding)
+  const float eps = 8.f * sqrtf(a.rc2) * 0x1p-21f * (reach + 2.f * fmaxf(g.box[0], fmaxf(g.box[1], g.box[2])));
+  const unsigned last_r = (unsigned)a.max_rad - 1, last_a = (unsigned)a.max_ang - 1;
+  unsigned starts = 0;   // chunks in which a species starts
+#pragma unroll
+  for (int s = 1; s < S; ++s)
+    if (first[s] < kCap) starts |= 1u << (first[s] >> 6);
+  auto slot_of = [&](int q) {   // q-th centre of the cell
+    int i = 0;
+#pragma unroll
+    for (int s = 0, at = 0; s < S; ++s) {
+      if (q >= at && q < at + own_n[s]) i = own_st[s] + q - at;
+      at += own_n[s];
+    }
+    return i;
+  };
+  for (int qb = q0; qb < q1; qb += 64) {   // 64 centres at a time, one per lane
+    const int my_i = slot_of(min(qb + lane, q1 - 1));
+    const float4 pc = a.spos[my_i];
+    const float px = shift(pc.x, mx, g.box[0], g.inv_box[0]), py = shift(pc.y, my, g.box[1], g.inv_box[1]),
+                pz = shift(pc.z, mz, g.box[2], g.inv_box[2]);
+    for (int q = qb; q < min(q1, qb + 64); ++q) {
+      const int from = q - qb;
+      const int i = __builtin_amdgcn_readlane(my_i, from);
+      int* rad = a.rad + (int64_t)i * a.max_rad;
+      int* ang = a.ang + (int64_t)i * a.max_ang;
+      int nr = 0, na = 0, ro[S], ao[S];
+#pragma unroll
+      for (int s = 0; s < S; ++s) ro[s] = ao[s] = 0;
+      bool again = !fast_cell;
+      if (fast_cell) {
+        const float x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(px), from));
+        const float y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(py), from));
+        const float z = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pz), from));
+        // every comparison counts on scalar instructions too, so the checks are
+        // per lane: the least distance of any r^2 to a cutoff, and places held
+        // below the capacity (a list that reaches it is done again)
+        float margin = 3e18f;
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) {
+          if (c < nch) {
+            const float dx = cx[c] - x, dy = cy[c] - y, dz = cz[c] - z;
+            float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+            r2 = cj[c] == i ? 3e18f : r2;
+            const uint64_t mr = __builtin_amdgcn_ballot_w64(r2 < a.rc2), ma = __builtin_amdgcn_ballot_w64(r2 < a.rca2);
+            margin = fminf(margin, fminf(fabsf(r2 - a.rc2), fabsf(r2 - a.rca2)));
+            const unsigned pr = min(place(mr, nr), last_r), pa = min(place(ma, na), last_a);
+            if (starts >> c & 1) {   // a species starts in this chunk
+#pragma unroll
+              for (int s = 1; s < S; ++s)
+                if ((first[s] >> 6) == c) {
+                  const uint64_t before = (uint64_t(1) << (first[s] & 63)) - 1;
+                  ro[s] = nr + __popcll(mr & before);
+                  ao[s] = na + __popcll(ma & before);
+                }
+            }
             nr += __popcll(mr);
             na += __popcll(ma);
-            if (nr > a.max_rad || na > a.max_ang) {
-              overflow = true;
-              nr = min(nr, a.max_rad);
-              na = min(na, a.max_ang);
-            }
+            if (__builtin_amdgcn_inverse_ballot_w64(mr)) rad[pr] = cj[c];
+            if (__builtin_amdgcn_inverse_ballot_w64(ma)) ang[pa] = cj[c];
           }
         }
+        again = nr > a.max_rad || na > a.max_ang || __ballot(!(margin > eps)) != 0;
+#pragma unroll
+        for (int s = 1; s < S; ++s)
+          if ((first[s] >> 6) >= nch) {   // no candidate of species s or later
+            ro[s] = nr;
+            ao[s] = na;
+          }
       }
+      if (again) {   // the predicate itself, with the lists' capacities
+        nr = na = 0;
+        bool overflow = false;
+        const float4 pi = a.spos[i];
+        int next = 1;   // species whose start comes next
+        for (int c0 = 0; c0 < total; c0 += 64) {
+          const int c = c0 + lane;
+          int j = -1;
+          if (c < total) {
+            if (c < kCap) {
+              j = s_cand[c];
+            } else {
+              int lo = 0, hi = S * kMaxStencil - 1;
+              while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (s_off[mid] <= c) lo = mid; else hi = mid - 1;
+              }
+              j = s_start[lo] + (c - s_off[lo]);
+            }
+          }
+          const bool valid = j >= 0 && j != i;
+          const float r2 = pair_r2_exact(pi, a.spos[valid ? j : i], mi);
+          const uint64_t mr = __ballot(valid && r2 < a.rc2);
+          const int pr = nr + below(mr);
+          const uint64_t ma = __ballot(valid && r2 < a.rca2 && pr < a.max_rad);
+          const int pa = na + below(ma);
+#pragma unroll
+          for (int s = 1; s < S; ++s)
+            if (s == next && first[s] < c0 + 64) {
+              const uint64_t before = (uint64_t(1) << (first[s] - c0)) - 1;
+              ro[s] = min(nr + __popcll(mr & before), a.max_rad);
+              ao[s] = min(na + __popcll(ma & before), a.max_ang);
+              ++next;
+            }
+          if ((mr >> lane & 1) && pr < a.max_rad) rad[pr] = j;
+          if ((ma >> lane & 1) && pa < a.max_ang) ang[pa] = j;
+          nr += __popcll(mr);
+          na += __popcll(ma);
+          if (nr > a.max_rad || na > a.max_ang) {
+            overflow = true;
+            nr = min(nr, a.max_rad);
+            na = min(na, a.max_ang);
+          }
+        }
+#pragma unroll
+        for (int s = 1; s < S; ++s)
+          if (s >= next) {   // species s starts behind the last candidate
+            ro[s] = nr;
+            ao[s] = na;
+          }
+        if (overflow && lane == 0) atomicOr(a.status, kStatusCapacity);
+      }
+      // species offsets: lanes 0 .. S the radial ones, 16 .. 16 + S the angular ones
+      const int t = lane & 15;
+      int v = lane < 16 ? nr : na;
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        if (t == s) v = lane < 16 ? ro[s] : ao[s];
+      int* dst = (lane < 16 ? a.rad_off : a.ang_off) + (int64_t)i * (S + 1) + t;
+      if (lane < 32 && t <= S) *dst = v;
     }
-    if (lane < nc) {
-      a.rad_off[(int64_t)my_i * (a.S + 1) + a.S] = nr;
-      a.ang_off[(int64_t)my_i * (a.S + 1) + a.S] = na;
-      if (overflow) atomicOr(a.status, kStatusCapacity);
-    }
-    __syncthreads();   // s_cid / s_cpos are rewritten by the next centre block
   }
+}
+
+// The cell kernel's conditions: a periodic box of at least three cells per
+// dimension, and where there are three, cells longer than the cutoff by the
+// margin (see k_neighbours_cell).
+bool cells_fast(const Geometry& g, float rc) {
+  if (!g.periodic) return false;
+  for (int k = 0; k < 3; ++k)
+    if (g.nc[k] < 3 || (g.nc[k] == 3 && g.cell_len[k] < rc + kCullMargin)) return false;
+  return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -1162,15 +1265,17 @@ hipError_t launch_cells(nnp_model& m, const float* pos, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Wavefronts per cell share the candidate loads and the stencil set-up among
-// a few centre atoms each; that wins on large periodic grids (98k atoms:
-// 114 us against 156 us per atom), one wavefront per atom on smaller ones
-// (12k atoms: 32 us against 36 us) and for open systems.  A pinned or tuned
-// choice overrides the default.
+// 0: one wavefront per atom; 1 / 2 / 3: the cell kernel with about 16 / 8 / 4
+// centres per wavefront (only where its conditions hold).  Without a pinned or
+// tuned choice, the cell kernel from 40,000 atoms on, when its wavefronts, each
+// a long chain, come to more than a few per SIMD: 27,000 atoms 35 us against
+// 32 for variant 0, 48,000 atoms 45 against 51, 98,304 atoms 65 against 96,
+// 261,000 atoms 136 (variant 1) against 225.
 int neighbour_variant(const nnp_model& m, int n) {
-  if (m.geo.n_bins < 2) return 0;
+  if (!cells_fast(m.geo, m.dp.rc_rad)) return 0;
   const int v = stage_variant(m, kTuneNeighbours, n);
-  return v >= 0 ? v : 0;
+  if (v >= 0) return v;
+  return n < 40000 ? 0 : m.geo.n_bins < 48 * m.n_cu ? 2 : 1;
 }
 
 hipError_t launch_neighbours(nnp_model& m, int n, hipStream_t st) {
@@ -1199,11 +1304,17 @@ hipError_t launch_neighbours(nnp_model& m, int n, hipStream_t st) {
   a.status = m.d_status;
   const int v = neighbour_variant(m, n);
   if (v >= 1) {
-    // K wavefronts share a cell, each with about 8 / 5 / 3 centre atoms
-    const int target = v == 1 ? 8 : (v == 2 ? 5 : 3);
-    const int per_bin = (n + m.geo.n_bins - 1) / m.geo.n_bins;
-    const int K = std::max(1, std::min(16, (per_bin + target - 1) / target));
-    hipLaunchKernelGGL(k_neighbours_cell, dim3((unsigned)(m.geo.n_bins * K)), dim3(64), 0, st, a, m.geo, K);
+    // K wavefronts share a cell
+    const int target = v == 1 ? 16 : (v == 2 ? 8 : 4);
+    const float per_bin = (float)n / (float)m.geo.n_bins;
+    const int K = std::max(1, std::min(64, (int)std::lround(per_bin / target)));
+    // registers for the candidates of a cell a fifth denser than the average
+    const bool more = 1.2f * kMaxStencil * per_bin > 512.f;
+    auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)(m.geo.n_bins * K)), dim3(64), 0, st, a, m.geo, K);
+    };
+    if (m.S == 2) run(more ? k_neighbours_cell<2, 12> : k_neighbours_cell<2, 8>);
+    else run(more ? k_neighbours_cell<4, 12> : k_neighbours_cell<4, 8>);   // nnp_create accepts two or four species
   } else {
     hipLaunchKernelGGL(k_neighbours, dim3(n), dim3(64), 0, st, a, m.geo);
   }
