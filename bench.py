@@ -130,7 +130,7 @@ def network_form(prec, cfg):
     return "bf16" if prec == "bf16" else ("fp32" if cfg.get("extra_inputs", 0) else "split")
 
 
-def stage_kernel(stage, variants, prec, cfg, periodic=True):
+def stage_kernel(stage, variants, prec, cfg, periodic=True, n=0):
     """Name (as the profiler prints it, without namespaces and arguments) of the kernel
     that runs a stage, given the variants the library reports."""
     widths = list(cfg["widths"])
@@ -140,7 +140,8 @@ def stage_kernel(stage, variants, prec, cfg, periodic=True):
     if stage == "neighbours":
         return "k_neighbours" if v.get("neighbours", 0) == 0 else "k_neighbours_cell"
     if stage == "descriptor":
-        return ["k_desc_fwd", "k_desc_fwd_rows<16>", "k_desc_fwd_rows<8>", "k_desc_fwd_pool<2>",
+        small = "k_desc_fwd_pool<1>" if 0 < n <= 8 * 256 else "k_desc_fwd_pool<2>"   # eight atoms per CU
+        return ["k_desc_fwd", "k_desc_fwd_rows<16>", "k_desc_fwd_rows<8>", small,
                 "k_desc_fwd_pool<4>"][v.get("descriptor", 1)]
     if stage == "network":
         nv = v.get("network", 2)
@@ -528,7 +529,7 @@ def roofline(res, cfg, prec, stage, workload, periodic):
 
 def _roofline(res, cfg, prec, stage, workload, periodic):
     widths = list(cfg["widths"])
-    kernel = stage_kernel(stage, res["tuned"], prec, cfg, periodic)
+    kernel = stage_kernel(stage, res["tuned"], prec, cfg, periodic, res["n"])
     traffic = profile_traffic(workload, kernel)
     n = res["n"]
     t = res["stage_ms"][stage] * 1e-3

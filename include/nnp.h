@@ -311,7 +311,7 @@ nnp_status nnp_read_buffer(nnp_model* m, nnp_buffer which, void* dst_host, size_
  * or of 32 atoms with 16 for the smallest species, with four or eight
  * wavefronts;
  * descriptor forward: a wavefront, a 16-lane or an 8-lane row per atom, or
- * wavefronts of two or four atoms sharing their lanes over chunks; neighbour
+ * wavefronts of one to four atoms sharing their lanes over chunks; neighbour
  * search: one wavefront per atom, or several per cell sharing its centre
  * atoms; the descriptor adjoint has one kernel).
  * nnp_autotune reruns the
@@ -344,9 +344,11 @@ typedef enum {
  *     about 16 / 8 / 4 centre atoms each (periodic boxes of at least three
  *     cells per dimension, else 0 is used);
  *   descriptor forward: 0 one wavefront per atom; 1 / 2 one 16-lane / 8-lane
- *     row per atom; 3 / 4 two / four atoms per wavefront, their radial
- *     segments and angular classes cut into equal chunks, one per lane
- *     (for several elements, whose classes hold few pairs each);
+ *     row per atom; 3 / 4 two / four atoms per wavefront (3: one while the
+ *     system has at most eight atoms per CU), their radial segments and
+ *     angular classes cut into equal chunks, one per lane (default: 3 for
+ *     three and four elements and for small systems, 4 for large ones, 1 in
+ *     between and in the BF16 form);
  *   network: 0 register-resident wavefronts; 1 / 2 / 3 row-split workgroups
  *     of 16 / 32 / 64 atoms (64 for water-sized networks only, in the FP32
  *     form with eight wavefronts; wider ones use 32); 4 workgroups of 32 atoms, 16 for the species with the fewest

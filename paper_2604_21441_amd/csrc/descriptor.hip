@@ -4,10 +4,10 @@
 // models the paper runs and benchmarks (Methods; performance section); the
 // adjoint gives F = -grad E (Theory, eq. 2).
 //
-// The forward runs one 16-lane row per atom (k_desc_fwd_rows, default), one
-// wavefront per atom (k_desc_fwd), or several atoms per wavefront with the
-// lanes balanced over chunks of all their work (k_desc_fwd_pool, for many
-// elements); the adjoint one wavefront (or half of one) per atom.  An output block is either the radial block of one neighbour
+// The forward runs one 16-lane row per atom (k_desc_fwd_rows), one wavefront
+// per atom (k_desc_fwd), or one to four atoms per wavefront with the lanes
+// balanced over chunks of all their work (k_desc_fwd_pool), chosen by elements
+// and size (descriptor_variant); the adjoint one wavefront per atom.  An output block is either the radial block of one neighbour
 // species (16 outputs) or the angular block of one unordered species pair
 // (8 x 4 outputs).
 //
@@ -1310,12 +1310,29 @@ hipError_t launch_link_redistribute(nnp_model& m, const float* pos, double* forc
 }
 
 // Forward descriptor variants: 0 = one wavefront per atom, 1 = one 16-lane
-// row per atom (default), 2 = one 8-lane row per atom (fewer idle lanes,
-// half the wavefronts: for large systems), 3 and 4 = the pool kernel with two
-// and four atoms per wavefront (many elements: few pairs per class).
+// row per atom, 2 = one 8-lane row per atom (fewer idle lanes, half the
+// wavefronts), 3 and 4 = the pool kernel with two and four atoms per
+// wavefront (3: with one while that still leaves lanes idle, see
+// launch_descriptor_fwd).
+//
+// The default.  With three or four elements a centre has many classes of few
+// pairs, which rows of lanes walk one after the other: the pool is faster at
+// every size (us, variant 1 -> 3): 60 atoms 21.0 -> 11.3, 1,000 atoms 33.8 ->
+// 17, 25,000 atoms 104 -> 58.  With two elements the line is drawn by what
+// there is to hide latency with: up to 24 atoms per CU the pool's even split
+// is faster (192 atoms 14.7 -> 12.8, 5,400 atoms 21.5 -> 18.1), in between
+// the rows (12,288 atoms 21.4, pool 22.0 to 23.7), and from 72 atoms per CU
+// on four pooled atoms per wavefront waste the fewest lanes (27,000 atoms
+// 39.1 -> 36.0, 87,000 atoms 95.1 -> 87.6).
+// The BF16 form rounds the descriptors to eight bits; there another order of
+// summation turns single roundings over and moves forces by 1e-4, so its
+// default stays the row kernel at every size.
 int descriptor_variant(const nnp_model& m, int n) {
   const int v = stage_variant(m, kTuneDescriptor, n);
-  return v >= 0 ? v : 1;
+  if (v >= 0) return v;
+  if (m.prec == NNP_BF16) return 1;
+  if (m.S > 2) return 3;
+  return n <= 24 * m.n_cu ? 3 : n >= 72 * m.n_cu ? 4 : 1;
 }
 
 hipError_t launch_descriptor_fwd(nnp_model& m, int n, hipStream_t st) {
@@ -1333,11 +1350,17 @@ hipError_t launch_descriptor_fwd(nnp_model& m, int n, hipStream_t st) {
   a.x = m.d_x;
   const int v = descriptor_variant(m, n);
   if (v == 3 || v == 4) {
-    const int aw = v == 3 ? 2 : 4;
+    // Up to two wavefronts of one atom per SIMD run side by side anyway, and
+    // one atom's work is the shorter chain: 300 H/C/N/O atoms 20 -> 14 us per
+    // descriptor, 900 atoms of water 13.3 -> 12.2; 6,400 H/C/N/O atoms 29.4
+    // -> 30.2, 3,000 of water 15.5 -> 16.1.
+    const int aw = v == 4 ? 4 : n <= 8 * m.n_cu ? 1 : 2;
     const size_t area = (std::max((size_t)aw * m.max_ang * 5, (size_t)64 * kPoolPitch) + 3) & ~(size_t)3;
     const size_t lds = 4 * sizeof(float) * (area + 64);   // four wavefronts, each with its own slice
     const unsigned blocks = (unsigned)((n + 4 * aw - 1) / (4 * aw));
-    if (v == 3)
+    if (aw == 1)
+      hipLaunchKernelGGL(k_desc_fwd_pool<1>, dim3(blocks), dim3(256), lds, st, a, m.dp, m.geo);
+    else if (aw == 2)
       hipLaunchKernelGGL(k_desc_fwd_pool<2>, dim3(blocks), dim3(256), lds, st, a, m.dp, m.geo);
     else
       hipLaunchKernelGGL(k_desc_fwd_pool<4>, dim3(blocks), dim3(256), lds, st, a, m.dp, m.geo);
