@@ -78,7 +78,6 @@ size_t carve_workspace(const nnp_model& m, Workspace& w, char* base) {
   take(w.d_sbin, n);
   take(w.d_loc, n);
   take(w.d_islot, n);
-  take(w.d_pcount, n);
   take(w.d_spos, n);
   take(w.d_stg, n);
   take(w.d_bin_count, (size_t)w.max_bins);
@@ -570,8 +569,9 @@ nnp_status run_path(nnp_model* m, int n, const float* pos, int n_mm, const float
                     int assign_forces, int n_atoms, int n_pairs, const int* pairs, hipStream_t st) {
   m->last_n = n;
   StageTimer tm(m, st);
-  STAGE(NNP_STAGE_CELLS, launch_cells(*m, pos, n, st), "cell list");
-  if (pairs != nullptr || n_pairs > 0)
+  const bool pair_list = pairs != nullptr || n_pairs > 0;
+  STAGE(NNP_STAGE_CELLS, launch_cells(*m, pos, n, pair_list, st), "cell list");
+  if (pair_list)
     STAGE(NNP_STAGE_NEIGHBOURS, launch_pair_lists(*m, n, n_atoms, n_pairs, pairs, st), "pair lists");
   else
     STAGE(NNP_STAGE_NEIGHBOURS, launch_neighbours(*m, n, st), "neighbours");

@@ -38,6 +38,19 @@ __device__ __forceinline__ float3 nnp_position(const float* __restrict__ pos, in
   return make_float3(p.x + s * ux, p.y + s * uy, p.z + s * uz);
 }
 
+// Counters of a pair list's radial entries, one per slot, at the start of the
+// slot's row of force contributions (unused until the adjoint, and a cache
+// line of its own): 52,000 atomics on counters that shared 29 lines took 15
+// us, spread out they take 6.  Without a pair list `at` is null.
+struct PairCount {
+  int* at;
+  int stride;
+};
+
+inline PairCount pair_count(const nnp_model& m) {
+  return PairCount{reinterpret_cast<int*>(m.d_contrib), (int)(sizeof(float3) / sizeof(int)) * m.max_rad};
+}
+
 // Bin of one position in the periodic grid.
 __device__ __forceinline__ int cell_of(float x, float y, float z, const Geometry& g) {
 #pragma clang fp contract(off)
@@ -400,7 +413,7 @@ __global__ __launch_bounds__(kScanThreads) void k_cells_small(const float* __res
                                                               int* __restrict__ perm, float4* __restrict__ spos,
                                                               int* __restrict__ slot_atom,
                                                               int* __restrict__ order, int* __restrict__ sbin,
-                                                              int* __restrict__ islot, int* __restrict__ pcount,
+                                                              int* __restrict__ islot, PairCount pc,
                                                               int* __restrict__ status) {
   __shared__ int wsum[2 * (kScanThreads / 64) + 1];
   __shared__ int hist[scan_lds_words<PER>()];   // counts per key, then species-major starts
@@ -472,7 +485,7 @@ __global__ __launch_bounds__(kScanThreads) void k_cells_small(const float* __res
     order[o0 + rank] = slot;
     sbin[slot] = ((cxy / g.nc[1]) << 20) | ((cxy % g.nc[1]) << 10) | cz;
     islot[t] = slot;
-    pcount[slot] = 0;
+    if (pc.at != nullptr) pc.at[(int64_t)slot * pc.stride] = 0;
     spos[slot] = make_float4(pp[u].x, pp[u].y, pp[u].z, __int_as_float(ss[u]));
     slot_atom[slot] = aa[u];
   }
@@ -491,7 +504,7 @@ __global__ __launch_bounds__(kBlock) void k_binsort(const int* __restrict__ star
                                                     float4* __restrict__ spos,
                                                     int* __restrict__ slot_atom,
                                                     int* __restrict__ order, int* __restrict__ sbin,
-                                                    int* __restrict__ islot, int* __restrict__ pcount,
+                                                    int* __restrict__ islot, PairCount pc,
                                                     int* __restrict__ count) {
   int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   int lane = threadIdx.x & 63;
@@ -520,7 +533,7 @@ __global__ __launch_bounds__(kBlock) void k_binsort(const int* __restrict__ star
     order[o0 + rank] = slot;
     sbin[slot] = packed;
     islot[t] = slot;
-    pcount[slot] = 0;
+    if (pc.at != nullptr) pc.at[(int64_t)slot * pc.stride] = 0;
     spos[slot] = stg[t];   // staged by k_stage: no second trip through idx and pos
     slot_atom[slot] = idx[t];
   }
@@ -539,7 +552,7 @@ __global__ __launch_bounds__(64) void k_rank_systems(const int* __restrict__ sys
                                                       int* __restrict__ perm, float4* __restrict__ spos,
                                                       int* __restrict__ slot_atom, int* __restrict__ order,
                                                       int* __restrict__ count, int* __restrict__ sbin,
-                                                      int* __restrict__ islot, int* __restrict__ pcount) {
+                                                      int* __restrict__ islot, PairCount pc) {
   const int m = blockIdx.x;
   const int lane = threadIdx.x;
   if (lane < S) count[lane * n_sys + m] = 0;   // the histogram starts from zero in the next call
@@ -586,7 +599,7 @@ __global__ __launch_bounds__(64) void k_rank_systems(const int* __restrict__ sys
       order[o] = slot;
       sbin[slot] = m;
       islot[t] = slot;
-      pcount[slot] = 0;
+      if (pc.at != nullptr) pc.at[(int64_t)slot * pc.stride] = 0;
       spos[slot] = make_float4(p.x, p.y, p.z, __int_as_float(sg));
       slot_atom[slot] = a;
     }
@@ -1058,8 +1071,8 @@ __global__ __launch_bounds__(kBlock) void k_pairs_scatter(const int* __restrict_
                                                           const int* __restrict__ loc, int n_atoms,
                                                           const int* __restrict__ islot,
                                                           const float4* __restrict__ spos, Geometry g, float rc2,
-                                                          int* __restrict__ rad, int* __restrict__ pcount,
-                                                          int max_rad, int* __restrict__ status) {
+                                                          int* __restrict__ rad, PairCount pc, int max_rad,
+                                                          int* __restrict__ status) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
   if (p >= n_pairs) return;
   const int a = pairs[2 * (int64_t)p], b = pairs[2 * (int64_t)p + 1];
@@ -1071,7 +1084,7 @@ __global__ __launch_bounds__(kBlock) void k_pairs_scatter(const int* __restrict_
   if (la < 0 || lb < 0) return;   // a pair with an atom outside the index group
   const int sa = islot[la], sb = islot[lb];
   if (!(pair_r2(spos[sa], spos[sb], g) < rc2)) return;
-  const int pa = atomicAdd(&pcount[sa], 1), pb = atomicAdd(&pcount[sb], 1);
+  const int pa = atomicAdd(pc.at + (int64_t)sa * pc.stride, 1), pb = atomicAdd(pc.at + (int64_t)sb * pc.stride, 1);
   if (pa < max_rad) rad[(int64_t)sa * max_rad + pa] = sb;
   if (pb < max_rad) rad[(int64_t)sb * max_rad + pb] = sa;
 }
@@ -1083,7 +1096,7 @@ __global__ __launch_bounds__(kBlock) void k_pairs_scatter(const int* __restrict_
 // index.  The NNP-local indices of the link atoms are [n - n_links, n).
 __global__ __launch_bounds__(64) void k_link_pairs(int n, int n_links, const int* __restrict__ islot,
                                                    const float4* __restrict__ spos, Geometry g, float rc2,
-                                                   int* __restrict__ rad, int* __restrict__ pcount, int max_rad) {
+                                                   int* __restrict__ rad, PairCount pc, int max_rad) {
   const int tl = n - n_links + (int)blockIdx.x;
   const int sl = islot[tl];
   const float4 pl = spos[sl];
@@ -1091,85 +1104,124 @@ __global__ __launch_bounds__(64) void k_link_pairs(int n, int n_links, const int
     if (t >= n - n_links && t <= tl) continue;
     const int st = islot[t];
     if (!(pair_r2(pl, spos[st], g) < rc2)) continue;
-    const int pa = atomicAdd(&pcount[sl], 1), pb = atomicAdd(&pcount[st], 1);
+    const int pa = atomicAdd(pc.at + (int64_t)sl * pc.stride, 1), pb = atomicAdd(pc.at + (int64_t)st * pc.stride, 1);
     if (pa < max_rad) rad[(int64_t)sl * max_rad + pa] = st;
     if (pb < max_rad) rad[(int64_t)st * max_rad + pb] = sl;
   }
 }
 
-// One wavefront per slot: bitonic sort of the row (padded to a power of two,
-// at most kPairRowMax entries), then the species offsets and the angular list.
-constexpr int kPairSort = kPairRowMax;
+// One wavefront per slot: sorts the row by slot, then the species offsets and
+// the angular list.  The place of an entry (up to four per lane) is the count
+// of smaller ones, read from LDS four at a time; equal entries (a pair given
+// twice, an input error) would take the same place and leave the next one
+// empty, and are then placed in the order of the row.  While the counting
+// runs, the entries' positions arrive, so that each entry carries its angular
+// flag (bit 31) to its place.
+//
+// Bound by the latency of one wavefront's chain: for 900 atoms 5.9 us; with a
+// bitonic sort, the positions read after it and the segments counted entry by
+// entry, 11.3 us.
+constexpr int kPairRank = kPairRowMax / 64;
 
-__global__ __launch_bounds__(64) void k_pairs_lists(NeighArgs a, Geometry g, const int* __restrict__ pcount) {
-  __shared__ int row[kPairSort];
-  __shared__ int arow[kPairSort];   // angular entries (slots), for the species counts
+__global__ __launch_bounds__(64) void k_pairs_lists(NeighArgs a, Geometry g, PairCount pc) {
+  __shared__ int4 row4[kPairRowMax / 4];
+  __shared__ int sorted[kPairRowMax];
+  int* row = reinterpret_cast<int*>(row4);
   const int i = blockIdx.x;
   const int lane = threadIdx.x;
-  const int cnt = pcount[i];
+  int* rrow = a.rad + (int64_t)i * a.max_rad;
+  const int first = lane < a.max_rad ? rrow[lane] : 0;   // in flight with the count
+  const float4 pi = a.spos[i];
+  int bound[kMaxSpecies];   // first slot of species s + 1
+#pragma unroll
+  for (int s = 0; s < kMaxSpecies; ++s) bound[s] = s + 1 < a.S ? a.bin_start[(s + 1) * g.n_bins] : INT_MAX;
+  const int cnt = pc.at[(int64_t)i * pc.stride];
   bool overflow = cnt > a.max_rad;
   const int n = min(cnt, a.max_rad);
-  int P = 64;
-  while (P < n) P <<= 1;
-  int* rrow = a.rad + (int64_t)i * a.max_rad;
-  for (int t = lane; t < P; t += 64) row[t] = t < n ? rrow[t] : 0x7fffffff;
-  __syncthreads();
-  for (int k = 2; k <= P; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int t = lane; t < P; t += 64) {
-        const int u = t ^ j;
-        if (u > t) {
-          const int x = row[t], y = row[u];
-          const bool up = (t & k) == 0;
-          if ((x > y) == up) {
-            row[t] = y;
-            row[u] = x;
-          }
-        }
-      }
-      __syncthreads();
+  const int nk = (n + 63) >> 6;
+  int e[kPairRank], place[kPairRank];
+#pragma unroll
+  for (int k = 0; k < kPairRank; ++k) {
+    const int t = 64 * k + lane;
+    e[k] = INT_MAX;
+    place[k] = 0;
+    if (k < nk) {
+      if (t < n) e[k] = k == 0 ? first : rrow[t];
+      row[t] = e[k];
+      sorted[t] = -1;
     }
   }
-  const float4 pi = a.spos[i];
-  const uint64_t lt = __lanemask_lt();
+  __syncthreads();
+  float4 pj[kPairRank];
+#pragma unroll
+  for (int k = 0; k < kPairRank; ++k)
+    if (k < nk) pj[k] = a.spos[64 * k + lane < n ? e[k] : i];
+  for (int t = 0; t < n; t += 4) {
+    const int4 x = row4[t >> 2];
+#pragma unroll
+    for (int k = 0; k < kPairRank; ++k)
+      if (k < nk) place[k] += (x.x < e[k]) + (x.y < e[k]) + (x.z < e[k]) + (x.w < e[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < kPairRank; ++k)
+    if (k < nk && 64 * k + lane < n) {
+      if (pair_r2(pi, pj[k], g) < a.rca2) e[k] |= INT_MIN;
+      sorted[place[k]] = e[k];
+    }
+  __syncthreads();
+  bool dup = false;   // places nothing came to (no slot is INT_MAX, so no entry is -1)
+#pragma unroll
+  for (int k = 0; k < kPairRank; ++k)
+    if (64 * k + lane < n && sorted[64 * k + lane] == -1) dup = true;
+  dup = __ballot(dup) != 0;
+  if (dup) {
+    for (int t = 0; t < n; ++t)
+#pragma unroll
+      for (int k = 0; k < kPairRank; ++k) place[k] += row[t] == (e[k] & INT_MAX) && t < 64 * k + lane;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kPairRank; ++k)
+      if (64 * k + lane < n) sorted[place[k]] = e[k];
+    __syncthreads();
+  }
   int* ang = a.ang + (int64_t)i * a.max_ang;
   int na = 0;
-  bool dup = false;
+  int seg_r[kMaxSpecies] = {}, seg_a[kMaxSpecies] = {};   // entries below each bound
   for (int c0 = 0; c0 < n; c0 += 64) {
     const int t = c0 + lane;
-    int j = -1;
-    bool in_a = false;
-    if (t < n) {
-      j = row[t];
-      rrow[t] = j;
-      if (t > 0 && row[t - 1] == j) dup = true;
-      in_a = pair_r2(pi, a.spos[j], g) < a.rca2;
-    }
+    const int v = t < n ? sorted[t] : INT_MAX;
+    const bool in_a = v < 0;
+    const int j = v & INT_MAX;
+    if (t < n) rrow[t] = j;
     const uint64_t ma = __ballot(in_a);
-    const int pa = na + __popcll(ma & lt);
-    if (in_a && pa < a.max_ang) {
-      ang[pa] = j;
-      arow[pa] = j;
-    }
+    const int pa = na + __popcll(ma & __lanemask_lt());
+    if (in_a && pa < a.max_ang) ang[pa] = j;
+#pragma unroll
+    for (int s = 0; s < kMaxSpecies; ++s)
+      if (s + 1 < a.S) {
+        seg_r[s] += __popcll(__ballot(j < bound[s]));
+        seg_a[s] += __popcll(__ballot(in_a && pa < a.max_ang && j < bound[s]));
+      }
     na += __popcll(ma);
   }
-  __syncthreads();
   if (na > a.max_ang) {
     overflow = true;
     na = a.max_ang;
   }
-  // species segments: slots below each species' first slot
-  if (lane <= a.S) {
-    const int bound = lane < a.S ? a.bin_start[lane * g.n_bins] : 0x7fffffff;
+  if (lane <= a.S) {   // offset of species `lane`: the entries below its first slot
     int r = 0, q = 0;
-    for (int t = 0; t < n; ++t) r += row[t] < bound;
-    for (int t = 0; t < na; ++t) q += arow[t] < bound;
+#pragma unroll
+    for (int s = 0; s < kMaxSpecies; ++s)
+      if (s + 1 == lane) {
+        r = seg_r[s];
+        q = seg_a[s];
+      }
     if (lane == a.S) { r = n; q = na; }
     a.rad_off[(int64_t)i * (a.S + 1) + lane] = r;
     a.ang_off[(int64_t)i * (a.S + 1) + lane] = q;
   }
   if (lane == 0 && overflow) atomicOr(a.status, kStatusCapacity);
-  if (__ballot(dup) != 0 && lane == 0) atomicOr(a.status, kStatusInput);
+  if (lane == 0 && dup) atomicOr(a.status, kStatusInput);
 }
 
 inline int blocks_for(int64_t n, int b) { return (int)((n + b - 1) / b); }
@@ -1199,10 +1251,10 @@ void launch_scan(nnp_model& m, hipStream_t st) {
 }
 
 template <int PER>
-void launch_cells_small(nnp_model& m, const float* pos, int n, const LinkArgs& L, hipStream_t st) {
+void launch_cells_small(nnp_model& m, const float* pos, int n, const LinkArgs& L, const PairCount& pc, hipStream_t st) {
   hipLaunchKernelGGL(k_cells_small<PER>, dim3(1), dim3(kScanThreads), 0, st, pos, n, m.d_idx, m.d_sigma, m.geo, L,
                      m.S, m.d_key, m.d_bin_start, m.d_perm, m.d_spos, m.d_slot_atom, m.d_order, m.d_sbin,
-                     m.d_islot, m.d_pcount, m.d_status);
+                     m.d_islot, pc, m.d_status);
 }
 
 template <int PER>
@@ -1213,17 +1265,18 @@ void launch_scan_scatter(nnp_model& m, int n, hipStream_t st) {
 
 }  // namespace
 
-hipError_t launch_cells(nnp_model& m, const float* pos, int n, hipStream_t st) {
+hipError_t launch_cells(nnp_model& m, const float* pos, int n, bool pair_list, hipStream_t st) {
+  const PairCount pc = pair_list ? pair_count(m) : PairCount{nullptr, 0};
   const Geometry& g = m.geo;
   LinkArgs L{m.d_link_ml, m.d_link_mm, m.link_d, m.n_links_dev};
   int nb = m.S * g.n_bins;
   if (n > 0 && g.periodic && n <= kSmallCells && nb <= kScanChunk) {
     switch (scan_entries_per_thread(nb)) {
-      case 1: launch_cells_small<1>(m, pos, n, L, st); break;
-      case 2: launch_cells_small<2>(m, pos, n, L, st); break;
-      case 4: launch_cells_small<4>(m, pos, n, L, st); break;
-      case 8: launch_cells_small<8>(m, pos, n, L, st); break;
-      default: launch_cells_small<16>(m, pos, n, L, st); break;
+      case 1: launch_cells_small<1>(m, pos, n, L, pc, st); break;
+      case 2: launch_cells_small<2>(m, pos, n, L, pc, st); break;
+      case 4: launch_cells_small<4>(m, pos, n, L, pc, st); break;
+      case 8: launch_cells_small<8>(m, pos, n, L, pc, st); break;
+      default: launch_cells_small<16>(m, pos, n, L, pc, st); break;
     }
     return hipGetLastError();
   }
@@ -1253,14 +1306,14 @@ hipError_t launch_cells(nnp_model& m, const float* pos, int n, hipStream_t st) {
   if (n > 0 && !g.periodic) {
     hipLaunchKernelGGL(k_rank_systems, dim3(g.n_bins), dim3(64), 0, st, m.d_sys_off, g.n_bins, m.S, m.d_bin_start,
                        m.d_sigma, m.d_idx, pos, g, L, m.d_cmstart, m.d_perm, m.d_spos, m.d_slot_atom,
-                       m.d_order, m.d_bin_count, m.d_sbin, m.d_islot, m.d_pcount);
+                       m.d_order, m.d_bin_count, m.d_sbin, m.d_islot, pc);
   } else if (n > 0) {
     if (!fused)
       hipLaunchKernelGGL(k_scatter, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, st, m.d_key, m.d_rank, n,
                          m.d_bin_start, m.d_tmp);
     hipLaunchKernelGGL(k_binsort, dim3(blocks_for((int64_t)nb * 64, kBlock)), dim3(kBlock), 0, st,
                        m.d_bin_start, nb, m.d_tmp, m.d_stg, m.d_idx, g, m.d_cmstart, m.S, m.d_perm,
-                       m.d_spos, m.d_slot_atom, m.d_order, m.d_sbin, m.d_islot, m.d_pcount, m.d_bin_count);
+                       m.d_spos, m.d_slot_atom, m.d_order, m.d_sbin, m.d_islot, pc, m.d_bin_count);
   }
   return hipGetLastError();
 }
@@ -1323,14 +1376,15 @@ hipError_t launch_neighbours(nnp_model& m, int n, hipStream_t st) {
 
 hipError_t launch_pair_lists(nnp_model& m, int n, int n_atoms, int n_pairs, const int* pairs, hipStream_t st) {
   if (n == 0) return hipSuccess;
+  const PairCount pc = pair_count(m);
   if (n_pairs > 0) {
     hipLaunchKernelGGL(k_pairs_scatter, dim3(blocks_for(n_pairs, kBlock)), dim3(kBlock), 0, st, pairs, n_pairs,
                        m.d_loc, n_atoms, m.d_islot, m.d_spos, m.geo, m.dp.rc_rad * m.dp.rc_rad, m.d_nbr_rad,
-                       m.d_pcount, m.max_rad, m.d_status);
+                       pc, m.max_rad, m.d_status);
   }
   if (m.n_links_dev > 0) {
     hipLaunchKernelGGL(k_link_pairs, dim3(m.n_links_dev), dim3(64), 0, st, n, m.n_links_dev, m.d_islot, m.d_spos,
-                       m.geo, m.dp.rc_rad * m.dp.rc_rad, m.d_nbr_rad, m.d_pcount, m.max_rad);
+                       m.geo, m.dp.rc_rad * m.dp.rc_rad, m.d_nbr_rad, pc, m.max_rad);
   }
   NeighArgs a;
   a.order = m.d_order;
@@ -1354,7 +1408,7 @@ hipError_t launch_pair_lists(nnp_model& m, int n, int n_atoms, int n_pairs, cons
   a.max_rad = m.max_rad;
   a.max_ang = m.max_ang;
   a.status = m.d_status;
-  hipLaunchKernelGGL(k_pairs_lists, dim3(n), dim3(64), 0, st, a, m.geo, m.d_pcount);
+  hipLaunchKernelGGL(k_pairs_lists, dim3(n), dim3(64), 0, st, a, m.geo, pc);
   return hipGetLastError();
 }
 

@@ -264,7 +264,6 @@ struct Workspace {
   int* d_sbin = nullptr;       // slot -> cell coordinates x<<20 | y<<10 | z (periodic) or system
   int* d_loc = nullptr;        // system atom -> NNP-local index or -1 (pair lists)
   int* d_islot = nullptr;      // NNP-local index -> slot
-  int* d_pcount = nullptr;     // radial entries per slot while a pair list is scattered
   int* d_nbr_rad = nullptr;
   int* d_nbr_ang = nullptr;
   int* d_rad_off = nullptr;
@@ -406,7 +405,7 @@ void pack_weights(const nnp_model& m, std::vector<uint8_t>& mat, std::vector<flo
 void pack_rows_bf16(const nnp_model& m, std::vector<uint16_t>& out, int64_t& per_species);
 
 // cells.hip
-hipError_t launch_cells(nnp_model& m, const float* pos, int n_nnp, hipStream_t st);
+hipError_t launch_cells(nnp_model& m, const float* pos, int n_nnp, bool pair_list, hipStream_t st);
 hipError_t launch_neighbours(nnp_model& m, int n_nnp, hipStream_t st);
 hipError_t launch_pair_lists(nnp_model& m, int n, int n_atoms, int n_pairs, const int* pairs, hipStream_t st);
 

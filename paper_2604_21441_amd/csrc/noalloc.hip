@@ -108,9 +108,10 @@ extern "C" nnp_status nnp_compute_noalloc(nnp_model* m, int32_t n_atoms, const f
 
   Workspace w = workspace_caps(*m, n_atoms, 1, 0, 128, 64);
   // The documented capacity (about 8,900 atoms of the two-species model, 5,700
-  // of the four-species one) counts one more word per angular entry than the
-  // layout uses; it stays.
-  const size_t need = carve_workspace(*m, w, nullptr) + (((size_t)n_atoms * w.max_ang * sizeof(int) + 255) & ~(size_t)255);
+  // of the four-species one) counts one more word per angular entry and per
+  // atom than the layout uses; it stays.
+  auto words = [](size_t n) { return (n * sizeof(int) + 255) & ~(size_t)255; };
+  const size_t need = carve_workspace(*m, w, nullptr) + words((size_t)n_atoms * w.max_ang) + words((size_t)n_atoms);
   if (need > kNoallocScratchBytes)
     return set_error(NNP_ECAPACITY, std::to_string(n_atoms) + " atoms need " + std::to_string(need) +
                                         " bytes of workspace; the static array holds " +
