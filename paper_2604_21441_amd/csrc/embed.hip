@@ -4,23 +4,42 @@
 //   E = sum_{i in ML} sum_{j in MM, r < rc} ke q_i q_j / r + 4 eps_ij ((s_ij/r)^12 - (s_ij/r)^6)
 // with Lorentz-Berthelot mixing s_ij = (s_i + s_j)/2, eps_ij = sqrt(eps_i eps_j).
 //
-// One lane per MM atom; the ML atoms (a small region) are staged in LDS in
-// chunks and every lane walks them.  Each pair is evaluated in FP32; the MM
-// atom's force and the lane's energy accumulate in FP64 registers; an ML
-// atom's force is reduced over the wavefront and added with one FP64 atomic
-// per wavefront (skipped when no lane of the wavefront is inside the cutoff).
+// A workgroup takes 64 MM atoms, one per lane of each of its eight
+// wavefronts, and the wavefronts share the ML atoms (staged in LDS) between
+// them.  Each pair is evaluated in FP32.  An MM atom's force and the energy
+// accumulate in FP64 registers and are summed over the wavefronts through
+// LDS, in order; an ML atom's force is summed over the wavefront's lanes and
+// added with FP64 atomics (skipped when no lane is inside the cutoff).
+//
+// Bound by the chain of one wavefront through its ML atoms: a sphere around
+// the ML region holds few of the MM atoms' wavefronts, and these few meet
+// nearly every ML atom inside the cutoff.  One wavefront walking all 60 ML
+// atoms for its 64 of 30,000 MM atoms took 52 us; eight that walk a share
+// each take 19 us.
 #include "nnp_internal.h"
 
 namespace nnp {
 namespace {
 
-constexpr int kMeBlock = 256;
+constexpr int kMeWaves = 8;
+constexpr int kMeBlock = 64 * kMeWaves;
 constexpr int kMeChunk = 256;   // ML atoms per LDS chunk
 
-__device__ __forceinline__ float wsum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+// v + (v of the lane that the DPP control names; 0 where there is none)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_add(float v) {
+  return v + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
+
+// Sum over the wavefront, in lane 63 (row shifts by 1, 2, 4 and 8, then the
+// rows' totals passed on).
+__device__ __forceinline__ float wsum63(float v) {
+  v = dpp_add<0x111, 0xf>(v);
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);
+  return dpp_add<0x143, 0xc>(v);
 }
 
 __device__ __forceinline__ double wsum_d(double v) {
@@ -38,8 +57,10 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
                                                        int accumulate) {
   __shared__ float4 sx[kMeChunk];   // ML x, y, z, q
   __shared__ float2 sp[kMeChunk];   // ML sigma, eps
-  const int j = blockIdx.x * kMeBlock + threadIdx.x;
+  __shared__ double sf[kMeWaves][4][64];   // per wavefront and MM atom: force, energy
   const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int j = blockIdx.x * 64 + lane;
   const bool ok = j < n_mm;
   float yx = 0.f, yy = 0.f, yz = 0.f, qj = 0.f, sj = 0.f, ej = 0.f;
   if (ok) {
@@ -61,7 +82,7 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
       sp[t] = make_float2(ml_par[3 * (int64_t)i + 1], ml_par[3 * (int64_t)i + 2]);
     }
     __syncthreads();
-    for (int t = 0; t < nc; ++t) {
+    for (int t = wave; t < nc; t += kMeWaves) {
       const float4 xi = sx[t];
       float dx = yx - xi.x, dy = yy - xi.y, dz = yz - xi.z;
       if (g.periodic) {
@@ -71,6 +92,7 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
       }
       const float r2 = dx * dx + dy * dy + dz * dz;
       const bool in = ok && r2 < rc2;
+      if (__builtin_amdgcn_ballot_w64(in) == 0) continue;
       float vx = 0.f, vy = 0.f, vz = 0.f;
       if (in) {
         const float2 pi = sp[t];
@@ -92,30 +114,42 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
         fy += vy;
         fz += vz;
       }
-      if (__ballot(in) != 0) {
-        const float rx = wsum(vx), ry = wsum(vy), rz = wsum(vz);
-        if (lane == 0) {
-          double* f = ml_f + 3 * (int64_t)(c0 + t);
-          unsafeAtomicAdd(f + 0, -(double)rx);
-          unsafeAtomicAdd(f + 1, -(double)ry);
-          unsafeAtomicAdd(f + 2, -(double)rz);
-        }
+      const float rx = wsum63(vx), ry = wsum63(vy), rz = wsum63(vz);
+      if (lane == 63) {
+        double* f = ml_f + 3 * (int64_t)(c0 + t);
+        unsafeAtomicAdd(f + 0, -(double)rx);
+        unsafeAtomicAdd(f + 1, -(double)ry);
+        unsafeAtomicAdd(f + 2, -(double)rz);
       }
     }
   }
-  if (ok) {
-    double* f = mm_f + 3 * (int64_t)j;
-    if (accumulate) {
-      fx += f[0];
-      fy += f[1];
-      fz += f[2];
+  sf[wave][0][lane] = fx;
+  sf[wave][1][lane] = fy;
+  sf[wave][2][lane] = fz;
+  sf[wave][3][lane] = eacc;
+  __syncthreads();
+  // wavefronts 0 to 2 write a component of the MM forces each, 3 adds the energy
+  if (wave > 3) return;
+  double v = 0.0;
+#pragma unroll
+  for (int w = 0; w < kMeWaves; ++w) v += sf[w][wave][lane];
+  if (wave < 3) {
+    if (ok) {
+      double* f = mm_f + 3 * (int64_t)j + wave;
+      *f = accumulate ? v + *f : v;
     }
-    f[0] = fx;
-    f[1] = fy;
-    f[2] = fz;
+  } else {
+    v = wsum_d(v);
+    if (lane == 0 && v != 0.0) unsafeAtomicAdd(energy, v);
   }
-  eacc = wsum_d(eacc);
-  if (lane == 0 && eacc != 0.0) unsafeAtomicAdd(energy, eacc);
+}
+
+// The outputs that k_me_pairs adds to, cleared in one launch.
+__global__ __launch_bounds__(kMeBlock) void k_me_clear(double* __restrict__ energy, double* __restrict__ ml_f,
+                                                       int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * kMeBlock + threadIdx.x;
+  if (i < n) ml_f[i] = 0.0;
+  if (i == 0) *energy = 0.0;
 }
 
 }  // namespace
@@ -123,15 +157,15 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
 hipError_t launch_me_pairs(int n_ml, const float* ml_pos, const float* ml_par, int n_mm, const float* mm_pos,
                            const float* mm_par, const Geometry& g, float cutoff, float ke, double* energy,
                            double* ml_f, double* mm_f, int accumulate, hipStream_t st) {
-  hipError_t e = hipSuccess;
   if (!accumulate) {
-    e = launch_fill_f64(energy, 1, st);
-    if (e == hipSuccess) e = launch_fill_f64(ml_f, 3 * (int64_t)n_ml, st);
+    const int64_t n = 3 * (int64_t)n_ml;
+    hipLaunchKernelGGL(k_me_clear, dim3((unsigned)(n / kMeBlock + 1)), dim3(kMeBlock), 0, st, energy, ml_f, n);
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   if (n_mm == 0) return hipSuccess;
   const float rc2 = cutoff > 0.f ? cutoff * cutoff : INFINITY;
-  hipLaunchKernelGGL(k_me_pairs, dim3((n_mm + kMeBlock - 1) / kMeBlock), dim3(kMeBlock), 0, st, ml_pos, ml_par,
+  hipLaunchKernelGGL(k_me_pairs, dim3((n_mm + 63) / 64), dim3(kMeBlock), 0, st, ml_pos, ml_par,
                      n_ml, mm_pos, mm_par, n_mm, g, rc2, ke, energy, ml_f, mm_f, accumulate);
   return hipGetLastError();
 }
