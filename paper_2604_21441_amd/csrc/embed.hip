@@ -4,18 +4,19 @@
 //   E = sum_{i in ML} sum_{j in MM, r < rc} ke q_i q_j / r + 4 eps_ij ((s_ij/r)^12 - (s_ij/r)^6)
 // with Lorentz-Berthelot mixing s_ij = (s_i + s_j)/2, eps_ij = sqrt(eps_i eps_j).
 //
-// A workgroup takes 64 MM atoms, one per lane of each of its eight
+// A workgroup takes 128 MM atoms, two per lane of each of its eight
 // wavefronts, and the wavefronts share the ML atoms (staged in LDS) between
 // them.  Each pair is evaluated in FP32.  An MM atom's force and the energy
 // accumulate in FP64 registers and are summed over the wavefronts through
 // LDS, in order; an ML atom's force is summed over the wavefront's lanes and
 // added with FP64 atomics (skipped when no lane is inside the cutoff).
 //
-// Bound by the chain of one wavefront through its ML atoms: a sphere around
+// Bound by the chain of one wavefront through its ML atoms (a sphere around
 // the ML region holds few of the MM atoms' wavefronts, and these few meet
-// nearly every ML atom inside the cutoff.  One wavefront walking all 60 ML
-// atoms for its 64 of 30,000 MM atoms took 52 us; eight that walk a share
-// each take 19 us.
+// nearly every ML atom inside the cutoff) and by the atomics on the few lines
+// of ML forces.  60 x 30,000 atoms: one wavefront walking all ML atoms for 64
+// MM atoms 52 us; eight sharing them 19 us; with two MM atoms per lane, which
+// halves the sums over lanes and the atomics, 15 us (four: 16, eight: 21).
 #include "nnp_internal.h"
 
 namespace nnp {
@@ -23,6 +24,7 @@ namespace {
 
 constexpr int kMeWaves = 8;
 constexpr int kMeBlock = 64 * kMeWaves;
+constexpr int kMeTiles = 2;     // 64 MM atoms each
 constexpr int kMeChunk = 256;   // ML atoms per LDS chunk
 
 // v + (v of the lane that the DPP control names; 0 where there is none)
@@ -57,21 +59,23 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
                                                        int accumulate) {
   __shared__ float4 sx[kMeChunk];   // ML x, y, z, q
   __shared__ float2 sp[kMeChunk];   // ML sigma, eps
-  __shared__ double sf[kMeWaves][4][64];   // per wavefront and MM atom: force, energy
+  __shared__ double sf[kMeWaves][4][64];   // per wavefront and MM atom of a tile: force, energy
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int j = blockIdx.x * 64 + lane;
-  const bool ok = j < n_mm;
-  float yx = 0.f, yy = 0.f, yz = 0.f, qj = 0.f, sj = 0.f, ej = 0.f;
-  if (ok) {
-    yx = mm_pos[3 * (int64_t)j];
-    yy = mm_pos[3 * (int64_t)j + 1];
-    yz = mm_pos[3 * (int64_t)j + 2];
-    qj = mm_par[3 * (int64_t)j];
-    sj = mm_par[3 * (int64_t)j + 1];
-    ej = mm_par[3 * (int64_t)j + 2];
+  const int j0 = blockIdx.x * (64 * kMeTiles) + lane;
+  float4 y[kMeTiles];    // MM x, y, z, q
+  float2 yp[kMeTiles];   // MM sigma, eps
+#pragma unroll
+  for (int u = 0; u < kMeTiles; ++u) {
+    const int64_t j = 3 * (int64_t)(j0 + 64 * u);
+    y[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    yp[u] = make_float2(0.f, 0.f);
+    if (j0 + 64 * u < n_mm) {
+      y[u] = make_float4(mm_pos[j], mm_pos[j + 1], mm_pos[j + 2], mm_par[j]);
+      yp[u] = make_float2(mm_par[j + 1], mm_par[j + 2]);
+    }
   }
-  double fx = 0.0, fy = 0.0, fz = 0.0, eacc = 0.0;
+  double f[kMeTiles][3] = {}, eacc = 0.0;
   for (int c0 = 0; c0 < n_ml; c0 += kMeChunk) {
     const int nc = min(kMeChunk, n_ml - c0);
     __syncthreads();
@@ -84,63 +88,72 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
     __syncthreads();
     for (int t = wave; t < nc; t += kMeWaves) {
       const float4 xi = sx[t];
-      float dx = yx - xi.x, dy = yy - xi.y, dz = yz - xi.z;
-      if (g.periodic) {
-        dx -= g.box[0] * rintf(dx * g.inv_box[0]);
-        dy -= g.box[1] * rintf(dy * g.inv_box[1]);
-        dz -= g.box[2] * rintf(dz * g.inv_box[2]);
+      const float2 pi = sp[t];
+      float ax = 0.f, ay = 0.f, az = 0.f;
+      bool any = false;
+#pragma unroll
+      for (int u = 0; u < kMeTiles; ++u) {
+        float dx = y[u].x - xi.x, dy = y[u].y - xi.y, dz = y[u].z - xi.z;
+        if (g.periodic) {
+          dx -= g.box[0] * rintf(dx * g.inv_box[0]);
+          dy -= g.box[1] * rintf(dy * g.inv_box[1]);
+          dz -= g.box[2] * rintf(dz * g.inv_box[2]);
+        }
+        const float r2 = dx * dx + dy * dy + dz * dz;
+        if (j0 + 64 * u < n_mm && r2 < rc2) {
+          any = true;
+          const float ir2 = 1.f / r2;
+          const float ir = sqrtf(ir2);
+          const float qq = ke * xi.w * y[u].w;
+          const float s = 0.5f * (pi.x + yp[u].x);
+          const float eps = sqrtf(pi.y * yp[u].y);
+          const float s2 = s * s * ir2;
+          const float s6 = s2 * s2 * s2;
+          const float s12 = s6 * s6;
+          const float ec = qq * ir;
+          eacc += (double)ec + (double)(4.f * eps * (s12 - s6));
+          const float w = (ec + eps * (48.f * s12 - 24.f * s6)) * ir2;   // -dE/dr / r
+          const float vx = w * dx, vy = w * dy, vz = w * dz;
+          ax += vx;
+          ay += vy;
+          az += vz;
+          f[u][0] += vx;
+          f[u][1] += vy;
+          f[u][2] += vz;
+        }
       }
-      const float r2 = dx * dx + dy * dy + dz * dz;
-      const bool in = ok && r2 < rc2;
-      if (__builtin_amdgcn_ballot_w64(in) == 0) continue;
-      float vx = 0.f, vy = 0.f, vz = 0.f;
-      if (in) {
-        const float2 pi = sp[t];
-        const float ir2 = 1.f / r2;
-        const float ir = sqrtf(ir2);
-        const float qq = ke * xi.w * qj;
-        const float s = 0.5f * (pi.x + sj);
-        const float eps = sqrtf(pi.y * ej);
-        const float s2 = s * s * ir2;
-        const float s6 = s2 * s2 * s2;
-        const float s12 = s6 * s6;
-        const float ec = qq * ir;
-        eacc += (double)ec + (double)(4.f * eps * (s12 - s6));
-        const float w = (ec + eps * (48.f * s12 - 24.f * s6)) * ir2;   // -dE/dr / r
-        vx = w * dx;
-        vy = w * dy;
-        vz = w * dz;
-        fx += vx;
-        fy += vy;
-        fz += vz;
-      }
-      const float rx = wsum63(vx), ry = wsum63(vy), rz = wsum63(vz);
+      if (__builtin_amdgcn_ballot_w64(any) == 0) continue;
+      const float rx = wsum63(ax), ry = wsum63(ay), rz = wsum63(az);
       if (lane == 63) {
-        double* f = ml_f + 3 * (int64_t)(c0 + t);
-        unsafeAtomicAdd(f + 0, -(double)rx);
-        unsafeAtomicAdd(f + 1, -(double)ry);
-        unsafeAtomicAdd(f + 2, -(double)rz);
+        double* o = ml_f + 3 * (int64_t)(c0 + t);
+        unsafeAtomicAdd(o + 0, -(double)rx);
+        unsafeAtomicAdd(o + 1, -(double)ry);
+        unsafeAtomicAdd(o + 2, -(double)rz);
       }
     }
   }
-  sf[wave][0][lane] = fx;
-  sf[wave][1][lane] = fy;
-  sf[wave][2][lane] = fz;
   sf[wave][3][lane] = eacc;
-  __syncthreads();
-  // wavefronts 0 to 2 write a component of the MM forces each, 3 adds the energy
-  if (wave > 3) return;
-  double v = 0.0;
 #pragma unroll
-  for (int w = 0; w < kMeWaves; ++w) v += sf[w][wave][lane];
-  if (wave < 3) {
-    if (ok) {
-      double* f = mm_f + 3 * (int64_t)j + wave;
-      *f = accumulate ? v + *f : v;
+  for (int u = 0; u < kMeTiles; ++u) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) sf[wave][k][lane] = f[u][k];
+    __syncthreads();
+    // wavefronts 0 to 2 write a component of the MM forces each, 3 adds the energy
+    if (wave < 3 || (u == 0 && wave == 3)) {
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < kMeWaves; ++w) v += sf[w][wave][lane];
+      if (wave < 3) {
+        if (j0 + 64 * u < n_mm) {
+          double* o = mm_f + 3 * (int64_t)(j0 + 64 * u) + wave;
+          *o = accumulate ? v + *o : v;
+        }
+      } else {
+        v = wsum_d(v);
+        if (lane == 0 && v != 0.0) unsafeAtomicAdd(energy, v);
+      }
     }
-  } else {
-    v = wsum_d(v);
-    if (lane == 0 && v != 0.0) unsafeAtomicAdd(energy, v);
+    if (u + 1 < kMeTiles) __syncthreads();
   }
 }
 
@@ -165,8 +178,8 @@ hipError_t launch_me_pairs(int n_ml, const float* ml_pos, const float* ml_par, i
   }
   if (n_mm == 0) return hipSuccess;
   const float rc2 = cutoff > 0.f ? cutoff * cutoff : INFINITY;
-  hipLaunchKernelGGL(k_me_pairs, dim3((n_mm + 63) / 64), dim3(kMeBlock), 0, st, ml_pos, ml_par,
-                     n_ml, mm_pos, mm_par, n_mm, g, rc2, ke, energy, ml_f, mm_f, accumulate);
+  hipLaunchKernelGGL(k_me_pairs, dim3((n_mm + 64 * kMeTiles - 1) / (64 * kMeTiles)), dim3(kMeBlock), 0, st, ml_pos,
+                     ml_par, n_ml, mm_pos, mm_par, n_mm, g, rc2, ke, energy, ml_f, mm_f, accumulate);
   return hipGetLastError();
 }
 
