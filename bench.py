@@ -55,13 +55,12 @@ WORKLOADS = {
                      "with network-predicted atomic charges (E_i = e_i + q_i phi_i), periodic L=68.3 A"),
 }
 
-# Peaks (MI355X, published): HBM 8 TB/s; dense MFMA FP32 157.3 TFLOP/s, BF16 2.5 PFLOP/s.
+# Peaks (MI355X, published): HBM 8 TB/s; dense MFMA BF16 and FP16 2.5 PFLOP/s.
 # VALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 3.93e13 lane-operations/s (unpacked FP32
 # and FP64 issue at that rate; transcendentals at a quarter of it, counted as 4 operations).
 PEAK_HBM_GBS = 8000.0
-# The FP32 network form runs on FP16 operand pairs, three FP16 products per FP32 one ("split"); with
-# the MM channel it uses the FP32 matrix instructions.
-PEAK_MFMA_TFLOPS = {"fp32": 157.3, "split": 2500.0 / 3, "bf16": 2500.0}
+# The FP32 network form runs on FP16 operand pairs, three FP16 products per FP32 one ("split").
+PEAK_MFMA_TFLOPS = {"split": 2500.0 / 3, "bf16": 2500.0}
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 
 # Algorithmic VALU lane-operations per unit of work (transcendental = 4): the arithmetic the
@@ -125,9 +124,9 @@ def kernel_sources():
     return out
 
 
-def network_form(prec, cfg):
+def network_form(prec):
     """How the network's products run (a key of PEAK_MFMA_TFLOPS)."""
-    return "bf16" if prec == "bf16" else ("fp32" if cfg.get("extra_inputs", 0) else "split")
+    return "bf16" if prec == "bf16" else "split"
 
 
 def stage_kernel(stage, variants, prec, cfg, periodic=True, n=0):
@@ -135,7 +134,7 @@ def stage_kernel(stage, variants, prec, cfg, periodic=True, n=0):
     that runs a stage, given the variants the library reports."""
     widths = list(cfg["widths"])
     k0 = (widths[0] + 31) // 32 * 32
-    op = {"fp32": 0, "bf16": 1, "split": 2}[network_form(prec, cfg)]
+    op = {"bf16": 1, "split": 2}[network_form(prec)]
     v = variants or {}
     if stage == "neighbours":
         return "k_neighbours" if v.get("neighbours", 0) == 0 else "k_neighbours_cell"
@@ -537,7 +536,7 @@ def _roofline(res, cfg, prec, stage, workload, periodic):
     if stage == "network":
         flops = network_flops_per_atom(widths) * n * res.get("n_members", 1)
         ach = flops / t / 1e12
-        peak = PEAK_MFMA_TFLOPS[network_form(prec, cfg)]
+        peak = PEAK_MFMA_TFLOPS[network_form(prec)]
         return {"kernel": kernel, "bound": "mfma", "achieved": ach, "peak": peak,
                 "unit": "TFLOP/s", "frac": ach / peak, "traffic": traffic,
                 "algorithmic_per_launch": flops}

@@ -422,12 +422,12 @@ nnp_status nnp_create(const nnp_config* cfg, uint64_t seed, const float* weights
   }
   std::vector<uint8_t> mat;
   std::vector<float> vec;
-  if (split_form(*m)) weight_bounds(*m);
+  if (prec == NNP_FP32) weight_bounds(*m);
   pack_weights(*m, mat, vec, m->mat_per_species, m->vec_per_species);
   const size_t shifts_at = vec.size();
   vec.insert(vec.end(), p.rad_shift_s, p.rad_shift_s + kRadShifts);
   hipError_t e;
-  if (split_form(*m)) {
+  if (prec == NNP_FP32) {
     float* raw = nullptr;
     e = hipMalloc(&m->d_wmat, (size_t)m->mat_per_species * S * m->n_members * sizeof(float));
     if (e == hipSuccess) e = dalloc(&raw, total);

@@ -35,7 +35,6 @@ constexpr int kBlock = 256;
 constexpr float kLog2e = 1.4426950408889634f;
 
 // How a product is computed.
-//   kOpF32   FP32 operands, 16x16x4 FP32 matrix instructions;
 //   kOpBF16  BF16 operands, 16x16x32;
 //   kOpSplit the FP32 form on the FP16 matrix cores: an operand x is held as
 //     hi = fp16(x s) and lo = fp16((x s - hi) 2^11), s a power of two for the
@@ -53,7 +52,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 //     (14 TB/s; 205 us when every fragment is a cache hit, 161 with variant 2)
 //     and the six dependent products of a tile; the matrix cores are busy for
 //     67 us of it and the VALU for about 100.
-enum Op { kOpF32 = 0, kOpBF16 = 1, kOpSplit = 2 };
+enum Op { kOpBF16 = 1, kOpSplit = 2 };
 constexpr float kSplitUp = 2048.f, kSplitDown = 1.f / 2048.f;
 
 struct SplitFrag {
@@ -105,19 +104,13 @@ __device__ __forceinline__ SplitFrag to_split8(const v4f& a, const v4f& b, float
 // deeper.
 template <int OP, bool WIDE>
 struct PrefetchDepth {
-  static constexpr int value = OP == kOpBF16 ? (WIDE ? 3 : 6) : OP == kOpSplit ? 2 : (WIDE ? 2 : 3);
+  static constexpr int value = OP == kOpBF16 ? (WIDE ? 3 : 6) : 2;
 };
 
-// Operand fragments (FP32: 16 K values per step, four per lane; else 32 and
-// eight) and accumulators of one 16 x 16 tile.
+// Operand fragments (32 K values per step, eight per lane) and accumulators of
+// one 16 x 16 tile.
 template <int OP>
 struct Ops;
-template <>
-struct Ops<kOpF32> {
-  using Frag = v4f;
-  using Acc = v4f;
-  static constexpr int kK = 16;
-};
 template <>
 struct Ops<kOpBF16> {
   using Frag = v8bf;
@@ -134,12 +127,6 @@ struct Ops<kOpSplit> {
 };
 using SplitAcc = Ops<kOpSplit>::Acc;
 
-__device__ __forceinline__ void mma(const v4f& w, const v4f& b, v4f& c) {
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[0], b[0], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[1], b[1], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[2], b[2], c, 0, 0, 0);
-  c = __builtin_amdgcn_mfma_f32_16x16x4f32(w[3], b[3], c, 0, 0, 0);
-}
 __device__ __forceinline__ void mma(const v8bf& w, const v8bf& b, v4f& c) {
   c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, b, c, 0, 0, 0);
 }
@@ -167,9 +154,6 @@ __device__ __forceinline__ v4f acc_value(const SplitAcc& c, const v4f& bias, flo
 // Fragment f of the packed weights, this lane's part (split: all hi parts of
 // the fragment, then all lo parts).  The fragment's address is uniform and
 // the lane's a 32-bit offset, so that no address is computed per lane.
-__device__ __forceinline__ void load_frag(const void* W, int f, int lane, v4f* out) {
-  *out = *reinterpret_cast<const v4f*>(static_cast<const char*>(W) + (size_t)f * 1024 + (uint32_t)lane * 16u);
-}
 __device__ __forceinline__ void load_frag(const void* W, int f, int lane, v8bf* out) {
   *out = *reinterpret_cast<const v8bf*>(static_cast<const char*>(W) + (size_t)f * 1024 + (uint32_t)lane * 16u);
 }
@@ -179,8 +163,19 @@ __device__ __forceinline__ void load_frag(const void* W, int f, int lane, SplitF
   out->lo = *reinterpret_cast<const v8h*>(p + 1024 + (uint32_t)lane * 16u);
 }
 
+// The MM potential is an input without a bound.  The scales hold up to
+// kPhiRef; beyond it, an atom's operands are taken down, and its products up,
+// by the power of two that its potential exceeds kPhiRef by (every bound grows
+// at most in proportion).
+constexpr int kMmInput = 416;   // padded input width of the networks with the MM channel
+__device__ __forceinline__ void phi_scale(float phi, float* down, float* up) {
+  constexpr int ref = __builtin_ctz((unsigned)kPhiRef);
+  const int over = max(0, __builtin_amdgcn_frexp_expf(phi) - ref);
+  *down = ldexpf(1.f, -over);
+  *up = ldexpf(1.f, over);
+}
+
 // B fragment of K block kb from register tiles of 16 features.
-__device__ __forceinline__ void make_frag(const v4f* in, int kb, float, v4f* out) { *out = in[kb]; }
 __device__ __forceinline__ void make_frag(const v4f* in, int kb, float, v8bf* out) {
   *out = to_bf16x8(in[2 * kb], in[2 * kb + 1]);
 }
@@ -279,7 +274,6 @@ __device__ __forceinline__ void load_bias(const float* b, int w, int q, v4f* out
 }
 
 // Layer outputs in LDS, per column tile c and row tile r (16 features):
-//   FP32: one v4f per lane at [(c * tiles + r) * 64 + lane];
 //   BF16: rounded once by the producer, two row tiles form the 16-byte B
 //     fragment of one 32-wide K block, [(c * tiles/2 + r/2) * 64 + lane],
 //     row tile r filling half r % 2 (the K permutation of the packed weights);
@@ -289,20 +283,15 @@ __device__ __forceinline__ void put_tile(v4f* buf, int tiles, int plane, int c, 
                                          float s) {
   if constexpr (OP == kOpBF16) {
     reinterpret_cast<v4bf*>(buf)[((c * (tiles / 2) + (r >> 1)) * 64 + lane) * 2 + (r & 1)] = to_bf16x4(v);
-  } else if constexpr (OP == kOpSplit) {
+  } else {
     v4h hi, lo;
     to_split4(v, s, &hi, &lo);
     v4h* b = reinterpret_cast<v4h*>(buf) + ((c * (tiles / 2) + (r >> 1)) * 64 + lane) * 2 + (r & 1);
     b[0] = hi;
     b[2 * plane] = lo;
-  } else {
-    buf[(c * tiles + r) * 64 + lane] = v;
   }
 }
 
-__device__ __forceinline__ void get_frag(const v4f* buf, int tiles, int, int c, int kb, int lane, v4f* out) {
-  *out = buf[(c * tiles + kb) * 64 + lane];
-}
 __device__ __forceinline__ void get_frag(const v4f* buf, int tiles, int, int c, int kb, int lane, v8bf* out) {
   *out = reinterpret_cast<const v8bf*>(buf)[(c * (tiles / 2) + kb) * 64 + lane];
 }
@@ -317,7 +306,7 @@ __device__ __forceinline__ void get_frag(const v4f* buf, int tiles, int plane, i
 // the LDS tiles `in` (in_tiles row tiles per column tile).
 template <int R, int K, int OP, int C, int NW, int NJ>
 __device__ __forceinline__ void gemm_lds_rows(const void* __restrict__ W, const v4f* in, int in_tiles, int plane,
-                                              const v4f* bias, v4f (*out)[C], int w, int lane, int cw, float s_out) {
+                                              const v4f* bias, v4f (*out)[C], int w, int lane, int cw, float s_out, const float* up) {
   constexpr int KB = K / Ops<OP>::kK;
   constexpr int kPrefetch = PrefetchDepth<OP, (16 * R > 160 || K > 160)>::value;
   using F = typename Ops<OP>::Frag;
@@ -355,20 +344,20 @@ __device__ __forceinline__ void gemm_lds_rows(const void* __restrict__ W, const 
 #pragma unroll
   for (int j = 0; j < NJ; ++j)
 #pragma unroll
-    for (int c = 0; c < C; ++c) out[j][c] = acc_value(acc[j][c], bias[j], s_out);
+    for (int c = 0; c < C; ++c) out[j][c] = acc_value(acc[j][c], bias[j], s_out * up[c]);
 }
 
 // One wavefront-uniform branch on the number of row tiles the wavefront owns:
 // a test per tile inside the loop would cut it into short blocks.
 template <int R, int K, int OP, int C, int NW>
 __device__ __forceinline__ void gemm_lds(const void* __restrict__ W, const v4f* in, int in_tiles, int plane,
-                                         const v4f* bias, v4f (*out)[C], int w, int lane, int cw, float s_out) {
+                                         const v4f* bias, v4f (*out)[C], int w, int lane, int cw, float s_out, const float* up) {
   constexpr int most = Own<R, NW>::n, rest = R % NW;
   if (rest == 0 || w < rest) {
-    gemm_lds_rows<R, K, OP, C, NW, most>(W, in, in_tiles, plane, bias, out, w, lane, cw, s_out);
+    gemm_lds_rows<R, K, OP, C, NW, most>(W, in, in_tiles, plane, bias, out, w, lane, cw, s_out, up);
   } else {
     if constexpr (most > 1)
-      gemm_lds_rows<R, K, OP, C, NW, most - 1>(W, in, in_tiles, plane, bias, out, w, lane, cw, s_out);
+      gemm_lds_rows<R, K, OP, C, NW, most - 1>(W, in, in_tiles, plane, bias, out, w, lane, cw, s_out, up);
 #pragma unroll
     for (int c = 0; c < C; ++c) out[most - 1][c] = v4f{0.f, 0.f, 0.f, 0.f};
   }
@@ -427,13 +416,22 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
   float e_acc[C], q_acc[C];
 #pragma unroll
   for (int c = 0; c < C; ++c) e_acc[c] = q_acc[c] = 0.f;
-  float phi[C];   // MM potential of each column's atom (CHG)
+  constexpr bool kPhi = OP == kOpSplit && K0 == kMmInput;
+  float phi[C];            // MM potential of each column's atom
+  float dn[C], up[C];      // its factors on the operands' and products' scales,
+  float bdn[C], bup[C];    // and those of the backward products (seeded with phi under CHG)
 #pragma unroll
   for (int c = 0; c < C; ++c) {
     phi[c] = 0.f;
-    if constexpr (CHG) {
+    if constexpr (CHG || kPhi) {
       const int row = row0 + c * 16 + col;
       if (row < row_end) phi[c] = a.x[(int64_t)row * a.stride + a.phi_col];
+    }
+    dn[c] = up[c] = bdn[c] = bup[c] = 1.f;
+    if constexpr (kPhi) phi_scale(phi[c], &dn[c], &up[c]);
+    if constexpr (kPhi && CHG) {
+      bdn[c] = dn[c];
+      bup[c] = up[c];
     }
   }
 
@@ -443,32 +441,25 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
 
     // stage x in fragment layout (again for every member: the buffer is reused
     // by later products): tile (c, kb), lane l holds x[row c*16 + l%16][16 kb + 4 (l/16) .. +3]
-    if constexpr (OP != kOpF32) {   // K block kb of 32 features: tiles 2 kb and 2 kb + 1
-      for (int t = threadIdx.x; t < C * (K0 / 32) * 64; t += 64 * NW) {
-        const int l = t & 63, kb = (t >> 6) % (K0 / 32), c = (t >> 6) / (K0 / 32);
-        const int row = row0 + c * 16 + (l & 15);
-        v4f lo = v4f{0.f, 0.f, 0.f, 0.f}, hi = lo;
-        if (row < row_end) {
-          const float* src = a.x + (int64_t)row * a.stride + 32 * kb + 4 * (l >> 4);
-          lo = *reinterpret_cast<const v4f*>(src);
-          hi = *reinterpret_cast<const v4f*>(src + 16);
-        }
-        const int at = (c * (TX / 2) + kb) * 64 + l;
-        if constexpr (OP == kOpBF16) {
-          reinterpret_cast<v8bf*>(bufX)[at] = to_bf16x8(lo, hi);
-        } else {
-          const SplitFrag f = to_split8(lo, hi, a.split.x);
-          reinterpret_cast<v8h*>(bufX)[at] = f.hi;
-          reinterpret_cast<v8h*>(bufX)[PX + at] = f.lo;
-        }
+    for (int t = threadIdx.x; t < C * (K0 / 32) * 64; t += 64 * NW) {   // K block kb: feature tiles 2 kb and 2 kb + 1
+      const int l = t & 63, kb = (t >> 6) % (K0 / 32), c = (t >> 6) / (K0 / 32);
+      const int row = row0 + c * 16 + (l & 15);
+      v4f lo = v4f{0.f, 0.f, 0.f, 0.f}, hi = lo;
+      if (row < row_end) {
+        const float* src = a.x + (int64_t)row * a.stride + 32 * kb + 4 * (l >> 4);
+        lo = *reinterpret_cast<const v4f*>(src);
+        hi = *reinterpret_cast<const v4f*>(src + 16);
       }
-    } else {
-      for (int t = threadIdx.x; t < C * (K0 / 16) * 64; t += 64 * NW) {
-        const int l = t & 63, kb = (t >> 6) % (K0 / 16), c = (t >> 6) / (K0 / 16);
-        const int row = row0 + c * 16 + (l & 15);
-        v4f v = v4f{0.f, 0.f, 0.f, 0.f};
-        if (row < row_end) v = *reinterpret_cast<const v4f*>(a.x + (int64_t)row * a.stride + 16 * kb + 4 * (l >> 4));
-        bufX[(c * TX + kb) * 64 + l] = v;
+      const int at = (c * (TX / 2) + kb) * 64 + l;
+      if constexpr (OP == kOpBF16) {
+        reinterpret_cast<v8bf*>(bufX)[at] = to_bf16x8(lo, hi);
+      } else {
+        float down = 1.f;   // of column c (l is this lane)
+#pragma unroll
+        for (int k = 0; k < C; ++k) down = k == c ? dn[k] : down;
+        const SplitFrag f = to_split8(lo, hi, a.split.x * down);
+        reinterpret_cast<v8h*>(bufX)[at] = f.hi;
+        reinterpret_cast<v8h*>(bufX)[PX + at] = f.lo;
       }
     }
     __syncthreads();
@@ -478,7 +469,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
     {
       v4f bias[Own<N1 / 16, NW>::n];
       load_bias<N1, NW>(V + ob1, w, q, bias);
-      gemm_lds<N1 / 16, K0, OP, C, NW>(Wm + oF1, bufX, TX, PX, bias, h1, w, lane, cw, a.split.f1);
+      gemm_lds<N1 / 16, K0, OP, C, NW>(Wm + oF1, bufX, TX, PX, bias, h1, w, lane, cw, a.split.f1, up);
     }
 #pragma unroll
     for (int j = 0; j < Own<N1 / 16, NW>::n; ++j) {
@@ -488,7 +479,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
         for (int c = 0; c < C; ++c) {
 #pragma unroll
           for (int t = 0; t < 4; ++t) h1[j][c][t] = celu_of<OP>(h1[j][c][t], alpha, inv_alpha_l2);
-          put_tile<OP>(bufA, TA, PA, c, r, lane, h1[j][c], a.split.h1);
+          put_tile<OP>(bufA, TA, PA, c, r, lane, h1[j][c], a.split.h1 * dn[c]);
         }
       }
     }
@@ -499,7 +490,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
     {
       v4f bias[Own<N2 / 16, NW>::n];
       load_bias<N2, NW>(V + ob2, w, q, bias);
-      gemm_lds<N2 / 16, N1, OP, C, NW>(Wm + oF2, bufA, TA, PA, bias, h2, w, lane, cw, a.split.f2);
+      gemm_lds<N2 / 16, N1, OP, C, NW>(Wm + oF2, bufA, TA, PA, bias, h2, w, lane, cw, a.split.f2, up);
     }
     __syncthreads();   // everyone has read A (h1) and X (x) before X is overwritten
 #pragma unroll
@@ -510,7 +501,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
         for (int c = 0; c < C; ++c) {
 #pragma unroll
           for (int t = 0; t < 4; ++t) h2[j][c][t] = celu_of<OP>(h2[j][c][t], alpha, inv_alpha_l2);
-          put_tile<OP>(bufX, TX, PX, c, r, lane, h2[j][c], a.split.h2);
+          put_tile<OP>(bufX, TX, PX, c, r, lane, h2[j][c], a.split.h2 * dn[c]);
         }
       }
     }
@@ -521,7 +512,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
     {
       v4f bias[Own<N3 / 16, NW>::n];
       load_bias<N3, NW>(V + ob3, w, q, bias);
-      gemm_lds<N3 / 16, N2, OP, C, NW>(Wm + oF3, bufX, TX, PX, bias, h3, w, lane, cw, a.split.f3);
+      gemm_lds<N3 / 16, N2, OP, C, NW>(Wm + oF3, bufX, TX, PX, bias, h3, w, lane, cw, a.split.f3, up);
     }
     float ep[C];
     float eq[C];
@@ -548,7 +539,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
               d[t] = w4[t] * celu_grad_of<OP>(h, inv_alpha);
             }
           }
-          put_tile<OP>(bufA, TA, PA, c, r, lane, d, a.split.d3);
+          put_tile<OP>(bufA, TA, PA, c, r, lane, d, a.split.d3 * bdn[c]);
         }
       }
     }
@@ -588,7 +579,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
 
     // ---- delta2 = (W3^T delta3) o celu'(h2)    A -> X
     v4f d2[Own<N2 / 16, NW>::n][C];
-    gemm_lds<N2 / 16, N3, OP, C, NW>(Wm + oB3, bufA, TA, PA, zeros, d2, w, lane, cw, a.split.b3);
+    gemm_lds<N2 / 16, N3, OP, C, NW>(Wm + oB3, bufA, TA, PA, zeros, d2, w, lane, cw, a.split.b3, bup);
 #pragma unroll
     for (int j = 0; j < Own<N2 / 16, NW>::n; ++j) {
       const int r = w + NW * j;
@@ -597,7 +588,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
         for (int c = 0; c < C; ++c) {
 #pragma unroll
           for (int t = 0; t < 4; ++t) d2[j][c][t] *= celu_grad_of<OP>(h2[j][c][t], inv_alpha);
-          put_tile<OP>(bufX, TX, PX, c, r, lane, d2[j][c], a.split.d2);
+          put_tile<OP>(bufX, TX, PX, c, r, lane, d2[j][c], a.split.d2 * bdn[c]);
         }
       }
     }
@@ -605,7 +596,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
 
     // ---- delta1 = (W2^T delta2) o celu'(h1)    X -> A
     v4f d1[Own<N1 / 16, NW>::n][C];
-    gemm_lds<N1 / 16, N2, OP, C, NW>(Wm + oB2, bufX, TX, PX, zeros, d1, w, lane, cw, a.split.b2);
+    gemm_lds<N1 / 16, N2, OP, C, NW>(Wm + oB2, bufX, TX, PX, zeros, d1, w, lane, cw, a.split.b2, bup);
 #pragma unroll
     for (int j = 0; j < Own<N1 / 16, NW>::n; ++j) {
       const int r = w + NW * j;
@@ -614,7 +605,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
         for (int c = 0; c < C; ++c) {
 #pragma unroll
           for (int t = 0; t < 4; ++t) d1[j][c][t] *= celu_grad_of<OP>(h1[j][c][t], inv_alpha);
-          put_tile<OP>(bufA, TA, PA, c, r, lane, d1[j][c], a.split.d1);
+          put_tile<OP>(bufA, TA, PA, c, r, lane, d1[j][c], a.split.d1 * bdn[c]);
         }
       }
     }
@@ -623,7 +614,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
     // ---- dE/dx = W1^T delta1 (row tiles over the input features), to memory
     {
       v4f gx[Own<K0 / 16, NW>::n][C];
-      gemm_lds<K0 / 16, N1, OP, C, NW>(Wm + oB1, bufA, TA, PA, zeros, gx, w, lane, cw, a.split.b1);
+      gemm_lds<K0 / 16, N1, OP, C, NW>(Wm + oB1, bufA, TA, PA, zeros, gx, w, lane, cw, a.split.b1, bup);
 #pragma unroll
       for (int j = 0; j < Own<K0 / 16, NW>::n; ++j) {
         const int r = w + NW * j;
@@ -732,6 +723,8 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
   const float* xrow = a.x + (int64_t)row * a.stride;
   float* grow = a.g + (int64_t)row * a.stride;
   float e_sum = 0.f;
+  float dn = 1.f, up = 1.f;   // (phi_scale)
+  if constexpr (OP == kOpSplit && K0 == kMmInput) phi_scale(valid ? xrow[a.phi_col] : 0.f, &dn, &up);
 
   for (int mem = 0; mem < a.n_members; ++mem) {
     const Elem* Wm = reinterpret_cast<const Elem*>(a.wmat) + (int64_t)(mem * a.S + s) * a.mat_per_species;
@@ -751,10 +744,10 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
         v4f xt[2] = {v4f{0.f, 0.f, 0.f, 0.f}, v4f{0.f, 0.f, 0.f, 0.f}};
         if (valid) {
           xt[0] = *reinterpret_cast<const v4f*>(xrow + kK * kb + 4 * q);
-          if constexpr (kK == 32) xt[1] = *reinterpret_cast<const v4f*>(xrow + kK * kb + 16 + 4 * q);
+          xt[1] = *reinterpret_cast<const v4f*>(xrow + kK * kb + 16 + 4 * q);
         }
         typename Ops<OP>::Frag xb;
-        make_frag(xt, 0, a.split.x, &xb);
+        make_frag(xt, 0, a.split.x * dn, &xb);
 #pragma unroll
         for (int r = 0; r < N1 / 16; ++r) {
           typename Ops<OP>::Frag wf;
@@ -763,7 +756,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
         }
       }
 #pragma unroll
-      for (int r = 0; r < N1 / 16; ++r) h1[r] = acc_value(acc[r], h1[r], a.split.f1);
+      for (int r = 0; r < N1 / 16; ++r) h1[r] = acc_value(acc[r], h1[r], a.split.f1 * up);
     }
 #pragma unroll
     for (int r = 0; r < N1 / 16; ++r)
@@ -774,7 +767,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
     v4f h2[N2 / 16];
 #pragma unroll
     for (int r = 0; r < N2 / 16; ++r) h2[r] = *reinterpret_cast<const v4f*>(V + ob2 + 16 * r + 4 * q);
-    gemm_regs<N2, N1, OP, 4>(Wm + oF2, h1, h2, lane, a.split.h1, a.split.f2);
+    gemm_regs<N2, N1, OP, 4>(Wm + oF2, h1, h2, lane, a.split.h1 * dn, a.split.f2 * up);
 #pragma unroll
     for (int r = 0; r < N2 / 16; ++r)
 #pragma unroll
@@ -784,7 +777,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
     v4f h3[N3 / 16];
 #pragma unroll
     for (int r = 0; r < N3 / 16; ++r) h3[r] = *reinterpret_cast<const v4f*>(V + ob3 + 16 * r + 4 * q);
-    gemm_regs<N3, N2, OP, 4>(Wm + oF3, h2, h3, lane, a.split.h2, a.split.f3);
+    gemm_regs<N3, N2, OP, 4>(Wm + oF3, h2, h3, lane, a.split.h2 * dn, a.split.f3 * up);
 #pragma unroll
     for (int r = 0; r < N3 / 16; ++r)
 #pragma unroll
@@ -1418,7 +1411,8 @@ struct PackArgs {
   int64_t w_per_species; // floats per (member, species)
   _Float16* out;
   int64_t out_per_species;   // FP16 values per (member, species)
-  int widths[4];         // K0, N1, N2, N3
+  int widths[4];         // K0 (padded with zero columns), N1, N2, N3
+  int inputs;            // real input width
   float scale[3];
 };
 
@@ -1434,13 +1428,14 @@ __global__ __launch_bounds__(kBlock) void k_pack_split(PackArgs a) {
   int l = 0;
   for (; t >= a.widths[l] * a.widths[l + 1]; ++l) {
     t -= a.widths[l] * a.widths[l + 1];
-    src += (int64_t)a.widths[l] * a.widths[l + 1] + a.widths[l + 1];
+    src += (int64_t)(l == 0 ? a.inputs : a.widths[l]) * a.widths[l + 1] + a.widths[l + 1];
   }
-  const int in = a.widths[l], cols = trans ? a.widths[l + 1] : in;
+  const int in = l == 0 ? a.inputs : a.widths[l], cols = trans ? a.widths[l + 1] : a.widths[l];
   const int f = t >> 9, lane = (t >> 3) & 63, j = t & 7, q = lane >> 4;
   const int row = 16 * (f / (cols / 32)) + (lane & 15);
   const int k = 32 * (f % (cols / 32)) + (j < 4 ? 4 * q + j : 16 + 4 * q + (j - 4));
-  const float x = W[src + (trans ? (int64_t)k * in + row : (int64_t)row * in + k)] * a.scale[l];
+  const bool real = (trans ? row : k) < in;
+  const float x = real ? W[src + (trans ? (int64_t)k * in + row : (int64_t)row * in + k)] * a.scale[l] : 0.f;
   const _Float16 hi = (_Float16)x;
   _Float16* o = out + 2 * (int64_t)(e - t) + (2 * f * 64 + lane) * 8 + j;
   o[0] = hi;
@@ -1457,7 +1452,7 @@ __global__ __launch_bounds__(kBlock) void k_pack_split(PackArgs a) {
 //   while every 16-atom tile has a compute unit of its own, 16-atom tiles over
 //   8 wavefronts (the shortest chain per tile): 192 atoms FP32 11 us against
 //   15 for variant 2, 3,000 atoms 11.5 against 16, 60 H/C/N/O atoms with the
-//   MM channel 36 against 66, 8 networks and 3,900 atoms 69 against 111;
+//   MM channel 19 against 27, 8 networks and 3,900 atoms 69 against 111;
 //   beyond that 32-atom tiles over 8 wavefronts: FP32 6,600 atoms 14.4 against
 //   17.6, 48,000 atoms 48 against 51, 261,000 atoms 239 against 249, H/C/N/O
 //   batch of 29,000 atoms 105 against 116;
@@ -1481,10 +1476,11 @@ hipError_t pack_split(const nnp_model& m, const float* weights, void* out) {
   a.out = static_cast<_Float16*>(out);
   a.out_per_species = 2 * m.mat_per_species;
   int total = 0;
-  for (int l = 0; l < 4; ++l) a.widths[l] = m.widths[l];
+  for (int l = 0; l < 4; ++l) a.widths[l] = l == 0 ? m.stride : m.widths[l];
+  a.inputs = m.widths[0];
   for (int l = 0; l < 3; ++l) {
     a.scale[l] = m.w_scale[l];
-    total += m.widths[l] * m.widths[l + 1];
+    total += a.widths[l] * a.widths[l + 1];
   }
   hipLaunchKernelGGL(k_pack_split, dim3((unsigned)((2 * total + kBlock - 1) / kBlock), (unsigned)(m.S * m.n_members)),
                      dim3(kBlock), 0, nullptr, a);
@@ -1526,9 +1522,9 @@ hipError_t launch_mlp(nnp_model& m, int n, hipStream_t st) {
     case 2:
       if (m.charges)
         return bf ? run_mlp_q<416, 256, 192, 160, kOpBF16>(m, a, n, v, st)
-                  : run_mlp_q<416, 256, 192, 160, kOpF32>(m, a, n, v, st);
+                  : run_mlp_q<416, 256, 192, 160, kOpSplit>(m, a, n, v, st);
       return bf ? run_mlp<416, 256, 192, 160, kOpBF16>(m, a, n, v, st)
-                : run_mlp<416, 256, 192, 160, kOpF32>(m, a, n, v, st);
+                : run_mlp<416, 256, 192, 160, kOpSplit>(m, a, n, v, st);
     default:
       return hipErrorInvalidValue;
   }

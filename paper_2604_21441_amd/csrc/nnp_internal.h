@@ -211,10 +211,12 @@ struct SplitScales {
   float f1 = 1.f, f2 = 1.f, f3 = 1.f, b3 = 1.f, b2 = 1.f, b1 = 1.f;  // products
 };
 
+constexpr double kPhiRef = 64;   // MM potential that the scales provide for
+
 // Bounds of a model's matrices, largest over members and species: weights,
 // absolute row sums of the inputs of each kind, absolute column sums, biases.
 struct WeightBounds {
-  double w[3] = {0, 0, 0}, rad = 0, ang = 0, row[3] = {0, 0, 0}, col[3] = {0, 0, 0}, b[3] = {0, 0, 0}, w4 = 0;
+  double w[3] = {0, 0, 0}, rad = 0, ang = 0, phi = 0, row[3] = {0, 0, 0}, col[3] = {0, 0, 0}, b[3] = {0, 0, 0}, w4 = 0, wq = 0;
 };
 
 // Network tile schedule: species buckets are bins [s*n_bins, (s+1)*n_bins).
@@ -222,7 +224,7 @@ struct MlpArgs {
   const float* x;          // [n][stride]
   float* g;                // [n][stride]  dE/dx (output)
   float* e;                // [n] atomic energies (output)
-  const void* wmat;        // fragment-packed matrices (FP32 or BF16)
+  const void* wmat;        // fragment-packed matrices (FP16 pairs or BF16)
   const float* wvec;       // biases and output weights (FP32)
   const int* bin_start;    // species bucket boundaries
   int n_bins, S, n_members, stride;
@@ -231,7 +233,7 @@ struct MlpArgs {
   double* part;            // per-wavefront FP64 energy partials, or null
   int* status;
   float* q;                // predicted atomic charges (output), or null: no charge head
-  int phi_col;             // column of x holding the MM potential (models with charges)
+  int phi_col;             // column of x holding the MM potential (models with the MM channel)
   const void* wrow;        // BF16 models: W1, W2, W3 row-major per (member, species), or null
   int64_t wrow_per_species;
   SplitScales split;       // split FP32 form
@@ -395,7 +397,6 @@ void draw_weights(uint64_t seed, const std::vector<int>& widths, int n_species, 
                   std::vector<float>& out);
 // Bounds of the weights, the scales of the packed matrices, and the scales of
 // the operands for lists of up to max_rad radial and max_ang angular neighbours.
-bool split_form(const nnp_model& m);   // the model's products run in the split FP32 form
 void weight_bounds(nnp_model& m);
 SplitScales split_scales(const nnp_model& m, int max_rad, int max_ang);
 void pack_weights(const nnp_model& m, std::vector<uint8_t>& mat, std::vector<float>& vec,

@@ -36,37 +36,24 @@ inline uint16_t bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// Pack M [R x C] (zero outside rows x cols) as A-operand fragments.  FP32
-// (16x16x4): element (rt, kb, lane, s) = M[16 rt + lane%16][16 kb + 4 (lane/16) + s].
-// BF16 (16x16x32): element (rt, kb, lane, j) = M[16 rt + lane%16][32 kb + k(j)],
+// Pack M [R x C] (zero outside rows x cols) as the BF16 form's A-operand
+// fragments (16x16x32): element (rt, kb, lane, j) = M[16 rt + lane%16][32 kb + k(j)],
 // k(j) = 4 (lane/16) + j for j < 4 and 16 + 4 (lane/16) + (j - 4) otherwise --
 // the same K permutation the kernel applies to the activations.  (The split
 // FP32 form is packed on the device, mlp.hip.)
 template <typename Get>
-void pack_matrix(Get get, int R, int C, bool bf16, std::vector<uint8_t>& out) {
-  if (!bf16) {
-    size_t base = out.size();
-    out.resize(base + (size_t)R * C * 4);
-    float* d = reinterpret_cast<float*>(out.data() + base);
-    for (int rt = 0; rt < R / 16; ++rt)
-      for (int kb = 0; kb < C / 16; ++kb)
-        for (int lane = 0; lane < 64; ++lane)
-          for (int s = 0; s < 4; ++s)
-            d[(((size_t)rt * (C / 16) + kb) * 64 + lane) * 4 + s] =
-                get(16 * rt + (lane & 15), 16 * kb + 4 * (lane >> 4) + s);
-  } else {
-    size_t base = out.size();
-    out.resize(base + (size_t)R * C * 2);
-    uint16_t* d = reinterpret_cast<uint16_t*>(out.data() + base);
-    for (int rt = 0; rt < R / 16; ++rt)
-      for (int kb = 0; kb < C / 32; ++kb)
-        for (int lane = 0; lane < 64; ++lane)
-          for (int j = 0; j < 8; ++j) {
-            int q = lane >> 4;
-            int k = 32 * kb + (j < 4 ? 4 * q + j : 16 + 4 * q + (j - 4));
-            d[(((size_t)rt * (C / 32) + kb) * 64 + lane) * 8 + j] = bf16_rne(get(16 * rt + (lane & 15), k));
-          }
-  }
+void pack_matrix(Get get, int R, int C, std::vector<uint8_t>& out) {
+  size_t base = out.size();
+  out.resize(base + (size_t)R * C * 2);
+  uint16_t* d = reinterpret_cast<uint16_t*>(out.data() + base);
+  for (int rt = 0; rt < R / 16; ++rt)
+    for (int kb = 0; kb < C / 32; ++kb)
+      for (int lane = 0; lane < 64; ++lane)
+        for (int j = 0; j < 8; ++j) {
+          int q = lane >> 4;
+          int k = 32 * kb + (j < 4 ? 4 * q + j : 16 + 4 * q + (j - 4));
+          d[(((size_t)rt * (C / 32) + kb) * 64 + lane) * 8 + j] = bf16_rne(get(16 * rt + (lane & 15), k));
+        }
 }
 
 // 2^(to - ceil(log2 bound)), within FP32's normal range; 1 for a bound of zero
@@ -97,8 +84,6 @@ void draw_weights(uint64_t seed, const std::vector<int>& widths, int n_species, 
       }
 }
 
-bool split_form(const nnp_model& m) { return m.prec == NNP_FP32 && m.extra == 0; }
-
 void weight_bounds(nnp_model& m) {
   const int* n = m.widths.data();
   WeightBounds& q = m.bounds;
@@ -109,6 +94,7 @@ void weight_bounds(nnp_model& m) {
   for (int t = 0; t < m.n_members * m.S; ++t)
     for (int l = 0; l < 4; ++l) {
       const int in = n[l], out = n[l + 1], cut = l == 0 ? kRadShifts * m.S : 0;
+      const int end = l == 0 ? in - m.extra : in;   // the MM potential, where there is one, is the last input
       const float* W = p;
       const float* b = p + (size_t)in * out;
       p = b + out;
@@ -116,15 +102,16 @@ void weight_bounds(nnp_model& m) {
       for (int r = 0; r < out; ++r, W += in) {
         float head = 0.f, tail = 0.f, top = 0.f;   // FP32 sums: a bound may be a little off, the scales have room
         for (int c = 0; c < cut; ++c) head += std::fabs(W[c]);
-        for (int c = cut; c < in; ++c) tail += std::fabs(W[c]);
+        for (int c = cut; c < end; ++c) tail += std::fabs(W[c]);
         for (int c = 0; c < in; ++c) {
           const float v = std::fabs(W[c]);
           top = v > top ? v : top;
           col[c] += v;
         }
         if (l == 0) { upto(q.rad, head); upto(q.ang, tail); }
+        if (l == 0 && m.extra) upto(q.phi, std::fabs(W[in - 1]));
         if (l < 3) { upto(q.w[l], top); upto(q.row[l], (double)head + tail); upto(q.b[l], std::fabs(b[r])); }
-        else upto(q.w4, top);
+        else upto(r == 0 ? q.w4 : q.wq, top);
       }
       if (l < 3)
         for (float v : col) upto(q.col[l], v);
@@ -133,16 +120,19 @@ void weight_bounds(nnp_model& m) {
 }
 
 // Each radial entry sums at most max_rad terms of at most 1, each angular one
-// at most max_ang (max_ang - 1) / 2 terms of at most 2; |celu(u)| <= |u| + alpha
-// and 0 <= celu' <= 1 carry the bounds through the layers.
+// at most max_ang (max_ang - 1) / 2 terms of at most 2, the MM potential counts
+// with kPhiRef (an atom beyond it has its scales changed in the kernel);
+// |celu(u)| <= |u| + alpha and 0 <= celu' <= 1 carry the bounds through the
+// layers.
 SplitScales split_scales(const nnp_model& m, int max_rad, int max_ang) {
   const WeightBounds& q = m.bounds;
   const double rad = max_rad, ang = (double)max_ang * (max_ang - 1);
-  const double h1 = q.rad * rad + q.ang * ang + q.b[0] + m.celu_alpha;
+  const double phi = m.extra ? kPhiRef : 0.0;
+  const double h1 = q.rad * rad + q.ang * ang + q.phi * phi + q.b[0] + m.celu_alpha;
   const double h2 = q.row[1] * h1 + q.b[1] + m.celu_alpha;
-  const double d3 = q.w4, d2 = q.col[2] * d3, d1 = q.col[1] * d2;
+  const double d3 = q.w4 + q.wq * phi, d2 = q.col[2] * d3, d1 = q.col[1] * d2;
   SplitScales s;
-  s.x = scale_to(std::max(rad, ang), 15);
+  s.x = scale_to(std::max({rad, ang, phi}), 15);
   s.h1 = scale_to(h1, 15);
   s.h2 = scale_to(h2, 15);
   s.d3 = scale_to(d3, 15);
@@ -159,7 +149,7 @@ SplitScales split_scales(const nnp_model& m, int max_rad, int max_ang) {
 
 void pack_weights(const nnp_model& m, std::vector<uint8_t>& mat, std::vector<float>& vec,
                   int64_t& mat_per_species, int64_t& vec_per_species) {
-  const bool bf = m.prec == NNP_BF16, matrices = !split_form(m);
+  const bool matrices = m.prec == NNP_BF16;
   const int K0 = m.widths[0];          // real input width
   const int K0p = m.stride;            // padded
   const int N1 = m.widths[1], N2 = m.widths[2], N3 = m.widths[3];
@@ -189,12 +179,12 @@ void pack_weights(const nnp_model& m, std::vector<uint8_t>& mat, std::vector<flo
       auto t2 = [&](int r, int c) { return W2[(size_t)c * N1 + r]; };
       auto t3 = [&](int r, int c) { return W3[(size_t)c * N2 + r]; };
       if (matrices) {
-        pack_matrix(g1, N1, K0p, bf, mat);
-        pack_matrix(g2, N2, N1, bf, mat);
-        pack_matrix(g3, N3, N2, bf, mat);
-        pack_matrix(t1, K0p, N1, bf, mat);
-        pack_matrix(t2, N1, N2, bf, mat);
-        pack_matrix(t3, N2, N3, bf, mat);
+        pack_matrix(g1, N1, K0p, mat);
+        pack_matrix(g2, N2, N1, mat);
+        pack_matrix(g3, N3, N2, mat);
+        pack_matrix(t1, K0p, N1, mat);
+        pack_matrix(t2, N1, N2, mat);
+        pack_matrix(t3, N2, N3, mat);
       }
       vec.insert(vec.end(), b1, b1 + N1);
       vec.insert(vec.end(), b2, b2 + N2);
