@@ -579,10 +579,10 @@ nnp_status run_path(nnp_model* m, int n, const float* pos, int n_mm, const float
   if (m->extra) STAGE(NNP_STAGE_MM, launch_mm_fwd(*m, n, n_mm, mm_pos, mm_q, st), "mm channel");
   STAGE(NNP_STAGE_NETWORK, launch_mlp(*m, n, st), "network");
   STAGE(NNP_STAGE_ADJOINT, launch_descriptor_bwd(*m, n, st), "descriptor adjoint");
-  STAGE(NNP_STAGE_GATHER, launch_force_gather(*m, n, forces, assign_forces, energies, n_sys, accumulate, st),
-        "force gather and energy");
   if (m->extra)
-    STAGE(NNP_STAGE_MM_ADJOINT, launch_mm_bwd(*m, n, n_mm, mm_pos, mm_q, forces, mm_forces, st), "mm adjoint");
+    STAGE(NNP_STAGE_MM_ADJOINT, launch_mm_bwd(*m, n, n_mm, mm_pos, mm_q, mm_forces, accumulate, st), "mm adjoint");
+  STAGE(NNP_STAGE_GATHER, launch_force_gather(*m, n, n_mm, forces, assign_forces, energies, n_sys, accumulate, st),
+        "force gather and energy");
   tm.done();
   return NNP_OK;
 }
@@ -699,7 +699,8 @@ nnp_status compute_single(nnp_model* m, int32_t n_atoms, const float* pos, const
     if (!accumulate) {
       if (!assign && (e = launch_fill_f64(forces, 3 * (int64_t)n_atoms, s)) != hipSuccess)
         return hip_error(e, "fill");
-      if (mm_forces && (e = launch_fill_f64(mm_forces, 3 * (int64_t)n_mm, s)) != hipSuccess)
+      // (the MM channel's adjoint writes the MM forces itself)
+      if (mm_forces && !m->extra && (e = launch_fill_f64(mm_forces, 3 * (int64_t)n_mm, s)) != hipSuccess)
         return hip_error(e, "fill");
     }
     if (n_links > 0 && (e = launch_fill_f64(m->d_link_F, 3 * (int64_t)n_links, s)) != hipSuccess)

@@ -1212,8 +1212,9 @@ __device__ __forceinline__ void energy_block(const EnergyArgs& ea, int sys) {
 }
 
 // F_atom += self + sum over the atom's angular list entries (its radial ones
-// after a list overflow, see k_desc_adj; FP64): 16 lanes
-// per atom, each summing a strided part of the row, then a shuffle tree.
+// after a list overflow, see k_desc_adj), and with the MM channel its partials
+// of k_mm_bwd (FP64): 16 lanes per atom, each summing a strided part of the
+// row, then a shuffle tree.
 // With `assign` the sum overwrites F_atom (every row of the output is an NNP
 // atom and the call does not accumulate), which saves clearing it first.
 // Blocks from gather_blocks on reduce the energies instead.
@@ -1224,7 +1225,8 @@ __global__ __launch_bounds__(kBlock) void k_force_gather(const float3* __restric
                                                          const int* __restrict__ slot_atom, int n, int S,
                                                          int max_rad, int max_ang, double* __restrict__ forces,
                                                          double* __restrict__ link_forces, int assign,
-                                                         int gather_blocks, EnergyArgs ea) {
+                                                         int gather_blocks, EnergyArgs ea,
+                                                         const float* __restrict__ mm_part, int mm_blocks) {
   // the energy blocks come first, so that their serial reduction runs beside
   // the gather instead of after it
   const int energy_blocks = (int)gridDim.x - gather_blocks;
@@ -1243,6 +1245,13 @@ __global__ __launch_bounds__(kBlock) void k_force_gather(const float3* __restric
     for (int t = sub; t < cnt; t += 16) {
       const float3 v = row[t];
       fx += v.x; fy += v.y; fz += v.z;
+    }
+    const float* mp = mm_part + (int64_t)i * 3 * mm_blocks;   // MM channel: partials of the three components
+#pragma unroll 4
+    for (int b = sub; b < mm_blocks; b += 16) {
+      fx += (double)mp[b];
+      fy += (double)mp[b + mm_blocks];
+      fz += (double)mp[b + 2 * mm_blocks];
     }
   }
 #pragma unroll
@@ -1412,8 +1421,8 @@ hipError_t launch_descriptor_bwd(nnp_model& m, int n, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_force_gather(nnp_model& m, int n, double* forces, int assign, double* energies, int n_sys,
-                               int accumulate, hipStream_t st) {
+hipError_t launch_force_gather(nnp_model& m, int n, int n_mm, double* forces, int assign, double* energies,
+                               int n_sys, int accumulate, hipStream_t st) {
   EnergyArgs ea;
   const bool single = m.geo.periodic || m.geo.n_bins == 1;
   ea.part = single ? m.d_part : nullptr;
@@ -1431,8 +1440,8 @@ hipError_t launch_force_gather(nnp_model& m, int n, double* forces, int assign, 
   const int energy_blocks = single ? 1 : n_sys;
   hipLaunchKernelGGL(k_force_gather, dim3((unsigned)(gather_blocks + energy_blocks)), dim3(kBlock), 0, st,
                      m.d_contrib, m.d_self, m.d_rad_off, m.d_ang_off, m.d_slot_atom, n, m.S, m.max_rad, m.max_ang, forces,
-                     m.d_link_F,
-                     assign, gather_blocks, ea);
+                     m.d_link_F, assign, gather_blocks, ea, m.d_mm_part,
+                     m.extra && n_mm > 0 ? mm_partial_blocks(n_mm) : 0);
   return hipGetLastError();
 }
 

@@ -3,19 +3,20 @@
 // interface passes MM positions and charges, and the model may put forces on
 // MM atoms):
 //   phi_i = ke * sum_j q_j fc(r_ij; Rm) / r_ij     over MM atoms j, r_ij < Rm
-// The pass is all-pairs over (NNP atom, MM atom).  A workgroup takes a row of
-// kNnpChunk NNP atoms (grid y) and a range of MM atoms, one per lane (grid x,
-// at most kMaxMmBlocks workgroups; more MM atoms loop); each lane keeps one
-// running sum per NNP atom of the row, and after its MM atoms the sums are
-// reduced across lanes (a DPP transposing butterfly within each 16-lane row:
-// 15 exchanges for all 16 sums, where a shuffle tree per sum took 96 LDS
-// round trips) and wavefronts, and stored as the workgroup's partial.
-// A second launch adds the partials of every NNP atom in a fixed order (FP64).
+// The passes are all-pairs over (NNP atom, MM atom), each wavefront taking 16
+// (forward) or 8 (adjoint) NNP atoms and one MM atom per lane.  A lane keeps
+// one running sum per NNP atom; these are reduced across lanes (a DPP
+// transposing butterfly within each 16-lane row: 15 exchanges for all 16 sums,
+// where a shuffle tree per sum took 96 LDS round trips) and stored as the
+// workgroup's partial.  The partials of an NNP atom are added in a fixed order
+// (FP64), the forward's by a second launch, the adjoint's by the force gather.
 // No atomics on the NNP side: with a small ML region every NNP atom collects
 // a term from each of hundreds of workgroups, and FP64 atomics on one address
 // serialise (60 NNP atoms, 30,000 charges: 10.9 us forward and 15.7 us
 // adjoint with per-wavefront atomics).  Intended for ML regions of up to a
 // few thousand atoms.
+#include <algorithm>
+
 #include "nnp_internal.h"
 
 namespace nnp {
@@ -24,6 +25,8 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kNnpChunk = 16;       // NNP atoms per workgroup row (= lanes of a DPP row)
 constexpr int kMaxMmBlocks = 512;   // workgroups along the MM atoms
+constexpr int kBwdChunk = 8;        // NNP atoms per adjoint wavefront
+constexpr int kBwdWaves = 16;       // most wavefronts of an adjoint workgroup
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -38,6 +41,17 @@ __device__ __forceinline__ void row_sum16(float* v, int lane) {
   halve<4, kDppHalfMirror>(v, lane & 4);
   halve<2, kDppXor2>(v, lane & 2);
   halve<1, kDppXor1>(v, lane & 1);
+}
+
+// v[0 .. 8) summed over the wavefront: lane l ends with the total of value l & 7.
+__device__ __forceinline__ float wave_sum8(float* v, int lane) {
+  halve<4, kDppHalfMirror>(v, lane & 4);
+  halve<2, kDppXor2>(v, lane & 2);
+  halve<1, kDppXor1>(v, lane & 1);
+  float s = v[0];
+#pragma unroll
+  for (int off = 8; off <= 32; off *= 2) s += __shfl_xor(s, off, 64);
+  return s;
 }
 
 __device__ __forceinline__ void mm_disp(const float4& pi, float yx, float yy, float yz, const Geometry& g,
@@ -113,105 +127,102 @@ __global__ __launch_bounds__(kBlock) void k_mm_finish(const float* __restrict__ 
 
 // Adjoint: dE/dphi_i = g[i][D] (+ the predicted charge q_i of a network with
 // a charge output, whose energy holds q_i phi_i);  dphi_i/dy_j = ke q_j f'(r) u,  f(r) = fc(r)/r,
-// u = (y_j - x_i)/r.  MM atom j gets -sum_i dE/dphi_i dphi_i/dy_j (owned by
-// its lane when one row covers every NNP atom, else FP64 atomics from each
-// row, on distinct addresses); NNP atom i gets the opposite of its column
-// sum, as per-workgroup partials part[(i * gridDim.x + blockIdx.x) * 3 + k].
-__global__ __launch_bounds__(kBlock) void k_mm_bwd(const float4* __restrict__ spos, int n,
-                                                   const float* __restrict__ mm_pos,
-                                                   const float* __restrict__ mm_q, int n_mm,
-                                                   const float* __restrict__ gx,
-                                                   const float* __restrict__ qpred, DescParams p, Geometry g,
-                                                   float* __restrict__ part,
-                                                   double* __restrict__ mm_forces) {
-  __shared__ float red[3][kBlock / kNnpChunk][kNnpChunk];   // [component][wavefront row][NNP atom]
+// u = (y_j - x_i)/r.  MM atom j gets -sum_i dE/dphi_i dphi_i/dy_j, NNP atom i
+// the opposite of its column sum, as per-workgroup partials
+// part[(3 i + k) * gridDim.x + blockIdx.x].
+//
+// The wavefronts of a workgroup take 8 NNP atoms each, of the same 64 MM
+// atoms, whose forces they add up through LDS: with one grid row the workgroup
+// owns them and writes or adds them plainly; grid rows (few MM atoms and many
+// NNP atoms) add with FP64 atomics.  Bound by the chain of pairs of the few
+// wavefronts inside the cutoff, hence 8 atoms each: 60 NNP atoms, 30,000
+// charges 7.4 us (16 atoms and two MM atoms per lane: 11.8), and the partials
+// 1.5 in the gather.  Workgroups of 16 NNP atoms that added to cleared MM
+// forces with atomics, and a launch for the partials, took 10.5 + 4.1 us and
+// the clearing 2.1.
+__global__ __launch_bounds__(64 * kBwdWaves) void k_mm_bwd(const float4* __restrict__ spos, int n,
+                                                           const float* __restrict__ mm_pos,
+                                                           const float* __restrict__ mm_q, int n_mm,
+                                                           const float* __restrict__ gx,
+                                                           const float* __restrict__ qpred, DescParams p, Geometry g,
+                                                           float* __restrict__ part,
+                                                           double* __restrict__ mm_forces, int assign) {
+  __shared__ double sf[kBwdWaves][3][64];   // MM forces of each wavefront
   const int lane = threadIdx.x & 63;
-  const int i0 = blockIdx.y * kNnpChunk, cnt = min(n - i0, kNnpChunk);
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), waves = blockDim.x >> 6;
+  const int rows = kBwdChunk * waves;
   const float rm2 = p.mm_cutoff * p.mm_cutoff;
   const float inv2rm = 0.5f / p.mm_cutoff;
   const float dfc_s = -0.5f * 3.14159265358979323846f / p.mm_cutoff;
-  float ax[kNnpChunk], ay[kNnpChunk], az[kNnpChunk], ke_g[kNnpChunk];
+  for (int r0 = blockIdx.y * rows; r0 < n; r0 += gridDim.y * rows) {
+    const int i0 = r0 + kBwdChunk * wave, cnt = min(n - i0, kBwdChunk);   // (cnt <= 0: only the forces' sums)
+    float ax[kBwdChunk], ay[kBwdChunk], az[kBwdChunk], ke_g[kBwdChunk];
 #pragma unroll
-  for (int c = 0; c < kNnpChunk; ++c) {
-    ax[c] = ay[c] = az[c] = 0.f;
-    ke_g[c] = 0.f;
-    if (c < cnt) {
-      const int i = i0 + c;
-      float gi = gx[(int64_t)i * p.stride + p.D];
-      if (qpred != nullptr) gi += qpred[i];
-      ke_g[c] = (float)p.ke * gi;
-    }
-  }
-  for (int j = blockIdx.x * kBlock + threadIdx.x; j < n_mm; j += gridDim.x * kBlock) {
-    const float yx = mm_pos[3 * (int64_t)j], yy = mm_pos[3 * (int64_t)j + 1], yz = mm_pos[3 * (int64_t)j + 2];
-    const float q = mm_q[j];
-    double fx = 0.0, fy = 0.0, fz = 0.0;
-#pragma unroll
-    for (int c = 0; c < kNnpChunk; ++c) {
+    for (int c = 0; c < kBwdChunk; ++c) {
+      ax[c] = ay[c] = az[c] = 0.f;
+      ke_g[c] = 0.f;
       if (c < cnt) {
-        const float4 pi = spos[i0 + c];
-        float dx, dy, dz, r2;
-        mm_disp(pi, yx, yy, yz, g, dx, dy, dz, r2);
-        if (r2 < rm2) {
-          float ir = __builtin_amdgcn_rsqf(r2);
-          float r = r2 * ir;
-          float arg = r * inv2rm;
-          float fc = 0.5f * __builtin_amdgcn_cosf(arg) + 0.5f;
-          float dfc = dfc_s * __builtin_amdgcn_sinf(arg);
-          float fp = (dfc - fc * ir) * ir;            // d/dr (fc / r)
-          float w = ke_g[c] * q * fp * ir;   // times u = d / r
-          const float vx = w * dx, vy = w * dy, vz = w * dz;
-          ax[c] += vx; ay[c] += vy; az[c] += vz;
-          fx -= vx; fy -= vy; fz -= vz;
+        const int i = i0 + c;
+        float gi = gx[(int64_t)i * p.stride + p.D];
+        if (qpred != nullptr) gi += qpred[i];
+        ke_g[c] = (float)p.ke * gi;
+      }
+    }
+    for (int64_t j0 = (int64_t)blockIdx.x * 64; j0 < n_mm; j0 += (int64_t)gridDim.x * 64) {
+      {
+        const int64_t j = j0 + lane;
+        double fx = 0.0, fy = 0.0, fz = 0.0;
+        if (j < n_mm) {
+          const float yx = mm_pos[3 * j], yy = mm_pos[3 * j + 1], yz = mm_pos[3 * j + 2];
+          const float q = mm_q[j];
+#pragma unroll
+          for (int c = 0; c < kBwdChunk; ++c) {
+            if (c < cnt) {
+              const float4 pi = spos[i0 + c];
+              float dx, dy, dz, r2;
+              mm_disp(pi, yx, yy, yz, g, dx, dy, dz, r2);
+              if (r2 < rm2) {
+                float ir = __builtin_amdgcn_rsqf(r2);
+                float r = r2 * ir;
+                float arg = r * inv2rm;
+                float fc = 0.5f * __builtin_amdgcn_cosf(arg) + 0.5f;
+                float dfc = dfc_s * __builtin_amdgcn_sinf(arg);
+                float fp = (dfc - fc * ir) * ir;            // d/dr (fc / r)
+                float w = ke_g[c] * q * fp * ir;   // times u = d / r
+                const float vx = w * dx, vy = w * dy, vz = w * dz;
+                ax[c] += vx; ay[c] += vy; az[c] += vz;
+                fx -= vx; fy -= vy; fz -= vz;
+              }
+            }
+          }
+        }
+        sf[wave][0][lane] = fx;
+        sf[wave][1][lane] = fy;
+        sf[wave][2][lane] = fz;
+      }
+      if (mm_forces == nullptr) continue;
+      __syncthreads();
+      const int used = min(waves, (n - r0 + kBwdChunk - 1) / kBwdChunk);
+      for (int t = threadIdx.x; t < 3 * 64; t += blockDim.x) {
+        const int c = t / 3, k = t - 3 * c;
+        if (j0 + c >= n_mm) continue;
+        double v = 0.0;
+        for (int w = 0; w < used; ++w) v += sf[w][k][c];
+        double* f = mm_forces + 3 * j0 + t;
+        if (gridDim.y > 1) {
+          if (v != 0.0) unsafeAtomicAdd(f, v);
+        } else if (assign && r0 == 0) {
+          *f = v;
+        } else if (v != 0.0) {
+          *f += v;
         }
       }
+      __syncthreads();
     }
-    if (mm_forces != nullptr) {
-      double* f = mm_forces + 3 * (int64_t)j;
-      if (gridDim.y == 1) {
-        f[0] += fx; f[1] += fy; f[2] += fz;
-      } else if (fx != 0.0 || fy != 0.0 || fz != 0.0) {
-        unsafeAtomicAdd(f + 0, fx);
-        unsafeAtomicAdd(f + 1, fy);
-        unsafeAtomicAdd(f + 2, fz);
-      }
-    }
-  }
-  row_sum16(ax, lane);
-  row_sum16(ay, lane);
-  row_sum16(az, lane);
-  red[0][threadIdx.x >> 4][lane & 15] = ax[0];
-  red[1][threadIdx.x >> 4][lane & 15] = ay[0];
-  red[2][threadIdx.x >> 4][lane & 15] = az[0];
-  __syncthreads();
-  if ((int)threadIdx.x < 3 * cnt) {
-    const int c = threadIdx.x / 3, k = threadIdx.x - 3 * c;
-    float s = red[k][0][c];
+    const float s[3] = {wave_sum8(ax, lane), wave_sum8(ay, lane), wave_sum8(az, lane)};
 #pragma unroll
-    for (int r = 1; r < kBlock / kNnpChunk; ++r) s += red[k][r][c];
-    part[((int64_t)(i0 + c) * gridDim.x + blockIdx.x) * 3 + k] = s;
-  }
-}
-
-// NNP atom i: its partials summed in order (FP64) and added to its force
-// row (or its link atom's); one wavefront per atom, so each row has one writer.
-__global__ __launch_bounds__(kBlock) void k_mm_bwd_finish(const float* __restrict__ part, int nbx, int n,
-                                                          const int* __restrict__ slot_atom,
-                                                          double* __restrict__ forces,
-                                                          double* __restrict__ link_forces) {
-  const int i = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
-  const int lane = threadIdx.x & 63;
-  if (i >= n) return;   // wavefront-uniform
-  double sx = 0.0, sy = 0.0, sz = 0.0;
-  for (int b = lane; b < nbx; b += 64) {
-    const float* v = part + ((int64_t)i * nbx + b) * 3;
-    sx += (double)v[0]; sy += (double)v[1]; sz += (double)v[2];
-  }
-  sx = wave_sum(sx); sy = wave_sum(sy); sz = wave_sum(sz);
-  if (lane == 0) {
-    const int a = slot_atom[i];   // a < 0: link atom -1 - a
-    double* f = a >= 0 ? forces + 3 * (int64_t)a : link_forces + 3 * (int64_t)(-1 - a);
-    f[0] += sx; f[1] += sy; f[2] += sz;
+    for (int k = 0; k < 3; ++k)
+      if (lane < cnt) part[((int64_t)(i0 + lane) * 3 + k) * gridDim.x + blockIdx.x] = s[k];
   }
 }
 
@@ -224,8 +235,13 @@ inline int wave_blocks(int n) { return (int)(((int64_t)n * 64 + kBlock - 1) / kB
 
 }  // namespace
 
+int mm_partial_blocks(int n_mm) {
+  const int b = (n_mm + 63) / 64;
+  return b < kMaxMmBlocks ? b : kMaxMmBlocks;
+}
+
 size_t mm_partial_floats(int max_atoms, int max_mm) {
-  return max_mm > 0 ? 3 * (size_t)max_atoms * (size_t)mm_blocks(max_mm) : 0;
+  return max_mm > 0 ? 3 * (size_t)max_atoms * (size_t)mm_partial_blocks(max_mm) : 0;
 }
 
 hipError_t launch_mm_fwd(nnp_model& m, int n, int n_mm, const float* mm_pos, const float* mm_q,
@@ -242,16 +258,23 @@ hipError_t launch_mm_fwd(nnp_model& m, int n, int n_mm, const float* mm_pos, con
   return hipGetLastError();
 }
 
-hipError_t launch_mm_bwd(nnp_model& m, int n, int n_mm, const float* mm_pos, const float* mm_q,
-                         double* forces, double* mm_forces, hipStream_t st) {
-  if (n == 0 || n_mm == 0) return hipSuccess;
-  const int nbx = mm_blocks(n_mm);
+hipError_t launch_mm_bwd(nnp_model& m, int n, int n_mm, const float* mm_pos, const float* mm_q, double* mm_forces,
+                         int accumulate, hipStream_t st) {
+  if (n == 0 || n_mm == 0)
+    return mm_forces != nullptr && !accumulate ? launch_fill_f64(mm_forces, 3 * (int64_t)n_mm, st) : hipSuccess;
+  const int nbx = mm_partial_blocks(n_mm);
   if (m.d_mm_part == nullptr || 3 * (size_t)n * nbx > mm_partial_floats(m.max_atoms, m.max_mm))
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_mm_bwd, dim3(nbx, (n + kNnpChunk - 1) / kNnpChunk), dim3(kBlock), 0, st, m.d_spos, n,
-                     mm_pos, mm_q, n_mm, m.d_g, m.charges ? m.d_q : nullptr, m.dp, m.geo, m.d_mm_part, mm_forces);
-  hipLaunchKernelGGL(k_mm_bwd_finish, dim3(wave_blocks(n)), dim3(kBlock), 0, st, m.d_mm_part, nbx, n,
-                     m.d_slot_atom, forces, m.d_link_F);
+  // as many wavefronts as there are rows of 8 NNP atoms; with more rows than
+  // one workgroup takes, grid rows until there are two workgroups per CU
+  const int rows = (n + kBwdChunk - 1) / kBwdChunk, waves = std::min(rows, kBwdWaves);
+  const int gy = std::min((rows + waves - 1) / waves, std::max(1, 2 * m.n_cu / nbx));
+  if (gy > 1 && mm_forces != nullptr && !accumulate) {
+    const hipError_t e = launch_fill_f64(mm_forces, 3 * (int64_t)n_mm, st);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(k_mm_bwd, dim3(nbx, gy), dim3(64 * waves), 0, st, m.d_spos, n, mm_pos, mm_q, n_mm, m.d_g,
+                     m.charges ? m.d_q : nullptr, m.dp, m.geo, m.d_mm_part, mm_forces, !accumulate);
   return hipGetLastError();
 }
 

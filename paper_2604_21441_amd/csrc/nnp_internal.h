@@ -413,15 +413,16 @@ hipError_t launch_pair_lists(nnp_model& m, int n, int n_atoms, int n_pairs, cons
 // descriptor.hip
 hipError_t launch_descriptor_fwd(nnp_model& m, int n, hipStream_t st);
 hipError_t launch_descriptor_bwd(nnp_model& m, int n, hipStream_t st);
-hipError_t launch_force_gather(nnp_model& m, int n, double* forces, int assign, double* energies, int n_sys,
-                               int accumulate, hipStream_t st);
+hipError_t launch_force_gather(nnp_model& m, int n, int n_mm, double* forces, int assign, double* energies,
+                               int n_sys, int accumulate, hipStream_t st);
 
 // mm.hip
+int mm_partial_blocks(int n_mm);   // adjoint partials per component of an NNP atom
 size_t mm_partial_floats(int max_atoms, int max_mm);   // floats of the MM partial buffer
 hipError_t launch_mm_fwd(nnp_model& m, int n, int n_mm, const float* mm_pos, const float* mm_q,
                          hipStream_t st);
-hipError_t launch_mm_bwd(nnp_model& m, int n, int n_mm, const float* mm_pos, const float* mm_q,
-                         double* forces, double* mm_forces, hipStream_t st);
+hipError_t launch_mm_bwd(nnp_model& m, int n, int n_mm, const float* mm_pos, const float* mm_q, double* mm_forces,
+                         int accumulate, hipStream_t st);
 
 // mlp.hip
 // Device copy of the canonical weights -> the split FP32 form's fragments.
