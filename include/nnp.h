@@ -215,7 +215,7 @@ nnp_status nnp_compute_pairs(nnp_model* m, int32_t n_atoms, const float* pos, co
  * one adjoint launch cover all systems.  The boxes are kept in device memory:
  * a call whose boxes differ from the previous call's uploads them (this
  * synchronises the stream and is refused under stream capture, as a topology
- * change is) and replays the captured graph.  A batched call has no index
+ * change is) and, where calls replay a graph, replays the captured one.  A batched call has no index
  * group, so link atoms (nnp_set_links) do not apply to it.
  */
 nnp_status nnp_compute_batch(nnp_model* m, int32_t n_sys, const int32_t* atom_offsets_host,
@@ -375,20 +375,23 @@ nnp_status nnp_set_variant(nnp_model* m, int32_t stage, int32_t variant);
 nnp_status nnp_get_variants(nnp_model* m, int32_t* chosen);
 
 /*
- * HIP-graph replay (enabled by default).  The first call of a configuration
- * is captured into a HIP graph; a later call with the same arguments (device
- * pointers, sizes, flags and box) replays it with one launch.  A call whose
- * arguments differ (a new box every step under a barostat, other output
- * buffers) is captured again and the instantiated graph is updated in place
- * with the new kernel arguments (hipGraphExecUpdate), which costs far less
- * than building a new graph; a graph is only rebuilt when the update is
- * refused (a different sequence of kernels, e.g. another cell grid).  The
- * per-system boxes of nnp_compute_batch live in device memory and never
- * change the graph.  Device memory contents (positions, topology arrays) may
- * change between replays.  Calls made while the stream is already capturing,
- * or while stage timing is on, launch their kernels directly.  enable = 0
- * turns replay off and frees the cached graph.  NNP_BUF_GRAPH counts builds,
- * updates and replays.
+ * HIP-graph replay.  By default, calls with fewer than three atoms per CU and
+ * no MM atoms use it, where the host's time per call counts; for larger ones
+ * direct launches finish 4 to 5 us earlier on the GPU.  enable = 1: every
+ * call; enable = 0: none, and the cached graph is freed.  The first call of a
+ * configuration is captured into a HIP graph; a later call with the same
+ * arguments (device pointers, sizes, flags and box) replays it with one
+ * launch.  A call whose arguments differ (a new box every step under a
+ * barostat, other output buffers) is captured again and the instantiated
+ * graph is updated in place with the new kernel arguments
+ * (hipGraphExecUpdate), which costs far less than building a new graph; a
+ * graph is only rebuilt when the update is refused (a different sequence of
+ * kernels, e.g. another cell grid).  The per-system boxes of
+ * nnp_compute_batch live in device memory and never change the graph.  Device
+ * memory contents (positions, topology arrays) may change between replays.
+ * Calls made while the stream is already capturing, or while stage timing is
+ * on, launch their kernels directly.  NNP_BUF_GRAPH counts builds, updates
+ * and replays.
  */
 nnp_status nnp_set_graph(nnp_model* m, int32_t enable);
 

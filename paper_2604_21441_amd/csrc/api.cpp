@@ -153,10 +153,19 @@ std::vector<uint8_t> make_key(const T&... parts) {
 // is far cheaper than instantiating; only if that fails is the graph rebuilt.
 // Capture happens on the model's own stream (the caller's may be the legacy
 // default stream, which cannot be captured); the graph runs on the caller's.
+// Unless nnp_set_graph asked for it, a graph is used only where the host's time
+// per call counts: it costs the host 22 us for the six kernels of 192 atoms of
+// water (direct launches 26, 34 for eight kernels), but the GPU 4 to 5 us more
+// per call than direct launches (12,288 atoms 105.3 against 100.4 us, 900 atoms
+// with a pair list 63.6 against 58.8, 256 conformers 293 against 288).  From
+// three atoms per CU on, and with MM atoms, the kernels outlast their launches
+// (50 us and more).
 template <typename F>
-nnp_status dispatch(nnp_model* m, std::vector<uint8_t> key, hipStream_t st, F launch) {
+nnp_status dispatch(nnp_model* m, std::vector<uint8_t> key, int n, int n_mm, hipStream_t st, F launch) {
+  const bool replay = m->graph_mode == kGraphAlways ||
+                      (m->graph_mode == kGraphAuto && n < 3 * m->n_cu && n_mm == 0);
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (!m->graph_enabled || !m->cap_stream || m->prof_calls < m->prof_max_calls ||
+  if (!replay || !m->cap_stream || m->prof_calls < m->prof_max_calls ||
       (st != nullptr && (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone))) {
     return launch(st);
   }
@@ -717,7 +726,7 @@ nnp_status compute_single(nnp_model* m, int32_t n_atoms, const float* pos, const
   const int lv = m->link_version;
   return dispatch(m, make_key(mode, pos, energy, forces, mm_forces, mm_pos, mm_q, n_atoms, n_nnp, n_mm, accumulate,
                               lv, m->geo, n_pairs, pairs),
-                  stream, launch);
+                  n_loc, n_mm, stream, launch);
 }
 
 }  // namespace
@@ -825,7 +834,7 @@ nnp_status nnp_compute_batch(nnp_model* m, int32_t n_sys, const int32_t* atom_of
     return run_path(m, n, pos, 0, nullptr, nullptr, energies, n_sys, forces, nullptr, 0, 1, n, 0, nullptr, s);
   };
   const int mode = 1;
-  return dispatch(m, make_key(mode, pos, energies, forces, n, n_sys, m->geo), stream, launch);
+  return dispatch(m, make_key(mode, pos, energies, forces, n, n_sys, m->geo), n, 0, stream, launch);
 }
 
 nnp_status nnp_get_status(nnp_model* m, hipStream_t stream) {
@@ -1027,8 +1036,8 @@ nnp_status nnp_set_links(nnp_model* m, int32_t n_links, const int32_t* ml_idx_ho
 
 nnp_status nnp_set_graph(nnp_model* m, int32_t enable) {
   if (!m) return set_error(NNP_EINVAL, "null model");
-  m->graph_enabled = enable != 0;
-  if (!m->graph_enabled) drop_graph(m);
+  m->graph_mode = enable != 0 ? kGraphAlways : kGraphOff;
+  if (!enable) drop_graph(m);
   return NNP_OK;
 }
 

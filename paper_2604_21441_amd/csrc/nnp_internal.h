@@ -82,6 +82,7 @@ __device__ __forceinline__ int narrow_species(const int* bin_start, int S, int n
 constexpr int kStatusCapacity = 1;
 constexpr int kStatusNonFinite = 2;
 constexpr int kStatusInput = 4;      // bad entry in a caller's pair list
+enum { kGraphOff = 0, kGraphAlways = 1, kGraphAuto = 2 };   // how calls are launched (dispatch)
 constexpr int kPairRowMax = 256;     // radial capacity the pair-list sort supports
 
 // Descriptor constants, passed by value to the kernels.
@@ -337,7 +338,7 @@ struct nnp_model : nnp::Workspace {
   int n_nnp = 0;
 
   // graph replay of identical calls
-  bool graph_enabled = true;
+  int graph_mode = nnp::kGraphAuto;
   hipStream_t cap_stream = nullptr;  // capture stream (default priority)
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;

@@ -37,6 +37,7 @@ def test_sizes(n, n_mm):
     out = (torch.full((1,), 7.0, dtype=torch.float64, device="cuda"),
            torch.full((n, 3), 7.0, dtype=torch.float64, device="cuda"),
            torch.full((n_mm, 3), 7.0, dtype=torch.float64, device="cuda"))
+    m.set_graph(True)
     for _ in range(2):   # the second call runs from the captured graph
         m.compute(t(pos), Z, None, None, t(mm), t(q), out=out)
     torch.cuda.synchronize()
