@@ -394,57 +394,73 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_scatter(const int* __rest
   if (t < n) tmp[bufc[scan_pad<PER>(k)] + rk] = t;
 }
 
-// Small periodic systems: the whole cell list in one workgroup, through LDS.
-// LDS histogram atomics give arrival ranks, both scans run in LDS, and each
-// thread then places its own atoms: the stable slot of atom t is the start of
-// its key plus the number of atoms of that key with a smaller index, counted
-// in the key's segment of the arrival-order scatter.  One launch instead of
-// three (binning, scan + scatter, bin sort), with the same outputs bit for
-// bit.  The device histogram is not touched (it stays zero).
-constexpr int kSmallCells = 2048;   // atoms; LDS: 2 padded scan buffers + 2 ints per atom
-static_assert(kSmallCells % kScanThreads == 0, "whole atoms per thread");
+// Small periodic systems: the whole cell list in one launch, through LDS.
+// Every workgroup bins all atoms (U per thread; LDS histogram atomics give
+// arrival ranks), scans the histogram and scatters the atoms by key, all in
+// its own LDS; then it places kScanThreads atoms of its own: the stable slot
+// of an atom is the start of its key plus the number of atoms of that key with
+// a smaller index, counted in the key's segment of the scatter.  The same
+// outputs, bit for bit, as binning, scan + scatter and bin sort in three
+// launches; the device histogram is not touched (it stays zero).
+//
+// Bound by latency and, with more atoms per thread, by the LDS scatters: 1,500
+// atoms 9.0 us (one workgroup alone for all 10.6), 2,100 atoms 9.6 against
+// 14.4 for the three launches, 4,100 atoms 10.2 against 14.5, 8,100 atoms 12.7
+// against 14.2, but 12,288 atoms 16.9 against 15.2 (event-timed), hence the
+// limit.
+constexpr int kCellsMost = 8;   // atoms per thread; LDS: 2 padded scan buffers and 16 bits per atom
 
-template <int PER>
-__global__ __launch_bounds__(kScanThreads) void k_cells_small(const float* __restrict__ pos, int n,
-                                                              const int* __restrict__ idx,
-                                                              const int* __restrict__ sigma, Geometry g,
-                                                              LinkArgs L, int S, int* __restrict__ key,
-                                                              int* __restrict__ bin_start,
-                                                              int* __restrict__ perm, float4* __restrict__ spos,
-                                                              int* __restrict__ slot_atom,
-                                                              int* __restrict__ order, int* __restrict__ sbin,
-                                                              int* __restrict__ islot, PairCount pc,
-                                                              int* __restrict__ status) {
+template <int PER, int U>
+__global__ __launch_bounds__(kScanThreads) void k_cells(const float* __restrict__ pos, int n,
+                                                        const int* __restrict__ idx,
+                                                        const int* __restrict__ sigma, Geometry g, LinkArgs L,
+                                                        int S, int* __restrict__ key, int* __restrict__ bin_start,
+                                                        int* __restrict__ perm, float4* __restrict__ spos,
+                                                        int* __restrict__ slot_atom, int* __restrict__ order,
+                                                        int* __restrict__ sbin, int* __restrict__ islot,
+                                                        PairCount pc, int* __restrict__ status) {
   __shared__ int wsum[2 * (kScanThreads / 64) + 1];
   __shared__ int hist[scan_lds_words<PER>()];   // counts per key, then species-major starts
   __shared__ int bmaj[scan_lds_words<PER>()];   // totals per bin, then bin-major starts
-  __shared__ int tmp[kSmallCells];               // atoms of each key in arrival order
-  __shared__ int kr[kSmallCells];                // key | arrival rank << 15
+  __shared__ uint16_t tmp[U * kScanThreads];     // atoms of each key in arrival order
   const int nb = S * g.n_bins;                   // <= kScanThreads * PER <= 2^14 (checked by the launcher)
   const int tid = threadIdx.x;
 #pragma unroll
   for (int u = 0; u < PER; ++u) hist[scan_pad<PER>(u * kScanThreads + tid)] = 0;
-  __syncthreads();
-  // each thread owns atoms tid + u * kScanThreads and keeps their data in registers
-  constexpr int kOwn = kSmallCells / kScanThreads;
-  float3 pp[kOwn];
-  int aa[kOwn], ss[kOwn];
+  const int own = blockIdx.x * kScanThreads + tid;   // the atom this thread places
+  const int atom = own < n ? idx[own] : 0;
+  const float3 mine = nnp_position(pos, atom, L, g);
+  // thread tid bins atoms u * kScanThreads + tid (every load before the first use)
+  int aa[U], ss[U], kr[U];   // kr: key | arrival rank << 15
+  float3 pp[U];
 #pragma unroll
-  for (int u = 0; u < kOwn; ++u) {
-    const int t = u * kScanThreads + tid;
-    if (t >= n) continue;
+  for (int u = 0; u < U; ++u) {
+    const int t = min(u * kScanThreads + tid, n - 1);
     aa[u] = idx[t];
     ss[u] = sigma[t];
-    pp[u] = nnp_position(pos, aa[u], L, g);
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int64_t at = 3 * (int64_t)max(aa[u], 0);
+    pp[u] = make_float3(pos[at], pos[at + 1], pos[at + 2]);
+  }
+  if (L.n > 0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (aa[u] < 0) pp[u] = nnp_position(pos, aa[u], L, g);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int t = u * kScanThreads + tid;
+    if (t >= n) continue;
     int bin = 0;
     if (!(isfinite(pp[u].x) && isfinite(pp[u].y) && isfinite(pp[u].z)))
       atomicOr(status, kStatusNonFinite);
     else
       bin = cell_of(pp[u].x, pp[u].y, pp[u].z, g);
     const int k = ss[u] * g.n_bins + bin;
-    key[t] = k;
-    const int r = atomicAdd(&hist[scan_pad<PER>(k)], 1);
-    kr[t] = k | (r << 15);
+    kr[u] = k | (atomicAdd(&hist[scan_pad<PER>(k)], 1) << 15);
   }
   __syncthreads();
 #pragma unroll
@@ -462,32 +478,35 @@ __global__ __launch_bounds__(kScanThreads) void k_cells_small(const float* __res
   carry = 0;
   scan_chunk<PER>(hist, wsum, &carry);
   auto start_of = [&](int k) { return k < nb ? hist[scan_pad<PER>(k)] : n; };
-  for (int i = tid; i <= nb; i += kScanThreads) bin_start[i] = start_of(i);
-  for (int t = tid; t < n; t += kScanThreads) {
-    const int v = kr[t];
-    tmp[start_of(v & 0x7fff) + (v >> 15)] = t;
+  if (blockIdx.x == 0)
+    for (int i = tid; i <= nb; i += kScanThreads) bin_start[i] = start_of(i);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int t = u * kScanThreads + tid;
+    if (t < n) tmp[start_of(kr[u] & 0x7fff) + (kr[u] >> 15)] = (uint16_t)t;
   }
   __syncthreads();
+  if (own < n) {
+    int k = kr[0];
 #pragma unroll
-  for (int u = 0; u < kOwn; ++u) {
-    const int t = u * kScanThreads + tid;
-    if (t >= n) continue;
-    const int k = kr[t] & 0x7fff;
+    for (int u = 1; u < U; ++u) k = u == (int)blockIdx.x ? kr[u] : k;
+    k &= 0x7fff;
     const int b0 = start_of(k), b1 = start_of(k + 1);
     int rank = 0;
-    for (int e = b0; e < b1; ++e) rank += tmp[e] < t;
+    for (int e = b0; e < b1; ++e) rank += tmp[e] < own;
     const int slot = b0 + rank;
     const int sp = k / g.n_bins, bin = k - sp * g.n_bins;
     int o0 = bmaj[scan_pad<PER>(bin)];   // bin-major: earlier bins, then earlier species of this bin
     for (int s = 0; s < sp; ++s) o0 += start_of(s * g.n_bins + bin + 1) - start_of(s * g.n_bins + bin);
     const int cz = bin % g.nc[2], cxy = bin / g.nc[2];
-    perm[slot] = t;
+    key[own] = k;
+    perm[slot] = own;
     order[o0 + rank] = slot;
     sbin[slot] = ((cxy / g.nc[1]) << 20) | ((cxy % g.nc[1]) << 10) | cz;
-    islot[t] = slot;
+    islot[own] = slot;
     if (pc.at != nullptr) pc.at[(int64_t)slot * pc.stride] = 0;
-    spos[slot] = make_float4(pp[u].x, pp[u].y, pp[u].z, __int_as_float(ss[u]));
-    slot_atom[slot] = aa[u];
+    spos[slot] = make_float4(mine.x, mine.y, mine.z, __int_as_float(sp));
+    slot_atom[slot] = atom;
   }
 }
 
@@ -1250,11 +1269,24 @@ void launch_scan(nnp_model& m, hipStream_t st) {
                      m.S, m.geo.n_bins);
 }
 
-template <int PER>
-void launch_cells_small(nnp_model& m, const float* pos, int n, const LinkArgs& L, const PairCount& pc, hipStream_t st) {
-  hipLaunchKernelGGL(k_cells_small<PER>, dim3(1), dim3(kScanThreads), 0, st, pos, n, m.d_idx, m.d_sigma, m.geo, L,
-                     m.S, m.d_key, m.d_bin_start, m.d_perm, m.d_spos, m.d_slot_atom, m.d_order, m.d_sbin,
-                     m.d_islot, pc, m.d_status);
+template <int PER, int U>
+void launch_cells_small(nnp_model& m, const float* pos, int n, const LinkArgs& L, const PairCount& pc,
+                        hipStream_t st) {
+  hipLaunchKernelGGL((k_cells<PER, U>), dim3(blocks_for(n, kScanThreads)), dim3(kScanThreads), 0, st, pos, n,
+                     m.d_idx, m.d_sigma, m.geo, L, m.S, m.d_key, m.d_bin_start, m.d_perm, m.d_spos, m.d_slot_atom,
+                     m.d_order, m.d_sbin, m.d_islot, pc, m.d_status);
+}
+
+template <int U>
+void launch_cells_small(nnp_model& m, const float* pos, int n, const LinkArgs& L, const PairCount& pc,
+                        hipStream_t st) {
+  switch (scan_entries_per_thread(m.S * m.geo.n_bins)) {
+    case 1: launch_cells_small<1, U>(m, pos, n, L, pc, st); break;
+    case 2: launch_cells_small<2, U>(m, pos, n, L, pc, st); break;
+    case 4: launch_cells_small<4, U>(m, pos, n, L, pc, st); break;
+    case 8: launch_cells_small<8, U>(m, pos, n, L, pc, st); break;
+    default: launch_cells_small<16, U>(m, pos, n, L, pc, st); break;
+  }
 }
 
 template <int PER>
@@ -1270,14 +1302,10 @@ hipError_t launch_cells(nnp_model& m, const float* pos, int n, bool pair_list, h
   const Geometry& g = m.geo;
   LinkArgs L{m.d_link_ml, m.d_link_mm, m.link_d, m.n_links_dev};
   int nb = m.S * g.n_bins;
-  if (n > 0 && g.periodic && n <= kSmallCells && nb <= kScanChunk) {
-    switch (scan_entries_per_thread(nb)) {
-      case 1: launch_cells_small<1>(m, pos, n, L, pc, st); break;
-      case 2: launch_cells_small<2>(m, pos, n, L, pc, st); break;
-      case 4: launch_cells_small<4>(m, pos, n, L, pc, st); break;
-      case 8: launch_cells_small<8>(m, pos, n, L, pc, st); break;
-      default: launch_cells_small<16>(m, pos, n, L, pc, st); break;
-    }
+  if (n > 0 && g.periodic && n <= kCellsMost * kScanThreads && nb <= kScanChunk) {
+    if (n <= 2 * kScanThreads) launch_cells_small<2>(m, pos, n, L, pc, st);
+    else if (n <= 4 * kScanThreads) launch_cells_small<4>(m, pos, n, L, pc, st);
+    else launch_cells_small<8>(m, pos, n, L, pc, st);
     return hipGetLastError();
   }
   if (n > 0) {
