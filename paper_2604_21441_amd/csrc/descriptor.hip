@@ -1159,6 +1159,7 @@ struct EnergyArgs {
   const int* bin_start;    // species buckets [s * n_bins, (s + 1) * n_bins)
   int n_bins, S, tile_rows;
   int mixed;               // the network's narrow species used 16-atom tiles
+  int sums;                // partials of summed ensemble members (k_mlp_sum), else 0
   int empty;               // no atoms: the energies are zero (the buckets are not read)
   double* out;
   int accumulate;
@@ -1171,8 +1172,8 @@ __device__ __forceinline__ void energy_block(const EnergyArgs& ea, int sys) {
   if (ea.empty) {
   } else if (ea.part != nullptr) {
     const int narrow = ea.mixed ? narrow_species(ea.bin_start, ea.S, ea.n_bins) : -1;
-    int tiles = 0;
-    for (int s = 0; s < ea.S; ++s) {
+    int tiles = ea.sums;
+    for (int s = 0; s < ea.S && ea.sums == 0; ++s) {
       const int rows = s == narrow ? 16 : ea.tile_rows;
       tiles += (ea.bin_start[(s + 1) * ea.n_bins] - ea.bin_start[s * ea.n_bins] + rows - 1) / rows;
     }
@@ -1432,6 +1433,7 @@ hipError_t launch_force_gather(nnp_model& m, int n, int n_mm, double* forces, in
   ea.S = m.S;
   ea.tile_rows = 16 * m.mlp_cols;
   ea.mixed = m.mlp_mixed;
+  ea.sums = m.mlp_sums;
   ea.empty = n == 0;
   ea.out = energies;
   ea.accumulate = accumulate;

@@ -676,6 +676,25 @@ __global__ __launch_bounds__(512, K0 <= 128 && OP == kOpSplit && C <= 2 ? 4 : 2)
 // count matches the CUs better than one size does (water, 4,096 molecules:
 // 256 + 256 instead of 384 tiles).  Every atom's arithmetic is the same as
 // in the uniform tiling.
+// The same with an ensemble's members shared over the grid's rows (k_mlp_sum
+// adds the rows up): row y evaluates its members as an ensemble of its own.
+// (Kept apart: the rows' addresses cost the plain kernel registers it spills
+// for, 98,304 atoms 95 -> 104 us.)
+__host__ __device__ __forceinline__ int first_member(int members, int y, int rows) { return members * y / rows; }
+
+template <int K0, int N1, int N2, int N3, int OP, int C>
+__global__ __launch_bounds__(512, K0 <= 128 && OP == kOpSplit ? 4 : 2) void k_mlp_members(MlpArgs a, float alpha) {
+  using Elem = typename std::conditional<OP == kOpBF16, __bf16, float>::type;
+  const int y = blockIdx.y, m0 = first_member(a.n_members, y, gridDim.y);
+  a.n_members = first_member(a.n_members, y + 1, gridDim.y) - m0;
+  a.wmat = reinterpret_cast<const Elem*>(a.wmat) + (int64_t)m0 * a.S * a.mat_per_species;
+  a.wvec += (int64_t)m0 * a.S * a.vec_per_species;
+  if (y > 0) a.g = a.g_part + (int64_t)(y - 1) * a.n * a.stride;
+  a.e = a.e_part + (int64_t)y * a.n;
+  a.part = nullptr;
+  mlp_split_body<K0, N1, N2, N3, OP, C, false, 8, false>(a, alpha);
+}
+
 template <int K0, int N1, int N2, int N3, int OP>
 __global__ __launch_bounds__(256, K0 <= 128 ? 2 : 1) void k_mlp_mixed(MlpArgs a, float alpha) {
   mlp_split_body<K0, N1, N2, N3, OP, 2, true, 4, false>(a, alpha);
@@ -1316,6 +1335,43 @@ __global__ __launch_bounds__(64 * NW, 1) void k_mlp_lds(MlpArgs a, float alpha) 
   }
 }
 
+// The averages over all members from the grid rows' averages, kSumAtoms atoms
+// per workgroup; part: FP64 sum of the workgroup's energies.
+constexpr int kSumAtoms = kTileAtoms;   // (the energy partials are sized for them)
+constexpr int kMaxMemberRows = 4;   // (three doubles per atom hold the energies of six)
+
+__global__ __launch_bounds__(kBlock) void k_mlp_sum(MlpArgs a, int rows) {
+  const int i0 = blockIdx.x * kSumAtoms, cnt = min(kSumAtoms, a.n - i0);
+  float share[kMaxMemberRows];   // of the members, per row
+#pragma unroll
+  for (int y = 0; y < kMaxMemberRows; ++y)
+    share[y] = (float)(first_member(a.n_members, y + 1, rows) - first_member(a.n_members, y, rows)) /
+               (float)a.n_members;
+  const int64_t step = (int64_t)a.n * a.stride, first = (int64_t)i0 * a.stride;
+  for (int t = threadIdx.x; t < cnt * (a.stride / 4); t += kBlock) {
+    const int64_t at = first + 4 * t;
+    v4f v = *reinterpret_cast<const v4f*>(a.g + at) * share[0];
+#pragma unroll
+    for (int y = 1; y < kMaxMemberRows; ++y)
+      if (y < rows) v += *reinterpret_cast<const v4f*>(a.g_part + (y - 1) * step + at) * share[y];
+    *reinterpret_cast<v4f*>(a.g + at) = v;
+  }
+  if (threadIdx.x < 64) {
+    double ev = 0.0;
+    if ((int)threadIdx.x < cnt) {
+      float e = 0.f;
+#pragma unroll
+      for (int y = 0; y < kMaxMemberRows; ++y)
+        if (y < rows) e = fmaf(a.e_part[(int64_t)y * a.n + i0 + threadIdx.x], share[y], e);
+      a.e[i0 + threadIdx.x] = e;
+      ev = (double)e;
+    }
+#pragma unroll
+    for (int off = kSumAtoms / 2; off >= 1; off >>= 1) ev += __shfl_xor(ev, off, 64);
+    if (threadIdx.x == 0 && a.part != nullptr) a.part[blockIdx.x] = ev;
+  }
+}
+
 // One workgroup per CU at most (each holds a species' weights in LDS), no
 // more than the tiles need, at least one per species.
 template <int K0, int N1, int N2, int N3, int C, int NW>
@@ -1328,8 +1384,16 @@ void launch_lds(const nnp_model& m, const MlpArgs& a, int n, hipStream_t st) {
 }
 
 template <int K0, int N1, int N2, int N3, int OP>
-hipError_t run_mlp(nnp_model& m, const MlpArgs& a, int n, int variant, hipStream_t st) {
-  if (variant == 0) {        // register-resident, one wavefront per 16 atoms
+hipError_t run_mlp(nnp_model& m, const MlpArgs& a, int n, int variant, int rows, hipStream_t st) {
+  if (rows > 1) {   // variants 5 and 7, the members shared
+    const int64_t tiles = (n + 16 * m.mlp_cols - 1) / (16 * m.mlp_cols) + m.S;
+    const dim3 grid((unsigned)tiles, (unsigned)rows);
+    if (variant == 5)
+      hipLaunchKernelGGL((k_mlp_members<K0, N1, N2, N3, OP, 1>), grid, dim3(512), 0, st, a, m.celu_alpha);
+    else
+      hipLaunchKernelGGL((k_mlp_members<K0, N1, N2, N3, OP, 2>), grid, dim3(512), 0, st, a, m.celu_alpha);
+    hipLaunchKernelGGL(k_mlp_sum, dim3((unsigned)m.mlp_sums), dim3(kBlock), 0, st, a, rows);
+  } else if (variant == 0) {        // register-resident, one wavefront per 16 atoms
     const int64_t waves = (n + 15) / 16 + m.S;
     hipLaunchKernelGGL((k_mlp_reg<K0, N1, N2, N3, OP>), dim3((unsigned)((waves * 64 + kBlock - 1) / kBlock)),
                        dim3(kBlock), 0, st, a, m.celu_alpha);
@@ -1487,6 +1551,24 @@ hipError_t pack_split(const nnp_model& m, const float* weights, void* out) {
   return hipGetLastError();
 }
 
+// Grid rows that share an ensemble's members: doubled while there are fewer
+// than three workgroups for two CUs, every row has a member and the partial
+// sums fit the force contributions and totals, which are unused until the
+// adjoint.  With few tiles CUs idle while each tile's workgroup walks all
+// members: 8 networks, 600 atoms 68 -> 26 us, 3,900 atoms 68 -> 53, 8,100
+// atoms 89 -> 70, 5 networks, 2,100 atoms 44 -> 36.  Beyond (8 networks,
+// 12,288 atoms, 386 tiles: 111 us, two rows 110; 2 networks 32.7 and 35.3) the
+// sum takes what a more even load gives.
+int member_rows(const nnp_model& m, int n, int variant) {
+  if (m.charges || (variant != 5 && variant != 7)) return 1;   // (charges are not summed up)
+  const int tiles = (n + 16 * m.mlp_cols - 1) / (16 * m.mlp_cols) + m.S;
+  int rows = 1;
+  while (2 * rows <= m.n_members && 2 * rows <= kMaxMemberRows &&
+         (int64_t)(2 * rows - 1) * m.stride <= 3 * (int64_t)m.max_rad && 2 * tiles * rows < 3 * m.n_cu)
+    rows *= 2;
+  return rows;
+}
+
 hipError_t launch_mlp(nnp_model& m, int n, hipStream_t st) {
   if (n == 0) return hipSuccess;
   MlpArgs a;
@@ -1513,18 +1595,23 @@ hipError_t launch_mlp(nnp_model& m, int n, hipStream_t st) {
   m.mlp_cols = v == 3 ? (m.net_kind == 0 ? 4 : 2) : (v == 2 || v == 4 || v == 6 || v == 7 || v == 8 ? 2 : 1);
   m.mlp_mixed = v == 4 || v == 6;
   a.split = split_scales(m, m.max_rad, m.max_ang);
+  a.n = n;
+  a.g_part = reinterpret_cast<float*>(m.d_contrib);
+  a.e_part = reinterpret_cast<float*>(m.d_self);
+  const int rows = member_rows(m, n, v);
+  m.mlp_sums = rows > 1 ? (n + kSumAtoms - 1) / kSumAtoms : 0;
   switch (m.net_kind) {
     case 0:
-      return bf ? run_mlp<128, 160, 128, 96, kOpBF16>(m, a, n, v, st) : run_mlp<128, 160, 128, 96, kOpSplit>(m, a, n, v, st);
+      return bf ? run_mlp<128, 160, 128, 96, kOpBF16>(m, a, n, v, rows, st) : run_mlp<128, 160, 128, 96, kOpSplit>(m, a, n, v, rows, st);
     case 1:
-      return bf ? run_mlp<384, 256, 192, 160, kOpBF16>(m, a, n, v, st)
-                : run_mlp<384, 256, 192, 160, kOpSplit>(m, a, n, v, st);
+      return bf ? run_mlp<384, 256, 192, 160, kOpBF16>(m, a, n, v, rows, st)
+                : run_mlp<384, 256, 192, 160, kOpSplit>(m, a, n, v, rows, st);
     case 2:
       if (m.charges)
         return bf ? run_mlp_q<416, 256, 192, 160, kOpBF16>(m, a, n, v, st)
                   : run_mlp_q<416, 256, 192, 160, kOpSplit>(m, a, n, v, st);
-      return bf ? run_mlp<416, 256, 192, 160, kOpBF16>(m, a, n, v, st)
-                : run_mlp<416, 256, 192, 160, kOpSplit>(m, a, n, v, st);
+      return bf ? run_mlp<416, 256, 192, 160, kOpBF16>(m, a, n, v, rows, st)
+                : run_mlp<416, 256, 192, 160, kOpSplit>(m, a, n, v, rows, st);
     default:
       return hipErrorInvalidValue;
   }

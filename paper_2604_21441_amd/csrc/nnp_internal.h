@@ -238,6 +238,9 @@ struct MlpArgs {
   const void* wrow;        // BF16 models: W1, W2, W3 row-major per (member, species), or null
   int64_t wrow_per_species;
   SplitScales split;       // split FP32 form
+  int n;
+  float* g_part;           // members shared over grid rows: dE/dx sums of rows 1, 2, ... [rows - 1][n][stride]
+  float* e_part;           // and atomic energy sums of every row [rows][n]
 };
 
 // Per-call device workspace: capacities and the arrays sized from them.
@@ -301,6 +304,7 @@ struct nnp_model : nnp::Workspace {
   nnp::DescParams dp{};
   int mlp_cols = 1;                     // column tiles (16 atoms each) per network workgroup
   int mlp_mixed = 0;                    // the species with the fewest atoms uses one column tile
+  int mlp_sums = 0;                     // energy partials if the members were summed by k_mlp_sum, else 0
   std::map<std::pair<int, int>, int> tuned;   // (stage, size bucket) -> variant
   int force_variant[nnp::kTuneStages] = {-1, -1, -1, -1};   // set while timing candidates
   int pinned[nnp::kTuneStages] = {-1, -1, -1, -1};          // nnp_set_variant
