@@ -729,25 +729,27 @@ __global__ __launch_bounds__(64) void k_neighbours(NeighArgs a, Geometry g) {
   int* ang = a.ang + (int64_t)i * a.max_ang;
   int nr = 0, na = 0;   // list lengths so far (wavefront-uniform)
   bool overflow = false;
+  // candidate ranges of a species, one stencil cell per lane; those of the
+  // next species are on their way while this one's candidates are tested
+  int st_next = 0, end_next = 0;
+  auto fetch = [&](int s) {
+    st_next = end_next = 0;
+    if (s < a.S && lane < nst && !culled) {
+      const int b = s * g.n_bins + my_cell;
+      st_next = a.bin_start[b];
+      end_next = a.bin_start[b + 1];
+    }
+  };
+  fetch(0);
   for (int s = 0; s < a.S; ++s) {
     if (lane == 0) {
       a.rad_off[(int64_t)i * (a.S + 1) + s] = nr;
       a.ang_off[(int64_t)i * (a.S + 1) + s] = na;
     }
-    // candidate ranges of this species, one stencil cell per lane, and their prefix sums
-    int st = 0, cnt = 0;
-    if (lane < nst && !culled) {
-      const int b = s * g.n_bins + my_cell;
-      st = a.bin_start[b];
-      cnt = a.bin_start[b + 1] - st;
-    }
-    int inc = cnt;
-#pragma unroll
-    for (int off = 1; off < 32; off <<= 1) {
-      const int u = __shfl_up(inc, off, 64);
-      if (lane >= off) inc += u;
-    }
-    const int total = __builtin_amdgcn_readfirstlane(__shfl(inc, nst - 1, 64));
+    const int st = st_next, cnt = end_next - st_next;
+    fetch(s + 1);
+    const int inc = wave_scan_dpp<false>(cnt);
+    const int total = __builtin_amdgcn_readlane(inc, 63);
     // one range (an open system): slots follow directly; short per-cell ranges
     // are flattened into LDS by their lanes; otherwise search the ranges
     const int st0 = __builtin_amdgcn_readfirstlane(st);

@@ -458,30 +458,6 @@ __global__ __launch_bounds__(256) void k_desc_fwd_rows(FwdArgs a, DescParams p, 
 // dead while the other is live).
 constexpr int kPoolPitch = 20;   // LDS row of one lane's 16 partial sums (16-byte aligned)
 
-// Inclusive prefix sum / maximum over the 64 lanes with DPP: row shifts
-// within each 16-lane row, then the row broadcasts of lanes 15 and 31.
-constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
-constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
-
-template <bool MAX>
-__device__ __forceinline__ int wave_scan_dpp(int v) {
-  // out-of-row sources read as the identity (0 for the sums; counts and
-  // packed owners here are never negative, so 0 also serves the maximum)
-#define NNP_SCAN_STEP(CTRL, RM)                                               \
-  {                                                                           \
-    const int t = __builtin_amdgcn_update_dpp(0, v, CTRL, RM, 0xF, true);     \
-    v = MAX ? max(v, t) : v + t;                                              \
-  }
-  NNP_SCAN_STEP(kDppRowShr1, 0xF)
-  NNP_SCAN_STEP(kDppRowShr2, 0xF)
-  NNP_SCAN_STEP(kDppRowShr4, 0xF)
-  NNP_SCAN_STEP(kDppRowShr8, 0xF)
-  NNP_SCAN_STEP(kDppRowBcast15, 0xA)
-  NNP_SCAN_STEP(kDppRowBcast31, 0xC)
-#undef NNP_SCAN_STEP
-  return v;
-}
-
 __device__ __forceinline__ int wave_total(int v) {
   return __builtin_amdgcn_readlane(wave_scan_dpp<false>(v), 63);
 }

@@ -43,6 +43,30 @@ constexpr int kDppHalfMirror = 0x141;
 constexpr int kDppXor2 = 0x4E;       // quad_perm(2, 3, 0, 1)
 constexpr int kDppXor1 = 0xB1;       // quad_perm(1, 0, 3, 2)
 
+// Inclusive prefix sum / maximum over the 64 lanes with DPP: row shifts
+// within each 16-lane row, then the row broadcasts of lanes 15 and 31.
+constexpr int kDppRowShr1 = 0x111, kDppRowShr2 = 0x112, kDppRowShr4 = 0x114, kDppRowShr8 = 0x118;
+constexpr int kDppRowBcast15 = 0x142, kDppRowBcast31 = 0x143;
+
+template <bool MAX>
+__device__ __forceinline__ int wave_scan_dpp(int v) {
+  // out-of-row sources read as the identity (0 for the sums; counts and
+  // packed owners here are never negative, so 0 also serves the maximum)
+#define NNP_SCAN_STEP(CTRL, RM)                                               \
+  {                                                                           \
+    const int t = __builtin_amdgcn_update_dpp(0, v, CTRL, RM, 0xF, true);     \
+    v = MAX ? max(v, t) : v + t;                                              \
+  }
+  NNP_SCAN_STEP(kDppRowShr1, 0xF)
+  NNP_SCAN_STEP(kDppRowShr2, 0xF)
+  NNP_SCAN_STEP(kDppRowShr4, 0xF)
+  NNP_SCAN_STEP(kDppRowShr8, 0xF)
+  NNP_SCAN_STEP(kDppRowBcast15, 0xA)
+  NNP_SCAN_STEP(kDppRowBcast31, 0xC)
+#undef NNP_SCAN_STEP
+  return v;
+}
+
 template <int CTRL>
 __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
