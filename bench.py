@@ -5,8 +5,8 @@ One step is one full energy + force evaluation through the C ABI
 (``nnp_compute``): cell list, neighbour lists, descriptors, per-species
 networks (forward + backward), FP64 energy sum, descriptor adjoint and FP64
 force gather.  The neighbour search reruns every step; inputs stay resident
-in device memory.  The timed steps use the library's production path (one
-HIP-graph replay per step); a second pass of the same length with per-stage
+in device memory.  The timed steps use the library's production path (direct
+launches, one HIP-graph replay for few atoms); a second pass of the same length with per-stage
 HIP events gives the kernel durations used for the roofline entry.
 
 Default workload: the largest configuration, a periodic water box of 87,000
@@ -119,7 +119,7 @@ def kernel_sources():
     for f in sorted(glob.glob(os.path.join(CSRC, "*.hip"))):
         src = code(f)
         dig = hashlib.sha256(src + common).hexdigest()[:16]
-        for m in re.finditer(rb"__global__\s+(?:__launch_bounds__\([^)]*\)\s+)?void\s+(k_\w+)\s*\(", src):
+        for m in re.finditer(rb"__global__\s+(?:__launch_bounds__\((?:[^()]|\([^()]*\))*\)\s+)?void\s+(k_\w+)\s*\(", src):
             out[m.group(1).decode()] = {"file": os.path.basename(f), "digest": dig}
     return out
 
@@ -273,7 +273,7 @@ def summarize_profiles(out_dir, workload):
         json.dump(doc, f, indent=1)
     lines = [f"# Kernel durations and HBM traffic: {WORKLOADS[workload]['desc']}", "",
              "rocprofv3 kernel-trace statistics (every dispatch of the run: autotuning candidates, the",
-             "FP32 and BF16 forms, graph replays and the event-timed pass) and per-dispatch HBM bytes",
+             "FP32 and BF16 forms, the production calls and the event-timed pass) and per-dispatch HBM bytes",
              "from FETCH_SIZE / WRITE_SIZE, scaled by what the same counters read for a plain",
              f"{CALIB_BYTES >> 20} MiB device copy (fetch x{calib['FETCH_SIZE']:.3f}, "
              f"write x{calib['WRITE_SIZE']:.3f}).", "", "Commands ($ROOT = repository root, $OUT = output folder):",
@@ -359,7 +359,7 @@ def build_inputs(name):
 
 
 def run_form(P, cfg, flat, inp, prec, steps, warmup, autotune=True):
-    """Time `steps` production calls (HIP-graph replay, preallocated outputs, topology
+    """Time `steps` production calls (the library's own launches, preallocated outputs, topology
     reused), then the same number of calls with per-stage HIP-event timing."""
     import numpy as np
     import torch
@@ -514,7 +514,7 @@ def roofline(res, cfg, prec, stage, workload, periodic):
     the committed rocprofv3 average of the same kernel beside it."""
     out = _roofline(res, cfg, prec, stage, workload, periodic)
     out["timing"] = ("HIP events on the call's stream around the stage's direct launches, averaged "
-                     "over the profiled pass (graph replay runs each kernel 1-3 us shorter)")
+                     "over the profiled pass (without the events each kernel runs 1-3 us shorter)")
     out["event_us"] = res["stage_ms"][stage] * 1e3
     k = profile_entry(workload, out.get("kernel"))
     if k is not None and k.get("avg_us"):

@@ -347,7 +347,7 @@ typedef enum {
  *     row per atom; 3 / 4 two / four atoms per wavefront (3: one while the
  *     system has at most eight atoms per CU), their radial segments and
  *     angular classes cut into equal chunks, one per lane (default: 3 for
- *     three and four elements and for small systems, 4 for large ones, 1 in
+ *     four elements and for small systems, 4 for large ones, 1 in
  *     between and in the BF16 form);
  *   network: 0 register-resident wavefronts; 1 / 2 / 3 row-split workgroups
  *     of 16 / 32 / 64 atoms (64 for water-sized networks only, in the FP32

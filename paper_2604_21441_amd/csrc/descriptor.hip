@@ -1301,9 +1301,8 @@ hipError_t launch_link_redistribute(nnp_model& m, const float* pos, double* forc
 // wavefront (3: with one while that still leaves lanes idle, see
 // launch_descriptor_fwd).
 //
-// The default.  With three or four elements a centre has many classes of few
-// pairs, which rows of lanes walk one after the other: the pool is faster at
-// every size (us, variant 1 -> 3): 60 atoms 21.0 -> 11.3, 1,000 atoms 33.8 ->
+// The default.  With four elements a centre has ten classes of few pairs, which rows of lanes walk one after the other: the pool is faster at every
+// size (us, variant 1 -> 3): 60 atoms 21.0 -> 11.3, 1,000 atoms 33.8 ->
 // 17, 25,000 atoms 104 -> 58.  With two elements the line is drawn by what
 // there is to hide latency with: up to 24 atoms per CU the pool's even split
 // is faster (192 atoms 14.7 -> 12.8, 5,400 atoms 21.5 -> 18.1), in between
