@@ -4,7 +4,7 @@
 //   E = sum_{i in ML} sum_{j in MM, r < rc} ke q_i q_j / r + 4 eps_ij ((s_ij/r)^12 - (s_ij/r)^6)
 // with Lorentz-Berthelot mixing s_ij = (s_i + s_j)/2, eps_ij = sqrt(eps_i eps_j).
 //
-// A workgroup takes 128 MM atoms, two per lane of each of its eight
+// A workgroup takes 128 MM atoms, two per lane of each of its 16
 // wavefronts, and the wavefronts share the ML atoms (staged in LDS) between
 // them.  Each pair is evaluated in FP32.  An MM atom's force and the energy
 // accumulate in FP64 registers and are summed over the wavefronts through
@@ -14,15 +14,17 @@
 // Bound by the chain of one wavefront through its ML atoms (a sphere around
 // the ML region holds few of the MM atoms' wavefronts, and these few meet
 // nearly every ML atom inside the cutoff) and by the atomics on the few lines
-// of ML forces.  60 x 30,000 atoms: one wavefront walking all ML atoms for 64
-// MM atoms 52 us; eight sharing them 19 us; with two MM atoms per lane, which
-// halves the sums over lanes and the atomics, 15 us (four: 16, eight: 21).
+// of ML forces, hence every workgroup begins at another ML atom.  60 x 30,000
+// atoms: one wavefront walking all ML atoms for 64 MM atoms 52 us; eight
+// sharing them 19; two MM atoms per lane, which halves the sums over lanes and
+// the atomics, 15; the turned order 11.5; 16 wavefronts 9.7 (one MM atom per
+// lane 13.6, four 14.6).
 #include "nnp_internal.h"
 
 namespace nnp {
 namespace {
 
-constexpr int kMeWaves = 8;
+constexpr int kMeWaves = 16;
 constexpr int kMeBlock = 64 * kMeWaves;
 constexpr int kMeTiles = 2;     // 64 MM atoms each
 constexpr int kMeChunk = 256;   // ML atoms per LDS chunk
@@ -86,7 +88,9 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
       sp[t] = make_float2(ml_par[3 * (int64_t)i + 1], ml_par[3 * (int64_t)i + 2]);
     }
     __syncthreads();
-    for (int t = wave; t < nc; t += kMeWaves) {
+    const int turn = (int)((blockIdx.x * 29u) % (unsigned)nc);
+    for (int k = wave; k < nc; k += kMeWaves) {
+      const int t = k + turn < nc ? k + turn : k + turn - nc;
       const float4 xi = sx[t];
       const float2 pi = sp[t];
       float ax = 0.f, ay = 0.f, az = 0.f;

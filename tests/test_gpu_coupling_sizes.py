@@ -1,4 +1,4 @@
-"""The mechanical-embedding coupling at the edges of its split: ML atoms shared by eight
+"""The mechanical-embedding coupling at the edges of its split: ML atoms shared by 16
 wavefronts and staged 256 at a time, MM atoms 128 to a workgroup in two tiles of 64."""
 import numpy as np
 import pytest
@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 # FP32 pair terms summed in FP64 over a wavefront's partial sums in FP32: 1e-6 of the summed
 # magnitudes for the energy, 1e-5 (rms) for the forces, as for the 60 x 30,000 workload
-@pytest.mark.parametrize("n_ml,n_mm,periodic", [(1, 1, False), (7, 63, False), (8, 64, True), (9, 65, False), (3, 127, False), (10, 129, True),
+@pytest.mark.parametrize("n_ml,n_mm,periodic", [(1, 1, False), (7, 63, False), (16, 64, True), (17, 65, False), (3, 127, False), (10, 129, True),
                                                 (256, 130, True), (257, 1000, False), (0, 5, False), (5, 0, False)])
 def test_sizes(n_ml, n_mm, periodic):
     import paper_2604_21441_amd as P
