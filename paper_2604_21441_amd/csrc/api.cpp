@@ -1,5 +1,6 @@
 // C ABI entry points: model lifecycle, argument validation, the topology
 // cache, and the per-call sequence of stage launches on the caller's stream.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -89,7 +90,8 @@ size_t carve_workspace(const nnp_model& m, Workspace& w, char* base) {
   take(w.d_nbr_ang, n * w.max_ang);
   take(w.d_rad_off, n * (m.S + 1));
   take(w.d_ang_off, n * (m.S + 1));
-  take(w.d_contrib, n * w.max_rad);
+  // (rows of max_ang entries, or of max_rad after a list overflow: either may be the larger)
+  take(w.d_contrib, n * std::max(w.max_rad, w.max_ang));
   take(w.d_self, 3 * n);
   take(w.d_part, (size_t)w.max_part);
   take(w.d_x, n * m.stride);
