@@ -232,18 +232,28 @@ __device__ __forceinline__ float celu_f(float u, float alpha, float inv_alpha_l2
 __device__ __forceinline__ float celu_grad_from_h(float h, float inv_alpha) {
   return h > 0.f ? 1.f : h * inv_alpha + 1.f;
 }
-// The forms the split products use: h = med3(u, alpha t - alpha, 0) with
-// t = 2^(u log2(e) / alpha), since 0 < u < alpha (t - 1) for u > 0 and
-// u <= alpha (t - 1) <= 0 otherwise, and celu' = min(h / alpha + 1, 1).
+// The forms that the split products and the LDS-resident kernel use, with
+// t = 2^(u log2(e) / alpha): h = max(u, min(alpha t - alpha, 0)), since
+// alpha (t - 1) > 0 for u > 0 and u <= alpha (t - 1) <= 0 otherwise, and celu' =
+// min(h / alpha + 1, 1).  The outer maximum and the minimum are the ones that
+// keep a NaN (v_maximum3, v_minimum3): a med3 or an ordinary minimum would
+// take the other operand, and coincident atoms or a NaN weight end in a finite
+// energy.  (One instruction more per activation than the med3: 261,000 atoms
+// 1,108 -> 1,110 us for the whole call, 12,288 atoms 100.0 -> 100.3.)
+__device__ __forceinline__ float celu_exp(float u, float t, float alpha) {
+  return __builtin_elementwise_maximum(u, __builtin_fminf(fmaf(alpha, t, -alpha), 0.f));
+}
+__device__ __forceinline__ float celu_grad_lean(float h, float inv_alpha) {
+  return __builtin_elementwise_minimum(fmaf(h, inv_alpha, 1.f), 1.f);
+}
 template <int OP>
 __device__ __forceinline__ float celu_of(float u, float alpha, float inv_alpha_l2) {
-  if constexpr (OP == kOpSplit)
-    return __builtin_amdgcn_fmed3f(u, fmaf(alpha, __builtin_amdgcn_exp2f(u * inv_alpha_l2), -alpha), 0.f);
+  if constexpr (OP == kOpSplit) return celu_exp(u, __builtin_amdgcn_exp2f(u * inv_alpha_l2), alpha);
   return celu_f(u, alpha, inv_alpha_l2);
 }
 template <int OP>
 __device__ __forceinline__ float celu_grad_of(float h, float inv_alpha) {
-  if constexpr (OP == kOpSplit) return fminf(fmaf(h, inv_alpha, 1.f), 1.f);
+  if constexpr (OP == kOpSplit) return celu_grad_lean(h, inv_alpha);
   return celu_grad_from_h(h, inv_alpha);
 }
 
@@ -1037,24 +1047,12 @@ __device__ __forceinline__ void chunk_to_frags(int r0, const v4f (*acc)[C], v8bf
       }
 }
 
-// CELU in the form the kernel evaluates it: t = 2^(u log2(e) / alpha) and
-// h = med3(u, alpha t - alpha, 0), since 0 < u < alpha (t - 1) for u > 0 and
-// u <= alpha (t - 1) <= 0 for u <= 0 (near u = 0, where rounding can swap
-// the order of the first two, either is returned; they then differ by about
-// alpha 2^-23); its derivative is min(t, 1) (t > 1 exactly when u > 0), kept
+// The derivative of celu_exp is min(t, 1) (t > 1 exactly when u > 0), kept
 // for the backward pass as packed FP16 (rounded toward zero: relative error
 // below 2^-10).
-__device__ __forceinline__ float celu_med3(float u, float t, float alpha) {
-  return __builtin_amdgcn_fmed3f(u, fmaf(alpha, t, -alpha), 0.f);
-}
-// celu' from the activation h (the output layer's, in FP32): 1 for h > 0,
-// else h / alpha + 1 = min(h / alpha + 1, 1) (h / alpha + 1 > 1 exactly when
-// h > 0).
-__device__ __forceinline__ float celu_grad_lean(float h, float inv_alpha) {
-  return fminf(fmaf(h, inv_alpha, 1.f), 1.f);
-}
 __device__ __forceinline__ uint32_t celu_grad_pk(float t0, float t1) {
-  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(fminf(t0, 1.f), fminf(t1, 1.f)));
+  return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(__builtin_elementwise_minimum(t0, 1.f),
+                                                                __builtin_elementwise_minimum(t1, 1.f)));
 }
 // x times the FP16 value in the low (HI false) or high half of d, rounded
 // once.  It is written as fma(x, d, +0), which the compiler must keep as an
@@ -1233,7 +1231,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_mlp_lds(MlpArgs a, float alpha) 
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             t[r][c][u] = __builtin_amdgcn_exp2f(acc[r][c][u] * inv_alpha_l2);
-            acc[r][c][u] = celu_med3(acc[r][c][u], t[r][c][u], alpha);
+            acc[r][c][u] = celu_exp(acc[r][c][u], t[r][c][u], alpha);
           }
     };
     // celu'(u) o acc with the FP16 derivatives of the forward pass
@@ -1281,7 +1279,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_mlp_lds(MlpArgs a, float alpha) 
         for (int c = 0; c < C; ++c)
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            const float h = celu_med3(acc[r][c][u], __builtin_amdgcn_exp2f(acc[r][c][u] * inv_alpha_l2), alpha);
+            const float h = celu_exp(acc[r][c][u], __builtin_amdgcn_exp2f(acc[r][c][u] * inv_alpha_l2), alpha);
             ep[c] = fmaf(w4[u], h, ep[c]);
             acc[r][c][u] = w4[u] * celu_grad_lean(h, inv_alpha);
           }
