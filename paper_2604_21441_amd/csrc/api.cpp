@@ -93,6 +93,7 @@ size_t carve_workspace(const nnp_model& m, Workspace& w, char* base) {
   // (rows of max_ang entries, or of max_rad after a list overflow: either may be the larger)
   take(w.d_contrib, n * std::max(w.max_rad, w.max_ang));
   take(w.d_self, 3 * n);
+  take(w.d_cut, 1);
   take(w.d_part, (size_t)w.max_part);
   take(w.d_x, n * m.stride);
   take(w.d_g, n * m.stride);

@@ -77,9 +77,11 @@ __global__ __launch_bounds__(kBlock) void k_stage(const float* __restrict__ pos,
                                                   const int* __restrict__ sys, Geometry g, LinkArgs L,
                                                   int* __restrict__ key, int* __restrict__ rank,
                                                   float4* __restrict__ stg,
-                                                  int* __restrict__ bin_count, int* __restrict__ status) {
+                                                  int* __restrict__ bin_count, int* __restrict__ status,
+                                                  int* __restrict__ cut) {
   int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= n) return;
+  if (t == 0) *cut = 0;
   const float3 p = nnp_position(pos, idx[t], L, g);
   float x = p.x, y = p.y, z = p.z;
   if (g.periodic) stg[t] = make_float4(x, y, z, __int_as_float(sigma[t]));   // for the bin sort
@@ -418,13 +420,15 @@ __global__ __launch_bounds__(kScanThreads) void k_cells(const float* __restrict_
                                                         int* __restrict__ perm, float4* __restrict__ spos,
                                                         int* __restrict__ slot_atom, int* __restrict__ order,
                                                         int* __restrict__ sbin, int* __restrict__ islot,
-                                                        PairCount pc, int* __restrict__ status) {
+                                                        PairCount pc, int* __restrict__ status,
+                                                        int* __restrict__ cut) {
   __shared__ int wsum[2 * (kScanThreads / 64) + 1];
   __shared__ int hist[scan_lds_words<PER>()];   // counts per key, then species-major starts
   __shared__ int bmaj[scan_lds_words<PER>()];   // totals per bin, then bin-major starts
   __shared__ uint16_t tmp[U * kScanThreads];     // atoms of each key in arrival order
   const int nb = S * g.n_bins;                   // <= kScanThreads * PER <= 2^14 (checked by the launcher)
   const int tid = threadIdx.x;
+  if (blockIdx.x == 0 && tid == 0) *cut = 0;
 #pragma unroll
   for (int u = 0; u < PER; ++u) hist[scan_pad<PER>(u * kScanThreads + tid)] = 0;
   const int own = blockIdx.x * kScanThreads + tid;   // the atom this thread places
@@ -641,7 +645,13 @@ struct NeighArgs {
   int* ang_off;
   int max_rad, max_ang;
   int* status;
+  int* cut;                // set if a list of this call was cut off
 };
+
+__device__ __forceinline__ void list_overflow(const NeighArgs& a) {
+  atomicOr(a.status, kStatusCapacity);
+  *a.cut = 1;   // (any number of wavefronts, all the same value)
+}
 
 constexpr int kMaxStencil = 27;
 
@@ -815,7 +825,7 @@ __global__ __launch_bounds__(64) void k_neighbours(NeighArgs a, Geometry g) {
   if (lane == 0) {
     a.rad_off[(int64_t)i * (a.S + 1) + a.S] = nr;
     a.ang_off[(int64_t)i * (a.S + 1) + a.S] = na;
-    if (overflow) atomicOr(a.status, kStatusCapacity);
+    if (overflow) list_overflow(a);
   }
 }
 
@@ -1052,7 +1062,7 @@ __global__ __launch_bounds__(64) void k_neighbours_cell(NeighArgs a, Geometry g,
             ro[s] = nr;
             ao[s] = na;
           }
-        if (overflow && lane == 0) atomicOr(a.status, kStatusCapacity);
+        if (overflow && lane == 0) list_overflow(a);
       }
       // species offsets: lanes 0 .. S the radial ones, 16 .. 16 + S the angular ones
       const int t = lane & 15;
@@ -1241,7 +1251,7 @@ __global__ __launch_bounds__(64) void k_pairs_lists(NeighArgs a, Geometry g, Pai
     a.rad_off[(int64_t)i * (a.S + 1) + lane] = r;
     a.ang_off[(int64_t)i * (a.S + 1) + lane] = q;
   }
-  if (lane == 0 && overflow) atomicOr(a.status, kStatusCapacity);
+  if (lane == 0 && overflow) list_overflow(a);
   if (lane == 0 && dup) atomicOr(a.status, kStatusInput);
 }
 
@@ -1276,7 +1286,7 @@ void launch_cells_small(nnp_model& m, const float* pos, int n, const LinkArgs& L
                         hipStream_t st) {
   hipLaunchKernelGGL((k_cells<PER, U>), dim3(blocks_for(n, kScanThreads)), dim3(kScanThreads), 0, st, pos, n,
                      m.d_idx, m.d_sigma, m.geo, L, m.S, m.d_key, m.d_bin_start, m.d_perm, m.d_spos, m.d_slot_atom,
-                     m.d_order, m.d_sbin, m.d_islot, pc, m.d_status);
+                     m.d_order, m.d_sbin, m.d_islot, pc, m.d_status, m.d_cut);
 }
 
 template <int U>
@@ -1312,7 +1322,8 @@ hipError_t launch_cells(nnp_model& m, const float* pos, int n, bool pair_list, h
   }
   if (n > 0) {
     hipLaunchKernelGGL(k_stage, dim3(blocks_for(n, kBlock)), dim3(kBlock), 0, st, pos, n, m.d_idx,
-                       m.d_sigma, m.d_sys, g, L, m.d_key, m.d_rank, m.d_stg, m.d_bin_count, m.d_status);
+                       m.d_sigma, m.d_sys, g, L, m.d_key, m.d_rank, m.d_stg, m.d_bin_count, m.d_status,
+                       m.d_cut);
   }
   const bool fused = n > 0 && g.periodic && nb <= kScanChunk;
   const int per = scan_entries_per_thread(nb);
@@ -1385,6 +1396,7 @@ hipError_t launch_neighbours(nnp_model& m, int n, hipStream_t st) {
   a.max_rad = m.max_rad;
   a.max_ang = m.max_ang;
   a.status = m.d_status;
+  a.cut = m.d_cut;
   const int v = neighbour_variant(m, n);
   if (v >= 1) {
     // K wavefronts share a cell
@@ -1438,6 +1450,7 @@ hipError_t launch_pair_lists(nnp_model& m, int n, int n_atoms, int n_pairs, cons
   a.max_rad = m.max_rad;
   a.max_ang = m.max_ang;
   a.status = m.d_status;
+  a.cut = m.d_cut;
   hipLaunchKernelGGL(k_pairs_lists, dim3(n), dim3(64), 0, st, a, m.geo, pc);
   return hipGetLastError();
 }

@@ -767,11 +767,12 @@ __global__ __launch_bounds__(256) void k_desc_fwd_pool(FwdArgs a, DescParams p, 
 //   3. evaluates the angular triplets (adj_triplets);
 //   4. finds the places in the neighbours' lists, two lanes per neighbour.
 //
-// After a list has overflowed its capacity (the device status says so) lists
-// are cut off and no longer symmetric.  The wavefront then looks every place
-// up in the radial lists (contrib rows follow those), leaves out dE_j/dG for
-// a neighbour whose list does not hold the centre, and hands over through the
-// radial entries.
+// After a list of this call has overflowed its capacity (d_cut says so, for the
+// adjoint and the gather alike; the status word outlives the call and can be
+// cleared at any time) lists are cut off and no longer symmetric.  The
+// wavefront then looks every place up in the radial lists (contrib rows follow
+// those), leaves out dE_j/dG for a neighbour whose list does not hold the
+// centre, and hands over through the radial entries.
 //
 // Bound by VALU issue: 927 VALU instructions per wavefront in the water box
 // of 98,304 atoms, of which the triplet loop is 515 (210 per pass of 64), fill
@@ -793,7 +794,7 @@ struct BwdArgs {
   float rca2;              // the angular predicate of the neighbour search
   const float* g;
   const float4* shifts;    // the 16 scaled radial shifts
-  const int* status;
+  const int* cut;
   float3* contrib;   // [n][max_ang]; [n][max_rad] after an overflow
   double* self;      // [n][3]
 };
@@ -963,7 +964,7 @@ __global__ __launch_bounds__(64, 7) void k_desc_adj(BwdArgs a, DescParams p, Geo
   float* gl = reinterpret_cast<float*>(reinterpret_cast<char*>(sx) + adj_slots_bytes(a.max_ang));   // dE/dx row
   uint2* ex = reinterpret_cast<uint2*>(gl + p.stride);
   const int i = a.order[xcd_block(blockIdx.x, gridDim.x)];
-  const bool full = (*a.status & kStatusCapacity) != 0;
+  const bool full = *a.cut != 0;
   const float4 pi = a.spos[i];
   const int si = __float_as_int(pi.w);
   const MinImage mi = min_image_at(geo, i);
@@ -1199,6 +1200,7 @@ __global__ __launch_bounds__(kBlock) void k_force_gather(const float3* __restric
                                                          const double* __restrict__ self,
                                                          const int* __restrict__ rad_off,
                                                          const int* __restrict__ ang_off,
+                                                         const int* __restrict__ cut,
                                                          const int* __restrict__ slot_atom, int n, int S,
                                                          int max_rad, int max_ang, double* __restrict__ forces,
                                                          double* __restrict__ link_forces, int assign,
@@ -1216,7 +1218,7 @@ __global__ __launch_bounds__(kBlock) void k_force_gather(const float3* __restric
   const int sub = gid & 15;
   double fx = 0.0, fy = 0.0, fz = 0.0;
   if (i < n) {
-    const bool full = (*ea.status & kStatusCapacity) != 0;
+    const bool full = *cut != 0;
     const int cnt = (full ? rad_off : ang_off)[(int64_t)i * (S + 1) + S];
     const float3* row = contrib + (int64_t)i * (full ? max_rad : max_ang);   // 16 lanes read 192 contiguous bytes
     for (int t = sub; t < cnt; t += 16) {
@@ -1383,7 +1385,7 @@ hipError_t launch_descriptor_bwd(nnp_model& m, int n, hipStream_t st) {
   a.rca2 = m.dp.rc_ang * m.dp.rc_ang;
   a.g = m.d_g;
   a.shifts = reinterpret_cast<const float4*>(m.d_shifts);
-  a.status = m.d_status;
+  a.cut = m.d_cut;
   a.contrib = m.d_contrib;
   a.self = m.d_self;
   // one wavefront per workgroup: several, sharing nothing, measured slower
@@ -1416,8 +1418,8 @@ hipError_t launch_force_gather(nnp_model& m, int n, int n_mm, double* forces, in
   const int gather_blocks = (int)((16 * (int64_t)n + kBlock - 1) / kBlock);
   const int energy_blocks = single ? 1 : n_sys;
   hipLaunchKernelGGL(k_force_gather, dim3((unsigned)(gather_blocks + energy_blocks)), dim3(kBlock), 0, st,
-                     m.d_contrib, m.d_self, m.d_rad_off, m.d_ang_off, m.d_slot_atom, n, m.S, m.max_rad, m.max_ang, forces,
-                     m.d_link_F, assign, gather_blocks, ea, m.d_mm_part,
+                     m.d_contrib, m.d_self, m.d_rad_off, m.d_ang_off, m.d_cut, m.d_slot_atom, n, m.S, m.max_rad,
+                     m.max_ang, forces, m.d_link_F, assign, gather_blocks, ea, m.d_mm_part,
                      m.extra && n_mm > 0 ? mm_partial_blocks(n_mm) : 0);
   return hipGetLastError();
 }

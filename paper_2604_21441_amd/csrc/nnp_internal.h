@@ -300,6 +300,7 @@ struct Workspace {
   int* d_ang_off = nullptr;
   float3* d_contrib = nullptr; // force on atom i from the centre at its angular slot, [n][max_ang]; after
                                // a list overflow at its radial slot, [n][max_rad] (sized for the longer rows)
+  int* d_cut = nullptr;        // 1 if a list of the current call was cut off at its capacity
   double* d_self = nullptr;    // [n][3] force on each atom from its own environment
   double* d_part = nullptr;    // per-wavefront FP64 energy partials
   int max_part = 0;
