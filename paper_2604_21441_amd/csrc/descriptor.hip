@@ -984,7 +984,7 @@ __global__ __launch_bounds__(64, 7) void k_desc_adj(BwdArgs a, DescParams p, Geo
   }
 
   // 1., 2. geometry and radial pairs, 64 neighbours at a time
-  float fx = 0.f, fy = 0.f, fz = 0.f;   // this lane's share of the centre's radial total
+  double fx = 0.0, fy = 0.0, fz = 0.0;   // this lane's share of the centre's radial total (FP32 terms)
   int na_seen = 0;
   for (int c0 = 0; c0 < nr; c0 += 64) {
     const int cnt = min(64, nr - c0);
@@ -1049,9 +1049,9 @@ __global__ __launch_bounds__(64, 7) void k_desc_adj(BwdArgs a, DescParams p, Geo
       const float arg = r * p.inv2rc;
       const float fc = fmaf(0.5f, cos_rev(arg), 0.5f);
       const float w = fmaf(p.dfc_r * sin_rev(arg), s0, p.c1_rad * fc * s1) * ir;
-      fx = fmaf(w, dx, fx);
-      fy = fmaf(w, dy, fy);
-      fz = fmaf(w, dz, fz);
+      fx += (double)(w * dx);
+      fy += (double)(w * dy);
+      fz += (double)(w * dz);
     }
     wave_sync();
   }

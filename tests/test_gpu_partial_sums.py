@@ -1,0 +1,53 @@
+"""Sums that the kernels take in parts, on inputs whose terms cancel exactly, so that a part summed
+with fewer bits than the whole shows."""
+import numpy as np
+import pytest
+import torch
+
+import synthetic as sy
+
+pytestmark = pytest.mark.gpu
+
+
+def mirrored(n, lo, hi, rng):
+    """n random points in a shell and their mirror images, shuffled, each exact in FP32."""
+    d = rng.normal(size=(n, 3))
+    d = (d / np.linalg.norm(d, axis=1, keepdims=True) * rng.uniform(lo, hi, (n, 1))).astype(np.float32)
+    return d
+
+
+@pytest.mark.parametrize("n", [40, 90, 200])
+def test_radial_force_on_a_centre_of_symmetry(n):
+    """Networks in their linear range (large biases) with no angular weights: dE/dG is one row per
+    species, every pair's term has an exact opposite, and the centre's force is zero but for the
+    FP64 sums' rounding; a lane that summed its pairs in FP32 would leave about 1e-8 of the terms."""
+    import paper_2604_21441_amd as P
+    cfg = sy.model_config("water")
+    w = sy.model_weights(cfg, seed=1)
+    for s, layers in enumerate(w[0]):
+        for l, (W, b) in enumerate(layers):
+            W, b = W.copy(), b.copy()
+            if l == 0:
+                W[:, 32:] = 0
+            if l < 3:
+                b += 1e4
+                W[:] = np.abs(W) if l else W
+            layers[l] = (W, b)
+    rng = np.random.default_rng(n)
+    d = mirrored(n, 3.6, 5.1, rng)
+    both = np.concatenate([d, -d])
+    Z = np.tile(rng.choice(np.array([1, 8], np.int32), n), 2)
+    at = rng.permutation(2 * n)
+    pos = np.concatenate([np.zeros((1, 3), np.float32), both[at]])
+    Z = np.concatenate([[8], Z[at]]).astype(np.int32)
+    m = P.NNPModel(cfg, weights=sy.flat_weights(w))
+    m.reserve(len(Z), max_rad_nbr=512, max_ang_nbr=256)
+    E, F, _ = m.compute(torch.from_numpy(pos).cuda(), Z)
+    torch.cuda.synchronize()
+    assert m.status() == 0
+    F = F.cpu().numpy()
+    cnt = m.read(P._lib.NNP_BUF_NBR_COUNT)[m.read(P._lib.NNP_BUF_PERM) == 0][0]
+    assert cnt[0] == 2 * n and cnt[1] == 0
+    # 2 n terms, none above the largest force, each sum within 2^-53 of its magnitude per addition
+    assert np.abs(F[0]).max() < 1e-12 * np.abs(F).max(), (np.abs(F[0]).max(), np.abs(F).max())
+    m.close()
