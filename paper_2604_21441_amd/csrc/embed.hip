@@ -8,8 +8,9 @@
 // wavefronts, and the wavefronts share the ML atoms (staged in LDS) between
 // them.  Each pair is evaluated in FP32.  An MM atom's force and the energy
 // accumulate in FP64 registers and are summed over the wavefronts through
-// LDS, in order; an ML atom's force is summed over the wavefront's lanes and
-// added with FP64 atomics (skipped when no lane is inside the cutoff).
+// LDS, in order; an ML atom's force is summed over the lanes in FP32, the 64 MM
+// atoms of each tile by themselves, and added with FP64 atomics (skipped when
+// no lane is inside the cutoff).
 //
 // Bound by the chain of one wavefront through its ML atoms (a sphere around
 // the ML region holds few of the MM atoms' wavefronts, and these few meet
@@ -18,7 +19,9 @@
 // atoms: one wavefront walking all ML atoms for 64 MM atoms 52 us; eight
 // sharing them 19; two MM atoms per lane, which halves the sums over lanes and
 // the atomics, 15; the turned order 11.5; 16 wavefronts 9.7 (one MM atom per
-// lane 13.6, four 14.6).
+// lane 13.6, four 14.6).  That was with the two tiles added lane by lane before
+// the sum, an FP32 addition more: apart they take 11.2 us against 10.4 (the
+// call 15.9 both, bound by the caller).
 #include "nnp_internal.h"
 
 namespace nnp {
@@ -93,8 +96,8 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
       const int t = k + turn < nc ? k + turn : k + turn - nc;
       const float4 xi = sx[t];
       const float2 pi = sp[t];
-      float ax = 0.f, ay = 0.f, az = 0.f;
-      bool any = false;
+      float a[kMeTiles][3] = {};   // on this ML atom, each tile summed by itself
+      bool in[kMeTiles] = {};
 #pragma unroll
       for (int u = 0; u < kMeTiles; ++u) {
         float dx = y[u].x - xi.x, dy = y[u].y - xi.y, dz = y[u].z - xi.z;
@@ -105,7 +108,7 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
         }
         const float r2 = dx * dx + dy * dy + dz * dz;
         if (j0 + 64 * u < n_mm && r2 < rc2) {
-          any = true;
+          in[u] = true;
           const float ir2 = 1.f / r2;
           const float ir = sqrtf(ir2);
           const float qq = ke * xi.w * y[u].w;
@@ -117,22 +120,26 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
           const float ec = qq * ir;
           eacc += (double)ec + (double)(4.f * eps * (s12 - s6));
           const float w = (ec + eps * (48.f * s12 - 24.f * s6)) * ir2;   // -dE/dr / r
-          const float vx = w * dx, vy = w * dy, vz = w * dz;
-          ax += vx;
-          ay += vy;
-          az += vz;
-          f[u][0] += vx;
-          f[u][1] += vy;
-          f[u][2] += vz;
+          a[u][0] = w * dx;
+          a[u][1] = w * dy;
+          a[u][2] = w * dz;
+#pragma unroll
+          for (int c = 0; c < 3; ++c) f[u][c] += a[u][c];
         }
       }
-      if (__builtin_amdgcn_ballot_w64(any) == 0) continue;
-      const float rx = wsum63(ax), ry = wsum63(ay), rz = wsum63(az);
+      uint64_t any = 0;
+#pragma unroll
+      for (int u = 0; u < kMeTiles; ++u) any |= __builtin_amdgcn_ballot_w64(in[u]);
+      if (any == 0) continue;
+      double r[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+      for (int u = 0; u < kMeTiles; ++u)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) r[c] += (double)wsum63(a[u][c]);
       if (lane == 63) {
         double* o = ml_f + 3 * (int64_t)(c0 + t);
-        unsafeAtomicAdd(o + 0, -(double)rx);
-        unsafeAtomicAdd(o + 1, -(double)ry);
-        unsafeAtomicAdd(o + 2, -(double)rz);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) unsafeAtomicAdd(o + c, -r[c]);
       }
     }
   }

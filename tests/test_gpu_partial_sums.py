@@ -51,3 +51,28 @@ def test_radial_force_on_a_centre_of_symmetry(n):
     # 2 n terms, none above the largest force, each sum within 2^-53 of its magnitude per addition
     assert np.abs(F[0]).max() < 1e-12 * np.abs(F).max(), (np.abs(F[0]).max(), np.abs(F).max())
     m.close()
+
+
+@pytest.mark.parametrize("n_ml", [1, 20])
+def test_coupling_tiles_apart(n_ml):
+    """64 MM atoms whose strong forces on an ML atom cancel in neighbouring lanes, and 64 weak ones:
+    the weak sum keeps its FP32 accuracy (1e-5 of the force) only if the two are not added lane by
+    lane before they are summed."""
+    import oracle as orc
+    import paper_2604_21441_amd as P
+    rng = np.random.default_rng(2)
+    near = mirrored(32, 2.5, 4.0, rng)
+    far = mirrored(64, 7.0, 9.0, rng)
+    mm = np.concatenate([np.stack([near, -near], 1).reshape(-1, 3), far])
+    q = np.concatenate([np.full(64, 1000.0), rng.uniform(1e-4, 2e-4, 64)]).astype(np.float32)
+    mm_par = np.stack([q, np.full(128, 3.0), np.zeros(128)], 1).astype(np.float32)
+    ml = np.zeros((n_ml, 3), np.float32)
+    ml[1:, 0] = 300.0 + 5.0 * np.arange(n_ml - 1)   # the others beyond the cutoff
+    par = np.tile(np.array([[1.0, 3.0, 0.0]], np.float32), (n_ml, 1))
+    t = lambda a: torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    E, Fml, Fmm = P.nnp_me_coupling(t(ml), t(par), t(mm), t(mm_par), cutoff=12.0, ke=sy.KE_COULOMB)
+    torch.cuda.synchronize()
+    _, ref, _ = orc.me_coupling(ml[:1], par[:1], mm, mm_par, sy.KE_COULOMB, cutoff=12.0)
+    F = Fml.cpu().numpy()
+    assert np.linalg.norm(F[0] - ref[0]) < 1e-5 * np.linalg.norm(ref[0]), (F[0], ref[0])
+    assert not F[1:].any()
