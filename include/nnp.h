@@ -138,7 +138,8 @@ nnp_status nnp_create(const nnp_config* cfg, uint64_t seed, const float* weights
  * max_ang_nbr (within rc_ang); 0 selects the defaults 128 and 64.  For a
  * model with extra_inputs, max_mm also sizes the MM channel's per-workgroup
  * partial sums: 12 bytes per atom for every 256 charges, at most 512 such
- * groups (6 KiB per atom).  May be called again to grow or shrink;
+ * groups (6 KiB per atom); small reservations up to four times that, while it
+ * is no more than 1,536 bytes per CU.  May be called again to grow or shrink;
  * synchronises the device.  All device allocation of the model happens here
  * and in nnp_create.
  */

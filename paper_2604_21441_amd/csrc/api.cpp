@@ -99,7 +99,7 @@ size_t carve_workspace(const nnp_model& m, Workspace& w, char* base) {
   take(w.d_g, n * m.stride);
   take(w.d_e, n);
   w.d_mm_part = nullptr;
-  if (m.extra && w.max_mm > 0) take(w.d_mm_part, mm_partial_floats(w.max_atoms, w.max_mm));
+  if (m.extra && w.max_mm > 0) take(w.d_mm_part, mm_partial_floats(m, w.max_atoms, w.max_mm));
   w.d_q = nullptr;
   if (m.charges) take(w.d_q, n);
   take(w.d_sys_box, 2 * (size_t)w.max_sys);

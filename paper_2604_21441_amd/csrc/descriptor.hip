@@ -1420,7 +1420,7 @@ hipError_t launch_force_gather(nnp_model& m, int n, int n_mm, double* forces, in
   hipLaunchKernelGGL(k_force_gather, dim3((unsigned)(gather_blocks + energy_blocks)), dim3(kBlock), 0, st,
                      m.d_contrib, m.d_self, m.d_rad_off, m.d_ang_off, m.d_cut, m.d_slot_atom, n, m.S, m.max_rad,
                      m.max_ang, forces, m.d_link_F, assign, gather_blocks, ea, m.d_mm_part,
-                     m.extra && n_mm > 0 ? mm_partial_blocks(n_mm) : 0);
+                     m.extra && n_mm > 0 ? mm_partial_blocks(m, n, n_mm) : 0);
   return hipGetLastError();
 }
 

@@ -27,6 +27,7 @@ constexpr int kNnpChunk = 16;       // NNP atoms per workgroup row (= lanes of a
 constexpr int kMaxMmBlocks = 512;   // workgroups along the MM atoms
 constexpr int kBwdChunk = 8;        // NNP atoms per adjoint wavefront
 constexpr int kBwdWaves = 16;       // most wavefronts of an adjoint workgroup
+constexpr int kBwdTiles = kBlock / 64;   // MM atoms per lane of the adjoint, or one
 
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
@@ -131,15 +132,20 @@ __global__ __launch_bounds__(kBlock) void k_mm_finish(const float* __restrict__ 
 // the opposite of its column sum, as per-workgroup partials
 // part[(3 i + k) * gridDim.x + blockIdx.x].
 //
-// The wavefronts of a workgroup take 8 NNP atoms each, of the same 64 MM
-// atoms, whose forces they add up through LDS: with one grid row the workgroup
-// owns them and writes or adds them plainly; grid rows (few MM atoms and many
-// NNP atoms) add with FP64 atomics.  Bound by the chain of pairs of the few
-// wavefronts inside the cutoff, hence 8 atoms each: 60 NNP atoms, 30,000
-// charges 7.4 us (16 atoms and two MM atoms per lane: 11.8), and the partials
-// 1.5 in the gather.  Workgroups of 16 NNP atoms that added to cleared MM
-// forces with atomics, and a launch for the partials, took 10.5 + 4.1 us and
-// the clearing 2.1.
+// A lane holds T MM atoms. The wavefronts of a workgroup take 8 NNP atoms each,
+// of the same 64 T MM atoms, row after row of the grid; the MM forces of all
+// rows are added up in registers, then through LDS: with one grid row the
+// workgroup owns them and writes or adds them plainly; grid rows add with FP64
+// atomics.  Few NNP atoms: bound by the chain of pairs of the few wavefronts
+// inside the cutoff, hence 8 atoms each and T = 1: 60 NNP atoms, 30,000 charges
+// 7.4 us (16 atoms and two MM atoms per lane: 11.8), and the partials 1.5 in
+// the gather.  Workgroups of 16 NNP atoms that added to cleared MM forces with
+// atomics, and a launch for the partials, took 10.5 + 4.1 us and the clearing
+// 2.1.  Many: bound by the pairs and the sums over lanes after each 8 T of a
+// lane, hence T = 4 (mm_tiles), 30,000 charges, event-timed: 1,000 NNP atoms 43
+// us and 4,000 101 (T = 1, the forces exchanged after every row, 81 and 322; a
+// workgroup per 256 MM atoms and 16 NNP atoms, with atomics, 55 and 178).
+template <int T>
 __global__ __launch_bounds__(64 * kBwdWaves) void k_mm_bwd(const float4* __restrict__ spos, int n,
                                                            const float* __restrict__ mm_pos,
                                                            const float* __restrict__ mm_q, int n_mm,
@@ -154,75 +160,77 @@ __global__ __launch_bounds__(64 * kBwdWaves) void k_mm_bwd(const float4* __restr
   const float rm2 = p.mm_cutoff * p.mm_cutoff;
   const float inv2rm = 0.5f / p.mm_cutoff;
   const float dfc_s = -0.5f * 3.14159265358979323846f / p.mm_cutoff;
-  for (int r0 = blockIdx.y * rows; r0 < n; r0 += gridDim.y * rows) {
-    const int i0 = r0 + kBwdChunk * wave, cnt = min(n - i0, kBwdChunk);   // (cnt <= 0: only the forces' sums)
-    float ax[kBwdChunk], ay[kBwdChunk], az[kBwdChunk], ke_g[kBwdChunk];
+  for (int64_t j0 = (int64_t)blockIdx.x * (64 * T); j0 < n_mm; j0 += (int64_t)gridDim.x * (64 * T)) {
+    float4 y[T];   // MM x, y, z, q
+    double f[T][3];
 #pragma unroll
-    for (int c = 0; c < kBwdChunk; ++c) {
-      ax[c] = ay[c] = az[c] = 0.f;
-      ke_g[c] = 0.f;
-      if (c < cnt) {
+    for (int u = 0; u < T; ++u) {
+      const int64_t j = min(j0 + 64 * u + lane, (int64_t)n_mm - 1);
+      y[u] = make_float4(mm_pos[3 * j], mm_pos[3 * j + 1], mm_pos[3 * j + 2], mm_q[j]);
+      f[u][0] = f[u][1] = f[u][2] = 0.0;
+    }
+    for (int r0 = blockIdx.y * rows; r0 < n; r0 += gridDim.y * rows) {
+      const int i0 = r0 + kBwdChunk * wave, cnt = min(n - i0, kBwdChunk);
+      if (cnt <= 0) break;
+      float ax[kBwdChunk], ay[kBwdChunk], az[kBwdChunk];
+#pragma unroll
+      for (int c = 0; c < kBwdChunk; ++c) {
+        ax[c] = ay[c] = az[c] = 0.f;
+        if (c >= cnt) continue;
         const int i = i0 + c;
         float gi = gx[(int64_t)i * p.stride + p.D];
         if (qpred != nullptr) gi += qpred[i];
-        ke_g[c] = (float)p.ke * gi;
-      }
-    }
-    for (int64_t j0 = (int64_t)blockIdx.x * 64; j0 < n_mm; j0 += (int64_t)gridDim.x * 64) {
-      {
-        const int64_t j = j0 + lane;
-        double fx = 0.0, fy = 0.0, fz = 0.0;
-        if (j < n_mm) {
-          const float yx = mm_pos[3 * j], yy = mm_pos[3 * j + 1], yz = mm_pos[3 * j + 2];
-          const float q = mm_q[j];
+        const float ke_g = (float)p.ke * gi;
+        const float4 pi = spos[i];
 #pragma unroll
-          for (int c = 0; c < kBwdChunk; ++c) {
-            if (c < cnt) {
-              const float4 pi = spos[i0 + c];
-              float dx, dy, dz, r2;
-              mm_disp(pi, yx, yy, yz, g, dx, dy, dz, r2);
-              if (r2 < rm2) {
-                float ir = __builtin_amdgcn_rsqf(r2);
-                float r = r2 * ir;
-                float arg = r * inv2rm;
-                float fc = 0.5f * __builtin_amdgcn_cosf(arg) + 0.5f;
-                float dfc = dfc_s * __builtin_amdgcn_sinf(arg);
-                float fp = (dfc - fc * ir) * ir;            // d/dr (fc / r)
-                float w = ke_g[c] * q * fp * ir;   // times u = d / r
-                const float vx = w * dx, vy = w * dy, vz = w * dz;
-                ax[c] += vx; ay[c] += vy; az[c] += vz;
-                fx -= vx; fy -= vy; fz -= vz;
-              }
-            }
+        for (int u = 0; u < T; ++u) {
+          float dx, dy, dz, r2;
+          mm_disp(pi, y[u].x, y[u].y, y[u].z, g, dx, dy, dz, r2);
+          if (j0 + 64 * u + lane < n_mm && r2 < rm2) {
+            float ir = __builtin_amdgcn_rsqf(r2);
+            float r = r2 * ir;
+            float arg = r * inv2rm;
+            float fc = 0.5f * __builtin_amdgcn_cosf(arg) + 0.5f;
+            float dfc = dfc_s * __builtin_amdgcn_sinf(arg);
+            float fp = (dfc - fc * ir) * ir;            // d/dr (fc / r)
+            float w = ke_g * y[u].w * fp * ir;   // times u = d / r
+            const float vx = w * dx, vy = w * dy, vz = w * dz;
+            ax[c] += vx; ay[c] += vy; az[c] += vz;
+            f[u][0] -= vx; f[u][1] -= vy; f[u][2] -= vz;
           }
         }
-        sf[wave][0][lane] = fx;
-        sf[wave][1][lane] = fy;
-        sf[wave][2][lane] = fz;
       }
-      if (mm_forces == nullptr) continue;
+      const float s[3] = {wave_sum8(ax, lane), wave_sum8(ay, lane), wave_sum8(az, lane)};
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+        if (lane < cnt) {
+          float* o = part + ((int64_t)(i0 + lane) * 3 + k) * gridDim.x + blockIdx.x;
+          *o = j0 < (int64_t)gridDim.x * (64 * T) ? s[k] : *o + s[k];
+        }
+    }
+    if (mm_forces == nullptr) continue;
+    const int used = min(waves, (n - (int)blockIdx.y * rows + kBwdChunk - 1) / kBwdChunk);
+#pragma unroll
+    for (int u = 0; u < T; ++u) {
+#pragma unroll
+      for (int k = 0; k < 3; ++k) sf[wave][k][lane] = f[u][k];
       __syncthreads();
-      const int used = min(waves, (n - r0 + kBwdChunk - 1) / kBwdChunk);
       for (int t = threadIdx.x; t < 3 * 64; t += blockDim.x) {
         const int c = t / 3, k = t - 3 * c;
-        if (j0 + c >= n_mm) continue;
+        if (j0 + 64 * u + c >= n_mm) continue;
         double v = 0.0;
         for (int w = 0; w < used; ++w) v += sf[w][k][c];
-        double* f = mm_forces + 3 * j0 + t;
+        double* o = mm_forces + 3 * (j0 + 64 * u) + t;
         if (gridDim.y > 1) {
-          if (v != 0.0) unsafeAtomicAdd(f, v);
-        } else if (assign && r0 == 0) {
-          *f = v;
+          if (v != 0.0) unsafeAtomicAdd(o, v);
+        } else if (assign) {
+          *o = v;
         } else if (v != 0.0) {
-          *f += v;
+          *o += v;
         }
       }
       __syncthreads();
     }
-    const float s[3] = {wave_sum8(ax, lane), wave_sum8(ay, lane), wave_sum8(az, lane)};
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-      if (lane < cnt) part[((int64_t)(i0 + lane) * 3 + k) * gridDim.x + blockIdx.x] = s[k];
   }
 }
 
@@ -231,17 +239,31 @@ inline int mm_blocks(int n_mm) {
   return b < kMaxMmBlocks ? b : kMaxMmBlocks;
 }
 
+// MM atoms per lane of the adjoint: one, for as many wavefronts as there can
+// be, while pieces of 8 NNP and 64 MM atoms come to fewer than 16 per CU; four
+// from there on, a sum over lanes and an exchange through LDS then being shared
+// by 32 pairs instead of 8 (calls, us, one -> four: 60 NNP atoms and 30,000
+// charges 70.3 -> 71.1, 100 and 30,000 76.8 -> 74.7, 1,000 and 30,000 156 ->
+// 132, 500 and 3,000 84.4 -> 90.7).
+inline int mm_tiles(const nnp_model& m, int n, int n_mm) {
+  const int64_t rows = (n + kBwdChunk - 1) / kBwdChunk, groups = (n_mm + 63) / 64;
+  return groups <= kMaxMmBlocks && rows * groups <= 16 * (int64_t)m.n_cu ? 1 : kBwdTiles;
+}
+
 inline int wave_blocks(int n) { return (int)(((int64_t)n * 64 + kBlock - 1) / kBlock); }
 
 }  // namespace
 
-int mm_partial_blocks(int n_mm) {
-  const int b = (n_mm + 63) / 64;
-  return b < kMaxMmBlocks ? b : kMaxMmBlocks;
+int mm_partial_blocks(const nnp_model& m, int n, int n_mm) {
+  return mm_tiles(m, n, n_mm) == 1 ? (n_mm + 63) / 64 : mm_blocks(n_mm);
 }
 
-size_t mm_partial_floats(int max_atoms, int max_mm) {
-  return max_mm > 0 ? 3 * (size_t)max_atoms * (size_t)mm_partial_blocks(max_mm) : 0;
+// Three floats per partial: a partial per 256 MM atoms for every atom, or what
+// calls with one per 64 can use (mm_tiles).
+size_t mm_partial_floats(const nnp_model& m, int max_atoms, int max_mm) {
+  const size_t fine = std::min((size_t)max_atoms * std::min((max_mm + 63) / 64, kMaxMmBlocks),
+                               (size_t)kBwdChunk * 16 * m.n_cu);
+  return 3 * std::max(fine, (size_t)max_atoms * mm_blocks(max_mm));
 }
 
 hipError_t launch_mm_fwd(nnp_model& m, int n, int n_mm, const float* mm_pos, const float* mm_q,
@@ -249,7 +271,7 @@ hipError_t launch_mm_fwd(nnp_model& m, int n, int n_mm, const float* mm_pos, con
   if (n == 0) return hipSuccess;
   const int nbx = n_mm > 0 ? mm_blocks(n_mm) : 0;
   if (nbx > 0) {
-    if (m.d_mm_part == nullptr || (size_t)n * nbx > mm_partial_floats(m.max_atoms, m.max_mm))
+    if (m.d_mm_part == nullptr || (size_t)n * nbx > mm_partial_floats(m, m.max_atoms, m.max_mm))
       return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_mm_fwd, dim3(nbx, (n + kNnpChunk - 1) / kNnpChunk), dim3(kBlock), 0, st, m.d_spos, n,
                        mm_pos, mm_q, n_mm, m.dp, m.geo, m.d_mm_part);
@@ -262,8 +284,8 @@ hipError_t launch_mm_bwd(nnp_model& m, int n, int n_mm, const float* mm_pos, con
                          int accumulate, hipStream_t st) {
   if (n == 0 || n_mm == 0)
     return mm_forces != nullptr && !accumulate ? launch_fill_f64(mm_forces, 3 * (int64_t)n_mm, st) : hipSuccess;
-  const int nbx = mm_partial_blocks(n_mm);
-  if (m.d_mm_part == nullptr || 3 * (size_t)n * nbx > mm_partial_floats(m.max_atoms, m.max_mm))
+  const int nbx = mm_partial_blocks(m, n, n_mm);
+  if (m.d_mm_part == nullptr || 3 * (size_t)n * nbx > mm_partial_floats(m, m.max_atoms, m.max_mm))
     return hipErrorInvalidValue;
   // as many wavefronts as there are rows of 8 NNP atoms; with more rows than
   // one workgroup takes, grid rows until there are two workgroups per CU
@@ -273,8 +295,12 @@ hipError_t launch_mm_bwd(nnp_model& m, int n, int n_mm, const float* mm_pos, con
     const hipError_t e = launch_fill_f64(mm_forces, 3 * (int64_t)n_mm, st);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_mm_bwd, dim3(nbx, gy), dim3(64 * waves), 0, st, m.d_spos, n, mm_pos, mm_q, n_mm, m.d_g,
-                     m.charges ? m.d_q : nullptr, m.dp, m.geo, m.d_mm_part, mm_forces, !accumulate);
+  auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nbx, gy), dim3(64 * waves), 0, st, m.d_spos, n, mm_pos, mm_q, n_mm, m.d_g,
+                       m.charges ? m.d_q : nullptr, m.dp, m.geo, m.d_mm_part, mm_forces, !accumulate);
+  };
+  if (mm_tiles(m, n, n_mm) == 1) run(k_mm_bwd<1>);
+  else run(k_mm_bwd<kBwdTiles>);
   return hipGetLastError();
 }
 

@@ -451,8 +451,8 @@ hipError_t launch_force_gather(nnp_model& m, int n, int n_mm, double* forces, in
                                int n_sys, int accumulate, hipStream_t st);
 
 // mm.hip
-int mm_partial_blocks(int n_mm);   // adjoint partials per component of an NNP atom
-size_t mm_partial_floats(int max_atoms, int max_mm);   // floats of the MM partial buffer
+int mm_partial_blocks(const nnp_model& m, int n, int n_mm);   // adjoint partials per component of an NNP atom
+size_t mm_partial_floats(const nnp_model& m, int max_atoms, int max_mm);   // floats of the MM partial buffer
 hipError_t launch_mm_fwd(nnp_model& m, int n, int n_mm, const float* mm_pos, const float* mm_q,
                          hipStream_t st);
 hipError_t launch_mm_bwd(nnp_model& m, int n, int n_mm, const float* mm_pos, const float* mm_q, double* mm_forces,
