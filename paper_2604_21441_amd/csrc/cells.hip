@@ -1359,17 +1359,39 @@ hipError_t launch_cells(nnp_model& m, const float* pos, int n, bool pair_list, h
   return hipGetLastError();
 }
 
+// Candidates of a cell: on average, and whether the cell kernel's registers
+// should hold 768 rather than 512 (a tenth more time: 98,304 atoms 71 us against
+// 64).  A cell with more than that costs several times as much, so 512 have to
+// hold a fifth above the average, and are left to two elements at a density that
+// fills the box (water: 380 to 470); below that the box may hold a denser phase
+// beside vacuum, and organic matter is up to 1.4 times as dense.
+float cell_candidates(const nnp_model& m, int n) { return (float)kMaxStencil * (float)n / (float)m.geo.n_bins; }
+bool filled(float avg) { return avg >= 375.f && 1.2f * avg <= 512.f; }
+bool many_candidates(const nnp_model& m, float avg) { return m.S > 2 || !filled(avg); }
+
 // 0: one wavefront per atom; 1 / 2 / 3: the cell kernel with about 16 / 8 / 4
 // centres per wavefront (only where its conditions hold).  Without a pinned or
 // tuned choice, the cell kernel from 40,000 atoms on, when its wavefronts, each
-// a long chain, come to more than a few per SIMD: 27,000 atoms 35 us against
-// 32 for variant 0, 48,000 atoms 45 against 51, 98,304 atoms 65 against 96,
-// 261,000 atoms 136 (variant 1) against 225.
+// a long chain, come to more than a few per SIMD: 27,000 atoms 35 us against 32
+// for variant 0, 48,000 atoms 45 against 51, 98,304 atoms 65 against 96, 261,000
+// atoms 136 (variant 1) against 225; from 50,000 on where the cells hold more or
+// fewer (46,656 atoms, 460 candidates: 51 against 48; 50,653, 405: 47 against 51).
+// Not where the average shows that its cells are no good: mostly empty (a ball of
+// 46,656 atoms in a box of 300 A, where few wavefronts get crowded cells: 1,733
+// us against 63; slabs that fill 0.8, 0.7 and 0.5 of a box 60, 67 and 70 against
+// 65 to 66) or much larger than the cutoff (thin boxes: 111 against 53), nor in
+// boxes so long that rounding of the coordinates sends many centres to the
+// exact predicate (16.5 x 16.5 x 2,400 A: 86 against 48).
 int neighbour_variant(const nnp_model& m, int n) {
   if (!cells_fast(m.geo, m.dp.rc_rad)) return 0;
   const int v = stage_variant(m, kTuneNeighbours, n);
   if (v >= 0) return v;
-  return n < 40000 ? 0 : m.geo.n_bins < 48 * m.n_cu ? 2 : 1;
+  const float avg = cell_candidates(m, n);
+  const float longest = std::max(m.geo.box[0], std::max(m.geo.box[1], m.geo.box[2]));
+  if (n < (filled(avg) ? 40000 : 50000) || avg < 300.f || 1.2f * avg > 768.f ||
+      longest > 100.f * m.dp.rc_rad)
+    return 0;
+  return m.geo.n_bins < 48 * m.n_cu ? 2 : 1;
 }
 
 hipError_t launch_neighbours(nnp_model& m, int n, hipStream_t st) {
@@ -1403,8 +1425,7 @@ hipError_t launch_neighbours(nnp_model& m, int n, hipStream_t st) {
     const int target = v == 1 ? 16 : (v == 2 ? 8 : 4);
     const float per_bin = (float)n / (float)m.geo.n_bins;
     const int K = std::max(1, std::min(64, (int)std::lround(per_bin / target)));
-    // registers for the candidates of a cell a fifth denser than the average
-    const bool more = 1.2f * kMaxStencil * per_bin > 512.f;
+    const bool more = many_candidates(m, cell_candidates(m, n));
     auto run = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)(m.geo.n_bins * K)), dim3(64), 0, st, a, m.geo, K);
     };
