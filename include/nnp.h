@@ -348,8 +348,8 @@ typedef enum {
  *     row per atom; 3 / 4 two / four atoms per wavefront (3: one while the
  *     system has at most eight atoms per CU), their radial segments and
  *     angular classes cut into equal chunks, one per lane (default: 3 for
- *     four elements and for small systems, 4 for large ones, 1 in
- *     between and in the BF16 form);
+ *     four elements and for small systems, 4 for large ones with
+ *     angular capacities up to 96, 1 in between and in the BF16 form);
  *   network: 0 register-resident wavefronts; 1 / 2 / 3 row-split workgroups
  *     of 16 / 32 / 64 atoms (64 for water-sized networks only, in the FP32
  *     form with eight wavefronts; wider ones use 32); 4 workgroups of 32 atoms, 16 for the species with the fewest

@@ -1303,14 +1303,17 @@ hipError_t launch_link_redistribute(nnp_model& m, const float* pos, double* forc
 // wavefront (3: with one while that still leaves lanes idle, see
 // launch_descriptor_fwd).
 //
-// The default.  With four elements a centre has ten classes of few pairs, which rows of lanes walk one after the other: the pool is faster at every
-// size (us, variant 1 -> 3): 60 atoms 21.0 -> 11.3, 1,000 atoms 33.8 ->
-// 17, 25,000 atoms 104 -> 58.  With two elements the line is drawn by what
+// The default.  With four elements a centre has ten classes of few pairs, which
+// rows of lanes walk one after the other: the pool is faster at every size (us,
+// variant 1 -> 3): 60 atoms 21.0 -> 11.3, 1,000 atoms 33.8 -> 17, 25,000 atoms
+// 104 -> 58.  With two elements the line is drawn by what
 // there is to hide latency with: up to 24 atoms per CU the pool's even split
 // is faster (192 atoms 14.7 -> 12.8, 5,400 atoms 21.5 -> 18.1), in between
 // the rows (12,288 atoms 21.4, pool 22.0 to 23.7), and from 72 atoms per CU
 // on four pooled atoms per wavefront waste the fewest lanes (27,000 atoms
-// 39.1 -> 36.0, 87,000 atoms 95.1 -> 87.6).
+// 39.1 -> 36.0, 87,000 atoms 95.1 -> 87.6), while the angular capacity leaves
+// five of their workgroups per CU: 98,304 atoms with capacities of 64, 96, 112,
+// 128 and 256 rows 106, 108, 113, 113 and 155, pool 95, 102, 112, 130 and 296.
 // The BF16 form rounds the descriptors to eight bits; there another order of
 // summation turns single roundings over and moves forces by 1e-4, so its
 // default stays the row kernel at every size.
@@ -1319,7 +1322,7 @@ int descriptor_variant(const nnp_model& m, int n) {
   if (v >= 0) return v;
   if (m.prec == NNP_BF16) return 1;
   if (m.S > 2) return 3;
-  return n <= 24 * m.n_cu ? 3 : n >= 72 * m.n_cu ? 4 : 1;
+  return n <= 24 * m.n_cu ? 3 : n >= 72 * m.n_cu && m.max_ang <= 96 ? 4 : 1;
 }
 
 hipError_t launch_descriptor_fwd(nnp_model& m, int n, hipStream_t st) {
