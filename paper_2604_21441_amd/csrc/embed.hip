@@ -4,13 +4,13 @@
 //   E = sum_{i in ML} sum_{j in MM, r < rc} ke q_i q_j / r + 4 eps_ij ((s_ij/r)^12 - (s_ij/r)^6)
 // with Lorentz-Berthelot mixing s_ij = (s_i + s_j)/2, eps_ij = sqrt(eps_i eps_j).
 //
-// A workgroup takes 128 MM atoms, two per lane of each of its 16
-// wavefronts, and the wavefronts share the ML atoms (staged in LDS) between
-// them.  Each pair is evaluated in FP32.  An MM atom's force and the energy
-// accumulate in FP64 registers and are summed over the wavefronts through
-// LDS, in order; an ML atom's force is summed over the lanes in FP32, the 64 MM
-// atoms of each tile by themselves, and added with FP64 atomics (skipped when
-// no lane is inside the cutoff).
+// A workgroup takes 128 MM atoms, two per lane of each of its 16 wavefronts (4
+// beyond 262,144 MM atoms), and the wavefronts share the ML atoms (staged in
+// LDS) between them.  Each pair is evaluated in FP32.  An MM atom's force and
+// the energy accumulate in FP64 registers and are summed over the wavefronts
+// through LDS, in order; an ML atom's force is summed over the lanes in FP32,
+// the 64 MM atoms of each tile by themselves, and added with FP64 atomics
+// (skipped when no lane is inside the cutoff).
 //
 // Bound by the chain of one wavefront through its ML atoms (a sphere around
 // the ML region holds few of the MM atoms' wavefronts, and these few meet
@@ -27,8 +27,10 @@
 namespace nnp {
 namespace {
 
-constexpr int kMeWaves = 16;
-constexpr int kMeBlock = 64 * kMeWaves;
+constexpr int kMeWaves = 16;       // wavefronts of a workgroup; with many workgroups
+constexpr int kMeWavesMany = 4;    // (launch_me_pairs: more than kMeGroupsMost)
+constexpr int kMeGroupsMost = 2048;   // eight per CU
+constexpr int kMeBlock = 256;
 constexpr int kMeTiles = 2;     // 64 MM atoms each
 constexpr int kMeChunk = 256;   // ML atoms per LDS chunk
 
@@ -55,16 +57,17 @@ __device__ __forceinline__ double wsum_d(double v) {
   return v;
 }
 
-__global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__ ml_pos,
-                                                       const float* __restrict__ ml_par, int n_ml,
-                                                       const float* __restrict__ mm_pos,
-                                                       const float* __restrict__ mm_par, int n_mm, Geometry g,
-                                                       float rc2, float ke, double* __restrict__ energy,
-                                                       double* __restrict__ ml_f, double* __restrict__ mm_f,
-                                                       int accumulate) {
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_me_pairs(const float* __restrict__ ml_pos,
+                                                         const float* __restrict__ ml_par, int n_ml,
+                                                         const float* __restrict__ mm_pos,
+                                                         const float* __restrict__ mm_par, int n_mm, Geometry g,
+                                                         float rc2, float ke, double* __restrict__ energy,
+                                                         double* __restrict__ ml_f, double* __restrict__ mm_f,
+                                                         int accumulate) {
   __shared__ float4 sx[kMeChunk];   // ML x, y, z, q
   __shared__ float2 sp[kMeChunk];   // ML sigma, eps
-  __shared__ double sf[kMeWaves][4][64];   // per wavefront and MM atom of a tile: force, energy
+  __shared__ double sf[WAVES][4][64];   // per wavefront and MM atom of a tile: force, energy
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int j0 = blockIdx.x * (64 * kMeTiles) + lane;
@@ -84,7 +87,7 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
   for (int c0 = 0; c0 < n_ml; c0 += kMeChunk) {
     const int nc = min(kMeChunk, n_ml - c0);
     __syncthreads();
-    for (int t = threadIdx.x; t < nc; t += kMeBlock) {
+    for (int t = threadIdx.x; t < nc; t += 64 * WAVES) {
       const int i = c0 + t;
       sx[t] = make_float4(ml_pos[3 * (int64_t)i], ml_pos[3 * (int64_t)i + 1], ml_pos[3 * (int64_t)i + 2],
                           ml_par[3 * (int64_t)i]);
@@ -92,7 +95,7 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
     }
     __syncthreads();
     const int turn = (int)((blockIdx.x * 29u) % (unsigned)nc);
-    for (int k = wave; k < nc; k += kMeWaves) {
+    for (int k = wave; k < nc; k += WAVES) {
       const int t = k + turn < nc ? k + turn : k + turn - nc;
       const float4 xi = sx[t];
       const float2 pi = sp[t];
@@ -153,7 +156,7 @@ __global__ __launch_bounds__(kMeBlock) void k_me_pairs(const float* __restrict__
     if (wave < 3 || (u == 0 && wave == 3)) {
       double v = 0.0;
 #pragma unroll
-      for (int w = 0; w < kMeWaves; ++w) v += sf[w][wave][lane];
+      for (int w = 0; w < WAVES; ++w) v += sf[w][wave][lane];
       if (wave < 3) {
         if (j0 + 64 * u < n_mm) {
           double* o = mm_f + 3 * (int64_t)(j0 + 64 * u) + wave;
@@ -189,8 +192,18 @@ hipError_t launch_me_pairs(int n_ml, const float* ml_pos, const float* ml_par, i
   }
   if (n_mm == 0) return hipSuccess;
   const float rc2 = cutoff > 0.f ? cutoff * cutoff : INFINITY;
-  hipLaunchKernelGGL(k_me_pairs, dim3((n_mm + 64 * kMeTiles - 1) / (64 * kMeTiles)), dim3(kMeBlock), 0, st, ml_pos,
-                     ml_par, n_ml, mm_pos, mm_par, n_mm, g, rc2, ke, energy, ml_f, mm_f, accumulate);
+  // Most workgroups of a large surrounding have no pair inside the cutoff, and
+  // 16 wavefronts then only load, wait for each other and store zeros.  20 ML
+  // atoms, cutoff 12 A, 16 wavefronts -> 4: 1,000,000 MM atoms 48 -> 22 us,
+  // 400,000 22 -> 13, 200,000 14.3 -> 11.5; 200 ML atoms 97 -> 76, 47 -> 50, 32
+  // -> 43.
+  const int groups = (n_mm - 1) / (64 * kMeTiles) + 1;
+  auto run = [&](auto kernel, int waves) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3((unsigned)(64 * waves)), 0, st, ml_pos, ml_par, n_ml,
+                       mm_pos, mm_par, n_mm, g, rc2, ke, energy, ml_f, mm_f, accumulate);
+  };
+  if (groups <= kMeGroupsMost) run(k_me_pairs<kMeWaves>, kMeWaves);
+  else run(k_me_pairs<kMeWavesMany>, kMeWavesMany);
   return hipGetLastError();
 }
 
