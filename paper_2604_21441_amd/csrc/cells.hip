@@ -839,8 +839,8 @@ __global__ __launch_bounds__(64) void k_neighbours(NeighArgs a, Geometry g) {
 // unless it falls within eps of a cutoff: two comparisons, one on each side,
 // must agree for every lane of a chunk.  A centre with a chunk where they do
 // not (about one in twenty), or whose lists would overflow, is done again with
-// the predicate itself, as is every centre of a cell with more candidates than
-// the registers hold.
+// the predicate itself; where a cell has more candidates than the registers
+// hold, the rest of them go through the predicate for every centre.
 //
 // The shift picks the predicate's image: with at least four cells per
 // dimension a stencil pair is at most half a box apart; with three it can be
@@ -854,8 +854,8 @@ __global__ __launch_bounds__(64) void k_neighbours(NeighArgs a, Geometry g) {
 // 261,000 atoms from 181 to 136 us.
 template <int S, int NCH>
 __global__ __launch_bounds__(64) void k_neighbours_cell(NeighArgs a, Geometry g, int K) {
-  constexpr int kCap = 64 * NCH;
-  __shared__ int s_cand[kCap];
+  constexpr int kCap = 64 * NCH, kList = kCap + 512;   // candidates in registers, and in LDS
+  __shared__ int s_cand[kList];
   __shared__ int s_start[kMaxStencil * S], s_off[kMaxStencil * S + 1];
   const int b = xcd_block(blockIdx.x, gridDim.x);
   const int cell = b / K, part = b - cell * K;
@@ -900,7 +900,7 @@ __global__ __launch_bounds__(64) void k_neighbours_cell(NeighArgs a, Geometry g,
     if (lane < kMaxStencil) {
       s_start[s * kMaxStencil + lane] = st;
       s_off[s * kMaxStencil + lane] = at;
-      for (int q = 0; q < cnt && at + q < kCap; ++q) s_cand[at + q] = st + q;
+      for (int q = 0; q < cnt && at + q < kList; ++q) s_cand[at + q] = st + q;
     }
     own_st[s] = __builtin_amdgcn_readlane(st, own);
     own_n[s] = __builtin_amdgcn_readlane(cnt, own);
@@ -914,8 +914,7 @@ __global__ __launch_bounds__(64) void k_neighbours_cell(NeighArgs a, Geometry g,
   const int q0 = part * chunk, q1 = min(n_centres, q0 + chunk);
   if (q0 >= q1) return;
   __syncthreads();
-  const bool fast_cell = total <= kCap;
-  const int nch = (total + 63) >> 6;
+  const int nch = (min(total, kCap) + 63) >> 6;
   // candidates in registers, as the image nearest to the cell's centre
   const float mx = ((float)cc[0] + 0.5f) * g.cell_len[0], my = ((float)cc[1] + 0.5f) * g.cell_len[1],
               mz = ((float)cc[2] + 0.5f) * g.cell_len[2];
@@ -926,7 +925,7 @@ __global__ __launch_bounds__(64) void k_neighbours_cell(NeighArgs a, Geometry g,
   for (int c = 0; c < NCH; ++c) {
     cj[c] = -1;
     cx[c] = cy[c] = cz[c] = 3e18f;   // beyond every cutoff
-    if (fast_cell && c < nch && 64 * c + lane < total) cj[c] = s_cand[64 * c + lane];
+    if (c < nch && 64 * c + lane < total) cj[c] = s_cand[64 * c + lane];
   }
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
@@ -971,57 +970,60 @@ __global__ __launch_bounds__(64) void k_neighbours_cell(NeighArgs a, Geometry g,
       int nr = 0, na = 0, ro[S], ao[S];
 #pragma unroll
       for (int s = 0; s < S; ++s) ro[s] = ao[s] = 0;
-      bool again = !fast_cell;
-      if (fast_cell) {
-        const float x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(px), from));
-        const float y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(py), from));
-        const float z = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pz), from));
-        // every comparison counts on scalar instructions too, so the checks are
-        // per lane: the least distance of any r^2 to a cutoff, and places held
-        // below the capacity (a list that reaches it is done again)
-        float margin = 3e18f;
+      const float x = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(px), from));
+      const float y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(py), from));
+      const float z = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(pz), from));
+      // every comparison counts on scalar instructions too, so the checks are
+      // per lane: the least distance of any r^2 to a cutoff, and places held
+      // below the capacity (a list that reaches it is done again)
+      float margin = 3e18f;
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-          if (c < nch) {
-            const float dx = cx[c] - x, dy = cy[c] - y, dz = cz[c] - z;
-            float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-            r2 = cj[c] == i ? 3e18f : r2;
-            const uint64_t mr = __builtin_amdgcn_ballot_w64(r2 < a.rc2), ma = __builtin_amdgcn_ballot_w64(r2 < a.rca2);
-            margin = fminf(margin, fminf(fabsf(r2 - a.rc2), fabsf(r2 - a.rca2)));
-            const unsigned pr = min(place(mr, nr), last_r), pa = min(place(ma, na), last_a);
-            if (starts >> c & 1) {   // a species starts in this chunk
+      for (int c = 0; c < NCH; ++c) {
+        if (c < nch) {
+          const float dx = cx[c] - x, dy = cy[c] - y, dz = cz[c] - z;
+          float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+          r2 = cj[c] == i ? 3e18f : r2;
+          const uint64_t mr = __builtin_amdgcn_ballot_w64(r2 < a.rc2), ma = __builtin_amdgcn_ballot_w64(r2 < a.rca2);
+          margin = fminf(margin, fminf(fabsf(r2 - a.rc2), fabsf(r2 - a.rca2)));
+          const unsigned pr = min(place(mr, nr), last_r), pa = min(place(ma, na), last_a);
+          if (starts >> c & 1) {   // a species starts in this chunk
 #pragma unroll
-              for (int s = 1; s < S; ++s)
-                if ((first[s] >> 6) == c) {
-                  const uint64_t before = (uint64_t(1) << (first[s] & 63)) - 1;
-                  ro[s] = nr + __popcll(mr & before);
-                  ao[s] = na + __popcll(ma & before);
-                }
-            }
-            nr += __popcll(mr);
-            na += __popcll(ma);
-            if (__builtin_amdgcn_inverse_ballot_w64(mr)) rad[pr] = cj[c];
-            if (__builtin_amdgcn_inverse_ballot_w64(ma)) ang[pa] = cj[c];
+            for (int s = 1; s < S; ++s)
+              if ((first[s] >> 6) == c) {
+                const uint64_t before = (uint64_t(1) << (first[s] & 63)) - 1;
+                ro[s] = nr + __popcll(mr & before);
+                ao[s] = na + __popcll(ma & before);
+              }
           }
+          nr += __popcll(mr);
+          na += __popcll(ma);
+          if (__builtin_amdgcn_inverse_ballot_w64(mr)) rad[pr] = cj[c];
+          if (__builtin_amdgcn_inverse_ballot_w64(ma)) ang[pa] = cj[c];
         }
-        again = nr > a.max_rad || na > a.max_ang || __ballot(!(margin > eps)) != 0;
-#pragma unroll
-        for (int s = 1; s < S; ++s)
-          if ((first[s] >> 6) >= nch) {   // no candidate of species s or later
-            ro[s] = nr;
-            ao[s] = na;
-          }
       }
-      if (again) {   // the predicate itself, with the lists' capacities
-        nr = na = 0;
+      const bool again = nr > a.max_rad || na > a.max_ang || __ballot(!(margin > eps)) != 0;
+#pragma unroll
+      for (int s = 1; s < S; ++s)
+        if ((first[s] >> 6) >= nch) {   // no candidate of species s or later
+          ro[s] = nr;
+          ao[s] = na;
+        }
+      if (again || total > kCap) {   // the predicate itself, with the lists' capacities: all, or the rest
         bool overflow = false;
         const float4 pi = a.spos[i];
         int next = 1;   // species whose start comes next
-        for (int c0 = 0; c0 < total; c0 += 64) {
+        int c0 = kCap;
+        if (again) {
+          nr = na = c0 = 0;
+        } else {
+#pragma unroll
+          for (int s = 1; s < S; ++s) next += first[s] < kCap;
+        }
+        for (; c0 < total; c0 += 64) {
           const int c = c0 + lane;
           int j = -1;
           if (c < total) {
-            if (c < kCap) {
+            if (c < kList) {
               j = s_cand[c];
             } else {
               int lo = 0, hi = S * kMaxStencil - 1;
@@ -1359,15 +1361,12 @@ hipError_t launch_cells(nnp_model& m, const float* pos, int n, bool pair_list, h
   return hipGetLastError();
 }
 
-// Candidates of a cell: on average, and whether the cell kernel's registers
-// should hold 768 rather than 512 (a tenth more time: 98,304 atoms 71 us against
-// 64).  A cell with more than that costs several times as much, so 512 have to
-// hold a fifth above the average, and are left to two elements at a density that
-// fills the box (water: 380 to 470); below that the box may hold a denser phase
-// beside vacuum, and organic matter is up to 1.4 times as dense.
+// Candidates of a cell, on average, and whether that is a filled box of ordinary
+// density and cells (water: 380 to 470), for which the registers hold 512 of
+// them, a fifth above the average.  (768, used where that is not so, cost a tenth
+// more time: 98,304 atoms 71 us against 64.)
 float cell_candidates(const nnp_model& m, int n) { return (float)kMaxStencil * (float)n / (float)m.geo.n_bins; }
-bool filled(float avg) { return avg >= 375.f && 1.2f * avg <= 512.f; }
-bool many_candidates(const nnp_model& m, float avg) { return m.S > 2 || !filled(avg); }
+bool crowded(float avg) { return 1.2f * avg > 512.f; }
 
 // 0: one wavefront per atom; 1 / 2 / 3: the cell kernel with about 16 / 8 / 4
 // centres per wavefront (only where its conditions hold).  Without a pinned or
@@ -1377,7 +1376,7 @@ bool many_candidates(const nnp_model& m, float avg) { return m.S > 2 || !filled(
 // atoms 136 (variant 1) against 225; from 50,000 on where the cells hold more or
 // fewer (46,656 atoms, 460 candidates: 51 against 48; 50,653, 405: 47 against 51).
 // Not where the average shows that its cells are no good: mostly empty (a ball of
-// 46,656 atoms in a box of 300 A, where few wavefronts get crowded cells: 1,733
+// 46,656 atoms in a box of 300 A, where few wavefronts get all the cells: 1,733
 // us against 63; slabs that fill 0.8, 0.7 and 0.5 of a box 60, 67 and 70 against
 // 65 to 66) or much larger than the cutoff (thin boxes: 111 against 53), nor in
 // boxes so long that rounding of the coordinates sends many centres to the
@@ -1388,7 +1387,7 @@ int neighbour_variant(const nnp_model& m, int n) {
   if (v >= 0) return v;
   const float avg = cell_candidates(m, n);
   const float longest = std::max(m.geo.box[0], std::max(m.geo.box[1], m.geo.box[2]));
-  if (n < (filled(avg) ? 40000 : 50000) || avg < 300.f || 1.2f * avg > 768.f ||
+  if (n < (avg < 375.f || crowded(avg) ? 50000 : 40000) || avg < 300.f || 1.2f * avg > 768.f ||
       longest > 100.f * m.dp.rc_rad)
     return 0;
   return m.geo.n_bins < 48 * m.n_cu ? 2 : 1;
@@ -1425,7 +1424,7 @@ hipError_t launch_neighbours(nnp_model& m, int n, hipStream_t st) {
     const int target = v == 1 ? 16 : (v == 2 ? 8 : 4);
     const float per_bin = (float)n / (float)m.geo.n_bins;
     const int K = std::max(1, std::min(64, (int)std::lround(per_bin / target)));
-    const bool more = many_candidates(m, cell_candidates(m, n));
+    const bool more = crowded(cell_candidates(m, n));
     auto run = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)(m.geo.n_bins * K)), dim3(64), 0, st, a, m.geo, K);
     };
