@@ -326,7 +326,7 @@ nnp_status nnp_read_buffer(nnp_model* m, nnp_buffer which, void* dst_host, size_
  * network and adjoint stages, as nnp_get_variants.  Synchronises the stream; drops the
  * cached graph.  If the environment variable NNP_TUNE_CACHE names a file,
  * results are appended to it and read back by nnp_create for the same GPU
- * architecture and model shape.
+ * architecture, revision of the kernels and model shape.
  */
 nnp_status nnp_autotune(nnp_model* m, int32_t reps, int32_t* chosen, hipStream_t stream);
 

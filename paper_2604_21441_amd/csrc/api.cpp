@@ -257,13 +257,16 @@ nnp_status species_of(const nnp_model* m, int z, int* out) {
 }
 
 // Tuning cache file (NNP_TUNE_CACHE): one line per entry,
-// "<arch> <network kind> <precision> <stage> <size bucket> <variant>".
+// "<arch>/<revision> <network kind> <precision> <stage> <size bucket> <variant>".
+// The revision rises whenever variants change their meaning or their timings
+// change order; lines of another one, or of none, are left alone.
+constexpr int kTuneRevision = 2;
+
 std::string device_arch(int dev) {
   hipDeviceProp_t prop;
   if (hipGetDeviceProperties(&prop, dev) != hipSuccess) return "unknown";
   std::string a = prop.gcnArchName;
-  size_t colon = a.find(':');
-  return colon == std::string::npos ? a : a.substr(0, colon);
+  return a.substr(0, a.find(':')) + "/" + std::to_string(kTuneRevision);
 }
 
 void load_tuning(nnp_model* m) {
@@ -275,7 +278,8 @@ void load_tuning(nnp_model* m) {
   char a[64];
   int kind, prec, stage, bucket, variant;
   while (std::fscanf(f, "%63s %d %d %d %d %d", a, &kind, &prec, &stage, &bucket, &variant) == 6)
-    if (arch == a && kind == m->net_kind && prec == (int)m->prec && stage >= 0 && stage < kTuneStages)
+    if (arch == a && kind == m->net_kind && prec == (int)m->prec && stage >= 0 && stage < kTuneStages &&
+        variant >= 0 && variant < kStageVariants[stage])
       m->tuned[{stage, bucket}] = variant;
   std::fclose(f);
 }
