@@ -236,9 +236,9 @@ nnp_status nnp_compute_batch(nnp_model* m, int32_t n_sys, const int32_t* atom_of
  * nnp_reserve is not needed and the reserved workspace, the captured graph
  * and the topology cache of nnp_compute are left untouched (nnp_read_buffer
  * keeps reporting nnp_compute's last call).  Kernels are launched directly
- * on `stream` (no graph).  The array holds the workspace of up to about 8,900
- * atoms of the two-species model or 5,700 of the four-species one, at the
- * default neighbour capacities (128 radial, 64 angular); a larger call returns
+ * on `stream` (no graph).  The array holds the workspace of up to 8,960 atoms
+ * of the two-species model or 5,752 of the four-species one, at the default
+ * neighbour capacities (128 radial, 64 angular); a larger call returns
  * NNP_ECAPACITY before any work is queued.  All calls on one device share its
  * array: calls that overlap on a device (other streams, other threads) race
  * and must be serialised by the caller.  NNP_EINVAL for a model with the MM

@@ -420,6 +420,7 @@ nnp_status run_path(nnp_model* m, int n, const float* pos, int n_mm, const float
 // noalloc.hip: size of the static workspace of nnp_compute_noalloc, and the
 // once-per-device lookup of its device address (called by nnp_create)
 constexpr size_t kNoallocScratchBytes = size_t(32) << 20;
+constexpr int kNoallocAtoms2 = 8960, kNoallocAtoms4 = 5752;   // most atoms, two and four species
 nnp_status noalloc_scratch_setup(int device);
 
 // error helpers (api.cpp)

@@ -106,16 +106,15 @@ extern "C" nnp_status nnp_compute_noalloc(nnp_model* m, int32_t n_atoms, const f
   }
   if (!base) return set_error(NNP_ESTATE, "the static workspace of this device was not set up");
 
+  // The documented capacities are atom counts, so that they hold whatever the
+  // layout needs; the array has room for some more.
+  const int most = m->S == 2 ? kNoallocAtoms2 : kNoallocAtoms4;
+  if (n_atoms > most)
+    return set_error(NNP_ECAPACITY, std::to_string(n_atoms) + " atoms exceed the " + std::to_string(most) +
+                                        " that the static workspace is made for");
   Workspace w = workspace_caps(*m, n_atoms, 1, 0, 128, 64);
-  // The documented capacity (about 8,900 atoms of the two-species model, 5,700
-  // of the four-species one) counts one more word per angular entry and per
-  // atom than the layout uses; it stays.
-  auto words = [](size_t n) { return (n * sizeof(int) + 255) & ~(size_t)255; };
-  const size_t need = carve_workspace(*m, w, nullptr) + words((size_t)n_atoms * w.max_ang) + words((size_t)n_atoms);
-  if (need > kNoallocScratchBytes)
-    return set_error(NNP_ECAPACITY, std::to_string(n_atoms) + " atoms need " + std::to_string(need) +
-                                        " bytes of workspace; the static array holds " +
-                                        std::to_string(kNoallocScratchBytes));
+  if (carve_workspace(*m, w, nullptr) > kNoallocScratchBytes)
+    return set_error(NNP_ECAPACITY, "the static workspace is too small for " + std::to_string(n_atoms) + " atoms");
   carve_workspace(*m, w, static_cast<char*>(base));
 
   Restore restore(m);
