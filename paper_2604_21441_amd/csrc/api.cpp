@@ -433,6 +433,8 @@ nnp_status nnp_create(const nnp_config* cfg, uint64_t seed, const float* weights
   const size_t total = per_species * S * m->n_members;
   if (weights_host) {
     m->w_host.assign(weights_host, weights_host + total);
+    if (prec == NNP_BF16)   // rounding to BF16 would carry some NaN payloads into a zero
+      for (float& v : m->w_host) v = v == v ? v : NAN;
   } else {
     draw_weights(seed, w, S, m->n_members, m->w_host);
   }
