@@ -164,7 +164,7 @@ def stage_kernel(stage, variants, prec, cfg, periodic=True, n=0):
     if stage == "adjoint":
         return f"k_desc_adj<{len(cfg['species'])}>"
     return {"gather": "k_force_gather", "energy": "k_force_gather", "mm": "k_mm_fwd",
-            "mm_adjoint": "k_mm_bwd"}.get(stage)
+            "mm_adjoint": "k_mm_bwd<1>"}.get(stage)   # (small ML regions: one MM atom per lane)
 
 
 def profile_entry(workload, kernel):

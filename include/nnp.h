@@ -377,10 +377,11 @@ nnp_status nnp_get_variants(nnp_model* m, int32_t* chosen);
 
 /*
  * HIP-graph replay.  By default, calls with fewer than three atoms per CU and
- * no MM atoms use it, where the host's time per call counts; for larger ones
- * direct launches finish 4 to 5 us earlier on the GPU.  enable = 1: every
- * call; enable = 0: none, and the cached graph is freed.  The first call of a
- * configuration is captured into a HIP graph; a later call with the same
+ * no MM atoms use it: a caller that waits for each call of a small open system
+ * has it 4 to 11 us earlier, while in a stream of calls, and for larger
+ * systems, direct launches finish 2 to 5 us earlier on the GPU.  enable = 1:
+ * every call; enable = 0: none, and the cached graph is freed.  The first call
+ * of a configuration is captured into a HIP graph; a later call with the same
  * arguments (device pointers, sizes, flags and box) replays it with one
  * launch.  A call whose arguments differ (a new box every step under a
  * barostat, other output buffers) is captured again and the instantiated

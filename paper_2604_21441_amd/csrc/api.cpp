@@ -156,13 +156,17 @@ std::vector<uint8_t> make_key(const T&... parts) {
 // is far cheaper than instantiating; only if that fails is the graph rebuilt.
 // Capture happens on the model's own stream (the caller's may be the legacy
 // default stream, which cannot be captured); the graph runs on the caller's.
-// Unless nnp_set_graph asked for it, a graph is used only where the host's time
-// per call counts: it costs the host 22 us for the six kernels of 192 atoms of
-// water (direct launches 26, 34 for eight kernels), but the GPU 4 to 5 us more
-// per call than direct launches (12,288 atoms 105.3 against 100.4 us, 900 atoms
-// with a pair list 63.6 against 58.8, 256 conformers 293 against 288).  From
-// three atoms per CU on, and with MM atoms, the kernels outlast their launches
-// (50 us and more).
+// Unless nnp_set_graph asked for it, a graph is used only below three atoms per
+// CU and without MM atoms.  In a stream of calls direct launches are the faster
+// ones at every size (us per call, graph / direct: 192 atoms 41.8 / 39.3, 750
+// 50.2 / 47.7, open systems of 24 atoms 42.1 / 37.8, 10 H/C/N/O atoms 50.9 /
+// 47.1; 12,288 atoms 105.3 / 100.4, 900 with a pair list 63.6 / 58.8).  What the
+// graph is for is the caller that waits for each call: the nine kernels of a
+// small open system take the host 38 us to launch, replay 29 (waited for, 24
+// atoms 53.9 / 65, 60 H/C/N/O atoms 68.8 / 74.5, 300 86.7 / 90.6, 700 97.8 /
+// 96.5, which is where the line lies).  The six kernels of a small periodic
+// system are launched in 18.5 us, so that there replay only costs (192 atoms
+// waited for 58.5 / 54.7); it stays their default, one rule for both.
 template <typename F>
 nnp_status dispatch(nnp_model* m, std::vector<uint8_t> key, int n, int n_mm, hipStream_t st, F launch) {
   const bool replay = m->graph_mode == kGraphAlways ||

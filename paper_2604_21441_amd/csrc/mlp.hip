@@ -681,15 +681,10 @@ __global__ __launch_bounds__(512, K0 <= 128 && OP == kOpSplit && C <= 2 ? 4 : 2)
   mlp_split_body<K0, N1, N2, N3, OP, C, MIXED, 8, false>(a, alpha);
 }
 
-// Mixed tiling: tiles of 32 atoms, of 16 for the species with the fewest
-// atoms.  For a small system the workgroups then come in two sizes whose
-// count matches the CUs better than one size does (water, 4,096 molecules:
-// 256 + 256 instead of 384 tiles).  Every atom's arithmetic is the same as
-// in the uniform tiling.
-// The same with an ensemble's members shared over the grid's rows (k_mlp_sum
-// adds the rows up): row y evaluates its members as an ensemble of its own.
-// (Kept apart: the rows' addresses cost the plain kernel registers it spills
-// for, 98,304 atoms 95 -> 104 us.)
+// The eight-wavefront tiling (of 16 or 32 atoms) with an ensemble's members
+// shared over the grid's rows (k_mlp_sum adds the rows up): row y evaluates its
+// members as an ensemble of its own.  (Kept apart: the rows' addresses cost the
+// plain kernel registers it spills for, 98,304 atoms 95 -> 104 us.)
 __host__ __device__ __forceinline__ int first_member(int members, int y, int rows) { return members * y / rows; }
 
 template <int K0, int N1, int N2, int N3, int OP, int C>
@@ -705,6 +700,11 @@ __global__ __launch_bounds__(512, K0 <= 128 && OP == kOpSplit ? 4 : 2) void k_ml
   mlp_split_body<K0, N1, N2, N3, OP, C, false, 8, false>(a, alpha);
 }
 
+// Mixed tiling: tiles of 32 atoms, of 16 for the species with the fewest
+// atoms.  For a small system the workgroups then come in two sizes whose
+// count matches the CUs better than one size does (water, 4,096 molecules:
+// 256 + 256 instead of 384 tiles).  Every atom's arithmetic is the same as
+// in the uniform tiling.
 template <int K0, int N1, int N2, int N3, int OP>
 __global__ __launch_bounds__(256, K0 <= 128 ? 2 : 1) void k_mlp_mixed(MlpArgs a, float alpha) {
   mlp_split_body<K0, N1, N2, N3, OP, 2, true, 4, false>(a, alpha);
@@ -1509,8 +1509,9 @@ __global__ __launch_bounds__(kBlock) void k_pack_split(PackArgs a) {
 // Network kernel variant: 0 register-resident (16 atoms per wavefront),
 // 1 / 2 / 3 row split over 4 wavefronts with 16 / 32 / 64 atoms per workgroup
 // (64 only for the narrow water network; the wide one falls back to 32), 5 / 6
-// / 7 over 8 wavefronts.  A tuned choice for this size wins; else, all of them
-// giving the same results bit for bit:
+// / 7 over 8 wavefronts.  A tuned choice for this size wins; else one of these,
+// which give the same results bit for bit for one network, and for an ensemble
+// while its members are not shared over grid rows (member_rows):
 //   while every 16-atom tile has a compute unit of its own, 16-atom tiles over
 //   8 wavefronts (the shortest chain per tile): 192 atoms FP32 11 us against
 //   15 for variant 2, 3,000 atoms 11.5 against 16, 60 H/C/N/O atoms with the
@@ -1556,7 +1557,9 @@ hipError_t pack_split(const nnp_model& m, const float* weights, void* out) {
 // members: 8 networks, 600 atoms 68 -> 26 us, 3,900 atoms 68 -> 53, 8,100
 // atoms 89 -> 70, 5 networks, 2,100 atoms 44 -> 36.  Beyond (8 networks,
 // 12,288 atoms, 386 tiles: 111 us, two rows 110; 2 networks 32.7 and 35.3) the
-// sum takes what a more even load gives.
+// sum takes what a more even load gives.  The average over members is rounded
+// in the order of the rows, so it can differ in the last bits between system
+// sizes, variants and reserved capacities.
 int member_rows(const nnp_model& m, int n, int variant) {
   if (m.charges || (variant != 5 && variant != 7)) return 1;   // (charges are not summed up)
   const int tiles = (n + 16 * m.mlp_cols - 1) / (16 * m.mlp_cols) + m.S;
