@@ -59,8 +59,9 @@ WORKLOADS = {
 # VALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz = 3.93e13 lane-operations/s (unpacked FP32
 # and FP64 issue at that rate; transcendentals at a quarter of it, counted as 4 operations).
 PEAK_HBM_GBS = 8000.0
-# The FP32 network form runs on FP16 operand pairs, three FP16 products per FP32 one ("split").
-PEAK_MFMA_TFLOPS = {"split": 2500.0 / 3, "bf16": 2500.0}
+# The FP32 network form runs on FP16 operand pairs ("split"): four FP16 products per FP32 one in
+# the forward pass, three in the backward pass.
+PEAK_MFMA_TFLOPS = {"split": 2500.0 / 3.5, "bf16": 2500.0}
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 
 # Algorithmic VALU lane-operations per unit of work (transcendental = 4): the arithmetic the

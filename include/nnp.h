@@ -122,9 +122,9 @@ typedef struct {
  * z = sqrt(-2 ln(1-u0)) cos(2 pi u1); W ~ N(0, 2/(fan_in+fan_out)),
  * b ~ N(0, 0.01); each value rounded once to FP32.
  * prec selects the network arithmetic: NNP_FP32 (FP32 accuracy: FP16 operand
- * pairs of 22 bits with FP32 accumulation) or NNP_BF16 (BF16 operands, FP32
- * accumulation).  Descriptors and their derivatives are FP32 in both forms;
- * energies and force accumulation FP64.
+ * pairs of 22 bits, in the forward pass weights of 24, with FP32 accumulation)
+ * or NNP_BF16 (BF16 operands, FP32 accumulation).  Descriptors and their
+ * derivatives are FP32 in both forms; energies and force accumulation FP64.
  * Uses the current HIP device; allocates the device weights.  *out is set
  * on success.
  */

@@ -454,7 +454,8 @@ nnp_status nnp_create(const nnp_config* cfg, uint64_t seed, const float* weights
     e = hipMalloc(&m->d_wmat, (size_t)m->mat_per_species * S * m->n_members * sizeof(float));
     if (e == hipSuccess) e = dalloc(&raw, total);
     if (e == hipSuccess) e = hipMemcpy(raw, m->w_host.data(), total * sizeof(float), hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = pack_split(*m, raw, m->d_wmat);
+    if (e == hipSuccess) e = dalloc(&m->d_wunit, (size_t)m->mat_per_species / 2 * S * m->n_members);
+    if (e == hipSuccess) e = pack_split(*m, raw, m->d_wmat, m->d_wunit);
     if (raw) (void)hipFree(raw);   // waits for the packing
   } else {
     e = hipMalloc(&m->d_wmat, mat.size());
@@ -1140,6 +1141,7 @@ void nnp_destroy(nnp_model* m) {
   if (m->d_wmat) (void)hipFree(m->d_wmat);
   if (m->d_wrow) (void)hipFree(m->d_wrow);
   dfree(m->d_wvec);
+  dfree(m->d_wunit);
   dfree(m->d_status);
   delete m;
 }

@@ -44,14 +44,15 @@ constexpr float kLog2e = 1.4426950408889634f;
 //     256 matrix-core cycles per 16 x 16 x 32 block).  hi + lo 2^-11 carries 22
 //     to 23 significant bits, the products are exact in FP32, and the term left
 //     out (lo lo) is below 2^-22 of hi hi; one accumulator takes 8 times fewer
-//     roundings than with the FP32 instruction.  Force error against float64
-//     as before (water, 12,288 atoms: 1.5e-6 both).  Network, FP32
-//     instructions -> split: 261,000 atoms 569 -> 239 us, 12,288 atoms 36.4 ->
-//     21.2, eight networks 235 -> 110, 29,000 H/C/N/O atoms 231 -> 100.  What
-//     bounds it at 261,000 atoms: the stream of weight fragments from L2
-//     (14 TB/s; 205 us when every fragment is a cache hit, 161 with variant 2)
-//     and the six dependent products of a tile; the matrix cores are busy for
-//     67 us of it and the VALU for about 100.
+//     roundings than with the FP32 instruction.  In the forward products a
+//     fourth instruction adds what the weights' pairs leave out (mma_unit).
+//     Errors against float64, FP32 instructions -> split (water, 12,288 atoms):
+//     forces 1.5e-6 both, an atomic energy 9.5e-8 -> 4.5e-8 eV rms, the mean of
+//     all 4e-9 both.  Network, FP32 instructions -> split: 261,000 atoms 569 ->
+//     285 us, 12,288 atoms 36.4 -> 21.7, eight networks 235 -> 135, 29,000
+//     H/C/N/O atoms 231 -> 123.  What bounds it at 261,000 atoms: the stream of
+//     weight fragments from L2 (4.4 GB, 15 TB/s) and the six dependent products
+//     of a tile; the matrix cores are busy for 27 % of the time.
 enum Op { kOpBF16 = 1, kOpSplit = 2 };
 constexpr float kSplitUp = 2048.f, kSplitDown = 1.f / 2048.f;
 
@@ -136,6 +137,33 @@ __device__ __forceinline__ void mma(const SplitFrag& w, const SplitFrag& b, Spli
   c.l = __builtin_amdgcn_mfma_f32_16x16x32_f16(w.lo, b.hi, c.l, 0, 0, 0);
 }
 
+// The forward products' third plane.  22 bits and a sign leave a quarter of the
+// FP32 weights with a residual midway between two FP16 values; its rounding is
+// one unit in the weight's last place, the same for every atom, and moved all
+// atomic energies of a species by up to 3e-8 eV in one direction, so that the
+// total energy's error grew with the atoms (per atom 3e-8 eV against 1e-8 with
+// FP32 weights; 1e-8 with the units).  The unit, a power of two, is kept as the
+// high byte of an FP16 value, half the bytes of a plane, and multiplied with
+// the activations' hi parts.  Without -> with, network: 261,000 atoms 237 ->
+// 285 us, 12,288 atoms 18.3 -> 21.7, eight networks 110 -> 135, 192 atoms 10.5
+// -> 12, 29,000 H/C/N/O atoms 105 -> 123; the units loaded one step ahead
+// instead of through the fragments' ring: eight networks 145.  The backward
+// products go without: dE/dx has no such sum, and its error is 0.6 of what FP32
+// products gave.  (An FP8 product on the same accumulator would spare the byte
+// moves, but two instruction forms writing one accumulator gave wrong sums.)
+__device__ __forceinline__ void load_unit(const uint8_t* U, int f, int lane, uint2* out) {
+  *out = *reinterpret_cast<const uint2*>(U + (size_t)f * 512 + (uint32_t)lane * 8u);
+}
+__device__ __forceinline__ v8h unit_frag(const uint2& u) {   // bytes 0 .. 7 into the high bytes of eight halves
+  const uint4 h = make_uint4(__builtin_amdgcn_perm(0u, u.x, 0x010c000cu), __builtin_amdgcn_perm(0u, u.x, 0x030c020cu),
+                             __builtin_amdgcn_perm(0u, u.y, 0x010c000cu), __builtin_amdgcn_perm(0u, u.y, 0x030c020cu));
+  return __builtin_bit_cast(v8h, h);
+}
+__device__ __forceinline__ void mma_unit(const v8h& w, const SplitFrag& b, SplitAcc& c) {
+  c.l = __builtin_amdgcn_mfma_f32_16x16x32_f16(w, b.hi, c.l, 0, 0, 0);
+}
+__device__ __forceinline__ void mma_unit(const v8h&, const v8bf&, v4f&) {}
+
 // Start of an accumulator from the bias tile, and its value at the end (s:
 // the inverse of the operands' scales; it does not apply to unscaled forms).
 __device__ __forceinline__ void acc_start(v4f& c, const v4f& bias) { c = bias; }
@@ -186,9 +214,9 @@ __device__ __forceinline__ void make_frag(const v4f* in, int kb, float s, SplitF
 // out[R/16 tiles] = bias tiles `out` + W[R x C] * in[C/16 tiles]; `in` is
 // register resident.  Row tiles are processed in chunks of CH to bound the
 // live accumulators.
-template <int R, int C, int OP, int CH>
+template <int R, int C, int OP, int CH, bool UNITS = false>
 __device__ __forceinline__ void gemm_regs(const void* __restrict__ W, const v4f* in, v4f* out, int lane, float s_in,
-                                          float s_out) {
+                                          float s_out, const uint8_t* __restrict__ U = nullptr) {
   static_assert(R % 16 == 0 && C % Ops<OP>::kK == 0, "tile sizes");
   constexpr int kPrefetch = PrefetchDepth<OP, (R > 160 || C > 160)>::value;
   constexpr int RT = R / 16;
@@ -218,7 +246,14 @@ __device__ __forceinline__ void gemm_regs(const void* __restrict__ W, const v4f*
       make_frag(in, kb, s_in, &b);
 #pragma unroll
       for (int r = 0; r < CH; ++r)
-        if (r < nr) mma(cur[r], b, acc[r]);
+        if (r < nr) {
+          mma(cur[r], b, acc[r]);
+          if constexpr (UNITS) {
+            uint2 u;
+            load_unit(U, (r0 + r) * KB + kb, lane, &u);
+            mma_unit(unit_frag(u), b, acc[r]);
+          }
+        }
     }
 #pragma unroll
     for (int r = 0; r < CH; ++r)
@@ -314,19 +349,24 @@ __device__ __forceinline__ void get_frag(const v4f* buf, int tiles, int plane, i
 
 // out[j][c] = bias(j) + A-rows (w + NW j), j < NJ, of W [R tiles x K] times
 // the LDS tiles `in` (in_tiles row tiles per column tile).
-template <int R, int K, int OP, int C, int NW, int NJ>
-__device__ __forceinline__ void gemm_lds_rows(const void* __restrict__ W, const v4f* in, int in_tiles, int plane,
-                                              const v4f* bias, v4f (*out)[C], int w, int lane, int cw, float s_out, const float* up) {
+template <int R, int K, int OP, int C, int NW, int NJ, bool UNITS>
+__device__ __forceinline__ void gemm_lds_rows(const void* __restrict__ W, const uint8_t* __restrict__ U, const v4f* in,
+                                              int in_tiles, int plane, const v4f* bias, v4f (*out)[C], int w,
+                                              int lane, int cw, float s_out, const float* up) {
   constexpr int KB = K / Ops<OP>::kK;
   constexpr int kPrefetch = PrefetchDepth<OP, (16 * R > 160 || K > 160)>::value;
   using F = typename Ops<OP>::Frag;
   F ring[kPrefetch][NJ];
+  uint2 units[kPrefetch][UNITS ? NJ : 1];
   typename Ops<OP>::Acc acc[NJ][C];
 #pragma unroll
   for (int p = 0; p < kPrefetch; ++p)
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
-      if (p < KB) load_frag(W, (w + NW * j) * KB + p, lane, &ring[p][j]);
+      if (p < KB) {
+        load_frag(W, (w + NW * j) * KB + p, lane, &ring[p][j]);
+        if constexpr (UNITS) load_unit(U, (w + NW * j) * KB + p, lane, &units[p][j]);
+      }
 #pragma unroll
   for (int j = 0; j < NJ; ++j)
 #pragma unroll
@@ -334,10 +374,15 @@ __device__ __forceinline__ void gemm_lds_rows(const void* __restrict__ W, const 
 #pragma unroll
   for (int kb = 0; kb < KB; ++kb) {
     F cur[NJ];
+    uint2 unit[UNITS ? NJ : 1];
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       cur[j] = ring[kb % kPrefetch][j];
-      if (kb + kPrefetch < KB) load_frag(W, (w + NW * j) * KB + kb + kPrefetch, lane, &ring[kb % kPrefetch][j]);
+      if constexpr (UNITS) unit[j] = units[kb % kPrefetch][j];
+      if (kb + kPrefetch < KB) {
+        load_frag(W, (w + NW * j) * KB + kb + kPrefetch, lane, &ring[kb % kPrefetch][j]);
+        if constexpr (UNITS) load_unit(U, (w + NW * j) * KB + kb + kPrefetch, lane, &units[kb % kPrefetch][j]);
+      }
     }
     F bv[C];
 #pragma unroll
@@ -348,6 +393,14 @@ __device__ __forceinline__ void gemm_lds_rows(const void* __restrict__ W, const 
 #pragma unroll
       for (int c = 0; c < C; ++c)
         if (c < cw) mma(cur[j], bv[c], acc[j][c]);
+    if constexpr (UNITS)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const v8h u = unit_frag(unit[j]);
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+          if (c < cw) mma_unit(u, bv[c], acc[j][c]);
+      }
     // keep the ring: the scheduler would move the loads down to their use
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -359,15 +412,16 @@ __device__ __forceinline__ void gemm_lds_rows(const void* __restrict__ W, const 
 
 // One wavefront-uniform branch on the number of row tiles the wavefront owns:
 // a test per tile inside the loop would cut it into short blocks.
-template <int R, int K, int OP, int C, int NW>
+template <int R, int K, int OP, int C, int NW, bool UNITS = false>
 __device__ __forceinline__ void gemm_lds(const void* __restrict__ W, const v4f* in, int in_tiles, int plane,
-                                         const v4f* bias, v4f (*out)[C], int w, int lane, int cw, float s_out, const float* up) {
+                                         const v4f* bias, v4f (*out)[C], int w, int lane, int cw, float s_out,
+                                         const float* up, const uint8_t* __restrict__ U = nullptr) {
   constexpr int most = Own<R, NW>::n, rest = R % NW;
   if (rest == 0 || w < rest) {
-    gemm_lds_rows<R, K, OP, C, NW, most>(W, in, in_tiles, plane, bias, out, w, lane, cw, s_out, up);
+    gemm_lds_rows<R, K, OP, C, NW, most, UNITS>(W, U, in, in_tiles, plane, bias, out, w, lane, cw, s_out, up);
   } else {
     if constexpr (most > 1)
-      gemm_lds_rows<R, K, OP, C, NW, most - 1>(W, in, in_tiles, plane, bias, out, w, lane, cw, s_out, up);
+      gemm_lds_rows<R, K, OP, C, NW, most - 1, UNITS>(W, U, in, in_tiles, plane, bias, out, w, lane, cw, s_out, up);
 #pragma unroll
     for (int c = 0; c < C; ++c) out[most - 1][c] = v4f{0.f, 0.f, 0.f, 0.f};
   }
@@ -447,6 +501,7 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
 
   for (int mem = 0; mem < a.n_members; ++mem) {
     const Elem* Wm = reinterpret_cast<const Elem*>(a.wmat) + (int64_t)(mem * a.S + s) * a.mat_per_species;
+    const uint8_t* Um = a.wunit + (int64_t)(mem * a.S + s) * a.unit_per_species;   // (split form)
     const float* V = a.wvec + (int64_t)(mem * a.S + s) * a.vec_per_species;
 
     // stage x in fragment layout (again for every member: the buffer is reused
@@ -479,7 +534,8 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
     {
       v4f bias[Own<N1 / 16, NW>::n];
       load_bias<N1, NW>(V + ob1, w, q, bias);
-      gemm_lds<N1 / 16, K0, OP, C, NW>(Wm + oF1, bufX, TX, PX, bias, h1, w, lane, cw, a.split.f1, up);
+      gemm_lds<N1 / 16, K0, OP, C, NW, OP == kOpSplit>(Wm + oF1, bufX, TX, PX, bias, h1, w, lane, cw,
+                                                     a.split.f1, up, Um + oF1);
     }
 #pragma unroll
     for (int j = 0; j < Own<N1 / 16, NW>::n; ++j) {
@@ -500,7 +556,8 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
     {
       v4f bias[Own<N2 / 16, NW>::n];
       load_bias<N2, NW>(V + ob2, w, q, bias);
-      gemm_lds<N2 / 16, N1, OP, C, NW>(Wm + oF2, bufA, TA, PA, bias, h2, w, lane, cw, a.split.f2, up);
+      gemm_lds<N2 / 16, N1, OP, C, NW, OP == kOpSplit>(Wm + oF2, bufA, TA, PA, bias, h2, w, lane, cw,
+                                                     a.split.f2, up, Um + oF2);
     }
     __syncthreads();   // everyone has read A (h1) and X (x) before X is overwritten
 #pragma unroll
@@ -522,7 +579,8 @@ __device__ __forceinline__ void mlp_split_body(const MlpArgs& a, float alpha) {
     {
       v4f bias[Own<N3 / 16, NW>::n];
       load_bias<N3, NW>(V + ob3, w, q, bias);
-      gemm_lds<N3 / 16, N2, OP, C, NW>(Wm + oF3, bufX, TX, PX, bias, h3, w, lane, cw, a.split.f3, up);
+      gemm_lds<N3 / 16, N2, OP, C, NW, OP == kOpSplit>(Wm + oF3, bufX, TX, PX, bias, h3, w, lane, cw,
+                                                     a.split.f3, up, Um + oF3);
     }
     float ep[C];
     float eq[C];
@@ -694,6 +752,7 @@ __global__ __launch_bounds__(512, K0 <= 128 && OP == kOpSplit ? 4 : 2) void k_ml
   a.n_members = first_member(a.n_members, y + 1, gridDim.y) - m0;
   a.wmat = reinterpret_cast<const Elem*>(a.wmat) + (int64_t)m0 * a.S * a.mat_per_species;
   a.wvec += (int64_t)m0 * a.S * a.vec_per_species;
+  a.wunit += (int64_t)m0 * a.S * a.unit_per_species;
   if (y > 0) a.g = a.g_part + (int64_t)(y - 1) * a.n * a.stride;
   a.e = a.e_part + (int64_t)y * a.n;
   a.part = nullptr;
@@ -757,6 +816,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
 
   for (int mem = 0; mem < a.n_members; ++mem) {
     const Elem* Wm = reinterpret_cast<const Elem*>(a.wmat) + (int64_t)(mem * a.S + s) * a.mat_per_species;
+    const uint8_t* Um = a.wunit + (int64_t)(mem * a.S + s) * a.unit_per_species;   // (split form)
     const float* V = a.wvec + (int64_t)(mem * a.S + s) * a.vec_per_species;
 
     // ---- layer 1: h1 = celu(W1 x + b1); x streamed from memory
@@ -782,6 +842,11 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
           typename Ops<OP>::Frag wf;
           load_frag(Wm + oF1, r * KB + kb, lane, &wf);
           mma(wf, xb, acc[r]);
+          if constexpr (OP == kOpSplit) {
+            uint2 u;
+            load_unit(Um + oF1, r * KB + kb, lane, &u);
+            mma_unit(unit_frag(u), xb, acc[r]);
+          }
         }
       }
 #pragma unroll
@@ -796,7 +861,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
     v4f h2[N2 / 16];
 #pragma unroll
     for (int r = 0; r < N2 / 16; ++r) h2[r] = *reinterpret_cast<const v4f*>(V + ob2 + 16 * r + 4 * q);
-    gemm_regs<N2, N1, OP, 4>(Wm + oF2, h1, h2, lane, a.split.h1 * dn, a.split.f2 * up);
+    gemm_regs<N2, N1, OP, 4, OP == kOpSplit>(Wm + oF2, h1, h2, lane, a.split.h1 * dn, a.split.f2 * up, Um + oF2);
 #pragma unroll
     for (int r = 0; r < N2 / 16; ++r)
 #pragma unroll
@@ -806,7 +871,7 @@ __global__ __launch_bounds__(kBlock) void k_mlp_reg(MlpArgs a, float alpha) {
     v4f h3[N3 / 16];
 #pragma unroll
     for (int r = 0; r < N3 / 16; ++r) h3[r] = *reinterpret_cast<const v4f*>(V + ob3 + 16 * r + 4 * q);
-    gemm_regs<N3, N2, OP, 4>(Wm + oF3, h2, h3, lane, a.split.h2 * dn, a.split.f3 * up);
+    gemm_regs<N3, N2, OP, 4, OP == kOpSplit>(Wm + oF3, h2, h3, lane, a.split.h2 * dn, a.split.f3 * up, Um + oF3);
 #pragma unroll
     for (int r = 0; r < N3 / 16; ++r)
 #pragma unroll
@@ -1473,6 +1538,8 @@ struct PackArgs {
   int64_t w_per_species; // floats per (member, species)
   _Float16* out;
   int64_t out_per_species;   // FP16 values per (member, species)
+  uint8_t* unit;         // third plane of the forward matrices (mma_unit), in fragment order
+  int64_t unit_per_species;
   int widths[4];         // K0 (padded with zero columns), N1, N2, N3
   int inputs;            // real input width
   float scale[3];
@@ -1500,8 +1567,13 @@ __global__ __launch_bounds__(kBlock) void k_pack_split(PackArgs a) {
   const float x = real ? W[src + (trans ? (int64_t)k * in + row : (int64_t)row * in + k)] * a.scale[l] : 0.f;
   const _Float16 hi = (_Float16)x;
   _Float16* o = out + 2 * (int64_t)(e - t) + (2 * f * 64 + lane) * 8 + j;
+  const float rest = (x - (float)hi) * kSplitUp;   // exact
+  const _Float16 lo = (_Float16)rest;
   o[0] = hi;
-  o[512] = (_Float16)((x - (float)hi) * kSplitUp);
+  o[512] = lo;
+  if (!trans)   // the rounding of lo, as the high byte of an FP16 value
+    a.unit[(int64_t)blockIdx.y * a.unit_per_species + e] =
+        (uint8_t)(__builtin_bit_cast(uint16_t, (_Float16)(rest - (float)lo)) >> 8);
 }
 
 }  // namespace
@@ -1513,12 +1585,12 @@ __global__ __launch_bounds__(kBlock) void k_pack_split(PackArgs a) {
 // which give the same results bit for bit for one network, and for an ensemble
 // while its members are not shared over grid rows (member_rows):
 //   while every 16-atom tile has a compute unit of its own, 16-atom tiles over
-//   8 wavefronts (the shortest chain per tile): 192 atoms FP32 11 us against
-//   15 for variant 2, 3,000 atoms 11.5 against 16, 60 H/C/N/O atoms with the
-//   MM channel 19 against 27, 8 networks and 3,900 atoms 69 against 111;
-//   beyond that 32-atom tiles over 8 wavefronts: FP32 6,600 atoms 14.4 against
-//   17.6, 48,000 atoms 48 against 51, 261,000 atoms 239 against 249, H/C/N/O
-//   batch of 29,000 atoms 105 against 116;
+//   8 wavefronts (the shortest chain per tile): 192 atoms FP32 12 us against
+//   17.6 for variant 2, 3,000 atoms 12.7 against 18, 60 H/C/N/O atoms with the
+//   MM channel 22 against 30, 8 networks and 3,900 atoms 63 against 126;
+//   beyond that 32-atom tiles over 8 wavefronts: FP32 6,600 atoms 17 against
+//   21 (variant 5: 17.8), 48,000 atoms 57 against 61, 261,000 atoms 280 against
+//   301, H/C/N/O batch of 29,000 atoms 123 against 136;
 //   except for large BF16 systems, whose short products are better off with
 //   more, smaller workgroups: 18,000 atoms 17.5 us with variant 2 against 19.9,
 //   36,000 atoms 25.4 against 27.9, 14,000 H/C/N/O atoms 31 against 37.
@@ -1532,12 +1604,14 @@ int mlp_variant(const nnp_model& m, int n) {
   return m.prec == NNP_BF16 && tiles > most ? 2 : 7;
 }
 
-hipError_t pack_split(const nnp_model& m, const float* weights, void* out) {
+hipError_t pack_split(const nnp_model& m, const float* weights, void* out, uint8_t* unit) {
   PackArgs a;
   a.w = weights;
   a.w_per_species = (int64_t)m.w_host.size() / (m.S * m.n_members);
   a.out = static_cast<_Float16*>(out);
   a.out_per_species = 2 * m.mat_per_species;
+  a.unit = unit;
+  a.unit_per_species = m.mat_per_species / 2;
   int total = 0;
   for (int l = 0; l < 4; ++l) a.widths[l] = l == 0 ? m.stride : m.widths[l];
   a.inputs = m.widths[0];
@@ -1557,7 +1631,8 @@ hipError_t pack_split(const nnp_model& m, const float* weights, void* out) {
 // members: 8 networks, 600 atoms 68 -> 26 us, 3,900 atoms 68 -> 53, 8,100
 // atoms 89 -> 70, 5 networks, 2,100 atoms 44 -> 36.  Beyond (8 networks,
 // 12,288 atoms, 386 tiles: 111 us, two rows 110; 2 networks 32.7 and 35.3) the
-// sum takes what a more even load gives.  The average over members is rounded
+// sum takes what a more even load gives (all without the forward products'
+// units, which add a fifth to each side).  The average over members is rounded
 // in the order of the rows, so it can differ in the last bits between system
 // sizes, variants and reserved capacities.
 int member_rows(const nnp_model& m, int n, int variant) {
@@ -1578,6 +1653,8 @@ hipError_t launch_mlp(nnp_model& m, int n, hipStream_t st) {
   a.e = m.d_e;
   a.wmat = m.d_wmat;
   a.wvec = m.d_wvec;
+  a.wunit = m.d_wunit;
+  a.unit_per_species = m.mat_per_species / 2;
   a.bin_start = m.d_bin_start;
   a.n_bins = m.geo.n_bins;
   a.S = m.S;

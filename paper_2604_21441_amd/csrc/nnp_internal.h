@@ -229,12 +229,13 @@ struct NbrLists {
 // product's result by the inverse of its two operands' scales.  An operand's
 // scale takes a bound on its magnitude that follows from the weights and the
 // list capacities to 2^15 (split_scales), so that nothing overflows; values
-// down to 2^-29 of the bound keep the full 22 bits, smaller ones an absolute
-// error of 2^-50 of it.  The bounds are loose, but there is room for that: with
-// list capacities of 1,024 and 256, or one weight 2^14 times all the others,
-// the error against float64 stays half of what FP32 products gave; one weight
-// 2^18 times the others takes the atoms of the other species from 7e-7 (FP32
-// products) to 1.2e-6.
+// down to 2^-29 of the bound keep the full 22 bits (the forward products'
+// weights all 24, mlp.hip mma_unit), smaller ones an absolute error of 2^-50 of
+// it.  The bounds are loose, but there is room for that: with list capacities
+// of 1,024 and 256, or one weight 2^14 times all the others, the error against
+// float64 stays half of what FP32 products gave; one weight 2^18 times the
+// others takes the atoms of the other species from 7e-7 (FP32 products) to
+// 1.2e-6.
 struct SplitScales {
   float x = 1.f, h1 = 1.f, h2 = 1.f, d3 = 1.f, d2 = 1.f, d1 = 1.f;   // operands
   float f1 = 1.f, f2 = 1.f, f3 = 1.f, b3 = 1.f, b2 = 1.f, b1 = 1.f;  // products
@@ -255,6 +256,8 @@ struct MlpArgs {
   float* e;                // [n] atomic energies (output)
   const void* wmat;        // fragment-packed matrices (FP16 pairs or BF16)
   const float* wvec;       // biases and output weights (FP32)
+  const uint8_t* wunit;    // split FP32 form: third plane of W1, W2, W3 (mlp.hip, mma_unit)
+  int64_t unit_per_species;
   const int* bin_start;    // species bucket boundaries
   int n_bins, S, n_members, stride;
   int64_t mat_per_species; // elements per (member, species) in wmat
@@ -343,6 +346,7 @@ struct nnp_model : nnp::Workspace {
   // device weights
   void* d_wmat = nullptr;
   float* d_wvec = nullptr;
+  uint8_t* d_wunit = nullptr;           // split FP32 form: third plane of the forward matrices
   const float* d_shifts = nullptr;      // the scaled radial shifts (behind the vectors in d_wvec)
   void* d_wrow = nullptr;               // BF16: W1, W2, W3 row-major (the LDS-resident network kernel)
   int64_t wrow_per_species = 0;         // elements per (member, species) in d_wrow
@@ -461,7 +465,7 @@ hipError_t launch_mm_bwd(nnp_model& m, int n, int n_mm, const float* mm_pos, con
 
 // mlp.hip
 // Device copy of the canonical weights -> the split FP32 form's fragments.
-hipError_t pack_split(const nnp_model& m, const float* weights, void* out);
+hipError_t pack_split(const nnp_model& m, const float* weights, void* out, uint8_t* unit);
 hipError_t launch_mlp(nnp_model& m, int n, hipStream_t st);
 
 // fills (api.cpp)
