@@ -774,9 +774,9 @@ __global__ __launch_bounds__(256) void k_desc_fwd_pool(FwdArgs a, DescParams p, 
 // those), leaves out dE_j/dG for a neighbour whose list does not hold the
 // centre, and hands over through the radial entries.
 //
-// Bound by VALU issue: 927 VALU instructions per wavefront in the water box
-// of 98,304 atoms, of which the triplet loop is 515 (210 per pass of 64), fill
-// 98 % of the 161 us.  Handing over every radial neighbour through a search
+// Bound by VALU issue: 932 VALU instructions per wavefront in the water box
+// of 98,304 atoms, of which the triplet loop is 515 (210 per pass of 64), take
+// 149 of the 160 us to issue, 952 at 261,000 atoms 404 of 428.  Handing over every radial neighbour through a search
 // for its slot, as before, took 195 us there and 577 us (now 431) at 261,000
 // atoms, and moved 12 bytes per radial instead of per angular neighbour
 // through contrib (gather 46 -> 28 us).  Tried: the triplets' contractions on

@@ -49,9 +49,9 @@ constexpr float kLog2e = 1.4426950408889634f;
 //     Errors against float64, FP32 instructions -> split (water, 12,288 atoms):
 //     forces 1.5e-6 both, an atomic energy 9.5e-8 -> 4.5e-8 eV rms, the mean of
 //     all 4e-9 both.  Network, FP32 instructions -> split: 261,000 atoms 569 ->
-//     285 us, 12,288 atoms 36.4 -> 21.7, eight networks 235 -> 135, 29,000
-//     H/C/N/O atoms 231 -> 123.  What bounds it at 261,000 atoms: the stream of
-//     weight fragments from L2 (4.4 GB, 15 TB/s) and the six dependent products
+//     284 us, 12,288 atoms 36.4 -> 21.2, eight networks 235 -> 134, 31,000
+//     H/C/N/O atoms 231 -> 118.  What bounds it at 261,000 atoms: the stream of
+//     weight fragments from L2 (3.9 GB, 14 TB/s) and the six dependent products
 //     of a tile; the matrix cores are busy for 27 % of the time.
 enum Op { kOpBF16 = 1, kOpSplit = 2 };
 constexpr float kSplitUp = 2048.f, kSplitDown = 1.f / 2048.f;
@@ -145,8 +145,8 @@ __device__ __forceinline__ void mma(const SplitFrag& w, const SplitFrag& b, Spli
 // FP32 weights; 1e-8 with the units).  The unit, a power of two, is kept as the
 // high byte of an FP16 value, half the bytes of a plane, and multiplied with
 // the activations' hi parts.  Without -> with, network: 261,000 atoms 237 ->
-// 285 us, 12,288 atoms 18.3 -> 21.7, eight networks 110 -> 135, 192 atoms 10.5
-// -> 12, 29,000 H/C/N/O atoms 105 -> 123; the units loaded one step ahead
+// 284 us, 12,288 atoms 18.3 -> 21.2, eight networks 110 -> 134, 192 atoms 10.5
+// -> 12, 31,000 H/C/N/O atoms 101 -> 118; the units loaded one step ahead
 // instead of through the fragments' ring: eight networks 145.  The backward
 // products go without: dE/dx has no such sum, and its error is 0.6 of what FP32
 // products gave.  (An FP8 product on the same accumulator would spare the byte
@@ -1590,7 +1590,7 @@ __global__ __launch_bounds__(kBlock) void k_pack_split(PackArgs a) {
 //   MM channel 22 against 30, 8 networks and 3,900 atoms 63 against 126;
 //   beyond that 32-atom tiles over 8 wavefronts: FP32 6,600 atoms 17 against
 //   21 (variant 5: 17.8), 48,000 atoms 57 against 61, 261,000 atoms 280 against
-//   301, H/C/N/O batch of 29,000 atoms 123 against 136;
+//   301, H/C/N/O batch of 31,000 atoms 118 against 132;
 //   except for large BF16 systems, whose short products are better off with
 //   more, smaller workgroups: 18,000 atoms 17.5 us with variant 2 against 19.9,
 //   36,000 atoms 25.4 against 27.9, 14,000 H/C/N/O atoms 31 against 37.
